@@ -94,112 +94,98 @@ void Ctx::g_add_into(Grp& acc, const Grp& t) {
 
 // digits of poly 'poly' of every member, lifted to Q_l and P: [B][beta][ne][N]
 std::shared_ptr<DBuf> Ctx::g_lift(const Grp& a, int poly) {
-    const int level = a.level, nl = level + 1, ne = nl + n_p, B = a.B;
+    const int nl = a.level + 1, ne = nl + n_p, beta = (int)mu[a.level].size();
+    auto lift = std::make_shared<DBuf>(this, (size_t)a.B * beta * ne * N);
+    DBuf coef(this, (size_t)a.B * nl * N);
+    lift_into(a.p + poly * a.ps, a.cs, a.B, a.level, lift->p, coef.p);
+    // the digits' own limbs stay where they are: the inner product reads them from the
+    // polynomial (which outlives the lift wherever a lift is used)
+    lift_own[lift->p] = {a.p + poly * a.ps, a.cs};
+    return lift;
+}
+
+// The converted limbs of every digit of B polynomials d (evaluation form, limbs 0..level, member
+// stride d_cs) into lift [B][beta][ne][N]; a digit's own limbs are not written.  coef: B (level + 1)
+// N words of scratch.
+void Ctx::lift_into(const u64* d, int64_t d_cs, int B, int level, u64* lift, u64* coef) {
+    const int nl = level + 1, ne = nl + n_p;
     const auto& infos = mu[level];
     const int beta = (int)infos.size();
     const int64_t lcs = (int64_t)beta * ne * N;
-    auto lift = std::make_shared<DBuf>(this, (size_t)B * lcs);
-    DBuf coef(this, (size_t)B * nl * N);
-    // with the fused conversion, the inverse transform also applies each digit's (D/q_s)^-1;
-    // it reads the polynomial in place and writes its coefficient form to coef
-    bool fused = true;
+    const bool planned = conv_mfma_fits(T);
+    // otherwise with the fused conversion the inverse transform applies each digit's (D/q_s)^-1
+    bool fused = !planned;
     for (const auto& inf : infos) fused = fused && conv_cols_fits(T, inf.hi - inf.lo);
-    {
+    {  // the inverse transform (its row pass alone before a planned conversion) reads d, writes coef
         Jobs J;
-        J.base = coef.p;
+        J.base = coef;
         J.cstride = (int64_t)nl * N;
-        J.src = a.p + poly * a.ps;
-        J.src_cstride = a.cs;
+        J.src = d;
+        J.src_cstride = d_cs;
         J.nct = B;
         J.n = nl;
         for (int i = 0; i < nl; ++i) {
             J.off[i] = (uint16_t)i;
             J.mod[i] = (uint8_t)i;
         }
-        launch_ntt(T, J, true, stream, fused ? d_mu_scale->p + (size_t)level * n_q * 2 : nullptr, nl);
+        launch_ntt(T, J, true, stream, fused ? d_mu_scale->p + (size_t)level * n_q * 2 : nullptr, nl, !planned);
     }
+    if (planned) launch_conv_mfma(T, plan_mu[level], coef, 0, (int64_t)nl * N, lift, 0, lcs, 1, B, stream);
     Jobs J;
-    J.base = lift->p;
+    J.base = lift;
     J.cstride = lcs;
     J.nct = B;
     J.n = 0;
-    // every digit's conversion in one fused launch (one grid over all targets: the digits' few
-    // blocks each would leave the device part idle at their ends)
+    // the fused conversion takes every digit in one launch (one grid over all targets: the digits'
+    // few blocks each would leave the device part idle at their ends) while its lists hold them
     const bool merged = fused && beta <= HE_MAXDIG && beta * ne - nl <= HE_MAXT;
-    ConvDesc M;
-    memset(&M, 0, sizeof M);
-    if (merged) {
-        M.src = coef.p;
-        M.src_cstride = (int64_t)nl * N;
-        M.dst = lift->p;
-        M.dst_cstride = lcs;
-        M.nct = B;
-        M.npoly = 1;
-        M.tab = d_mu_tab->p;
-        M.tab_ld = ne;
-        M.prescaled = 1;
-        M.ndig = beta;
-    }
+    ConvDesc D;
     for (int j = 0; j < beta; ++j) {
         const ModUpInfo& inf = infos[j];
-        if (merged) {
-            M.dns[j] = inf.hi - inf.lo;
-            M.dsrc[j] = (int64_t)inf.lo * N;
-            M.dtab[j] = (int64_t)inf.off;
-            M.ns = std::max(M.ns, inf.hi - inf.lo);
-            for (int t = 0; t < ne; ++t) {
-                if (t >= inf.lo && t < inf.hi) continue;
-                M.doff[M.nt] = (uint16_t)(j * ne + t);
-                M.dmod[M.nt] = (uint8_t)ext_mod(level, t);
-                M.tcol[M.nt] = (uint16_t)t;
-                M.tdig[M.nt] = (uint8_t)j;
-                ++M.nt;
-                if (J.n >= HE_MAXJ) throw HeError(HE_EUNSUPPORTED);
-                J.off[J.n] = (uint16_t)(j * ne + t);
-                J.mod[J.n] = (uint8_t)ext_mod(level, t);
-                ++J.n;
-            }
-            continue;
+        if (!merged || j == 0) {
+            memset(&D, 0, sizeof D);
+            D.src = coef + (merged ? 0 : (size_t)inf.lo * N);
+            D.src_cstride = (int64_t)nl * N;
+            D.dst = lift + (merged ? 0 : (size_t)j * ne * N);
+            D.dst_cstride = lcs;
+            D.nct = B;
+            D.npoly = 1;
+            D.tab = d_mu_tab->p + (merged ? 0 : inf.off);
+            D.tab_ld = ne;
+            D.prescaled = fused ? 1 : 0;
+            D.ndig = merged ? beta : 0;
         }
-        ConvDesc D;
-        memset(&D, 0, sizeof D);
-        D.src = coef.p + (size_t)inf.lo * N;
-        D.src_cstride = (int64_t)nl * N;
-        D.dst = lift->p + (size_t)j * ne * N;
-        D.dst_cstride = lcs;
-        D.nct = B;
-        D.npoly = 1;
-        D.tab = d_mu_tab->p + inf.off;
-        D.tab_ld = ne;
-        D.ns = inf.hi - inf.lo;
-        int nt = 0;
+        const int ns = inf.hi - inf.lo;
+        D.ns = std::max(D.ns, ns);
+        if (merged) {
+            D.dns[j] = ns;
+            D.dsrc[j] = (int64_t)inf.lo * N;
+            D.dtab[j] = (int64_t)inf.off;
+        }
         for (int t = 0; t < ne; ++t) {
             if (t >= inf.lo && t < inf.hi) continue;
-            D.doff[nt] = (uint16_t)t;
-            D.dmod[nt] = (uint8_t)ext_mod(level, t);
-            D.tcol[nt] = (uint16_t)t;
-            ++nt;
             if (J.n >= HE_MAXJ) throw HeError(HE_EUNSUPPORTED);
             J.off[J.n] = (uint16_t)(j * ne + t);
             J.mod[J.n] = (uint8_t)ext_mod(level, t);
             ++J.n;
+            if (planned) continue;
+            D.doff[D.nt] = (uint16_t)((merged ? j * ne : 0) + t);
+            D.dmod[D.nt] = (uint8_t)ext_mod(level, t);
+            D.tcol[D.nt] = (uint16_t)t;
+            D.tdig[D.nt] = (uint8_t)j;
+            ++D.nt;
         }
-        D.nt = nt;
-        for (int s = 0; s < D.ns; ++s) {
+        if (planned || merged) continue;
+        for (int s = 0; s < ns; ++s) {
             D.smod[s] = inf.lo + s;
             D.hinv[s] = inf.hinv[s];
             D.hinv_sh[s] = inf.hinv_sh[s];
         }
-        D.prescaled = fused ? 1 : 0;
         if (fused) launch_conv_cols(T, D, stream);
         else launch_baseconv(T, D, stream);
     }
-    if (merged) launch_conv_cols(T, M, stream);
-    launch_ntt(T, J, false, stream, nullptr, 0, !fused);
-    // the digits' own limbs stay where they are: the inner product reads them from the
-    // polynomial (which outlives the lift wherever a lift is used)
-    lift_own[lift->p] = {a.p + poly * a.ps, a.cs};
-    return lift;
+    if (merged) launch_conv_cols(T, D, stream);
+    launch_ntt(T, J, false, stream, nullptr, 0, !planned && !fused);
 }
 
 // g^-1 mod 2N (g odd): Newton's iteration x <- x (2 - g x) doubles the correct low bits
@@ -215,6 +201,25 @@ static u64 galois_inverse(u64 g, int log_n) {
 // masked sum of two rotations (one ModDown then serves both)
 void Ctx::g_ks_inner_sets(u64* u, const u64* lift, int B, int level, std::vector<IpSet> sets, int nrot,
                           const u64* c0, int64_t c0_cs, bool accumulate) {
+    // every group lift leaves its digits' own limbs in the lifted polynomial
+    auto own_of = [&](const u64* l) {
+        auto it = lift_own.find(l);
+        if (it == lift_own.end()) throw HeError(HE_EUNSUPPORTED);
+        return it->second;
+    };
+    const auto own = own_of(lift);
+    for (auto& S : sets)
+        if (S.lift2) {
+            const auto o2 = own_of(S.lift2);
+            S.own2 = o2.first;
+            S.own2_cs = o2.second;
+        }
+    ip_into(u, lift, own.first, own.second, B, level, sets, nrot, c0, c0_cs, accumulate);
+}
+
+// the same with the lifted polynomial (own, member stride own_cs) given
+void Ctx::ip_into(u64* u, const u64* lift, const u64* own, int64_t own_cs, int B, int level,
+                  const std::vector<IpSet>& sets, int nrot, const u64* c0, int64_t c0_cs, bool accumulate) {
     const int nl = level + 1, ne = nl + n_p;
     const int beta = (int)mu[level].size();
     if (sets.empty() || sets.size() > IP_MAXSET) throw HeError(HE_EUNSUPPORTED);
@@ -232,16 +237,9 @@ void Ctx::g_ks_inner_sets(u64* u, const u64* lift, int B, int level, std::vector
     D.c0 = c0;
     D.c0_cs = c0_cs;
     D.nq = nl;
-    for (int t = 0; t < nl; ++t) D.pmont[t] = hm::to_mont(pmod[t], mods[t]);
-    // every group lift leaves its digits' own limbs in the lifted polynomial
-    auto own_of = [&](const u64* l) {
-        auto it = lift_own.find(l);
-        if (it == lift_own.end()) throw HeError(HE_EUNSUPPORTED);
-        return it->second;
-    };
-    const auto own = own_of(lift);
-    D.own = own.first;
-    D.own_cs = own.second;
+    for (int t = 0; t < nl; ++t) D.pmont[t] = pmod_mont[t];
+    D.own = own;
+    D.own_cs = own_cs;
     for (int j = 0; j < beta; ++j) {
         D.dlo[j] = (uint8_t)mu[level][j].lo;
         D.dhi[j] = (uint8_t)mu[level][j].hi;
@@ -251,11 +249,6 @@ void Ctx::g_ks_inner_sets(u64* u, const u64* lift, int B, int level, std::vector
     for (size_t j = 0; j < sets.size(); ++j) {
         D.s[j] = sets[j];
         D.s[j].ginv = galois_inverse(sets[j].g, log_n);
-        if (sets[j].lift2) {
-            const auto o2 = own_of(sets[j].lift2);
-            D.s[j].own2 = o2.first;
-            D.s[j].own2_cs = o2.second;
-        }
     }
     D.accumulate = accumulate ? 1 : 0;
     launch_inner_product(T, D, stream);
@@ -285,10 +278,30 @@ void Ctx::g_ks_inner(u64* u, const u64* lift, int B, int level, const u64* key, 
 void Ctx::g_moddown(u64* u, int B, int level, const u64* add0, const u64* add1, int64_t add_cs, u64* out0,
                     u64* out1, int64_t out_cs, u64 add_g, const u64* mask, const u64* acc0, const u64* acc1,
                     int64_t acc_cs) {
+    DBuf conv(this, (size_t)B * 2 * (level + 1) * N);
+    Epi E;
+    memset(&E, 0, sizeof E);
+    E.add[0] = add0;
+    E.add[1] = add1;
+    E.add_cs = add_cs;
+    E.out[0] = out0;
+    E.out[1] = out1;
+    E.out_cs = out_cs;
+    E.g = add_g;
+    E.mask = mask;
+    E.acc[0] = acc0;
+    E.acc[1] = acc1;
+    E.acc_cs = acc_cs;
+    moddown_into(u, conv.p, B, level, E);
+}
+
+// the same with the epilogue's operands in E and the converted limbs in conv [B][2][level + 1][N]
+void Ctx::moddown_into(u64* u, u64* conv, int B, int level, const Epi& part) {
     const int nl = level + 1, ne = nl + n_p;
     const int64_t ucs = 2 * (int64_t)ne * N, ccs = 2 * (int64_t)nl * N;
-    // with the fused conversion, the inverse transform also applies (P/p_k)^-1
-    const bool fused = conv_cols_fits(T, n_p);
+    const bool planned = conv_mfma_fits(T);
+    // otherwise with the fused conversion the inverse transform applies (P/p_k)^-1
+    const bool fused = !planned && conv_cols_fits(T, n_p);
     {
         Jobs J;
         J.base = u;
@@ -301,38 +314,42 @@ void Ctx::g_moddown(u64* u, int B, int level, const u64* add0, const u64* add1, 
                 J.mod[J.n] = (uint8_t)(n_q + k);
                 ++J.n;
             }
-        launch_ntt(T, J, true, stream, fused ? d_md_scale->p : nullptr, n_p);
+        launch_ntt(T, J, true, stream, fused ? d_md_scale->p : nullptr, n_p, !planned);
     }
-    DBuf conv(this, (size_t)B * ccs);
-    ConvDesc C;
-    memset(&C, 0, sizeof C);
-    C.src = u + (size_t)nl * N;
-    C.src_pstride = (int64_t)ne * N;
-    C.src_cstride = ucs;
-    C.dst = conv.p;
-    C.dst_pstride = (int64_t)nl * N;
-    C.dst_cstride = ccs;
-    C.nct = B;
-    C.tab = d_md_tab->p;
-    C.tab_ld = n_q;
-    C.ns = n_p;
-    C.nt = nl;
-    C.npoly = 2;
-    for (int s = 0; s < n_p; ++s) {
-        C.smod[s] = n_q + s;
-        C.hinv[s] = md_hinv[s];
-        C.hinv_sh[s] = md_hinv_sh[s];
+    if (planned) {
+        launch_conv_mfma(T, plan_md[level], u + (size_t)nl * N, (int64_t)ne * N, ucs, conv, (int64_t)nl * N, ccs, 2, B,
+                         stream);
+    } else {
+        ConvDesc C;
+        memset(&C, 0, sizeof C);
+        C.src = u + (size_t)nl * N;
+        C.src_pstride = (int64_t)ne * N;
+        C.src_cstride = ucs;
+        C.dst = conv;
+        C.dst_pstride = (int64_t)nl * N;
+        C.dst_cstride = ccs;
+        C.nct = B;
+        C.tab = d_md_tab->p;
+        C.tab_ld = n_q;
+        C.ns = n_p;
+        C.nt = nl;
+        C.npoly = 2;
+        for (int s = 0; s < n_p; ++s) {
+            C.smod[s] = n_q + s;
+            C.hinv[s] = md_hinv[s];
+            C.hinv_sh[s] = md_hinv_sh[s];
+        }
+        for (int t = 0; t < nl; ++t) {
+            C.doff[t] = (uint16_t)t;
+            C.dmod[t] = (uint8_t)t;
+            C.tcol[t] = (uint16_t)t;
+        }
+        C.prescaled = fused ? 1 : 0;
+        if (fused) launch_conv_cols(T, C, stream);
+        else launch_baseconv(T, C, stream);
     }
-    for (int t = 0; t < nl; ++t) {
-        C.doff[t] = (uint16_t)t;
-        C.dmod[t] = (uint8_t)t;
-        C.tcol[t] = (uint16_t)t;
-    }
-    C.prescaled = fused ? 1 : 0;
-    if (fused) launch_conv_cols(T, C, stream);
-    else launch_baseconv(T, C, stream);
     Jobs J;
-    J.base = conv.p;
+    J.base = conv;
     J.cstride = ccs;
     J.nct = B;
     J.n = 2 * nl;
@@ -341,27 +358,15 @@ void Ctx::g_moddown(u64* u, int B, int level, const u64* add0, const u64* add1, 
             J.off[p * nl + t] = (uint16_t)(p * nl + t);
             J.mod[p * nl + t] = (uint8_t)t;
         }
-    Epi E;
-    memset(&E, 0, sizeof E);
+    Epi E = part;
     E.on = 1;
     E.nl = nl;
     E.u = u;
     E.u_cs = ucs;
     E.u_ps = (int64_t)ne * N;
-    E.add[0] = add0;
-    E.add[1] = add1;
-    E.add_cs = add_cs;
-    E.out[0] = out0;
-    E.out[1] = out1;
-    E.out_cs = out_cs;
     E.pinv = d_pinv->p;
     E.pinv_sh = d_pinv->p + n_q;
-    E.g = add_g;
-    E.mask = mask;
-    E.acc[0] = acc0;
-    E.acc[1] = acc1;
-    E.acc_cs = acc_cs;
-    launch_ntt_moddown(T, J, E, stream, !fused);
+    launch_ntt_moddown(T, J, E, stream, !planned && !fused);
 }
 
 // ModDown(<lift o sigma_g, key>) (+ add) into out, for every member
@@ -595,42 +600,62 @@ Grp Ctx::g_mask_sum(const std::vector<std::pair<const Grp*, const u64*>>& terms,
 
 Grp Ctx::g_rescale(const Grp& a) {
     if (a.level < 1) throw HeError(HE_ELEVEL);
-    const int l = a.level, np = a.deg + 1, B = a.B;
-    DBuf last(this, (size_t)B * np * N);
-    copy2d(this, last.p, N, a.p + (size_t)l * N, a.ps, N, (int64_t)B * np);
-    {
-        Jobs J;
-        J.base = last.p;
-        J.cstride = N;
-        J.nct = B * np;
-        J.n = 1;
-        J.off[0] = 0;
-        J.mod[0] = (uint8_t)l;
-        launch_ntt(T, J, true, stream);
-    }
-    DBuf tmp(this, (size_t)B * np * l * N);
-    launch_rescale_spread(T, l, B * np, last.p, N, l, tmp.p, (int64_t)l * N, stream);
-    {
-        Jobs J;
-        J.base = tmp.p;
-        J.cstride = (int64_t)l * N;
-        J.nct = B * np;
-        J.n = l;
-        for (int i = 0; i < l; ++i) {
-            J.off[i] = (uint16_t)i;
-            J.mod[i] = (uint8_t)i;
-        }
-        launch_ntt(T, J, false, stream);
-    }
+    const int l = a.level;
+    if (a.cs != (a.deg + 1) * a.ps) throw HeError(HE_EUNSUPPORTED);
     std::vector<double> sc(a.scale);
     for (auto& s : sc) s /= (double)mods[l];
-    Grp out = g_new(B, l - 1, a.deg, sc);
+    Grp out = g_new(a.B, l - 1, a.deg, sc);
+    rescale_into(a.p, a.ps, l, a.deg + 1, a.B, out.p, out.ps);
+    cnt[C_RS] += a.B;
+    return out;
+}
+
+// (c - [c]_{q_l} centred) q_l^-1 of the limbs below l of np polynomials of B members (polynomial
+// strides a_ps and out_ps, members np polynomials apart).  A rescale is a ModDown by the one prime
+// q_l: the conversion has that limb as its only source, and the row pass's epilogue combines.
+void Ctx::rescale_into(const u64* a, int64_t a_ps, int l, int np, int B, u64* out, int64_t out_ps) {
+    const bool planned = rescale_mfma_fits(T);
+    const int n = B * np;
+    DBuf last(this, (size_t)n * N);
+    Jobs J;
+    J.base = last.p;
+    J.cstride = N;
+    J.src = a + (size_t)l * N;
+    J.src_cstride = a_ps;
+    J.nct = n;
+    J.n = 1;
+    J.off[0] = 0;
+    J.mod[0] = (uint8_t)l;
+    launch_ntt(T, J, true, stream, nullptr, 0, !planned);
+    DBuf tmp(this, (size_t)n * l * N);
+    J = Jobs();
+    J.base = tmp.p;
+    J.cstride = (int64_t)np * l * N;
+    J.nct = B;
+    J.n = 0;
+    for (int p = 0; p < np; ++p)
+        for (int i = 0; i < l; ++i) {
+            J.off[J.n] = (uint16_t)(p * l + i);
+            J.mod[J.n] = (uint8_t)i;
+            ++J.n;
+        }
     const u64* qi = d_rs->p + (size_t)l * n_q;
     const u64* qis = d_rs->p + (size_t)n_q * n_q + (size_t)l * n_q;
-    launch_rescale_combine(T, l, np, a.p, a.ps, tmp.p, (int64_t)l * N, qi, qis, out.p, out.ps, stream, B, a.cs,
-                           (int64_t)np * l * N, out.cs);
-    cnt[C_RS] += B;
-    return out;
+    if (!planned) launch_rescale_spread(T, l, n, last.p, N, l, tmp.p, (int64_t)l * N, stream);
+    else launch_conv_mfma(T, plan_rs[l], last.p, N, (int64_t)np * N, tmp.p, (int64_t)l * N, J.cstride, np, B, stream);
+    Epi E;
+    memset(&E, 0, sizeof E);
+    E.on = 1;
+    E.nl = l;
+    E.u = a;
+    E.u_cs = np * a_ps;
+    E.u_ps = a_ps;
+    for (int p = 0; p < np; ++p) E.out[p] = out + p * out_ps;
+    E.out_cs = np * out_ps;
+    E.pinv = qi;
+    E.pinv_sh = qis;
+    E.g = 1;
+    launch_ntt_moddown(T, J, E, stream, !planned);
 }
 
 Grp Ctx::g_tensor(const Grp& a, const Grp& b) {

@@ -459,6 +459,113 @@ void Ctx::build_tables() {
         upload(this, d_md_scale->p, mds.data(), mds.size() * 8);
     }
     gauss_cdt(cdt);
+    for (int t = 0; t < n_q; ++t) pmod_mont.push_back(to_mont(pmod[t], mods[t]));
+    if (rescale_mfma_fits(T)) build_plans();
+}
+
+// Conversion plans of every level.  The constants of target t and source s are w_d = centred((D/q_s)
+// 2^(8d) mod q_t), d < 8, each in signed bytes w_de; a set's A operands put byte e = 4 tile + r of
+// target g at row 4 g + r, and digit d of source b at byte d of word 0 of the lanes of k block b (the
+// layout in which the kernel holds the source words as B operands); source 4 + s is word 1 of the
+// xs k blocks from xs s.  A set of fewer than four targets repeats its first.
+void Ctx::build_plans() {
+    const auto signed_byte = [](int64_t w, int e) { return (u64)(((uint64_t)w + 0x8080808080808080ull) >> (8 * e) & 255) ^ 128; };
+    std::vector<ConvSet> sets;
+    std::vector<u64> tab, rs_scale(2 * (size_t)n_q);
+    // one digit: ns sources from limb slo with primes smod .., to the targets (limb offset, prime)
+    const auto add_digit = [&](ConvPlan& P, int slo, int ns, int smod, const std::vector<std::pair<int, int>>& targets) {
+        ConvDig& dg = P.dig[P.ndig++];
+        dg = ConvDig{slo, ns, smod, P.nset, 0};
+        P.src_limbs += ns;
+        std::vector<std::pair<int, int>> kind[2];  // integer targets, FP64 targets
+        for (auto& t : targets) kind[(T.fp64_mods >> t.second) & 1].push_back(t);
+        P.dst_limbs += (double)targets.size();
+        P.fp_limbs += (double)kind[1].size();
+        for (int fp = 1; fp >= 0; --fp)
+            for (size_t t0 = 0; t0 < kind[fp].size(); t0 += 4) {
+                ConvSet S;
+                memset(&S, 0, sizeof S);
+                S.tab = (uint32_t)tab.size();
+                S.nt = (uint8_t)std::min<size_t>(4, kind[fp].size() - t0);
+                S.fp = (uint8_t)fp;
+                const int ks = P.xs ? 2 : 1;
+                tab.resize(tab.size() + 128 * (size_t)ks, 0);
+                for (int g = 0; g < 4; ++g) {
+                    const auto& t = kind[fp][t0 + (g < S.nt ? g : 0)];
+                    const u64 q = mods[t.second];
+                    S.doff[g] = (uint16_t)t.first;
+                    S.dmod[g] = (uint8_t)t.second;
+                    if (q < (1ull << 43)) S.small = 1;
+                    const u64 c32 = (1ull << 32) % q;
+                    S.w32[g] = c32;
+                    S.w32_sh[g] = shoup(c32, q);
+                    const u64 c77 = mulmod(mulmod(c32, c32, q), (1ull << 13) % q, q);
+                    S.off[g] = (q - c77) % q;
+                    if (S.off[g] < (1ull << 45)) S.off[g] += q;
+                    for (int s = 0; s < ns; ++s) {
+                        u64 w = 1 % q;  // D / q_s mod q, then times 2^8 per byte of the source
+                        for (int r = 0; r < ns; ++r)
+                            if (r != s) w = mulmod(w, mods[smod + r] % q, q);
+                        for (int d = 0; d < 8; ++d) {
+                            const int64_t wc = w > (q - 1) / 2 ? (int64_t)w - (int64_t)q : (int64_t)w;
+                            for (int e = 0; e < 8; ++e) {
+                                const int word = s >> 2, rep = word ? P.xs : 1;
+                                for (int b = (word ? s - 4 : s) * rep, n = 0; n < rep; ++n, ++b)
+                                    tab[S.tab + ((size_t)(e >> 2) * 64 + b * 16 + 4 * g + (e & 3)) * ks + word] |=
+                                        signed_byte(wc, e) << (8 * d);
+                            }
+                            w = mulmod(w, 256 % q, q);
+                        }
+                    }
+                }
+                sets.push_back(S);
+                ++dg.nset;
+                ++P.nset;
+            }
+    };
+    std::vector<size_t> first;  // each plan's first set
+    plan_mu.assign(n_q, ConvPlan());
+    plan_md.assign(n_q, ConvPlan());
+    plan_rs.assign(n_q, ConvPlan());
+    for (int l = 0; l < n_q; ++l) {
+        const int nl = l + 1, ne = nl + n_p;
+        first.push_back(sets.size());
+        ConvPlan& U = plan_mu[l];
+        U.xs = conv_mfma_share(T, std::min(alpha, nl));
+        for (size_t j = 0; j < mu[l].size() && conv_mfma_fits(T); ++j) {
+            std::vector<std::pair<int, int>> t;
+            for (int i = 0; i < ne; ++i)
+                if (i < mu[l][j].lo || i >= mu[l][j].hi) t.push_back({(int)j * ne + i, ext_mod(l, i)});
+            add_digit(U, mu[l][j].lo, mu[l][j].hi - mu[l][j].lo, mu[l][j].lo, t);
+        }
+        first.push_back(sets.size());
+        ConvPlan& D = plan_md[l];
+        D.xs = conv_mfma_share(T, n_p);
+        std::vector<std::pair<int, int>> t;
+        for (int i = 0; i < nl; ++i) t.push_back({i, i});
+        if (conv_mfma_fits(T)) add_digit(D, 0, n_p, n_q, t);
+        first.push_back(sets.size());
+        ConvPlan& R = plan_rs[l];
+        t.pop_back();
+        add_digit(R, 0, 1, l, t);
+        rs_scale[2 * l] = host_mods[l].ninv;
+        rs_scale[2 * l + 1] = host_mods[l].ninv_sh;
+    }
+    d_plan_sets = std::make_unique<DBuf>(this, (sets.size() * sizeof(ConvSet) + 7) / 8);
+    d_plan_tab = std::make_unique<DBuf>(this, tab.size());
+    d_rs_scale = std::make_unique<DBuf>(this, rs_scale.size());
+    upload(this, d_plan_sets->p, sets.data(), sets.size() * sizeof(ConvSet));
+    upload(this, d_plan_tab->p, tab.data(), tab.size() * 8);
+    upload(this, d_rs_scale->p, rs_scale.data(), rs_scale.size() * 8);
+    for (int l = 0; l < n_q; ++l) {
+        ConvPlan* P[3] = {&plan_mu[l], &plan_md[l], &plan_rs[l]};
+        const u64* sc[3] = {d_mu_scale->p + (size_t)l * n_q * 2, d_md_scale->p, d_rs_scale->p + 2 * (size_t)l};
+        for (int k = 0; k < 3; ++k) {
+            P[k]->sets = (const ConvSet*)d_plan_sets->p + first[3 * (size_t)l + k];
+            P[k]->tab = d_plan_tab->p;
+            P[k]->scale = sc[k];
+        }
+    }
 }
 
 // ====================================================================== small helpers
@@ -704,207 +811,50 @@ CtPtr Ctx::tensor(const CtData& a, const CtData& b) {
 }
 
 // ---------------------------------------------------------------- key switching
-// Digits of d (evaluation form, limbs 0..level) lifted to Q_l and P: [beta][ne][N]
-std::unique_ptr<DBuf> Ctx::ks_lift(const u64* d, int level) {
-    const int nl = level + 1, ne = nl + n_p;
-    const int beta = (int)mu[level].size();
-    auto lift = std::make_unique<DBuf>(this, (size_t)beta * ne * N);
-    DBuf coef(this, (size_t)nl * N);
-    ks_lift_into(d, level, lift->p, coef.p);
-    return lift;
+// out [2][nl][N] = ModDown(<digits of d permuted by g, key>) (+ sigma_g(c0) in out_0 for a rotation,
+// + add [2][nl][N] for a relinearisation), on the caller's lift [beta][ne][N], u [2][ne][N] and tmp [2][nl][N]
+void Ctx::ks_single_into(const u64* d, int level, const u64* key, u64 g, const u64* c0, const u64* add, u64* out,
+                         u64* lift, u64* u, u64* tmp) {
+    const int64_t ps = (int64_t)(level + 1) * N;
+    lift_into(d, 0, 1, level, lift, tmp);
+    IpSet S;
+    memset(&S, 0, sizeof S);
+    S.key = key;
+    S.g = g;
+    ip_into(u, lift, d, 0, 1, level, {S}, 1, c0, 0, false);
+    Epi E;
+    memset(&E, 0, sizeof E);
+    if (add) {
+        E.add[0] = add;
+        E.add[1] = add + ps;
+    }
+    E.out[0] = out;
+    E.out[1] = out + ps;
+    E.g = 1;
+    moddown_into(u, tmp, 1, level, E);
 }
 
-// the same into caller buffers: lift [beta][ne][N], coef [nl][N] (the digits' coefficient form)
-void Ctx::ks_lift_into(const u64* d, int level, u64* lift, u64* coef) {
+// the same with buffers of the context's allocation cache
+void Ctx::ks_single(const u64* d, int level, const u64* key, u64 g, const u64* c0, const u64* add, u64* out) {
     const int nl = level + 1, ne = nl + n_p;
-    const auto& infos = mu[level];
-    const int beta = (int)infos.size();
-    {  // the digits' coefficient form: the inverse transform reads d in place, writes coef
-        Jobs Ji;
-        Ji.base = coef;
-        Ji.cstride = 0;
-        Ji.src = d;
-        Ji.nct = 1;
-        Ji.n = nl;
-        for (int i = 0; i < nl; ++i) {
-            Ji.off[i] = (uint16_t)i;
-            Ji.mod[i] = (uint8_t)i;
-        }
-        launch_ntt(T, Ji, true, stream);
-    }
-    Jobs J;
-    J.base = lift;
-    J.cstride = 0;
-    J.nct = 1;
-    J.n = 0;
-    for (int j = 0; j < beta; ++j) {
-        const ModUpInfo& inf = infos[j];
-        ConvDesc D;
-        memset(&D, 0, sizeof D);
-        D.nct = 1;
-        D.src = coef + (size_t)inf.lo * N;
-        D.src_pstride = 0;
-        D.dst = lift + (size_t)j * ne * N;
-        D.dst_pstride = 0;
-        D.tab = d_mu_tab->p + inf.off;
-        D.ns = inf.hi - inf.lo;
-        D.npoly = 1;
-        D.tab_ld = ne;
-        int nt = 0;
-        for (int t = 0; t < ne; ++t) {
-            if (t >= inf.lo && t < inf.hi) continue;
-            D.doff[nt] = (uint16_t)t;
-            D.dmod[nt] = (uint8_t)ext_mod(level, t);
-            D.tcol[nt] = (uint16_t)t;
-            ++nt;
-            J.off[J.n] = (uint16_t)(j * ne + t);
-            J.mod[J.n] = (uint8_t)ext_mod(level, t);
-            if (++J.n == HE_MAXJ) {
-                throw HeError(HE_EUNSUPPORTED);
-            }
-        }
-        D.nt = nt;
-        for (int s = 0; s < D.ns; ++s) {
-            D.smod[s] = inf.lo + s;
-            D.hinv[s] = inf.hinv[s];
-            D.hinv_sh[s] = inf.hinv_sh[s];
-        }
-        launch_baseconv(T, D, stream);
-        // the digit's own limbs are d itself
-        hip_check(hipMemcpyAsync(lift + ((size_t)j * ne + inf.lo) * N, d + (size_t)inf.lo * N,
-                                 (size_t)(inf.hi - inf.lo) * N * 8, hipMemcpyDeviceToDevice, stream),
-                  "lift digit");
-    }
-    launch_ntt(T, J, false, stream);
-}
-
-// (out0, out1) = ModDown(<lift permuted by g, key>) (+ add0, add1); out pointers [nl][N]
-void Ctx::ks_apply(const u64* lift, int level, const u64* key, u64 g, const u64* add0, const u64* add1, u64* out0,
-                   u64* out1) {
-    const int nl = level + 1, ne = nl + n_p;
-    DBuf u(this, 2 * (size_t)ne * N);
-    DBuf conv(this, 2 * (size_t)nl * N);
-    ks_apply_into(lift, level, key, g, add0, add1, out0, out1, u.p, conv.p);
-}
-
-// the same with caller buffers: u [2][ne][N] (the inner product over Q_l and P), conv [2][nl][N]
-void Ctx::ks_apply_into(const u64* lift, int level, const u64* key, u64 g, const u64* add0, const u64* add1,
-                        u64* out0, u64* out1, u64* u, u64* conv) {
-    const int nl = level + 1, ne = nl + n_p;
-    const int beta = (int)mu[level].size();
-    IpDesc D;
-    memset(&D, 0, sizeof D);
-    D.lift = lift;
-    D.u = u;
-    D.ne = ne;
-    D.beta = beta;
-    D.M = n_q + n_p;
-    D.nrot = 1;
-    D.nset = 1;
-    D.s[0].key = key;
-    D.s[0].g = g;
-    D.nct = 1;
-    D.lift_cs = 0;
-    D.u_cs = 0;
-    for (int t = 0; t < ne; ++t) D.mod[t] = (uint8_t)ext_mod(level, t);
-    launch_inner_product(T, D, stream);
-    // ModDown
-    Jobs J;
-    J.base = u;
-    J.cstride = 0;
-    J.nct = 1;
-    J.n = 0;
-    for (int p = 0; p < 2; ++p)
-        for (int k = 0; k < n_p; ++k) {
-            J.off[J.n] = (uint16_t)(p * ne + nl + k);
-            J.mod[J.n] = (uint8_t)(n_q + k);
-            ++J.n;
-        }
-    launch_ntt(T, J, true, stream);
-    ConvDesc C;
-    memset(&C, 0, sizeof C);
-    C.nct = 1;
-    C.src = u + (size_t)nl * N;
-    C.src_pstride = (int64_t)ne * N;
-    C.dst = conv;
-    C.dst_pstride = (int64_t)nl * N;
-    C.tab = d_md_tab->p;
-    C.tab_ld = n_q;
-    C.ns = n_p;
-    C.nt = nl;
-    C.npoly = 2;
-    for (int s = 0; s < n_p; ++s) {
-        C.smod[s] = n_q + s;
-        C.hinv[s] = md_hinv[s];
-        C.hinv_sh[s] = md_hinv_sh[s];
-    }
-    for (int t = 0; t < nl; ++t) {
-        C.doff[t] = (uint16_t)t;
-        C.dmod[t] = (uint8_t)t;
-        C.tcol[t] = (uint16_t)t;
-    }
-    launch_baseconv(T, C, stream);
-    ntt(conv, 2, nl, nl, false, -1);
-    const u64* pinv = d_pinv->p;
-    launch_moddown_combine(T, nl, 1, u, 0, conv, 0, pinv, pinv + n_q, add0, 0, out0, 0, stream);
-    launch_moddown_combine(T, nl, 1, u + (size_t)ne * N, 0, conv + (size_t)nl * N, 0, pinv, pinv + n_q, add1, 0,
-                           out1, 0, stream);
-    cnt[C_KS]++;
+    DBuf lift(this, mu[level].size() * (size_t)ne * N), u(this, 2 * (size_t)ne * N), tmp(this, 2 * (size_t)nl * N);
+    ks_single_into(d, level, key, g, c0, add, out, lift.p, u.p, tmp.p);
 }
 
 CtPtr Ctx::relin(const CtData& a) {
     if (a.deg != 2) throw HeError(HE_EMISMATCH);
-    const int nl = a.level + 1;
-    const int64_t ps = (int64_t)nl * N;
     const u64* key = relin_key();
-    auto lift = ks_lift(a.buf->p + 2 * ps, a.level);
     CtPtr r = new_ct(a.level, 1, a.scale);
-    ks_apply(lift->p, a.level, key, 1, a.buf->p, a.buf->p + ps, r->buf->p, r->buf->p + ps);
+    ks_single(a.buf->p + 2 * (int64_t)(a.level + 1) * N, a.level, key, 1, nullptr, a.buf->p, r->buf->p);
     return r;
 }
 
 CtPtr Ctx::rescale(const CtData& a) {
     if (a.level < 1) throw HeError(HE_ELEVEL);
-    const int l = a.level, nl = l + 1, np = a.deg + 1;
-    const int64_t ps = (int64_t)nl * N;
-    DBuf last(this, (size_t)np * N);
-    for (int p = 0; p < np; ++p)
-        hip_check(hipMemcpyAsync(last.p + (size_t)p * N, a.buf->p + p * ps + (size_t)l * N, N * 8,
-                                 hipMemcpyDeviceToDevice, stream),
-                  "rs copy");
-    {
-        Jobs J;
-        J.base = last.p;
-        J.cstride = 0;
-        J.nct = 1;
-        J.n = np;
-        for (int p = 0; p < np; ++p) {
-            J.off[p] = (uint16_t)p;
-            J.mod[p] = (uint8_t)l;
-        }
-        launch_ntt(T, J, true, stream);
-    }
-    DBuf tmp(this, (size_t)np * l * N);
-    launch_rescale_spread(T, l, np, last.p, N, l, tmp.p, (int64_t)l * N, stream);
-    ntt(tmp.p, np, l, l, false, -1);
+    const int l = a.level;
     CtPtr r = new_ct(l - 1, a.deg, a.scale / (double)mods[l]);
-    const u64* qi = d_rs->p + (size_t)l * n_q;
-    const u64* qis = d_rs->p + (size_t)n_q * n_q + (size_t)l * n_q;
-    launch_rescale_combine(T, l, np, a.buf->p, ps, tmp.p, (int64_t)l * N, qi, qis, r->buf->p, (int64_t)l * N, stream);
+    rescale_into(a.buf->p, (int64_t)(l + 1) * N, l, a.deg + 1, 1, r->buf->p, (int64_t)l * N);
     cnt[C_RS]++;
-    return r;
-}
-
-CtPtr Ctx::rotate_from_lift(const CtData& a, const u64* lift, int64_t k) {
-    const u64 g = galois(k);
-    if (g == 1) return drop(a, a.level);
-    const u64* key = rot_key(g, false);
-    const int nl = a.level + 1;
-    const int64_t ps = (int64_t)nl * N;
-    CtPtr r = new_ct(a.level, 1, a.scale);
-    launch_automorph(T, nl, 1, r->buf->p, 0, a.buf->p, 0, g, stream);
-    ks_apply(lift, a.level, key, g, r->buf->p, nullptr, r->buf->p, r->buf->p + ps);
-    cnt[C_ROT]++;
     return r;
 }
 
@@ -912,9 +862,11 @@ CtPtr Ctx::rotate(const CtData& a, int64_t k) {
     if (a.deg != 1) throw HeError(HE_EMISMATCH);
     const u64 g = galois(k);
     if (g == 1) return drop(a, a.level);
-    rot_key(g, false);
-    auto lift = ks_lift(a.buf->p + (size_t)(a.level + 1) * N, a.level);
-    return rotate_from_lift(a, lift->p, k);
+    const u64* key = rot_key(g, false);
+    CtPtr r = new_ct(a.level, 1, a.scale);
+    ks_single(a.buf->p + (int64_t)(a.level + 1) * N, a.level, key, g, a.buf->p, nullptr, r->buf->p);
+    cnt[C_ROT]++;
+    return r;
 }
 
 CtPtr Ctx::mul_int(const CtData& a, int64_t k) {
@@ -1526,9 +1478,7 @@ he_status he_rotate_noalloc(he_ctx* ctx, const uint64_t* in, uint32_t level, int
         }
         const u64* key = c->rot_key(g, false);
         u64 *lift = c->scratch, *u = lift + lift_w, *tmp = u + u_w;
-        c->ks_lift_into(in + (size_t)nl * N, (int)level, lift, tmp);
-        launch_automorph(c->T, nl, 1, out, 0, in, 0, g, c->stream);
-        c->ks_apply_into(lift, (int)level, key, g, out, nullptr, out, out + (size_t)nl * N, u, tmp);
+        c->ks_single_into(in + (size_t)nl * N, (int)level, key, g, in, nullptr, out, lift, u, tmp);
         c->cnt[C_ROT]++;
     });
 }

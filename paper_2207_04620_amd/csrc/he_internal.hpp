@@ -221,7 +221,7 @@ struct Ctx {
     Pool pool_side;
     bool alloc_side = false;
     hm::Encoder enc;
-    std::vector<u64> mods, roots, pmod;
+    std::vector<u64> mods, roots, pmod, pmod_mont;  // pmod: P mod q_t, plain and in Montgomery form
     std::vector<ModP> host_mods;
     DevTables T{};
     u64 cdt[19];
@@ -230,6 +230,10 @@ struct Ctx {
         d_pinv, d_mu_tab, d_mu_scale, d_md_scale;
     std::vector<u64> md_hinv, md_hinv_sh;
     std::vector<std::vector<ModUpInfo>> mu;  // [level][digit]
+    // conversion plans per level (rings that conv_mfma_fits): ModUp of every digit, ModDown, rescale
+    std::vector<ConvPlan> plan_mu, plan_md, plan_rs;
+    std::unique_ptr<DBuf> d_plan_sets, d_plan_tab, d_rs_scale;
+    void build_plans();
     // keys
     std::unique_ptr<DBuf> s_eval, s2_eval, pk, rlk;
     std::map<u64, std::unique_ptr<DBuf>> rot_keys;
@@ -256,15 +260,18 @@ struct Ctx {
     CtPtr drop(const CtData& a, int level);
     CtPtr add_sub(const CtData& a, const CtData& b, bool sub);
     CtPtr tensor(const CtData& a, const CtData& b);
-    std::unique_ptr<DBuf> ks_lift(const u64* d, int level);
-    void ks_lift_into(const u64* d, int level, u64* lift, u64* coef);
-    void ks_apply_into(const u64* lift, int level, const u64* key, u64 g, const u64* add0, const u64* add1,
-                       u64* out0, u64* out1, u64* u, u64* conv);
-    void ks_apply(const u64* lift, int level, const u64* key, u64 g, const u64* add0, const u64* add1, u64* out0,
-                  u64* out1);
+    // key switching on caller buffers, for B members (lockstep groups, single ciphertexts and the
+    // allocation-free rotation alike)
+    void lift_into(const u64* d, int64_t d_cs, int B, int level, u64* lift, u64* coef);
+    void ip_into(u64* u, const u64* lift, const u64* own, int64_t own_cs, int B, int level,
+                 const std::vector<IpSet>& sets, int nrot, const u64* c0, int64_t c0_cs, bool accumulate);
+    void moddown_into(u64* u, u64* conv, int B, int level, const Epi& part);
+    void rescale_into(const u64* a, int64_t a_ps, int l, int np, int B, u64* out, int64_t out_ps);
+    void ks_single(const u64* d, int level, const u64* key, u64 g, const u64* c0, const u64* add, u64* out);
+    void ks_single_into(const u64* d, int level, const u64* key, u64 g, const u64* c0, const u64* add, u64* out,
+                        u64* lift, u64* u, u64* tmp);
     CtPtr relin(const CtData& a);
     CtPtr rescale(const CtData& a);
-    CtPtr rotate_from_lift(const CtData& a, const u64* lift, int64_t k);
     CtPtr rotate(const CtData& a, int64_t k);
     CtPtr mul_int(const CtData& a, int64_t k);
     std::unique_ptr<DBuf> plaintext_mont(const int64_t* coeffs);
@@ -366,6 +373,7 @@ struct Ctx {
         d_mods.reset(); d_psi.reset(); d_psi_sh.reset(); d_ipsi.reset(); d_ipsi_sh.reset();
         d_rtw.reset(); d_irtw.reset(); d_rtwd.reset(); d_irtwd.reset(); d_cold.reset(); d_icold.reset();
         d_mu_scale.reset(); d_md_scale.reset();
+        d_plan_sets.reset(); d_plan_tab.reset(); d_rs_scale.reset();
         d_rs.reset(); d_md_tab.reset(); d_pinv.reset(); d_mu_tab.reset();
         pool.trim();
         pool_side.trim();

@@ -1242,13 +1242,605 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(8))) void k
 }
 
 
+// ---- base conversion on the matrix cores, with the column passes on both sides of it in
+// registers: inverse column pass of the sources, conversion, forward column pass of the targets.
+//
+// out_t = sum_s y_s (D/q_s) mod q_t is a matrix product over the sources once every y_s (a
+// centred signed word) is written in signed bytes: y_s = sum_d y_sd 2^(8d), and with the
+// constants w_sdt = centred((D/q_s) 2^(8d) mod q_t) = sum_e w_sdte 2^(8e),
+//   out_t = sum_e 2^(8e) (sum_{s,d} w_sdte y_sd)   (mod q_t).
+// The inner sum is an int8 product with K = 8 sources, rows (t, e) and coefficients as
+// columns: v_mfma_i32_16x16x32_i8 for up to four sources, 16x16x64 for up to eight, |sum| <=
+// ns 2^17 < 2^21, so nothing is rounded or wraps.  The B operand of a lane (column l & 15, k block l >> 4) is
+// the byte form of one source word (two for more than four sources), so a lane builds it from
+// the coefficients it transformed itself; the rows are ordered so that a lane's accumulators of
+// two products (e = 0..3 and 4..7) are the digits of one target (l >> 4) of a set of four.
+//
+// A wave owns 16 columns of one polynomial: lane l loads the N1 = 2^L1 rows of column l & 15 of
+// source l >> 4 (128-byte segments), runs their inverse column stages and the scaling in
+// registers, and then for each set of four targets of its digit multiplies, reduces and runs the
+// forward column stages of target l >> 4 in registers too: only the twiddles are in LDS, and neither
+// the prepared sources nor an unconverted word cross memory.  It replaces the inverse column pass
+// (a read and a write of every source limb) and a conversion of 4 v_mad_i64_i32 per source and
+// output on the vector unit.  Bound: the vector unit, about 85 % busy in the butterflies and
+// reductions (3890 instructions per wave of a ModDown from 4 primes to 13); the matrix unit is
+// busy a sixth of the time.  Measured at N = 2^15 (14 + 4 limbs), per batched step of 16 h = 64
+// products: 7.7 ms for every ModUp, ModDown and rescale against 10.4 ms of inverse column passes
+// and conversions (and 0.5 ms of separate rescale kernels) before; one rotation 137 -> 84 us.
+// keeps the scheduler from moving work across: without it every stage's twiddles and every row's
+// products are hoisted to the front and the registers spill
+__device__ __forceinline__ void stage_fence() { __builtin_amdgcn_sched_barrier(0); }
+// keeps a value's computation before a following branch (the compiler otherwise sinks the rows'
+// reductions under the store's condition and holds every product's four accumulators until then)
+template <class V>
+__device__ __forceinline__ void keep_here(V& v) { asm volatile("" : "+v"(v)); }
+// a lane's word at a wave-uniform base and a 32-bit byte offset of its own: the base stays in scalar
+// registers, so the N1 row addresses of a column cost no vector registers
+template <class V>
+__device__ __forceinline__ const V* lane_at(const void* base, uint32_t off) {
+    return reinterpret_cast<const V*>(static_cast<const char*>(base) + off);
+}
+template <class V>
+__device__ __forceinline__ V* lane_at(u64* base, uint32_t off) {
+    return reinterpret_cast<V*>(reinterpret_cast<char*>(base) + off);
+}
+__device__ __forceinline__ f64x2 pair_d(u64x2 w) { return f64x2{bits_d(w.x), bits_d(w.y)}; }
+template <int L1>
+__device__ __forceinline__ void inv_col_regs_d(double (&x)[1 << L1], const u64x2* W, double q, double qinv) {
+#pragma clang fp contract(off)
+    // |x| <= q/2 + 1 first; five stages then stay within 16 q, as mulmod_d needs
+#pragma unroll
+    for (int k = 0; k < (1 << L1); ++k) x[k] = red_d(x[k], q, qinv);
+#pragma unroll
+    for (int st = L1 - 1; st >= 0; --st) {
+        stage_fence();
+        const int d = (1 << L1) >> (st + 1);
+#pragma unroll
+        for (int i = 0; i < (1 << st); ++i) {
+            const f64x2 w = pair_d(W[(1 << st) + i]);
+#pragma unroll
+            for (int j = i * 2 * d; j < i * 2 * d + d; ++j) {
+                const double U = x[j], V = x[j + d];
+                x[j] = U + V;
+                x[j + d] = mulmod_d(U - V, w.x, w.y, q);
+            }
+        }
+    }
+}
+template <int L1>
+__device__ __forceinline__ void fwd_col_regs_d(double (&x)[1 << L1], const u64x2* W, double q) {
+#pragma clang fp contract(off)
+#pragma unroll
+    for (int st = 0; st < L1; ++st) {
+        stage_fence();
+        const int d = (1 << L1) >> (st + 1);
+#pragma unroll
+        for (int i = 0; i < (1 << st); ++i) {
+            const f64x2 w = pair_d(W[(1 << st) + i]);
+#pragma unroll
+            for (int j = i * 2 * d; j < i * 2 * d + d; ++j) {
+                const double V = mulmod_d(x[j + d], w.x, w.y, q);
+                const double U = x[j];
+                x[j] = U + V;
+                x[j + d] = U - V;
+            }
+        }
+    }
+}
+template <int L1>
+__device__ __forceinline__ void inv_col_regs(u64 (&x)[1 << L1], const u64x2* W, u64 q) {
+    const u64 q2 = 2 * q;
+#pragma unroll
+    for (int st = L1 - 1; st >= 0; --st) {
+        stage_fence();
+        const int d = (1 << L1) >> (st + 1);
+#pragma unroll
+        for (int i = 0; i < (1 << st); ++i) {
+            const u64x2 w = W[(1 << st) + i];
+#pragma unroll
+            for (int j = i * 2 * d; j < i * 2 * d + d; ++j) {
+                const u64 U = x[j], V = x[j + d];
+                x[j] = red4(U + V, q2);
+                x[j + d] = mul_shoup_lazy(U - V + q2, w.x, w.y, q);
+            }
+        }
+    }
+}
+template <int L1>
+__device__ __forceinline__ void fwd_col_regs(u64 (&x)[1 << L1], const u64x2* W, u64 q) {
+    const u64 q2 = 2 * q;
+#pragma unroll
+    for (int st = 0; st < L1; ++st) {
+        stage_fence();
+        const int d = (1 << L1) >> (st + 1);
+#pragma unroll
+        for (int i = 0; i < (1 << st); ++i) {
+            const u64x2 w = W[(1 << st) + i];
+#pragma unroll
+            for (int j = i * 2 * d; j < i * 2 * d + d; ++j) {
+                const u64 U = red4(x[j], q2);
+                const u64 V = mul_shoup_lazy(x[j + d], w.x, w.y, q);
+                x[j] = U + V;
+                x[j + d] = U - V + q2;
+            }
+        }
+    }
+}
+
+// The same columns spread over SP = 4 or 2 lane groups: lane group v = (lane >> 4) mod SP holds the rows SP j + v
+// of a column, j < N1 / SP.  The stages of distance 1 (and 2 for SP = 4) pair lanes 16 (and 32)
+// apart; both lanes of a pair run the product, the lower one by the unit twiddle of entry 0.
+__device__ __forceinline__ double lane_xor_d(double x, int mask) { return __shfl_xor(x, mask, 64); }
+__device__ __forceinline__ u64 lane_xor_u(u64 x, int mask) { return __shfl_xor((unsigned long long)x, mask, 64); }
+// twiddle entry of element j in a cross-lane stage (distance 1 or 2)
+template <int SP>
+__device__ __forceinline__ int cross_twiddle(int st, int d, int j, int v) {
+    const bool up = v & d;
+    return up ? (1 << st) + ((SP * j + v) >> d) : 0;  // block (SP j + v) / (2 d), d = 1 or 2
+}
+template <int L1, int SP>
+__device__ __forceinline__ void inv_col_split_d(double (&x)[(1 << L1) / SP], const u64x2* W, int v, double q, double qinv) {
+#pragma clang fp contract(off)
+    constexpr int M = (1 << L1) / SP;
+#pragma unroll
+    for (int j = 0; j < M; ++j) x[j] = red_d(x[j], q, qinv);
+#pragma unroll
+    for (int st = L1 - 1; st >= 0; --st) {
+        stage_fence();
+        const int d = (1 << L1) >> (st + 1);
+        if (d < SP) {
+            const double sgn = (v & d) ? -1.0 : 1.0;
+#pragma unroll
+            for (int j = 0; j < M; ++j) {
+                const f64x2 w = pair_d(W[cross_twiddle<SP>(st, d, j, v)]);
+                const double s = __fma_rn(x[j], sgn, lane_xor_d(x[j], 16 * d));
+                x[j] = mulmod_d(s, w.x, w.y, q);
+            }
+        } else {
+            const int dj = d / SP;
+#pragma unroll
+            for (int i = 0; i < (1 << st); ++i) {
+                const f64x2 w = pair_d(W[(1 << st) + i]);
+#pragma unroll
+                for (int j = i * 2 * dj; j < i * 2 * dj + dj; ++j) {
+                    const double U = x[j], V = x[j + dj];
+                    x[j] = U + V;
+                    x[j + dj] = mulmod_d(U - V, w.x, w.y, q);
+                }
+            }
+        }
+    }
+}
+template <int L1, int SP>
+__device__ __forceinline__ void fwd_col_split_d(double (&x)[(1 << L1) / SP], const u64x2* W, int v, double q) {
+#pragma clang fp contract(off)
+    constexpr int M = (1 << L1) / SP;
+#pragma unroll
+    for (int st = 0; st < L1; ++st) {
+        stage_fence();
+        const int d = (1 << L1) >> (st + 1);
+        if (d < SP) {
+            const double sgn = (v & d) ? -1.0 : 1.0;
+#pragma unroll
+            for (int j = 0; j < M; ++j) {
+                const f64x2 w = pair_d(W[cross_twiddle<SP>(st, d, j, v)]);
+                const double t = mulmod_d(x[j], w.x, w.y, q);
+                x[j] = __fma_rn(t, sgn, lane_xor_d(t, 16 * d));
+            }
+        } else {
+            const int dj = d / SP;
+#pragma unroll
+            for (int i = 0; i < (1 << st); ++i) {
+                const f64x2 w = pair_d(W[(1 << st) + i]);
+#pragma unroll
+                for (int j = i * 2 * dj; j < i * 2 * dj + dj; ++j) {
+                    const double V = mulmod_d(x[j + dj], w.x, w.y, q);
+                    const double U = x[j];
+                    x[j] = U + V;
+                    x[j + dj] = U - V;
+                }
+            }
+        }
+    }
+}
+template <int L1, int SP>
+__device__ __forceinline__ void inv_col_split(u64 (&x)[(1 << L1) / SP], const u64x2* W, int v, u64 q) {
+    constexpr int M = (1 << L1) / SP;
+    const u64 q2 = 2 * q;
+#pragma unroll
+    for (int st = L1 - 1; st >= 0; --st) {
+        stage_fence();
+        const int d = (1 << L1) >> (st + 1);
+        if (d < SP) {
+            const bool up = v & d;
+#pragma unroll
+            for (int j = 0; j < M; ++j) {
+                const u64x2 w = W[cross_twiddle<SP>(st, d, j, v)];
+                const u64 o = lane_xor_u(x[j], 16 * d);
+                x[j] = mul_shoup_lazy(o + (up ? q2 - x[j] : x[j]), w.x, w.y, q);
+            }
+        } else {
+            const int dj = d / SP;
+#pragma unroll
+            for (int i = 0; i < (1 << st); ++i) {
+                const u64x2 w = W[(1 << st) + i];
+#pragma unroll
+                for (int j = i * 2 * dj; j < i * 2 * dj + dj; ++j) {
+                    const u64 U = x[j], V = x[j + dj];
+                    x[j] = red4(U + V, q2);
+                    x[j + dj] = mul_shoup_lazy(U - V + q2, w.x, w.y, q);
+                }
+            }
+        }
+    }
+}
+template <int L1, int SP>
+__device__ __forceinline__ void fwd_col_split(u64 (&x)[(1 << L1) / SP], const u64x2* W, int v, u64 q) {
+    constexpr int M = (1 << L1) / SP;
+    const u64 q2 = 2 * q;
+#pragma unroll
+    for (int st = 0; st < L1; ++st) {
+        stage_fence();
+        const int d = (1 << L1) >> (st + 1);
+        if (d < SP) {
+            const bool up = v & d;
+#pragma unroll
+            for (int j = 0; j < M; ++j) {
+                const u64x2 w = W[cross_twiddle<SP>(st, d, j, v)];
+                const u64 t = mul_shoup_lazy(x[j], w.x, w.y, q);
+                x[j] = lane_xor_u(t, 16 * d) + (up ? q2 - t : t);
+            }
+        } else {
+            const int dj = d / SP;
+#pragma unroll
+            for (int i = 0; i < (1 << st); ++i) {
+                const u64x2 w = W[(1 << st) + i];
+#pragma unroll
+                for (int j = i * 2 * dj; j < i * 2 * dj + dj; ++j) {
+                    const u64 U = red4(x[j], q2);
+                    const u64 V = mul_shoup_lazy(x[j + dj], w.x, w.y, q);
+                    x[j] = U + V;
+                    x[j + dj] = U - V + q2;
+                }
+            }
+        }
+    }
+}
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+#define BYTE_BIAS 0x8080808080808080ull
+// a signed word |y| < 2^63 - 2^62 as eight signed bytes, y = sum_d byte_d 2^(8d)
+__device__ __forceinline__ u64 signed_bytes(u64 y) { return (y + BYTE_BIAS) ^ BYTE_BIAS; }
+
+// two products of K = 32 for more than four sources: one of K = 64 is half the matrix time, but
+// its operands are aligned register quads, which spill here (the vector unit is the busier one)
+template <int KS>
+__device__ __forceinline__ i32x4 mfma_bytes(const u64 (&a)[KS], const u64 (&b)[KS], i32x4 acc) {
+#pragma unroll
+    for (int k = 0; k < KS; ++k) acc = __builtin_amdgcn_mfma_i32_16x16x32_i8((long)a[k], (long)b[k], acc, 0, 0, 0);
+    return acc;
+}
+
+// sum_{e<6} a_e 2^(8e) mod q for an FP64 target, |a_e| <= 2^20: p_i = a_2i + 2^8 a_2i+1 in 32
+// bits, then p2 2^32 - rint(p2 2^32 / q) q exactly (one FMA), plus p0 + 2^16 p1 (below 2^44.1).
+// The result is below q/2 + 1 + 2^44.1, under 4q for q >= 2^43; smaller primes reduce once more
+__device__ __forceinline__ double digits_mod_d(i32x4 lo, i32x4 hi, double q, double qinv, bool small) {
+#pragma clang fp contract(off)
+    const double p0 = (double)(lo.x + (lo.y << 8)), p1 = (double)(lo.z + (lo.w << 8)),
+                 p2 = (double)(hi.x + (hi.y << 8)) * 4294967296.0;
+    double x = __fma_rn(-rint(p2 * qinv), q, p2) + __fma_rn(p1, 65536.0, p0);
+    if (small) x = red_d(x, q, qinv);
+    return x;
+}
+// sum_{e<8} a_e 2^(8e) mod q in [0, 4q) for an integer target (q > 2^46): V = H 2^32 + L with
+// |H|, |L| < 2^45; (H + 2^45) 2^32 by one lazy Shoup product (< 2q), L and the constant c = -2^77 mod
+// q (taken in [2^45, q + 2^45)) added
+__device__ __forceinline__ u64 digits_mod(i32x4 lo, i32x4 hi, u64 q, u64 w, u64 w_sh, u64 c) {
+    const int64_t L = (int64_t)(lo.x + (lo.y << 8)) + ((int64_t)(lo.z + (lo.w << 8)) << 16);
+    const int64_t H = (int64_t)(hi.x + (hi.y << 8)) + ((int64_t)(hi.z + (hi.w << 8)) << 16);
+    return mul_shoup_lazy((u64)(H + (1ll << 45)), w, w_sh, q) + (u64)L + c;
+}
+
+// f(0), ..., f(N - 1) with compile-time arguments (the unroller gives up on 32 rows)
+template <class F, int... I>
+__device__ __forceinline__ void unrolled_seq(F&& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void unrolled(F&& f) {
+    unrolled_seq(f, std::make_integer_sequence<int, N>{});
+}
+
+// Source words of the rows SP j + v (v = lane group mod SP; SP = 1: every row) of one source limb: row
+// pass output at src (uniform) + so bytes, inverse column stages, scaling (f = 0 drops the source),
+// centred, in signed bytes
+template <int L1, int SP>
+__device__ __forceinline__ void conv_source(u64 (&b)[(1 << L1) / SP], const ModP& m, const u64* src, uint32_t so,
+                                            const u64x2* W, int v, u64 f, u64 fs) {
+    constexpr int M = (1 << L1) / SP, N2 = NTT_E;
+    const u64 q = m.q;
+    so += (uint32_t)v * (N2 * 8u);
+    if (fp64_limb(q, L1, N2)) {
+        const double qd = (double)q, qinv = 1.0 / qd, fd = (double)f, fq = fd / qd;
+        double x[M];
+        unrolled<M>([&](auto j) { x[j] = *lane_at<double>(src + j * (SP * N2), so); });
+        if constexpr (SP == 1) inv_col_regs_d<L1>(x, W, qd, qinv);
+        else inv_col_split_d<L1, SP>(x, W, v, qd, qinv);
+        unrolled<M>([&](auto j) {
+            // centred exactly: |x f mod q| < q, so rint of the quotient is exact; as a word, the
+            // bits of y + 1.5 2^52 less those of 1.5 2^52
+            if (j % 4 == 0) stage_fence();
+            const double y = red_d(mulmod_d(x[j], fd, fq, qd), qd, qinv);
+            b[j] = signed_bytes(d_bits(y + 6755399441055744.0) - 0x4338000000000000ull);
+            keep_here(b[j]);
+        });
+    } else {
+        u64 x[M];
+        unrolled<M>([&](auto j) { x[j] = *lane_at<u64>(src + j * (SP * N2), so); });
+        if constexpr (SP == 1) inv_col_regs<L1>(x, W, q);
+        else inv_col_split<L1, SP>(x, W, v, q);
+        unrolled<M>([&](auto j) {
+            if (j % 2 == 0) stage_fence();
+            const u64 y = mul_shoup(x[j], f, fs, q);
+            b[j] = signed_bytes(y > m.half ? y - q : y);
+            keep_here(b[j]);
+        });
+    }
+}
+
+// XS: lane groups that share one of the sources beyond the fourth (0: at most four sources; 4: five;
+// 2: six; 1: up to eight).  With XS > 1 a lane holds such a source's words for every XS-th row only,
+// and the operand of row r takes them from the k block that has that row (the others give zero; the
+// constants are repeated over the XS k blocks), so the fifth source costs a quarter of the others.
+constexpr int conv_waves(int L1, int XS) {
+    return L1 <= 2 ? 6 : L1 == 3 ? (XS == 1 ? 4 : 5) : L1 == 4 ? (XS == 1 ? 3 : 4) : 2;
+}
+template <int L1, int XS>
+__global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(conv_waves(L1, XS)))) void k_conv_mfma(
+    DevTables T, ConvPlanDesc D) {
+    constexpr int N1 = 1 << L1, KS = XS ? 2 : 1, M1 = XS ? N1 / (XS ? XS : 1) : 1;
+    const int N = 1 << T.log_n, N2 = NTT_E;
+    const int lane = threadIdx.x & 63, grp = lane >> 4;
+    // blocks of one column group (all items of it) run back to back on one XCD
+    constexpr int TILES = NTT_E / 64;  // column groups of 4 waves
+    const int lb = blockIdx.x, j8 = lb >> 3;
+    const int pair = (j8 / D.nitem) * 8 + (lb & 7), item = j8 % D.nitem;
+    const int x0 = pair % TILES, pc = pair / TILES, p = pc % D.npoly, c = pc / D.npoly;
+    const int col = x0 * 64 + (threadIdx.x >> 6) * 16 + (lane & 15);
+    const ConvDig dg = D.dig[D.it_dig[item]];
+
+    // twiddles of the sources and of the item's targets into LDS, as (w, companion) pairs: one row of
+    // N1 (and a pad pair) per limb.  Read from global memory they cost the column stages 15 loads of
+    // 16 bytes per lane and target, which filled the CU's one address unit
+    constexpr int LD = N1 + 1;
+    extern __shared__ u64x2 tw[];
+    const int s0 = D.it_s0[item], s1 = D.it_s1[item], rows = dg.ns + 4 * (s1 - s0);
+    for (int e = threadIdx.x; e < rows * N1; e += TPB) {
+        const int r = e >> L1, i = e & (N1 - 1);
+        const bool inv = r < dg.ns;
+        const int k = r - dg.ns, mi = inv ? dg.smod + r : D.sets[s0 + (k >> 2)].dmod[k & 3];
+        u64x2 w;
+        if (fp64_limb(T.mods[mi].q, L1, N2)) {
+            w = ld2(reinterpret_cast<const u64*>(inv ? T.icold : T.cold) + 2 * (mi * N1 + i));
+        } else {
+            w.x = (inv ? T.ipsi : T.psi)[(int64_t)mi * N + i];
+            w.y = (inv ? T.ipsi_sh : T.psi_sh)[(int64_t)mi * N + i];
+        }
+        tw[r * LD + i] = w;
+    }
+    __syncthreads();
+
+    // the lane's sources in signed bytes: source grp of the digit, and its share of one beyond the
+    // fourth; lanes without a source repeat the first, times zero
+    const u64* src = D.src + c * D.src_cs + p * D.src_ps;  // uniform
+    u64 b0[N1], b1[M1];
+    const auto source = [&](auto sp, auto& b, int s) {
+        constexpr int SP = sp;
+        const bool has = s < dg.ns;
+        s = has ? s : 0;
+        const u64 f = has ? D.scale[2 * (dg.slo + s)] : 0, fs = has ? D.scale[2 * (dg.slo + s) + 1] : 0;
+        conv_source<L1, SP>(b, T.mods[dg.smod + s], src, ((uint32_t)(dg.slo + s) * N + col) * 8u, tw + s * LD,
+                            grp & (SP - 1), f, fs);
+    };
+    source(std::integral_constant<int, 1>{}, b0, grp);
+    if constexpr (XS != 0) source(std::integral_constant<int, XS>{}, b1, 4 + grp / XS);
+    // the operand of row r (share is remade opaquely for every set: known to be the same, the selected
+    // words of all rows would be kept across the sets, in registers that are not there)
+    int share = grp & (XS ? XS - 1 : 0);
+    const auto operand = [&](auto row, u64(&b)[KS]) {
+        constexpr int r = row;
+        b[0] = b0[r];
+        if constexpr (XS == 1) b[1] = b1[r];
+        else if constexpr (XS > 1) b[1] = share == (r & (XS - 1)) ? b1[r / XS] : 0;
+    };
+
+    u64* dst = D.dst + c * D.dst_cs + p * D.dst_ps;  // uniform
+    for (int si = s0; si < s1; ++si) {
+        if constexpr (XS > 1) keep_here(share);
+        const ConvSet& S = D.sets[si];
+        const u64* ta = D.tab + S.tab + lane * KS;
+        u64 a0[KS], a1[KS];
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            a0[k] = ta[k];
+            a1[k] = ta[64 * KS + k];
+        }
+        const u64 q = T.mods[S.dmod[grp]].q;
+        const double qd = (double)q, qinv = 1.0 / qd;
+        const bool small = S.small;
+        const u64 w32 = S.w32[grp], w32s = S.w32_sh[grp], cc = S.off[grp];
+        const u64x2* W = tw + (dg.ns + 4 * (si - s0) + grp) * LD;
+        uint32_t od = ((uint32_t)S.doff[grp] * N + col) * 8u;
+        if (N1 >= 4 && S.nt == 1) {
+            // one target: its rows are spread over the four lane groups (the set's operands and
+            // descriptors repeat it): row group v of the product takes row 4 j + v, four products by
+            // the operand masked to that row group
+            constexpr int M = N1 >= 4 ? N1 / 4 : 1;
+            i32x4 lo[M], hi[M];
+            const i32x4 zero = {0, 0, 0, 0};
+            unrolled<M>([&](auto j) { lo[j] = hi[j] = zero; });
+            unrolled<4>([&](auto v) {
+                stage_fence();
+                u64 m0[KS], m1[KS];
+#pragma unroll
+                for (int k = 0; k < KS; ++k) {
+                    const bool mine = ((lane >> 2) & 3) == v;
+                    m0[k] = mine ? a0[k] : 0;
+                    m1[k] = mine ? a1[k] : 0;
+                }
+                unrolled<M>([&](auto j) {
+                    u64 b[KS];
+                    operand(std::integral_constant<int, (N1 >= 4 ? 4 * j + v : 0)>{}, b);
+                    lo[j] = mfma_bytes<KS>(m0, b, lo[j]);
+                    hi[j] = mfma_bytes<KS>(m1, b, hi[j]);
+                });
+            });
+            od += (uint32_t)grp * (N2 * 8u);
+            if constexpr (N1 >= 4) {
+                if (S.fp) {
+                    double x[M];
+                    unrolled<M>([&](auto j) { x[j] = digits_mod_d(lo[j], hi[j], qd, qinv, small); });
+                    fwd_col_split_d<L1, 4>(x, W, grp, qd);
+                    unrolled<M>([&](auto j) { *lane_at<u64>(dst + j * (4 * N2), od) = d_bits(x[j]); });
+                } else {
+                    u64 x[M];
+                    unrolled<M>([&](auto j) { x[j] = digits_mod(lo[j], hi[j], q, w32, w32s, cc); });
+                    fwd_col_split<L1, 4>(x, W, grp, q);
+                    unrolled<M>([&](auto j) { *lane_at<u64>(dst + j * (4 * N2), od) = x[j]; });
+                }
+            }
+        } else if (S.fp) {
+            double x[N1];
+            unrolled<N1>([&](auto r) {
+                if (r % 2 == 0) stage_fence();
+                u64 b[KS];
+                operand(r, b);
+                x[r] = digits_mod_d(mfma_bytes<KS>(a0, b, i32x4{0, 0, 0, 0}), mfma_bytes<KS>(a1, b, i32x4{0, 0, 0, 0}), qd,
+                                    qinv, small);
+                keep_here(x[r]);
+            });
+            fwd_col_regs_d<L1>(x, W, qd);
+            unrolled<N1>([&](auto r) { keep_here(x[r]); });
+            if (grp < S.nt) unrolled<N1>([&](auto r) { *lane_at<u64>(dst + r * N2, od) = d_bits(x[r]); });
+        } else {
+            u64 x[N1];
+            unrolled<N1>([&](auto r) {
+                if (r % 2 == 0) stage_fence();
+                u64 b[KS];
+                operand(r, b);
+                x[r] = digits_mod(mfma_bytes<KS>(a0, b, i32x4{0, 0, 0, 0}), mfma_bytes<KS>(a1, b, i32x4{0, 0, 0, 0}), q, w32,
+                                  w32s, cc);
+                keep_here(x[r]);
+            });
+            fwd_col_regs<L1>(x, W, q);
+            unrolled<N1>([&](auto r) { keep_here(x[r]); });
+            if (grp < S.nt) unrolled<N1>([&](auto r) { *lane_at<u64>(dst + r * N2, od) = x[r]; });
+        }
+    }
+}
+
+int conv_mfma_share(const DevTables& T, int ns) {
+    if (ns <= 4) return 0;
+    return T.n1_log < 3 || ns > 6 ? 1 : ns == 5 ? 4 : 2;
+}
+// With five column stages (N = 2^16) a lane's 32 rows of up to eight sources leave two waves per
+// SIMD, and the conversions of five and six sources took 190 and 262 us where k_conv_cols and the
+// inverse column pass took 130 and 198 (16 members, 17 + 5 limbs); a rescale's single source is 120
+// us against 250 for the separate passes.
+bool conv_mfma_fits(const DevTables& T) { return T.n2_log == 11 && T.n1_log >= 1 && T.n1_log <= 4; }
+bool rescale_mfma_fits(const DevTables& T) { return T.n2_log == 11 && T.n1_log >= 1 && T.n1_log <= 5; }
+
+template <int L1>
+static void launch_conv_mfma_l(int xs, dim3 grid, int limbs, hipStream_t st, const DevTables& T, const ConvPlanDesc& D) {
+    const size_t lds = (size_t)limbs * ((1 << L1) + 1) * sizeof(u64x2);
+    switch (xs) {
+        case 0: HE_LAUNCH((k_conv_mfma<L1, 0>), grid, dim3(TPB), lds, st, T, D); return;
+        case 1:
+            if constexpr (L1 <= 4) {
+                HE_LAUNCH((k_conv_mfma<L1, 1>), grid, dim3(TPB), lds, st, T, D);
+                return;
+            }
+            break;
+        case 2:
+            if constexpr (L1 == 3 || L1 == 4) {
+                HE_LAUNCH((k_conv_mfma<L1, 2>), grid, dim3(TPB), lds, st, T, D);
+                return;
+            }
+            break;
+        case 4:
+            if constexpr (L1 == 3 || L1 == 4) {
+                HE_LAUNCH((k_conv_mfma<L1, 4>), grid, dim3(TPB), lds, st, T, D);
+                return;
+            }
+            break;
+    }
+    throw std::runtime_error("conversion plan: unsupported shape");
+}
+
+void launch_conv_mfma(const DevTables& T, const ConvPlan& P, const u64* src, int64_t src_ps, int64_t src_cs, u64* dst,
+                      int64_t dst_ps, int64_t dst_cs, int npoly, int nct, hipStream_t st) {
+    if (npoly * nct == 0 || P.nset == 0) return;
+    if (!rescale_mfma_fits(T) || P.ndig < 1 || P.ndig > HE_MAXDIG)
+        throw std::runtime_error("conversion plan: unsupported shape");
+    const int N = 1 << T.log_n;
+    ConvPlanDesc D;
+    D.src = src;
+    D.src_ps = src_ps;
+    D.src_cs = src_cs;
+    D.dst = dst;
+    D.dst_ps = dst_ps;
+    D.dst_cs = dst_cs;
+    D.scale = P.scale;
+    D.tab = P.tab;
+    D.sets = P.sets;
+    D.npoly = npoly;
+    for (int d = 0; d < P.ndig; ++d) D.dig[d] = P.dig[d];
+    // sets per wave: all of a digit's when the waves fill the device (the sources are then
+    // transformed once), one or a few when they do not
+    const int64_t waves = (int64_t)(NTT_E / 16) * npoly * nct;
+    int per = HE_MAXT;
+    while (per > 1) {
+        int items = 0;
+        for (int d = 0; d < P.ndig; ++d) items += (int)ceil_div(P.dig[d].nset, per);
+        if (waves * items >= CONV_WAVES) break;
+        int next = 0;
+        for (int d = 0; d < P.ndig; ++d) next += (int)ceil_div(P.dig[d].nset, per - 1);
+        if (next > CONV_MAXITEM) break;
+        --per;
+    }
+    D.nitem = 0;
+    int limbs = 0;  // twiddle rows of the largest item
+    for (int d = 0; d < P.ndig; ++d)
+        limbs = std::max(limbs, P.dig[d].ns + 4 * std::min(P.dig[d].nset, per));
+    for (int d = 0; d < P.ndig; ++d)
+        for (int s = 0; s < P.dig[d].nset; s += per) {
+            if (D.nitem == CONV_MAXITEM) throw std::runtime_error("conversion plan: too many items");
+            D.it_dig[D.nitem] = (uint8_t)d;
+            D.it_s0[D.nitem] = (uint8_t)(P.dig[d].set0 + s);
+            D.it_s1[D.nitem] = (uint8_t)(P.dig[d].set0 + std::min(P.dig[d].nset, s + per));
+            ++D.nitem;
+        }
+    const double pc = (double)npoly * nct;
+    ProfScope prof_(PK_CONV_COLS, (P.src_limbs + P.dst_limbs) * pc * 8.0 * N, st,
+                    (P.src_limbs + P.dst_limbs) * pc * (N / 2) * T.n1_log, P.fp_limbs * pc * (N / 2) * T.n1_log);
+    dim3 grid((unsigned)((int64_t)(NTT_E / 64) * npoly * nct * D.nitem));
+    switch (T.n1_log) {
+        case 1: launch_conv_mfma_l<1>(P.xs, grid, limbs, st, T, D); break;
+        case 2: launch_conv_mfma_l<2>(P.xs, grid, limbs, st, T, D); break;
+        case 3: launch_conv_mfma_l<3>(P.xs, grid, limbs, st, T, D); break;
+        case 4: launch_conv_mfma_l<4>(P.xs, grid, limbs, st, T, D); break;
+        default: launch_conv_mfma_l<5>(P.xs, grid, limbs, st, T, D); break;
+    }
+}
+
+
 // the NTT kernels move two residues per lane with 16-byte accesses
 static void check_ntt_alignment(const Jobs& J, const Epi* E) {
     bool bad = misaligned16(J.base) || (J.cstride & 1);
     if (E && E->on) {
         bad = bad || misaligned16(E->u) || ((E->u_cs | E->u_ps | E->add_cs | E->out_cs | E->acc_cs) & 1) ||
               misaligned16(E->mask);
-        for (int p = 0; p < 2; ++p) bad = bad || misaligned16(E->add[p]) || misaligned16(E->out[p]) ||
+        for (int p = 0; p < 3; ++p) bad = bad || misaligned16(E->add[p]) || misaligned16(E->out[p]) ||
                                           misaligned16(E->acc[p]);
     }
     if (bad) throw std::runtime_error("NTT operand not 16-byte aligned");
@@ -1273,7 +1865,8 @@ void launch_ntt_moddown(const DevTables& T, const Jobs& J, const Epi& E, hipStre
     }
     // reads the converted limb and u, writes the output; plus the optional add and
     // accumulator operands (per ciphertext) and the mask (shared by the group)
-    const double per_ct = (E.add[0] ? 1 : 0) + (E.add[1] ? 1 : 0) + (E.acc[0] ? 1 : 0) + (E.acc[1] ? 1 : 0);
+    double per_ct = 0;
+    for (int p = 0; p < 3; ++p) per_ct += (E.add[p] ? 1 : 0) + (E.acc[p] ? 1 : 0);
     const double rows_bytes = 8.0 * N * (3 * limbs + per_ct * E.nl * J.nct + (E.mask ? E.nl : 0));
     ProfScope p(PK_NTT_FWD_ROWS, rows_bytes, st, limbs * (N / 2) * T.n2_log, fl * (N / 2) * T.n2_log);
     if (!E.on) throw std::runtime_error("ModDown row pass without its epilogue");
@@ -1306,7 +1899,7 @@ void launch_ntt(const DevTables& T, const Jobs& J, bool inverse, hipStream_t st,
             ProfScope p(PK_NTT_INV_ROWS, bytes, st, b2, f2);
             HE_LAUNCH(k_ntt_inv_rows, grid_rows, dim3(TPB), 0, st, T, J, scale, scale_n);
         }
-        if (T.n1_log > 0) {
+        if (T.n1_log > 0 && cols) {
             ProfScope p(PK_NTT_INV_COLS, bytes, st, b1, f1);
             HE_LAUNCH(k_ntt_inv_cols, grid_cols, dim3(TPB), 0, st, T, J, scale, scale_n);
         }
@@ -1947,36 +2540,6 @@ void launch_inner_product(const DevTables& T, const IpDesc& D, hipStream_t st) {
     }
 }
 
-__global__ __launch_bounds__(TPB) void k_moddown_combine(DevTables T, int npoly, const u64* u, int64_t u_ps,
-                                                         const u64* conv, int64_t conv_ps, const u64* pinv,
-                                                         const u64* pinv_sh, const u64* add, int64_t add_ps,
-                                                         u64* out, int64_t out_ps, int64_t u_cs, int64_t conv_cs,
-                                                         int64_t add_cs, int64_t out_cs) {
-    const int N = 1 << T.log_n;
-    const int i = blockIdx.x * TPB + threadIdx.x;
-    const int l = blockIdx.y, p = blockIdx.z % npoly, c = blockIdx.z / npoly;
-    u += c * u_cs;
-    conv += c * conv_cs;
-    if (add) add += c * add_cs;
-    out += c * out_cs;
-    const u64 q = T.mods[l].q;
-    const int64_t o = (int64_t)l * N + i;
-    u64 v = mul_shoup(sub_mod(u[p * u_ps + o], conv[p * conv_ps + o], q), pinv[l], pinv_sh[l], q);
-    if (add) v = add_mod(v, add[p * add_ps + o], q);
-    out[p * out_ps + o] = v;
-}
-
-void launch_moddown_combine(const DevTables& T, int nl, int npoly, const u64* u, int64_t u_ps, const u64* conv,
-                            int64_t conv_ps, const u64* pinv, const u64* pinv_sh, const u64* add, int64_t add_ps,
-                            u64* out, int64_t out_ps, hipStream_t st, int nct, int64_t u_cs, int64_t conv_cs,
-                            int64_t add_cs, int64_t out_cs) {
-    ProfScope prof_(PK_MODDOWN, (add ? 4.0 : 3.0) * nl * npoly * nct * 8.0 * (1 << T.log_n), st);
-    const int N = 1 << T.log_n;
-    dim3 grid(ceil_div(N, TPB), nl, npoly * nct);
-    HE_LAUNCH(k_moddown_combine, grid, dim3(TPB), 0, st, T, npoly, u, u_ps, conv, conv_ps, pinv, pinv_sh,
-                       add, add_ps, out, out_ps, u_cs, conv_cs, add_cs, out_cs);
-}
-
 // ------------------------------------------------------------------ n-ary sum
 __global__ __launch_bounds__(TPB) void k_sum_many(DevTables T, SumDesc D, u64* out, int64_t out_ps, int accumulate) {
     const int N = 1 << T.log_n;
@@ -2016,29 +2579,6 @@ void launch_rescale_spread(const DevTables& T, int nl_out, int npoly, const u64*
     const int N = 1 << T.log_n;
     dim3 grid(ceil_div(N, TPB), nl_out, npoly);
     HE_LAUNCH(k_rescale_spread, grid, dim3(TPB), 0, st, T, last, last_ps, last_mod, tmp, tmp_ps);
-}
-
-__global__ __launch_bounds__(TPB) void k_rescale_combine(DevTables T, int npoly, const u64* c, int64_t c_ps,
-                                                         const u64* tmp, int64_t tmp_ps, const u64* qinv,
-                                                         const u64* qinv_sh, u64* out, int64_t out_ps, int64_t c_cs,
-                                                         int64_t tmp_cs, int64_t out_cs) {
-    const int N = 1 << T.log_n;
-    const int i = blockIdx.x * TPB + threadIdx.x;
-    const int l = blockIdx.y, p = blockIdx.z % npoly, ct = blockIdx.z / npoly;
-    const u64 q = T.mods[l].q;
-    const int64_t o = (int64_t)l * N + i;
-    out[ct * out_cs + p * out_ps + o] =
-        mul_shoup(sub_mod(c[ct * c_cs + p * c_ps + o], tmp[ct * tmp_cs + p * tmp_ps + o], q), qinv[l], qinv_sh[l], q);
-}
-
-void launch_rescale_combine(const DevTables& T, int nl_out, int npoly, const u64* c, int64_t c_ps, const u64* tmp,
-                            int64_t tmp_ps, const u64* qinv, const u64* qinv_sh, u64* out, int64_t out_ps,
-                            hipStream_t st, int nct, int64_t c_cs, int64_t tmp_cs, int64_t out_cs) {
-    ProfScope prof_(PK_RS_COMBINE, 3.0 * nl_out * npoly * nct * 8.0 * (1 << T.log_n), st);
-    const int N = 1 << T.log_n;
-    dim3 grid(ceil_div(N, TPB), nl_out, npoly * nct);
-    HE_LAUNCH(k_rescale_combine, grid, dim3(TPB), 0, st, T, npoly, c, c_ps, tmp, tmp_ps, qinv, qinv_sh, out,
-                       out_ps, c_cs, tmp_cs, out_cs);
 }
 
 // ------------------------------------------------------------------ products

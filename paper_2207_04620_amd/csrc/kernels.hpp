@@ -113,6 +113,49 @@ struct ConvDesc {
     uint8_t tdig[HE_MAXT];
 };
 
+// Conversion plans (k_conv_mfma): which sources go to which targets, and the byte-digit constants
+// in the matrix unit's operand layout.  Built once per context for every ModUp, ModDown and
+// rescale level; the sets and tables live in device memory.
+// A set: up to four targets of one digit, all FP64 limbs or all integer limbs.
+struct ConvSet {
+    uint32_t tab;        // A operands of the set: words tab .. tab + 128 (xs ? 2 : 1) of the plan's table
+    uint16_t doff[4];    // target limb offset from dst, in limbs
+    uint8_t dmod[4];     // its prime (a missing target repeats the first)
+    uint8_t nt, fp, small, pad;
+    u64 w32[4], w32_sh[4], off[4];  // integer targets: 2^32 mod q (Shoup pair), the offset of digits_mod
+};
+// A digit: ns consecutive source limbs from slo (prime smod + s), converted to nset sets
+struct ConvDig {
+    int slo, ns, smod, set0, nset;
+};
+struct ConvPlan {
+    int ndig = 0, nset = 0;
+    int xs = 0;  // how the sources beyond the fourth are shared out (conv_mfma_share of the widest digit)
+    ConvDig dig[HE_MAXDIG];
+    const ConvSet* sets = nullptr;
+    const u64* tab = nullptr;
+    const u64* scale = nullptr;  // per source limb: N^-1 (D/q_s)^-1 as a Shoup pair
+    double src_limbs = 0, dst_limbs = 0, fp_limbs = 0;
+};
+#define CONV_MAXITEM 64
+// A digit's sets are split over waves only while a launch has fewer waves than this (each wave
+// transforms its sources again): at N = 2^15, 16 members, a ModUp takes 98 us unsplit and 117 split to
+// 8192 waves; five members' ModDowns 35 us at this line, 42 at 8192; one member's ModUp 21 us, 28 at 512
+#ifndef CONV_WAVES
+#define CONV_WAVES 1024
+#endif
+struct ConvPlanDesc {
+    const u64* src;
+    u64* dst;
+    int64_t src_ps, src_cs, dst_ps, dst_cs;
+    const u64* scale;
+    const u64* tab;
+    const ConvSet* sets;
+    int npoly, nitem;
+    ConvDig dig[HE_MAXDIG];
+    uint8_t it_dig[CONV_MAXITEM], it_s0[CONV_MAXITEM], it_s1[CONV_MAXITEM];  // a wave's digit and sets
+};
+
 struct SampleArgs {
     u64 seed;
     uint32_t purpose;
@@ -221,8 +264,8 @@ struct Epi {
     int nl;
     const u64* u;
     int64_t u_cs, u_ps;
-    const u64* add[2];
-    u64* out[2];
+    const u64* add[3];
+    u64* out[3];
     int64_t add_cs, out_cs;
     const u64* pinv;
     const u64* pinv_sh;
@@ -230,7 +273,7 @@ struct Epi {
     // optional Mul_pt fused into the epilogue: out = w * mask (Montgomery form, rows = limbs)
     // (+ acc_p[c][t][i] when acc_p is set): one term of a diagonal sum (Eq. 1)
     const u64* mask;
-    const u64* acc[2];
+    const u64* acc[3];
     int64_t acc_cs;
 };
 
@@ -277,6 +320,15 @@ void launch_baseconv(const DevTables& T, const ConvDesc& D, hipStream_t st);
 // base conversion of prescaled sources fused with the forward column pass of every target
 // (N > 2^11); the row pass is then run with launch_ntt(..., cols = false)
 bool conv_cols_fits(const DevTables& T, int ns);
+// inverse column pass, conversion and forward column pass of a plan in one launch, for rings with
+// 2048-element rows and one to five column stages; sources as the inverse row pass leaves them
+// (launch_ntt(..., inverse, ..., cols = false)), targets as the forward row pass takes them
+bool conv_mfma_fits(const DevTables& T);     // for ModUp and ModDown
+bool rescale_mfma_fits(const DevTables& T);  // for rescales
+// k blocks that repeat one source beyond the fourth in the operands, for digits of up to ns sources (0: none)
+int conv_mfma_share(const DevTables& T, int ns);
+void launch_conv_mfma(const DevTables& T, const ConvPlan& P, const u64* src, int64_t src_ps, int64_t src_cs, u64* dst,
+                      int64_t dst_ps, int64_t dst_cs, int npoly, int nct, hipStream_t st);
 void launch_conv_cols(const DevTables& T, const ConvDesc& D, hipStream_t st);
 void launch_sample(const DevTables& T, const Jobs& J, const SampleArgs& A, hipStream_t st);
 // the regions of D (start[] is filled here)
@@ -297,18 +349,9 @@ void launch_to_mont(const DevTables& T, ModMap mm, int nl, int npoly, u64* x, in
 void launch_swk_finish(const DevTables& T, int M, u64* b, const u64* a, const u64* e, const u64* s,
                        const u64* sp, const u64* pmod, const uint8_t* in_digit, hipStream_t st);
 void launch_inner_product(const DevTables& T, const IpDesc& D, hipStream_t st);
-// out[p][t] = (u[p][t] - conv[p][t]) * Pinv_t (+ add[p][t])
-void launch_moddown_combine(const DevTables& T, int nl, int npoly, const u64* u, int64_t u_ps, const u64* conv,
-                            int64_t conv_ps, const u64* pinv, const u64* pinv_sh, const u64* add, int64_t add_ps,
-                            u64* out, int64_t out_ps, hipStream_t st, int nct = 1, int64_t u_cs = 0,
-                            int64_t conv_cs = 0, int64_t add_cs = 0, int64_t out_cs = 0);
 // tmp[p][i] = centered(last[p]) mod q_i (coefficient form)
 void launch_rescale_spread(const DevTables& T, int nl_out, int npoly, const u64* last, int64_t last_ps,
                            int last_mod, u64* tmp, int64_t tmp_ps, hipStream_t st);
-// out[p][i] = (c[p][i] - tmp[p][i]) * qinv_i
-void launch_rescale_combine(const DevTables& T, int nl_out, int npoly, const u64* c, int64_t c_ps, const u64* tmp,
-                            int64_t tmp_ps, const u64* qinv, const u64* qinv_sh, u64* out, int64_t out_ps,
-                            hipStream_t st, int nct = 1, int64_t c_cs = 0, int64_t tmp_cs = 0, int64_t out_cs = 0);
 // d0 (+)= a0 b0, d1 (+)= a0 b1 + a1 b0, d2 (+)= a1 b1
 void launch_tensor(const DevTables& T, int nl, const u64* a, int64_t a_ps, const u64* b, int64_t b_ps, u64* d,
                    int64_t d_ps, int acc, hipStream_t st, int nct = 1, int64_t a_cs = 0, int64_t b_cs = 0,
