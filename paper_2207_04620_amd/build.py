@@ -11,7 +11,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhe.so")
-SOURCES = ["kernels.hip", "he_host.hip", "group.hip", "serve.hip", "tune.hip", "graph.hip", "probe.hip"]
+SOURCES = ["kernels.hip", "he_host.hip", "group.hip", "serve.hip", "tune.hip", "graph.hip", "probe.hip",
+           "encode.hip"]
 
 # Packed FP32 instructions are disabled for all device code: the kernels compute in 64-bit
 # integers and FP64 only, and the flag keeps the compiler from ever emitting packed FP32.
@@ -26,13 +27,17 @@ def build(verbose: bool = False) -> str:
     objs = []
     bdir = os.path.join(HERE, "_build")
     os.makedirs(bdir, exist_ok=True)
+    running = []
     for src in SOURCES:
         obj = os.path.join(bdir, src.replace(".hip", ".o"))
         cmd = ["hipcc", *HIPFLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
-        subprocess.check_call(cmd)
+        running.append((cmd, subprocess.Popen(cmd)))
         objs.append(obj)
+    failed = [cmd for cmd, p in running if p.wait() != 0]
+    if failed:
+        raise subprocess.CalledProcessError(1, failed[0])
     tmp = LIB + f".tmp{os.getpid()}"
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
     if verbose:

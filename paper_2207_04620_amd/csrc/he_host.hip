@@ -569,10 +569,12 @@ void Ctx::build_plans() {
 }
 
 // ====================================================================== small helpers
-void Ctx::ntt(u64* base, int npoly, int64_t pstride_limbs, int nl, bool inverse, int level_for_ext) {
+// src: the inverse transform reads limb k from there (same layout) instead of from base
+void Ctx::ntt(u64* base, int npoly, int64_t pstride_limbs, int nl, bool inverse, int level_for_ext, const u64* src) {
     // job lists are capped; long ones are split
     Jobs J;
     J.base = base;
+    J.src = src;
     J.cstride = 0;
     J.nct = 1;
     J.n = 0;
@@ -605,9 +607,7 @@ void Ctx::sample_into(u64* dst, int nl_modidx_count, const int* modidx, int kind
     SampleArgs A;
     memset(&A, 0, sizeof A);
     A.seed = seed;
-    A.purpose = purpose;
-    A.index = index;
-    A.kind = kind;
+    A.poly[0] = {purpose, kind, index};
     if (uidx)
         for (int k = 0; k < J.n; ++k) A.uidx[k] = uidx[k];
     memcpy(A.cdt, cdt, sizeof cdt);
@@ -708,59 +708,156 @@ CtPtr Ctx::new_ct(int level, int deg, double scale) {
 
 CtPtr Ctx::encrypt_coeffs(const int64_t* m_host, int level, double scale, u64 nonce) {
     if (level < 0 || level >= n_q) throw HeError(HE_ELEVEL);
-    const int nl = level + 1;
-    std::vector<int> idx(nl);
-    for (int i = 0; i < nl; ++i) idx[i] = i;
-    DBuf v(this, (size_t)nl * N), x(this, 2 * (size_t)nl * N), dm(this, N);
-    sample_into(v.p, nl, idx.data(), 0, P_ENC_V, nonce, nullptr);
-    sample_into(x.p, nl, idx.data(), 1, P_ENC_E0, nonce, nullptr);
-    sample_into(x.p + (size_t)nl * N, nl, idx.data(), 1, P_ENC_E1, nonce, nullptr);
+    DBuf dm(this, N);
     upload(this, dm.p, m_host, N * 8);
-    launch_add_signed(T, nl, x.p, (const int64_t*)dm.p, stream);
-    ntt(v.p, 1, 0, nl, false, -1);
-    ntt(x.p, 2, nl, nl, false, -1);
+    return encrypt_dev((const int64_t*)dm.p, level, scale, nonce);
+}
+
+// Enc of N device coefficients: v, e0 and e1 in one block, one sampling launch and one transform for the three
+CtPtr Ctx::encrypt_dev(const int64_t* dev_coeffs, int level, double scale, u64 nonce) {
+    if (level < 0 || level >= n_q) throw HeError(HE_ELEVEL);
+    const int nl = level + 1;
+    const size_t ps = (size_t)nl * N;
+    DBuf x(this, 3 * ps);
+    Jobs J;
+    J.base = x.p;
+    J.cstride = (int64_t)ps;
+    J.nct = 3;
+    J.n = nl;
+    for (int i = 0; i < nl; ++i) {
+        J.off[i] = (uint16_t)i;
+        J.mod[i] = (uint8_t)i;
+    }
+    SampleArgs A;
+    memset(&A, 0, sizeof A);
+    A.seed = seed;
+    A.poly[0] = {P_ENC_V, 0, nonce};
+    A.poly[1] = {P_ENC_E0, 1, nonce};
+    A.poly[2] = {P_ENC_E1, 1, nonce};
+    memcpy(A.cdt, cdt, sizeof cdt);
+    launch_sample(T, J, A, stream);
+    launch_add_signed(T, nl, x.p + ps, dev_coeffs, stream);
+    launch_ntt(T, J, false, stream);
     CtPtr c = new_ct(level, 1, scale);
     u64* c0 = c->buf->p;
-    u64* c1 = c0 + (size_t)nl * N;
-    launch_enc_combine(T, nl, v.p, pk->p, pk->p + (size_t)n_q * N, x.p, x.p + (size_t)nl * N, c0, c1, stream);
-    // the host message buffer may be released by the caller once we return
-    hip_check(hipStreamSynchronize(stream), "encrypt");
+    launch_enc_combine(T, nl, x.p, pk->p, pk->p + (size_t)n_q * N, x.p + ps, x.p + 2 * ps, c0, c0 + ps, stream);
     return c;
 }
 
-void Ctx::decrypt_coeffs(const CtData& c, double* out) {
-    const int nl = c.level + 1;
-    DBuf m(this, (size_t)nl * N);
-    const int64_t ps = (int64_t)nl * N;
-    launch_dec_dot(T, nl, c.deg, c.buf->p, ps, s_eval->p, s2_eval->p, m.p, stream);
-    ntt(m.p, 1, 0, nl, true, -1);
-    std::vector<u64> h((size_t)nl * N);
-    hip_check(hipMemcpyAsync(h.data(), m.p, h.size() * 8, hipMemcpyDeviceToHost, stream), "dec copy");
-    hip_check(hipStreamSynchronize(stream), "dec sync");
-    const u64 q0 = mods[0];
-    bool bad = false;
-    if (nl == 1) {
-        for (int64_t t = 0; t < N; ++t) out[t] = (double)(h[t] > (q0 - 1) / 2 ? (int64_t)h[t] - (int64_t)q0 : (int64_t)h[t]);
+// Ecd of host values into N device coefficients, on the device where its fixed point holds them: finite
+// values, a positive scale, results below 2^62; the 113-bit host encoder takes the rest
+void Ctx::encode_into(const double* vals, int64_t n_vals, double sc, int64_t* dev_out) {
+    double mx = 0;
+    bool finite = true;
+    for (int64_t j = 0; j < n_vals; ++j) {
+        const double a = std::fabs(vals[j]);
+        finite = finite && a <= 1.7976931348623157e308;  // false for NaN
+        mx = a > mx ? a : mx;
+    }
+    int e = 0, es = 0;
+    const double f = std::frexp(sc, &es);
+    (void)std::frexp(mx, &e);
+    if (!finite || !(sc >= 2.2250738585072014e-308 && sc <= 1.7976931348623157e308) || (mx > 0 && e + es > 62) ||
+        !E.w) {
+        std::vector<int64_t> m(N);
+        enc.encode(vals, n_vals, sc, m.data());
+        upload(this, dev_out, m.data(), N * 8);
         return;
     }
-    const u64 q1 = mods[1];
-    const u64 q0inv = invmod(q0 % q1, q1);
-    const u128h Q2 = (u128h)q0 * q1;
-    for (int64_t t = 0; t < N; ++t) {
-        const u64 x0 = h[t], x1 = h[N + t];
-        const u64 d = (x1 + q1 - x0 % q1) % q1;
-        const u64 k = mulmod(d, q0inv, q1);
-        const u128h w = (u128h)x0 + (u128h)q0 * k;
-        __int128 v = w > Q2 / 2 ? (__int128)w - (__int128)Q2 : (__int128)w;
-        for (int i = 2; i < nl && !bad; ++i) {
-            const __int128 qi = (__int128)mods[i];
-            __int128 r = v % qi;
-            if (r < 0) r += qi;
-            if ((u64)r != h[(size_t)i * N + t]) bad = true;
-        }
-        out[t] = (double)v;
+    if (mx == 0) e = 62 - es;  // any range will do
+    DBuf z(this, (size_t)n_vals), x(this, (size_t)N * (sizeof(FixC) / 8));
+    upload(this, z.p, vals, n_vals * 8);
+    EncArgs A;
+    A.z = (const double*)z.p;
+    A.vmask = (uint32_t)(n_vals - 1);
+    A.shift = 125 - log_n - e;  // |values| 2^shift < 2^(125 - log N): sums of N stay below 2^125
+    A.mant = (u64)std::ldexp(f, 53);
+    A.sh = std::min(191, A.shift + log_n + 53 - es);  // 116 and up; at 191 every result rounds to 0
+    launch_encode(E, A, (FixC*)x.p, dev_out, stream);
+}
+
+// device tables of the encoder and decoder, from the host encoder's
+void Ctx::build_encoder() {
+    const auto fix = [](f128 v, u64& lo, u64& hi) {
+        const __int128 r = (__int128)(v * (f128)((__int128)1 << 126));  // exact: 113 bits
+        lo = (u64)r;
+        hi = (u64)((unsigned __int128)r >> 64);
+    };
+    const size_t n = (size_t)N;
+    std::vector<FixC> f(n + n / 2);
+    for (size_t k = 0; k < n / 2; ++k) {
+        fix(enc.wr[k], f[k].rl, f[k].rh);
+        fix(enc.wi[k], f[k].il, f[k].ih);
     }
+    for (size_t i = 0; i < n; ++i) {
+        fix(enc.zr[i], f[n / 2 + i].rl, f[n / 2 + i].rh);
+        fix(enc.zi[i], f[n / 2 + i].il, f[n / 2 + i].ih);
+    }
+    std::vector<uint32_t> slot(n), pos(n / 2);
+    for (size_t j = 0; j < n / 2; ++j) {
+        slot[enc.slot_pos[j]] = slot[enc.slot_neg[j]] = (uint32_t)j;
+        pos[j] = bitrev((uint32_t)enc.slot_pos[j], log_n);
+    }
+    const size_t fw = f.size() * sizeof(FixC) / 8;
+    d_enc = std::make_unique<DBuf>(this, fw + n / 2);
+    upload(this, d_enc->p, f.data(), fw * 8);
+    upload(this, d_enc->p + fw, slot.data(), n * 4);
+    E.log_n = log_n;
+    E.w = (const FixC*)d_enc->p;
+    E.twist = E.w + n / 2;
+    E.slot = (const uint32_t*)(d_enc->p + fw);
+    static_assert(sizeof(std::complex<double>) == sizeof(DblC), "double tables");
+    d_dec = std::make_unique<DBuf>(this, 3 * n + n / 4);
+    upload(this, d_dec->p, enc.dw.data(), n * 8);
+    upload(this, d_dec->p + n, enc.dz.data(), 2 * n * 8);
+    upload(this, d_dec->p + 3 * n, pos.data(), n * 2);
+    D.log_n = log_n;
+    D.w = (const DblC*)d_dec->p;
+    D.twist = (const DblC*)(d_dec->p + n);
+    D.pos = (const uint32_t*)(d_dec->p + 3 * n);
+}
+
+// Dec: the N centred integers as doubles, and one word after them that is set when they do not fit q_0 q_1
+std::unique_ptr<DBuf> Ctx::decrypt_lifted(const CtData& c) {
+    const int nl = c.level + 1;
+    DBuf m(this, (size_t)nl * N);
+    launch_dec_dot(T, nl, c.deg, c.buf->p, (int64_t)nl * N, s_eval->p, s2_eval->p, m.p, stream);
+    ntt(m.p, 1, 0, nl, true, -1);
+    auto out = std::make_unique<DBuf>(this, (size_t)N + 1);
+    launch_zero(out->p + N, 1, stream);
+    const u64 q1 = nl > 1 ? mods[1] : 1;
+    const u128h half = (u128h)mods[0] * q1 / 2;
+    launch_lift_centred(T, nl, m.p, nl > 1 ? invmod(mods[0] % q1, q1) : 0, (u64)half, (u64)(half >> 64), (double*)out->p,
+                        (uint32_t*)(out->p + N), stream);
+    return out;
+}
+
+void Ctx::decrypt_coeffs(const CtData& c, double* out) {
+    auto v = decrypt_lifted(c);
+    std::vector<double> h((size_t)N + 1);
+    hip_check(hipMemcpyAsync(h.data(), v->p, h.size() * 8, hipMemcpyDeviceToHost, stream), "dec copy");
+    hip_check(hipStreamSynchronize(stream), "dec sync");
+    uint32_t bad;
+    memcpy(&bad, &h[N], 4);
     if (bad) throw HeError(HE_ESCALE);
+    std::copy(h.begin(), h.begin() + N, out);
+}
+
+// Dec + Dcd: the first n_out slot values (at most N / 2)
+void Ctx::decrypt_values(const CtData& c, double* out, size_t n_out) {
+    const size_t n = std::min(n_out, (size_t)N / 2);
+    auto v = decrypt_lifted(c);
+    // the transform's buffer takes the values after use: x [N] complex, then values [n] and the flag
+    DBuf x(this, 2 * (size_t)N), vals(this, n + 1);
+    launch_decode(D, (const double*)v->p, c.scale, (DblC*)x.p, (int)n, (double*)vals.p, stream);
+    hip_check(hipMemcpyAsync(vals.p + n, v->p + N, 8, hipMemcpyDeviceToDevice, stream), "dec flag");
+    std::vector<double> h(n + 1);
+    hip_check(hipMemcpyAsync(h.data(), vals.p, h.size() * 8, hipMemcpyDeviceToHost, stream), "dec copy");
+    hip_check(hipStreamSynchronize(stream), "dec sync");
+    uint32_t bad;
+    memcpy(&bad, &h[n], 4);
+    if (bad) throw HeError(HE_ESCALE);
+    std::copy(h.begin(), h.begin() + n, out);
 }
 
 CtPtr Ctx::drop(const CtData& a, int level) {
@@ -892,15 +989,20 @@ CtPtr Ctx::mul_int(const CtData& a, int64_t k) {
 // a plaintext's residues on every modulus (Q and P, so that it can also multiply a value
 // in the extended basis), evaluation form, Montgomery form: [M][N]
 std::unique_ptr<DBuf> Ctx::plaintext_mont(const int64_t* coeffs) {
-    const int M = n_q + n_p;
-    auto pt = std::make_unique<DBuf>(this, (size_t)M * N);
     DBuf dm(this, N);
     upload(this, dm.p, coeffs, N * 8);
-    hip_check(hipMemsetAsync(pt->p, 0, (size_t)M * N * 8, stream), "pt zero");
-    launch_add_signed(T, M, pt->p, (const int64_t*)dm.p, stream);
+    auto pt = plaintext_mont_dev((const int64_t*)dm.p);
+    hip_check(hipStreamSynchronize(stream), "plaintext");
+    return pt;
+}
+
+std::unique_ptr<DBuf> Ctx::plaintext_mont_dev(const int64_t* dev_coeffs) {
+    const int M = n_q + n_p;
+    auto pt = std::make_unique<DBuf>(this, (size_t)M * N);
+    launch_zero(pt->p, (int64_t)M * N, stream);
+    launch_add_signed(T, M, pt->p, dev_coeffs, stream);
     ntt(pt->p, 1, 0, M, false, -1);
     launch_to_mont(T, ModMap{1 << 20, n_q}, M, 1, pt->p, 0, stream);
-    hip_check(hipStreamSynchronize(stream), "plaintext");
     return pt;
 }
 
@@ -931,10 +1033,10 @@ CtPtr Ctx::fl_update(const CtData& w, const std::vector<const CtData*>& grads, d
         launch_sum_many(T, nl, 2, D, sum->buf->p, (int64_t)nl * N, base > 0, stream);
     }
     cnt[C_ADD] += (int64_t)grads.size() - 1;
-    std::vector<int64_t> m(N);
     const double ql = (double)mods[lvl];
-    enc.encode(&coeff, 1, ql, m.data());
-    auto pt = plaintext_mont(m.data());
+    DBuf m(this, N);
+    encode_into(&coeff, 1, ql, (int64_t*)m.p);
+    auto pt = plaintext_mont_dev((const int64_t*)m.p);
     CtPtr t = mask_sum({{sum.get(), pt->p}}, ql);
     CtPtr u = rescale(*t);
     CtPtr wd = drop(w, std::min(u->level, w.level));
@@ -999,28 +1101,19 @@ void Ctx::prepare_masks(const std::vector<MaskKey>& keys) {
     for (auto& k : keys)
         if (!masks.count(k) && std::find(todo.begin(), todo.end(), k) == todo.end()) todo.push_back(k);
     if (todo.empty()) return;
-    std::vector<std::vector<int64_t>> coeffs(todo.size(), std::vector<int64_t>(N));
-    unsigned nth = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
-    std::vector<std::thread> th;
-    for (unsigned w = 0; w < nth; ++w)
-        th.emplace_back([&, w]() {
-            std::vector<double> u, ur;
-            for (size_t i = w; i < todo.size(); i += nth) {
-                const MaskKey& m = todo[i];
-                mask_slots(m.kind, m.h, m.k, u);
-                const int n = m.h * m.h;
-                // R(u, rot), each entry repeated beta times (packing iota_beta: entry t of every
-                // matrix sits at slots beta t .. beta t + beta - 1)
-                ur.resize((size_t)n * m.beta);
-                for (int t = 0; t < n; ++t)
-                    for (int e = 0; e < m.beta; ++e)
-                        ur[(size_t)m.beta * t + e] = u[(size_t)((((t + m.rot) % n) + n) % n)];
-                enc.encode(ur.data(), (int64_t)n * m.beta, scale, coeffs[i].data());
-            }
-        });
-    for (auto& t : th) t.join();
-    for (size_t i = 0; i < todo.size(); ++i) {
-        masks[todo[i]] = plaintext_mont(coeffs[i].data());
+    std::vector<double> u, ur;
+    DBuf coeffs(this, N);
+    for (const MaskKey& m : todo) {
+        mask_slots(m.kind, m.h, m.k, u);
+        const int n = m.h * m.h;
+        // R(u, rot), each entry repeated beta times (packing iota_beta: entry t of every
+        // matrix sits at slots beta t .. beta t + beta - 1)
+        ur.resize((size_t)n * m.beta);
+        for (int t = 0; t < n; ++t)
+            for (int e = 0; e < m.beta; ++e)
+                ur[(size_t)m.beta * t + e] = u[(size_t)((((t + m.rot) % n) + n) % n)];
+        encode_into(ur.data(), (int64_t)n * m.beta, scale, (int64_t*)coeffs.p);
+        masks[m] = plaintext_mont_dev((const int64_t*)coeffs.p);
         keys_bytes += (size_t)(n_q + n_p) * N * 8;
     }
 }
@@ -1230,6 +1323,7 @@ he_status he_ctx_create(const he_params* prm, const he_device* dev, he_ctx** out
             if (q >= (1ull << 60) + 1) throw HeError(HE_EINVAL);
         c->enc.init(c->log_n);
         c->build_tables();
+        c->build_encoder();
         c->keygen_base();
         c->relin_key();
         for (uint32_t i = 0; i < prm->n_h; ++i) c->prepare_h((int)prm->h_list[i]);
@@ -1299,18 +1393,23 @@ he_status he_pool_stats(he_ctx* ctx, uint64_t* in_use, uint64_t* peak, int reset
 
 he_status he_encode(he_ctx* ctx, const double* vals, size_t n_vals, double scale, int64_t* out) {
     if (!ctx || !vals || !out || n_vals == 0 || (size_t)(ctx->c->N / 2) % n_vals) return HE_EINVAL;
-    std::lock_guard<std::recursive_mutex> lk(ctx->c->api_mu);
-    ctx->c->enc.encode(vals, (int64_t)n_vals, scale, out);
-    return HE_OK;
+    return guardc(ctx, [&]() {
+        Ctx* c = ctx->c.get();
+        DBuf m(c, c->N);
+        c->encode_into(vals, (int64_t)n_vals, scale, (int64_t*)m.p);
+        hip_check(hipMemcpyAsync(out, m.p, c->N * 8, hipMemcpyDeviceToHost, c->stream), "encode d2h");
+        hip_check(hipStreamSynchronize(c->stream), "encode sync");
+    });
 }
 
 he_status he_encrypt(he_ctx* ctx, const double* vals, size_t n_vals, uint32_t level, uint64_t nonce, he_ct** out) {
     if (!ctx || !vals || !out || n_vals == 0 || (size_t)(ctx->c->N / 2) % n_vals) return HE_EINVAL;
     return guardc(ctx, [&]() {
         Ctx* c = ctx->c.get();
-        std::vector<int64_t> m(c->N);
-        c->enc.encode(vals, (int64_t)n_vals, c->scale, m.data());
-        *out = wrap(c, c->encrypt_coeffs(m.data(), (int)level, c->scale, nonce));
+        if ((int)level >= c->n_q || (int)level < 0) throw HeError(HE_ELEVEL);
+        DBuf m(c, c->N);
+        c->encode_into(vals, (int64_t)n_vals, c->scale, (int64_t*)m.p);
+        *out = wrap(c, c->encrypt_dev((const int64_t*)m.p, (int)level, c->scale, nonce));
     });
 }
 
@@ -1329,11 +1428,7 @@ he_status he_decrypt_coeffs(he_ctx* ctx, const he_ct* ct, double* out, size_t n)
 he_status he_decrypt(he_ctx* ctx, const he_ct* ct, double* out, size_t n_out) {
     if (!ctx || !ct || !out) return HE_EINVAL;
     if (ct->ctx != ctx->c.get()) return HE_EMISMATCH;
-    return guardc(ctx, [&]() {
-        std::vector<double> co(ctx->c->N);
-        ctx->c->decrypt_coeffs(*ct->c, co.data());
-        ctx->c->enc.decode(co.data(), ct->c->scale, out, (int64_t)n_out);
-    });
+    return guardc(ctx, [&]() { ctx->c->decrypt_values(*ct->c, out, n_out); });
 }
 
 void he_ct_free(he_ct* ct) {
@@ -1359,8 +1454,7 @@ he_status he_ct_export(he_ctx* ctx, const he_ct* ct, uint64_t* buf, size_t n) {
     if (n < tot) return HE_EINVAL;
     return guardc(ctx, [&]() {
         DBuf tmp(c, tot);
-        hip_check(hipMemcpyAsync(tmp.p, d.buf->p, tot * 8, hipMemcpyDeviceToDevice, c->stream), "export");
-        c->ntt(tmp.p, d.deg + 1, d.level + 1, d.level + 1, true, -1);
+        c->ntt(tmp.p, d.deg + 1, d.level + 1, d.level + 1, true, -1, d.buf->p);
         hip_check(hipMemcpyAsync(buf, tmp.p, tot * 8, hipMemcpyDeviceToHost, c->stream), "export d2h");
         hip_check(hipStreamSynchronize(c->stream), "export sync");
     });
@@ -1380,8 +1474,9 @@ he_status he_ct_import(he_ctx* ctx, const uint64_t* buf, size_t n, uint32_t leve
         for (size_t i = 0; i <= level; ++i) {
             const uint64_t q = c->mods[i];
             const uint64_t* w = buf + (p * (level + 1) + i) * c->N;
-            for (int64_t t = 0; t < c->N; ++t)
-                if (w[t] >= q) return HE_EINVAL;
+            uint64_t over = 0;  // no early exit: the loop runs as vector code
+            for (int64_t t = 0; t < c->N; ++t) over |= (uint64_t)(w[t] >= q);
+            if (over) return HE_EINVAL;
         }
     return guardc(ctx, [&]() {
         CtPtr r = c->new_ct((int)level, (int)degree, scale);

@@ -234,6 +234,16 @@ struct Ctx {
     std::vector<ConvPlan> plan_mu, plan_md, plan_rs;
     std::unique_ptr<DBuf> d_plan_sets, d_plan_tab, d_rs_scale;
     void build_plans();
+    // device encoder and decoder (tables made with the context)
+    EncTables E{};
+    DecTables D{};
+    std::unique_ptr<DBuf> d_enc, d_dec;
+    void build_encoder();
+    void encode_into(const double* vals, int64_t n_vals, double scale, int64_t* dev_out);
+    CtPtr encrypt_dev(const int64_t* dev_coeffs, int level, double scale, u64 nonce);
+    std::unique_ptr<DBuf> plaintext_mont_dev(const int64_t* dev_coeffs);
+    std::unique_ptr<DBuf> decrypt_lifted(const CtData& c);
+    void decrypt_values(const CtData& c, double* out, size_t n_out);
     // keys
     std::unique_ptr<DBuf> s_eval, s2_eval, pk, rlk;
     std::map<u64, std::unique_ptr<DBuf>> rot_keys;
@@ -246,7 +256,8 @@ struct Ctx {
 
     int ext_mod(int level, int i) const;
     void build_tables();
-    void ntt(u64* base, int npoly, int64_t pstride_limbs, int nl, bool inverse, int level_for_ext);
+    void ntt(u64* base, int npoly, int64_t pstride_limbs, int nl, bool inverse, int level_for_ext,
+             const u64* src = nullptr);
     void sample_into(u64* dst, int count, const int* modidx, int kind, uint32_t purpose, u64 index, const u64* uidx);
     void keygen_base();
     std::unique_ptr<DBuf> make_swk(u64 key_id, const u64* sp);
@@ -374,6 +385,7 @@ struct Ctx {
         d_rtw.reset(); d_irtw.reset(); d_rtwd.reset(); d_irtwd.reset(); d_cold.reset(); d_icold.reset();
         d_mu_scale.reset(); d_md_scale.reset();
         d_plan_sets.reset(); d_plan_tab.reset(); d_rs_scale.reset();
+        d_enc.reset(); d_dec.reset();
         d_rs.reset(); d_md_tab.reset(); d_pinv.reset(); d_mu_tab.reset();
         pool.trim();
         pool_side.trim();

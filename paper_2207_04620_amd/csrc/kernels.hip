@@ -51,27 +51,19 @@ static hipEvent_t ev_get() {
     return e;
 }
 
-struct ProfScope {
-    int kind;
-    double bytes, ops, fp_ops;
-    hipStream_t st;
-    hipEvent_t a = nullptr;
-    // ops: butterflies of the launch, fp_ops of them FP64
-    ProfScope(int k, double b, hipStream_t s, double o = 0, double fo = 0)
-        : kind(k), bytes(b), ops(o), fp_ops(fo), st(s) {
-        if (g_prof_on && (g_prof_only < 0 || g_prof_only == k)) {
-            a = ev_get();
-            (void)hipEventRecord(a, st);
-        }
+ProfScope::ProfScope(int k, double b, hipStream_t s, double o, double fo) : kind(k), bytes(b), ops(o), fp_ops(fo), st(s) {
+    if (g_prof_on && (g_prof_only < 0 || g_prof_only == k)) {
+        a = ev_get();
+        (void)hipEventRecord(a, st);
     }
-    ~ProfScope() {
-        if (g_prof_on && a) {
-            hipEvent_t b = ev_get();
-            (void)hipEventRecord(b, st);
-            g_prof.push_back({kind, a, b, bytes, ops, fp_ops});
-        }
+}
+ProfScope::~ProfScope() {
+    if (g_prof_on && a) {
+        hipEvent_t b = ev_get();
+        (void)hipEventRecord(b, st);
+        g_prof.push_back({kind, a, b, bytes, ops, fp_ops});
     }
-};
+}
 
 // ------------------------------------------------------------------ launch checks
 static std::atomic<uint64_t> g_inject{0};  // launches until the injected failure (0: none)
@@ -1941,6 +1933,16 @@ void launch_copy(CopyDesc& D, hipStream_t st) {
     HE_LAUNCH(k_copy, dim3((unsigned)bx, (unsigned)rmax, (unsigned)D.n), dim3(TPB), 0, st, D);
 }
 
+__global__ __launch_bounds__(TPB) void k_zero(u64* p, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TPB) p[i] = 0;
+}
+
+void launch_zero(u64* p, int64_t n, hipStream_t st) {
+    if (n <= 0) return;
+    ProfScope prof_(PK_EW, 8.0 * n, st);
+    HE_LAUNCH(k_zero, dim3((unsigned)std::min<int64_t>(ceil_div(n, TPB), 4096)), dim3(TPB), 0, st, p, n);
+}
+
 // ------------------------------------------------------------------ base conversion
 // Centered fast base conversion (Bajard et al. 2016 / Halevi-Polyakov-Shoup 2019 in
 // its centered form): y_s = centered([x_s (D/q_s)^-1]_{q_s}),
@@ -2102,30 +2104,36 @@ __device__ void chacha_block(u64 seed, u32 purpose, u64 index, u32 counter, u32 
 
 __device__ __forceinline__ u64 signed_to_res(int64_t v, u64 q) { return v >= 0 ? (u64)v : q - (u64)(-v); }
 
-// ternary / Gaussian: one 64-bit word per coefficient, word w = block w/8, words 2(w%8)+{0,1}
+// ternary / Gaussian: one 64-bit word per coefficient, word w = block w/8, words 2(w%8)+{0,1}.
+// A block of threads takes TPB coefficients of one polynomial: TPB / 8 threads run the cipher into LDS, then all
+// write the limbs coalesced (a thread writing its eight coefficients of every limb took 37 us
+// at N = 2^15 with 14 limbs).  Grid (N / TPB, polynomials): v, e0 and e1 of an encryption in one launch.
 __global__ __launch_bounds__(TPB) void k_sample_small(DevTables T, Jobs J, SampleArgs A) {
-    const int N = 1 << T.log_n;
-    const int blk = blockIdx.x * TPB + threadIdx.x;
-    if (blk * 8 >= N) return;
-    u32 o[16];
-    chacha_block(A.seed, A.purpose, A.index, (u32)blk, o);
-    for (int w = 0; w < 8; w++) {
-        const u64 word = (u64)o[2 * w] | ((u64)o[2 * w + 1] << 32);
-        int64_t v;
-        if (A.kind == 0) {
-            v = (int64_t)(word % 3) - 1;
-        } else {
-            const u64 u = word >> 1;
-            int mag = 0;
-            for (int k = 0; k < 19; k++) mag += (u >= A.cdt[k]) ? 1 : 0;
-            v = (word & 1) ? -mag : mag;
-        }
-        const int x = blk * 8 + w;
-        for (int k = 0; k < J.n; k++) {
-            const u64 q = T.mods[J.mod[k]].q;
-            J.base[(int64_t)J.off[k] * N + x] = signed_to_res(v, q);
+    __shared__ int8_t sv[TPB];
+    const int N = 1 << T.log_n, p = blockIdx.y;
+    const int blk = blockIdx.x * (TPB / 8) + threadIdx.x;
+    if (threadIdx.x < TPB / 8) {
+        u32 o[16];
+        chacha_block(A.seed, A.poly[p].purpose, A.poly[p].index, (u32)blk, o);
+        for (int w = 0; w < 8; w++) {
+            const u64 word = (u64)o[2 * w] | ((u64)o[2 * w + 1] << 32);
+            int v;
+            if (A.poly[p].kind == 0) {
+                v = (int)(word % 3) - 1;
+            } else {
+                const u64 u = word >> 1;
+                int mag = 0;
+                for (int k = 0; k < 19; k++) mag += (u >= A.cdt[k]) ? 1 : 0;
+                v = (word & 1) ? -mag : mag;
+            }
+            sv[threadIdx.x * 8 + w] = (int8_t)v;
         }
     }
+    __syncthreads();
+    const int x = blockIdx.x * TPB + threadIdx.x;
+    const int64_t v = sv[threadIdx.x];
+    for (int k = 0; k < J.n; k++)
+        J.base[p * J.cstride + (int64_t)J.off[k] * N + x] = signed_to_res(v, T.mods[J.mod[k]].q);
 }
 
 // uniform mod q: two words per coefficient, value = (w[2x+1] 2^64 + w[2x]) mod q
@@ -2135,7 +2143,7 @@ __global__ __launch_bounds__(TPB) void k_sample_uniform(DevTables T, Jobs J, Sam
     const int k = blockIdx.y;
     if (blk * 4 >= N) return;
     u32 o[16];
-    chacha_block(A.seed, A.purpose, A.uidx[k], (u32)blk, o);
+    chacha_block(A.seed, A.poly[0].purpose, A.uidx[k], (u32)blk, o);
     const ModP m = T.mods[J.mod[k]];
     for (int w = 0; w < 4; w++) {
         const u64 lo = (u64)o[4 * w] | ((u64)o[4 * w + 1] << 32);
@@ -2147,14 +2155,15 @@ __global__ __launch_bounds__(TPB) void k_sample_uniform(DevTables T, Jobs J, Sam
 }
 
 void launch_sample(const DevTables& T, const Jobs& J, const SampleArgs& A, hipStream_t st) {
-    ProfScope prof_(PK_EW, 1.0 * J.n * 8.0 * (1 << T.log_n), st);
+    ProfScope prof_(PK_EW, 1.0 * J.n * J.nct * 8.0 * (1 << T.log_n), st);
     const int N = 1 << T.log_n;
-    if (A.kind == 2) {
+    if (A.poly[0].kind == 2) {
+        if (J.nct != 1) throw std::runtime_error("sampler: one uniform polynomial per launch");
         dim3 grid(ceil_div(N / 4, TPB), J.n);
         HE_LAUNCH(k_sample_uniform, grid, dim3(TPB), 0, st, T, J, A);
     } else {
-        dim3 grid(ceil_div(N / 8, TPB));
-        HE_LAUNCH(k_sample_small, grid, dim3(TPB), 0, st, T, J, A);
+        if (N < TPB || J.nct < 1 || J.nct > SAMPLE_MAX) throw std::runtime_error("sampler: unsupported shape");
+        HE_LAUNCH(k_sample_small, dim3(N / TPB, J.nct), dim3(TPB), 0, st, T, J, A);
     }
 }
 

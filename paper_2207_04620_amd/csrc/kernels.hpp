@@ -156,11 +156,14 @@ struct ConvPlanDesc {
     uint8_t it_dig[CONV_MAXITEM], it_s0[CONV_MAXITEM], it_s1[CONV_MAXITEM];  // a wave's digit and sets
 };
 
+#define SAMPLE_MAX 3  // ternary / Gaussian polynomials per launch (member p of the job list)
 struct SampleArgs {
     u64 seed;
-    uint32_t purpose;
-    u64 index;
-    int kind;          // 0 ternary, 1 Gaussian, 2 uniform mod the limb's prime
+    struct {
+        uint32_t purpose;
+        int kind;  // 0 ternary, 1 Gaussian, 2 uniform mod the limb's prime (one polynomial)
+        u64 index;
+    } poly[SAMPLE_MAX];
     u64 uidx[HE_MAXJ]; // uniform: stream index of limb k
     u64 cdt[19];
 };
@@ -283,6 +286,16 @@ enum ProfKind {
     PK_RS_SPREAD, PK_RS_COMBINE, PK_TENSOR, PK_MASKMAC, PK_AUTOMORPH, PK_EW, PK_CONV_COLS, PK_COPY, PK_COUNT
 };
 #include <string>
+// times the launches in its scope while launch timing is on; ops: butterflies of the launch, fp_ops of
+// them FP64
+struct ProfScope {
+    int kind;
+    double bytes, ops, fp_ops;
+    hipStream_t st;
+    hipEvent_t a = nullptr;
+    ProfScope(int k, double b, hipStream_t s, double o = 0, double fo = 0);
+    ~ProfScope();
+};
 // Launch discipline: every kernel launch goes through HE_LAUNCH.  launch_gate() clears the
 // thread's last HIP error and, while a host-side failure injection is armed
 // (launch_inject), fails the launch before anything is queued, so tests of the error paths
@@ -331,6 +344,8 @@ void launch_conv_mfma(const DevTables& T, const ConvPlan& P, const u64* src, int
                       int64_t dst_ps, int64_t dst_cs, int npoly, int nct, hipStream_t st);
 void launch_conv_cols(const DevTables& T, const ConvDesc& D, hipStream_t st);
 void launch_sample(const DevTables& T, const Jobs& J, const SampleArgs& A, hipStream_t st);
+// n words to zero
+void launch_zero(u64* p, int64_t n, hipStream_t st);
 // the regions of D (start[] is filled here)
 void launch_copy(CopyDesc& D, hipStream_t st);
 // out[p][i] = a[p][i] (op) b[p][i] over nl limbs (prime map mm) and npoly polys;
@@ -367,3 +382,40 @@ void launch_enc_combine(const DevTables& T, int nl, const u64* v, const u64* pk0
                         const u64* x1, u64* c0, u64* c1, hipStream_t st);
 // x[i][j] += m[j] mod q_i (signed 64-bit message)
 void launch_add_signed(const DevTables& T, int nl, u64* x, const int64_t* m, hipStream_t st);
+
+// ------------------------------------------------------------------ encoding (encode.hip)
+// complex values: fixed point (two 128-bit words) and double
+struct __align__(16) FixC {
+    u64 rl, rh, il, ih;
+};
+struct __align__(16) DblC {
+    double re, im;
+};
+struct EncTables {
+    int log_n;
+    const uint32_t* slot;  // [N] position u of the transform's input holds slot value slot[u]
+    const FixC* w;         // [N/2] exp(-2 pi i k / N) 2^126
+    const FixC* twist;     // [N] exp(-pi i k / N) 2^126
+};
+// values z (slot j takes z[j & vmask]) scaled by 2^shift; the result is |y| mant 2^-sh
+struct EncArgs {
+    const double* z;
+    uint32_t vmask;
+    int shift, sh;
+    u64 mant;
+};
+struct DecTables {
+    int log_n;
+    const uint32_t* pos;  // [N/2] position of slot j in the transform's output
+    const DblC* w;        // [N/2] exp(+2 pi i k / N)
+    const DblC* twist;    // [N] exp(+pi i k / N)
+};
+// Ecd of the values into N coefficients; x: N FixC of scratch
+void launch_encode(const EncTables& E, const EncArgs& A, FixC* x, int64_t* out, hipStream_t st);
+// the integers of nl residue limbs (coefficient form), centred modulo q_0 q_1, as doubles; *bad is set
+// when the other limbs disagree.  half: (q_0 q_1) / 2
+void launch_lift_centred(const DevTables& T, int nl, const u64* m, u64 q0inv, u64 half_lo, u64 half_hi, double* out,
+                         uint32_t* bad, hipStream_t st);
+// the first n_out slot values of N coefficients; x: N DblC of scratch
+void launch_decode(const DecTables& D, const double* coeffs, double scale, DblC* x, int n_out, double* out,
+                   hipStream_t st);

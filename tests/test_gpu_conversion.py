@@ -31,6 +31,8 @@ CASES = [
 
 @pytest.mark.parametrize("log_n,q_bits,p_bits,alpha,levels", CASES)
 def test_conversion_edges(log_n, q_bits, p_bits, alpha, levels):
+    import torch  # its HIP runtime, before the library's
+    assert torch.cuda.is_available()
     from paper_2207_04620_amd import he
     prm = I.Params("conv", log_n, q_bits, p_bits, alpha, 30.0, 17 + log_n, [])
     print(f"[conversion] N=2^{log_n} Q={q_bits} P={p_bits} alpha={alpha}", flush=True)
