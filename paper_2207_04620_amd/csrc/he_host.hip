@@ -314,26 +314,26 @@ void Ctx::build_tables() {
         upload(this, d_irtw->p, irtw.data(), irtw.size() * 8);
         T.rtw = d_rtw->p;
         T.irtw = d_irtw->p;
-        // FP64 forms for primes below 2^46 (exact as doubles): w and fl(w / q)
-        std::vector<double> rtwd(rtw.size(), 0.0), irtwd(irtw.size(), 0.0), cold((size_t)M * N1 * 2, 0.0),
-            icold((size_t)M * N1 * 2, 0.0);
+        // FP64 forms for primes below 2^46 (exact as doubles), each group of 2^R - 1 padded to 2^R
+        std::vector<double> rtwd((size_t)M * N1 * ROW_TWD, 0.0), irtwd((size_t)M * N1 * ROW_TWD, 0.0),
+            cold((size_t)M * N1, 0.0), icold((size_t)M * N1, 0.0);
+        static const int fgroups[4][2] = {{1, 7}, {8, 7}, {64, 7}, {512, 3}}, igroups[4][2] = {{256, 7}, {32, 7}, {4, 7}, {1, 3}};
         for (int m = 0; m < M; ++m) {
-            const u64 q = mods[m];
-            if (q >= (1ull << 46)) continue;
-            const double qd = (double)q;
-            const size_t o = (size_t)m * N1 * ROW_TW * 2;
-            for (size_t k = 0; k < (size_t)N1 * ROW_TW; ++k) {
-                rtwd[o + 2 * k] = (double)rtw[o + 2 * k];
-                rtwd[o + 2 * k + 1] = (double)rtw[o + 2 * k] / qd;
-                irtwd[o + 2 * k] = (double)irtw[o + 2 * k];
-                irtwd[o + 2 * k + 1] = (double)irtw[o + 2 * k] / qd;
+            if (mods[m] >= (1ull << 46)) continue;
+            for (int r = 0; r < N1; ++r) {
+                const size_t src = ((size_t)m * N1 + r) * ROW_TW, dst = ((size_t)m * N1 + r) * ROW_TWD;
+                const auto pad = [&](const int (&groups)[4][2], const std::vector<u64>& from, std::vector<double>& to) {
+                    size_t i = src, o = dst;
+                    for (const auto& g : groups)
+                        for (int j = 0; j < g[0]; ++j, o += g[1] + 1)
+                            for (int e = 0; e < g[1]; ++e) to[o + e] = (double)from[2 * i++];
+                };
+                pad(fgroups, rtw, rtwd);
+                pad(igroups, irtw, irtwd);
             }
             for (int j = 0; j < N1; ++j) {
-                const size_t c = ((size_t)m * N1 + j) * 2;
-                cold[c] = (double)psi[(size_t)m * N + j];
-                cold[c + 1] = cold[c] / qd;
-                icold[c] = (double)ipsi[(size_t)m * N + j];
-                icold[c + 1] = icold[c] / qd;
+                cold[(size_t)m * N1 + j] = (double)psi[(size_t)m * N + j];
+                icold[(size_t)m * N1 + j] = (double)ipsi[(size_t)m * N + j];
             }
         }
         d_rtwd = std::make_unique<DBuf>(this, rtwd.size());

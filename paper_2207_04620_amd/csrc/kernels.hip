@@ -280,10 +280,17 @@ __device__ __forceinline__ void inv_all(u64* s, int L, int logT, u64 X, const u6
 
 // ---- row pass of a 2048-point block (N2 = 2^11), round structure fixed at compile time:
 // forward stages 0-2, 3-5, 6-8, 9-10; inverse 10-8, 7-5, 4-2, 1-0.  A group of 2^R elements
-// base + k d (base = (J << (ld + R)) + (g mod d)) sits at padded offsets base' + k d + (k d >> 5)
-// from its padded base, so its LDS accesses are one address plus constants; its 2^R - 1
-// twiddle pairs (w, w') are contiguous in a per-row table built on the host in the order the
-// round consumes them (ROW_TW pairs per row, round after round, group J after group J).
+// base + k d (base = (J << (ld + R)) + (g mod d)) sits at constant offsets from its padded base
+// (row_at), so its LDS accesses are one address plus constants; its 2^R - 1 twiddles are
+// contiguous in a per-row table built on the host in the order the round consumes them (round
+// after round, group J after group J; pairs (w, w') for the integer butterflies, the doubles w
+// alone for the FP64 ones).
+// Four pad words every 32 spread the strided accesses over the banks: lanes 4 apart in rounds of distance 4
+// and 8 apart in those of distance 8 land on different ones, and the addresses stay 16-byte
+// aligned, so the first inverse and the last forward round move two words at a time (one pad word
+// measured 0.54 conflict cycles per LDS cycle in the forward pass and 0.35 in the inverse).
+__host__ __device__ constexpr int row_at(int a) { return a + ((a >> 5) << 2); }
+#define ROW_LDS (NTT_E + NTT_E / 8)
 // butterflies of one forward group of 2^R elements in registers, twiddle pairs at t
 template <int R>
 __device__ __forceinline__ void fwd_group(u64 (&x)[1 << R], const u64* __restrict__ t, u64 q) {
@@ -340,13 +347,13 @@ __device__ __forceinline__ void fwd_row_round(u64* s, const u64* __restrict__ tw
         const int g = gg * TPB + threadIdx.x;
         const int J = g >> LD;
         const int base = (J << (LD + R)) + (g & (D - 1));
-        u64* sb = s + base + (base >> 5);
+        u64* sb = s + row_at(base);
         u64 x[G];
 #pragma unroll
-        for (int k = 0; k < G; ++k) x[k] = sb[k * D + ((k * D) >> 5)];
+        for (int k = 0; k < G; ++k) x[k] = sb[row_at(k * D)];
         fwd_group<R>(x, tw + 2 * (off + J * (G - 1)), q);
 #pragma unroll
-        for (int k = 0; k < G; ++k) sb[k * D + ((k * D) >> 5)] = x[k];
+        for (int k = 0; k < G; ++k) sb[row_at(k * D)] = x[k];
     }
 }
 
@@ -358,13 +365,13 @@ __device__ __forceinline__ void inv_row_round(u64* s, const u64* __restrict__ tw
         const int g = gg * TPB + threadIdx.x;
         const int J = g >> LD;
         const int base = (J << (LD + R)) + (g & (D - 1));
-        u64* sb = s + base + (base >> 5);
+        u64* sb = s + row_at(base);
         u64 x[G];
 #pragma unroll
-        for (int k = 0; k < G; ++k) x[k] = sb[k * D + ((k * D) >> 5)];
+        for (int k = 0; k < G; ++k) x[k] = sb[row_at(k * D)];
         inv_group<R>(x, tw + 2 * (off + J * (G - 1)), q);
 #pragma unroll
-        for (int k = 0; k < G; ++k) sb[k * D + ((k * D) >> 5)] = x[k];
+        for (int k = 0; k < G; ++k) sb[row_at(k * D)] = x[k];
     }
 }
 
@@ -381,9 +388,9 @@ __device__ __forceinline__ void fwd_rows_2048(u64* s, const u64* tw, u64 q, u64 
                                               F&& after_first) {
     const int tid = threadIdx.x;
     fwd_group<3>(x, tw, q);
-    u64* sb = s + tid + (tid >> 5);
+    u64* sb = s + row_at(tid);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) sb[264 * k] = x[k];
+    for (int k = 0; k < 8; ++k) sb[row_at(256 * k)] = x[k];
     after_first();
     __syncthreads();
     fwd_row_round<3, 3>(s, tw, 7, q);
@@ -393,10 +400,9 @@ __device__ __forceinline__ void fwd_rows_2048(u64* s, const u64* tw, u64 q, u64 
 #pragma unroll
     for (int gg = 0; gg < 2; ++gg) {
         const int g = gg * TPB + tid;
-        const u64* sg = s + 4 * g + (g >> 3);
-        u64 z[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) z[k] = sg[k];
+        const u64* sg = s + row_at(4 * g);
+        const u64x2 z0 = ld2(sg), z1 = ld2(sg + 2);
+        u64 z[4] = {z0.x, z0.y, z1.x, z1.y};
         fwd_group<2>(z, tw + 2 * (511 + 3 * g), q);
 #pragma unroll
         for (int k = 0; k < 4; ++k) y[4 * gg + k] = z[k];
@@ -406,9 +412,9 @@ __device__ __forceinline__ void fwd_rows_2048(u64* s, const u64* tw, u64 q, u64 
 __device__ __forceinline__ void inv_rows_2048(u64* s, const u64* tw, u64 q, u64 (&x)[8], u64 (&y)[8]) {
     const int tid = threadIdx.x;
     inv_group<3>(x, tw + 2 * 7 * tid, q);
-    u64* sb = s + 8 * tid + (tid >> 2);
+    u64* sb = s + row_at(8 * tid);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) sb[k] = x[k];
+    for (int k = 0; k < 8; k += 2) st2(sb + k, u64x2{x[k], x[k + 1]});
     __syncthreads();
     inv_row_round<3, 7>(s, tw, 1792, q);
     __syncthreads();
@@ -417,10 +423,10 @@ __device__ __forceinline__ void inv_rows_2048(u64* s, const u64* tw, u64 q, u64 
 #pragma unroll
     for (int gg = 0; gg < 2; ++gg) {
         const int g = gg * TPB + tid;
-        const u64* sg = s + g + (g >> 5);
+        const u64* sg = s + row_at(g);
         u64 z[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) z[k] = sg[528 * k];
+        for (int k = 0; k < 4; ++k) z[k] = sg[row_at(512 * k)];
         inv_group<2>(z, tw + 2 * 2044, q);
 #pragma unroll
         for (int k = 0; k < 4; ++k) y[4 * gg + k] = z[k];
@@ -546,12 +552,18 @@ __device__ __forceinline__ void inv_cols_any(u64* s, int L1, const u64* W, const
 
 // ---- FP64 butterflies for primes below 2^46.  A residue is held as an integer-valued double
 // (balanced: any sign, |x| a small multiple of q).  x w mod q: the product is split exactly as
-// hi + lo (hi = fl(x w), lo = fma(x, w, -hi)), c = rint(x fl(w / q)) is within one of the
-// rounded quotient, and fma(-c, q, hi) + lo = x w - c q exactly; for |x| < 32 q and q < 2^46 the
-// result lies in (-q, q).  Forward (Cooley-Tukey) passes add at most q per stage, so 15 stages
-// from |x| < 4q need no reduction; inverse (Gentleman-Sande) rounds reduce their inputs to
-// |x| <= q/2 + 1 first (x - rint(x / q) q).  One FP64 butterfly is 8 instructions (v_mul_f64,
-// v_fma_f64, v_rndne_f64, v_add_f64), against 27 for the 64-bit integer Shoup butterfly.
+// hi + lo (hi = fl(x w), lo = fma(x, w, -hi)), c = rint(hi fl(1 / q)), and fma(-c, q, hi) + lo = x w - c q
+// exactly.  hi, 1 / q and their product are each off by 2^-53 of themselves, so c is off the
+// quotient by at most 1/2 + 1.5 2^-52 |x w| / q; forward (Cooley-Tukey) passes start below 4q and add less than q per
+// stage: |x| < 19.3 q after 15 stages, where |x w mod q| < 0.95 q for q < 2^46.  Inverse
+// (Gentleman-Sande) rounds reduce their inputs to |x| <= q/2 + 1 first (x - rint(x / q) q) and stay
+// below 16 q.  One FP64 butterfly is 8 instructions (v_mul_f64, v_fma_f64, v_rndne_f64,
+// v_add_f64), against 27 for the 64-bit integer Shoup butterfly.  The quotient comes from the
+// product instead of from a second table word w / q: one more step in the chain, but half the
+// twiddle bytes, loads and registers (the row passes spent more address-unit cycles on twiddles
+// than on the limbs).  Per batched step of 16 h = 64 products at N = 2^15, with the bank padding and the
+// FP64 ModDown combine: ModDown row pass 7.76 -> 7.35 ms (six waves per SIMD; five 8.71, seven 9.33), plain
+// row pass 3.02 -> 2.86, inverse 3.64 -> 3.49.
 // Between the two passes of a transform the limb holds the raw double words; the transform's
 // output is canonical.  Both passes of a limb decide by the same rule (fp64_limb).
 typedef double f64x2 __attribute__((ext_vector_type(2)));
@@ -574,30 +586,48 @@ __device__ __forceinline__ u64 canon_d(double x, double q, double qinv) {
     r = r < 0.0 ? r + q : r;
     return (u64)__double_as_longlong(r + 4503599627370496.0) & 0xFFFFFFFFFFFFFull;
 }
-__device__ __forceinline__ double mulmod_d(double a, double w, double wq, double q) {
+__device__ __forceinline__ double mulmod_d(double a, double w, double q, double qinv) {
 #pragma clang fp contract(off)
     const double hi = a * w;
     const double lo = __fma_rn(a, w, -hi);
-    const double c = rint(a * wq);
+    const double c = rint(hi * qinv);
     return __fma_rn(-c, q, hi) + lo;
+}
+// an integer-valued x in (-q, q) as its residue in [0, q): x + 2^52 or x + q + 2^52 has it in its low bits
+__device__ __forceinline__ u64 signed_word_d(double x, double q) {
+#pragma clang fp contract(off)
+    return d_bits(x + (x < 0.0 ? q + 4503599627370496.0 : 4503599627370496.0)) & 0xFFFFFFFFFFFFFull;
+}
+// 2^R - 1 twiddles of a group from a 16-byte aligned row table (8 doubles per group of R = 3, 4 of R = 2)
+template <int R>
+struct TwD {
+    double w[1 << R];
+};
+template <int R>
+__device__ __forceinline__ TwD<R> ld_tw(const double* __restrict__ t) {
+    TwD<R> r;
+#pragma unroll
+    for (int i = 0; i < (1 << R); i += 2) {
+        const f64x2 v = ld2d(t + i);
+        r.w[i] = v.x;
+        r.w[i + 1] = v.y;
+    }
+    return r;
 }
 
 template <int R>
-__device__ __forceinline__ void fwd_group_d(double (&x)[1 << R], const double* __restrict__ t, double q) {
+__device__ __forceinline__ void fwd_group_d(double (&x)[1 << R], const TwD<R>& t, double q, double qinv) {
 #pragma clang fp contract(off)
     constexpr int G = 1 << R;
-    f64x2 w[G - 1];
-#pragma unroll
-    for (int i = 0; i < G - 1; ++i) w[i] = ld2d(t + 2 * i);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int half = G >> (r + 1);
 #pragma unroll
         for (int b = 0; b < (1 << r); ++b) {
-            const f64x2 wb = w[(1 << r) - 1 + b];
+            const double w = t.w[(1 << r) - 1 + b];
 #pragma unroll
             for (int k = b * 2 * half; k < b * 2 * half + half; ++k) {
-                const double V = mulmod_d(x[k + half], wb.x, wb.y, q);
+                const double V = mulmod_d(x[k + half], w, q, qinv);
                 const double U = x[k];
                 x[k] = U + V;
                 x[k + half] = U - V;
@@ -608,124 +638,103 @@ __device__ __forceinline__ void fwd_group_d(double (&x)[1 << R], const double* _
 
 // the inverse group reduces its inputs first (|x| <= q/2 + 1)
 template <int R>
-__device__ __forceinline__ void inv_group_d(double (&x)[1 << R], const double* __restrict__ t, double q,
-                                            double qinv) {
+__device__ __forceinline__ void inv_group_d(double (&x)[1 << R], const TwD<R>& t, double q, double qinv) {
 #pragma clang fp contract(off)
     constexpr int G = 1 << R;
 #pragma unroll
     for (int k = 0; k < G; ++k) x[k] = red_d(x[k], q, qinv);
-    f64x2 w[G - 1];
-#pragma unroll
-    for (int i = 0; i < G - 1; ++i) w[i] = ld2d(t + 2 * i);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int half = 1 << r;
 #pragma unroll
         for (int b = 0; b < (G >> (r + 1)); ++b) {
-            const f64x2 wb = w[G - (G >> r) + b];
+            const double w = t.w[G - (G >> r) + b];
 #pragma unroll
             for (int k = b * 2 * half; k < b * 2 * half + half; ++k) {
                 const double U = x[k], V = x[k + half];
                 x[k] = U + V;
-                x[k + half] = mulmod_d(U - V, wb.x, wb.y, q);
+                x[k + half] = mulmod_d(U - V, w, q, qinv);
             }
         }
     }
 }
 
-template <int R, int S0>
-__device__ __forceinline__ void fwd_row_round_d(double* s, const double* __restrict__ tw, int off, double q) {
-    constexpr int G = 1 << R, NG = 8 / G, LD = 11 - S0 - R, D = 1 << LD;
+// one round of eight elements per lane in LDS, D apart from base
+template <int D, class F>
+__device__ __forceinline__ void row_round_d(double* s, int base, F&& group) {
+    double* sb = s + row_at(base);
+    double x[8];
 #pragma unroll
-    for (int gg = 0; gg < NG; ++gg) {
-        const int g = gg * TPB + threadIdx.x;
-        const int J = g >> LD;
-        const int base = (J << (LD + R)) + (g & (D - 1));
-        double* sb = s + base + (base >> 5);
-        double x[G];
+    for (int k = 0; k < 8; ++k) x[k] = sb[row_at(k * D)];
+    group(x);
 #pragma unroll
-        for (int k = 0; k < G; ++k) x[k] = sb[k * D + ((k * D) >> 5)];
-        fwd_group_d<R>(x, tw + 2 * (off + J * (G - 1)), q);
-#pragma unroll
-        for (int k = 0; k < G; ++k) sb[k * D + ((k * D) >> 5)] = x[k];
-    }
+    for (int k = 0; k < 8; ++k) sb[row_at(k * D)] = x[k];
 }
 
-template <int R, int S0>
-__device__ __forceinline__ void inv_row_round_d(double* s, const double* __restrict__ tw, int off, double q,
-                                                double qinv) {
-    constexpr int G = 1 << R, NG = 8 / G, LD = 11 - S0 - 1, D = 1 << LD;
-#pragma unroll
-    for (int gg = 0; gg < NG; ++gg) {
-        const int g = gg * TPB + threadIdx.x;
-        const int J = g >> LD;
-        const int base = (J << (LD + R)) + (g & (D - 1));
-        double* sb = s + base + (base >> 5);
-        double x[G];
-#pragma unroll
-        for (int k = 0; k < G; ++k) x[k] = sb[k * D + ((k * D) >> 5)];
-        inv_group_d<R>(x, tw + 2 * (off + J * (G - 1)), q, qinv);
-#pragma unroll
-        for (int k = 0; k < G; ++k) sb[k * D + ((k * D) >> 5)] = x[k];
-    }
-}
-
-// register-first and register-last row passes, as the integer ones above
+// register-first and register-last row passes, as the integer ones above.  The twiddles of a round do
+// not depend on the data, so they are loaded a round ahead, before the barrier: in launches of a few
+// blocks per CU the rounds otherwise wait for them one after another.
+// Table of a row (ROW_TWD doubles): forward 8 | 8 x 8 | 64 x 8 | 512 x 4, inverse 256 x 8 | 32 x 8 | 4 x 8 | 4.
 template <class F>
-__device__ __forceinline__ void fwd_rows_2048_d(double* s, const double* tw, double q, double (&x)[8],
-                                                double (&y)[8], F&& after_first) {
+__device__ __forceinline__ void fwd_rows_2048_d(double* s, const double* __restrict__ tw, double q, double qinv,
+                                                double (&x)[8], double (&y)[8], F&& after_first) {
     const int tid = threadIdx.x;
-    fwd_group_d<3>(x, tw, q);
-    double* sb = s + tid + (tid >> 5);
+    const TwD<3> t2 = ld_tw<3>(tw + 8 + 8 * (tid >> 5));
+    fwd_group_d<3>(x, ld_tw<3>(tw), q, qinv);
+    double* sb = s + row_at(tid);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) sb[264 * k] = x[k];
+    for (int k = 0; k < 8; ++k) sb[row_at(256 * k)] = x[k];
     after_first();
+    const TwD<3> t3 = ld_tw<3>(tw + 72 + 8 * (tid >> 2));
     __syncthreads();
-    fwd_row_round_d<3, 3>(s, tw, 7, q);
+    row_round_d<32>(s, ((tid >> 5) << 8) + (tid & 31), [&](double(&v)[8]) { fwd_group_d<3>(v, t2, q, qinv); });
+    TwD<2> t4[2];
+#pragma unroll
+    for (int gg = 0; gg < 2; ++gg) t4[gg] = ld_tw<2>(tw + 584 + 4 * (gg * TPB + tid));
     __syncthreads();
-    fwd_row_round_d<3, 6>(s, tw, 63, q);
+    row_round_d<4>(s, ((tid >> 2) << 5) + (tid & 3), [&](double(&v)[8]) { fwd_group_d<3>(v, t3, q, qinv); });
     __syncthreads();
 #pragma unroll
     for (int gg = 0; gg < 2; ++gg) {
-        const int g = gg * TPB + tid;
-        const double* sg = s + 4 * g + (g >> 3);
-        double z[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) z[k] = sg[k];
-        fwd_group_d<2>(z, tw + 2 * (511 + 3 * g), q);
+        const double* sg = s + row_at(4 * (gg * TPB + tid));
+        const f64x2 z0 = ld2d(sg), z1 = ld2d(sg + 2);
+        double z[4] = {z0.x, z0.y, z1.x, z1.y};
+        fwd_group_d<2>(z, t4[gg], q, qinv);
 #pragma unroll
         for (int k = 0; k < 4; ++k) y[4 * gg + k] = z[k];
     }
 }
 
-__device__ __forceinline__ void inv_rows_2048_d(double* s, const double* tw, double q, double qinv,
+__device__ __forceinline__ void inv_rows_2048_d(double* s, const double* __restrict__ tw, double q, double qinv,
                                                 double (&x)[8], double (&y)[8]) {
     const int tid = threadIdx.x;
-    inv_group_d<3>(x, tw + 2 * 7 * tid, q, qinv);
-    double* sb = s + 8 * tid + (tid >> 2);
+    const TwD<3> t1 = ld_tw<3>(tw + 8 * tid), t2 = ld_tw<3>(tw + 2048 + 8 * (tid >> 3));
+    inv_group_d<3>(x, t1, q, qinv);
+    double* sb = s + row_at(8 * tid);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) sb[k] = x[k];
+    for (int k = 0; k < 8; k += 2) *reinterpret_cast<f64x2*>(sb + k) = f64x2{x[k], x[k + 1]};
+    const TwD<3> t3 = ld_tw<3>(tw + 2304 + 8 * (tid >> 6));
     __syncthreads();
-    inv_row_round_d<3, 7>(s, tw, 1792, q, qinv);
+    row_round_d<8>(s, ((tid >> 3) << 6) + (tid & 7), [&](double(&v)[8]) { inv_group_d<3>(v, t2, q, qinv); });
+    const TwD<2> t4 = ld_tw<2>(tw + 2336);
     __syncthreads();
-    inv_row_round_d<3, 4>(s, tw, 2016, q, qinv);
+    row_round_d<64>(s, ((tid >> 6) << 9) + (tid & 63), [&](double(&v)[8]) { inv_group_d<3>(v, t3, q, qinv); });
     __syncthreads();
 #pragma unroll
     for (int gg = 0; gg < 2; ++gg) {
-        const int g = gg * TPB + tid;
-        const double* sg = s + g + (g >> 5);
+        const double* sg = s + row_at(gg * TPB + tid);
         double z[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) z[k] = sg[528 * k];
-        inv_group_d<2>(z, tw + 2 * 2044, q, qinv);
+        for (int k = 0; k < 4; ++k) z[k] = sg[row_at(512 * k)];
+        inv_group_d<2>(z, t4, q, qinv);
 #pragma unroll
         for (int k = 0; k < 4; ++k) y[4 * gg + k] = z[k];
     }
 }
 
-// column rounds (L1 <= 5): wave-uniform twiddles (w, fl(w / q)) from the [M][N1] column table
+// column rounds (L1 <= 5): wave-uniform twiddles from the [M][N1] column table
 template <int R, int S0, int L1>
-__device__ __forceinline__ void fwd_col_round_d(double* s, const double* __restrict__ W, double q) {
+__device__ __forceinline__ void fwd_col_round_d(double* s, const double* __restrict__ W, double q, double qinv) {
 #pragma clang fp contract(off)
     constexpr int G = 1 << R, NG = 8 / G, LD = L1 - S0 - R, D = 1 << LD, LOGT = 11 - L1, TC = 1 << LOGT;
 #pragma unroll
@@ -744,10 +753,10 @@ __device__ __forceinline__ void fwd_col_round_d(double* s, const double* __restr
 #pragma unroll
             for (int b = 0; b < (1 << r); ++b) {
                 const int idx = (1 << (S0 + r)) + (J << r) + b;
-                const double w = W[2 * idx], wq = W[2 * idx + 1];
+                const double w = W[idx];
 #pragma unroll
                 for (int k = b * 2 * half; k < b * 2 * half + half; ++k) {
-                    const double V = mulmod_d(x[k + half], w, wq, q);
+                    const double V = mulmod_d(x[k + half], w, q, qinv);
                     const double U = x[k];
                     x[k] = U + V;
                     x[k + half] = U - V;
@@ -779,12 +788,12 @@ __device__ __forceinline__ void inv_col_round_d(double* s, const double* __restr
 #pragma unroll
             for (int b = 0; b < (G >> (r + 1)); ++b) {
                 const int idx = (1 << (S0 - r)) + (J << (R - 1 - r)) + b;
-                const double w = W[2 * idx], wq = W[2 * idx + 1];
+                const double w = W[idx];
 #pragma unroll
                 for (int k = b * 2 * half; k < b * 2 * half + half; ++k) {
                     const double U = x[k], V = x[k + half];
                     x[k] = U + V;
-                    x[k + half] = mulmod_d(U - V, w, wq, q);
+                    x[k + half] = mulmod_d(U - V, w, q, qinv);
                 }
             }
         }
@@ -794,12 +803,12 @@ __device__ __forceinline__ void inv_col_round_d(double* s, const double* __restr
 }
 
 template <int L1, int S0>
-__device__ __forceinline__ void fwd_cols_from_d(double* s, const double* W, double q) {
+__device__ __forceinline__ void fwd_cols_from_d(double* s, const double* W, double q, double qinv) {
     if constexpr (S0 < L1) {
         constexpr int R = L1 - S0 >= 3 ? 3 : L1 - S0;
-        fwd_col_round_d<R, S0, L1>(s, W, q);
+        fwd_col_round_d<R, S0, L1>(s, W, q, qinv);
         __syncthreads();
-        fwd_cols_from_d<L1, S0 + R>(s, W, q);
+        fwd_cols_from_d<L1, S0 + R>(s, W, q, qinv);
     }
 }
 
@@ -814,13 +823,13 @@ __device__ __forceinline__ void inv_cols_from_d(double* s, const double* W, doub
 }
 
 // L1 in 1..5 (fp64_limb holds)
-__device__ __forceinline__ void fwd_cols_any_d(double* s, int L1, const double* W, double q) {
+__device__ __forceinline__ void fwd_cols_any_d(double* s, int L1, const double* W, double q, double qinv) {
     switch (L1) {
-        case 1: fwd_cols_from_d<1, 0>(s, W, q); break;
-        case 2: fwd_cols_from_d<2, 0>(s, W, q); break;
-        case 3: fwd_cols_from_d<3, 0>(s, W, q); break;
-        case 4: fwd_cols_from_d<4, 0>(s, W, q); break;
-        default: fwd_cols_from_d<5, 0>(s, W, q); break;
+        case 1: fwd_cols_from_d<1, 0>(s, W, q, qinv); break;
+        case 2: fwd_cols_from_d<2, 0>(s, W, q, qinv); break;
+        case 3: fwd_cols_from_d<3, 0>(s, W, q, qinv); break;
+        case 4: fwd_cols_from_d<4, 0>(s, W, q, qinv); break;
+        default: fwd_cols_from_d<5, 0>(s, W, q, qinv); break;
     }
 }
 
@@ -853,7 +862,7 @@ __global__ __launch_bounds__(TPB) void k_ntt_fwd_cols(DevTables T, Jobs J) {
             sd[e + 1] = u2d(v.y);
         }
         __syncthreads();
-        fwd_cols_any_d(sd, L1, T.cold + (int64_t)mi * (2 << L1), (double)q);
+        fwd_cols_any_d(sd, L1, T.cold + ((int64_t)mi << L1), (double)q, 1.0 / (double)q);
         // raw double words for the FP64 row pass of this limb
         for (int e = 2 * threadIdx.x; e < NTT_E; e += 2 * TPB)
             st2(a + (int64_t)(e >> logC) * N2 + c0 + (e & (C - 1)), u64x2{d_bits(sd[e]), d_bits(sd[e + 1])});
@@ -876,8 +885,8 @@ __device__ __forceinline__ int perm_g(int j, u64 g, int log_n);
 // EPI: the ModDown epilogue (E.on) is compiled in; without it the plain transform keeps its
 // smaller register footprint
 template <bool EPI>
-__global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(6))) void k_ntt_fwd_rows(DevTables T, Jobs J, Epi E) {
-    __shared__ u64 s[NTT_LDS];
+__global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(EPI ? 6 : 7))) void k_ntt_fwd_rows(DevTables T, Jobs J, Epi E) {
+    __shared__ __align__(16) u64 s[ROW_LDS];
     const int N = 1 << T.log_n, L1 = T.n1_log, L2 = T.n2_log, N1 = 1 << L1, N2 = 1 << L2;
     // jobs in reverse order: the column pass before it wrote the last jobs last, so their limbs
     // are the likeliest to still be in the memory-side cache
@@ -887,9 +896,10 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(6))) void k
     const int mi = J.mod[k];
     const u64 q = T.mods[mi].q, q2 = 2 * q;
     const bool fp = fp64_limb(q, L1, N2), full = N2 == NTT_E;
-    // 2048-element rows: the last round's elements 4 g + k (g = tid, 256 + tid) as words,
-    // canonical (FP64 path) or lazy in [0, 4q) (integer path)
+    // 2048-element rows: the last round's elements 4 g + k (g = tid, 256 + tid), as raw doubles (FP64
+    // path) or words lazy in [0, 4q) (integer path)
     u64 y[8];
+    const double qd = (double)q, qinv = 1.0 / qd;
     // the ModDown epilogue's u words of those elements, loaded while the middle rounds run
     u64x2 uu[4];
     const u64* u = nullptr;
@@ -904,17 +914,15 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(6))) void k
         }
     };
     if (fp) {
-        const double qd = (double)q, qinv = 1.0 / qd;
         double x[8], yd[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {  // the column pass left raw doubles (N1 > 1), else canonical words
             const u64 v = a[tid + TPB * i];
             x[i] = L1 ? bits_d(v) : u2d(v);
         }
-        fwd_rows_2048_d(reinterpret_cast<double*>(s), T.rtwd + ((int64_t)mi * N1 + r) * (2 * ROW_TW), qd, x, yd,
-                        prefetch_u);
+        fwd_rows_2048_d(reinterpret_cast<double*>(s), T.rtwd + ((int64_t)mi * N1 + r) * ROW_TWD, qd, qinv, x, yd, prefetch_u);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) y[i] = canon_d(yd[i], qd, qinv);
+        for (int i = 0; i < 8; ++i) y[i] = d_bits(yd[i]);
     } else if (full) {
         u64 x[8];
 #pragma unroll
@@ -943,8 +951,8 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(6))) void k
             __syncthreads();
         }
     }
-    // emit(i, e, v0, v1): elements e, e + 1 of the row (words below 4q) to their destination;
-    // i is the pair's slot in uu (2048-element rows), or -1
+    // emit(i, e, v0, v1): elements e, e + 1 of the row (words below 4q, or the bits of raw doubles on
+    // the FP64 path) to their destination; i is the pair's slot in uu (2048-element rows), or -1
     auto for_pairs = [&](auto&& emit) {
         if (fp || full) {
 #pragma unroll
@@ -955,7 +963,10 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(6))) void k
     };
     if constexpr (!EPI) {
         for_pairs([&](int, int e, u64 v0, u64 v1) {
-            if (!fp) {
+            if (fp) {
+                v0 = canon_d(bits_d(v0), qd, qinv);
+                v1 = canon_d(bits_d(v1), qd, qinv);
+            } else {
                 v0 = red4(v0, q2);
                 v1 = red4(v1, q2);
                 v0 = v0 >= q ? v0 - q : v0;
@@ -969,15 +980,25 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(6))) void k
     const u64* add = E.add[p] ? E.add[p] + c * E.add_cs + (int64_t)t * N : nullptr;
     u64* out = E.out[p] + c * E.out_cs + (int64_t)t * N;
     const u64 pi = E.pinv[t], pis = E.pinv_sh[t];
+    const double pd = (double)pi;
     const u64* mask = E.mask ? E.mask + (int64_t)t * N : nullptr;
     const u64* acc = E.acc[p] ? E.acc[p] + c * E.acc_cs + (int64_t)t * N : nullptr;
     const u64 qninv = T.mods[mi].qninv;
     for_pairs([&](int slot, int e, u64 v0, u64 v1) {
         const int i = r * N2 + e;
-        const u64x2 uw = slot >= 0 ? uu[slot] : ld2(u + i);
-        // v is below 4q and u < q, so u + 4q - v lies in (0, 5q); the Shoup product
-        // reduces any 64-bit operand to [0, q)
-        u64 w[2] = {mul_shoup(uw.x + 2 * q2 - v0, pi, pis, q), mul_shoup(uw.y + 2 * q2 - v1, pi, pis, q)};
+        const u64x2 uw = slot >= 0 ? uu[slot & 3] : ld2(u + i);
+        u64 w[2];
+        if (fp) {
+            // |u - v| < 20.3 q, so the product lies in (-q, q): one conditional q makes it canonical
+            // (14 instructions a word against 33 for the canonical v and an integer Shoup product)
+            w[0] = signed_word_d(mulmod_d(u2d(uw.x) - bits_d(v0), pd, qd, qinv), qd);
+            w[1] = signed_word_d(mulmod_d(u2d(uw.y) - bits_d(v1), pd, qd, qinv), qd);
+        } else {
+            // v is below 4q and u < q, so u + 4q - v lies in (0, 5q); the Shoup product
+            // reduces any 64-bit operand to [0, q)
+            w[0] = mul_shoup(uw.x + 2 * q2 - v0, pi, pis, q);
+            w[1] = mul_shoup(uw.y + 2 * q2 - v1, pi, pis, q);
+        }
         if (add) {
             if (E.g == 1) {
                 const u64x2 ad = ld2(add + i);
@@ -1008,7 +1029,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(6))) void k
 // conversion that follows, and then stores the centred representative (y - q when y > (q-1)/2,
 // as a two's-complement word), so the conversion reads its prepared inputs directly.
 __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(8))) void k_ntt_inv_rows(DevTables T, Jobs J, const u64* scale, int scale_n) {
-    __shared__ u64 s[NTT_LDS];
+    __shared__ __align__(16) u64 s[ROW_LDS];
     const int N = 1 << T.log_n, L1 = T.n1_log, L2 = T.n2_log, N1 = 1 << L1, N2 = 1 << L2;
     const int job = blockIdx.y, c = job / J.n, k = job % J.n;
     const int r = blockIdx.x, tid = threadIdx.x;
@@ -1029,14 +1050,13 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(8))) void k
             x[2 * i] = u2d(v.x);
             x[2 * i + 1] = u2d(v.y);
         }
-        inv_rows_2048_d(reinterpret_cast<double*>(s), T.irtwd + ((int64_t)mi * N1 + r) * (2 * ROW_TW), qd, qinv, x,
-                        y);
+        inv_rows_2048_d(reinterpret_cast<double*>(s), T.irtwd + ((int64_t)mi * N1 + r) * ROW_TWD, qd, qinv, x, y);
         if (L1 == 0) {
             const u64 f = scale ? scale[2 * (k % scale_n)] : mp_.ninv;
-            const double fd = (double)f, fq = fd / qd;
+            const double fd = (double)f;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                u64 w = canon_d(mulmod_d(y[i], fd, fq, qd), qd, qinv);
+                u64 w = canon_d(mulmod_d(y[i], fd, qd, qinv), qd, qinv);
                 if (scale) w = w > mp_.half ? w - q : w;
                 a[(i >> 2) * TPB + tid + 512 * (i & 3)] = w;
             }
@@ -1124,14 +1144,14 @@ __global__ __launch_bounds__(TPB) void k_ntt_inv_cols(DevTables T, Jobs J, const
             sd[e + 1] = bits_d(v.y);
         }
         __syncthreads();
-        inv_cols_any_d(sd, L1, T.icold + (int64_t)mi * (2 << L1), qd, qinv);
+        inv_cols_any_d(sd, L1, T.icold + ((int64_t)mi << L1), qd, qinv);
         const u64 f = scale ? scale[2 * (k % scale_n)] : mp_.ninv;
-        const double fd = (double)f, fq = fd / qd;
+        const double fd = (double)f;
         for (int e = 2 * threadIdx.x; e < NTT_E; e += 2 * TPB) {
             u64 y[2];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                y[h] = canon_d(mulmod_d(sd[e + h], fd, fq, qd), qd, qinv);
+                y[h] = canon_d(mulmod_d(sd[e + h], fd, qd, qinv), qd, qinv);
                 if (scale) y[h] = y[h] > mp_.half ? y[h] - q : y[h];
             }
             st2(a + (int64_t)(e >> logC) * N2 + c0 + (e & (C - 1)), u64x2{y[0], y[1]});
@@ -1223,7 +1243,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(8))) void k
     __syncthreads();
     u64* a = D.dst + c * D.dst_cstride + p * D.dst_pstride + (int64_t)D.doff[t] * N;
     if (fp) {  // raw double words for the FP64 row pass of this limb
-        fwd_cols_any_d(sd, L1, T.cold + (int64_t)mi * (2 << L1), (double)m.q);
+        fwd_cols_any_d(sd, L1, T.cold + ((int64_t)mi << L1), (double)m.q, 1.0 / (double)m.q);
         for (int e = 2 * threadIdx.x; e < NTT_E; e += 2 * TPB)
             st2(a + (int64_t)(e >> logC) * N2 + col0 + (e & (C - 1)), u64x2{d_bits(sd[e]), d_bits(sd[e + 1])});
         return;
@@ -1276,7 +1296,6 @@ template <class V>
 __device__ __forceinline__ V* lane_at(u64* base, uint32_t off) {
     return reinterpret_cast<V*>(reinterpret_cast<char*>(base) + off);
 }
-__device__ __forceinline__ f64x2 pair_d(u64x2 w) { return f64x2{bits_d(w.x), bits_d(w.y)}; }
 template <int L1>
 __device__ __forceinline__ void inv_col_regs_d(double (&x)[1 << L1], const u64x2* W, double q, double qinv) {
 #pragma clang fp contract(off)
@@ -1289,18 +1308,18 @@ __device__ __forceinline__ void inv_col_regs_d(double (&x)[1 << L1], const u64x2
         const int d = (1 << L1) >> (st + 1);
 #pragma unroll
         for (int i = 0; i < (1 << st); ++i) {
-            const f64x2 w = pair_d(W[(1 << st) + i]);
+            const double w = bits_d(W[(1 << st) + i].x);
 #pragma unroll
             for (int j = i * 2 * d; j < i * 2 * d + d; ++j) {
                 const double U = x[j], V = x[j + d];
                 x[j] = U + V;
-                x[j + d] = mulmod_d(U - V, w.x, w.y, q);
+                x[j + d] = mulmod_d(U - V, w, q, qinv);
             }
         }
     }
 }
 template <int L1>
-__device__ __forceinline__ void fwd_col_regs_d(double (&x)[1 << L1], const u64x2* W, double q) {
+__device__ __forceinline__ void fwd_col_regs_d(double (&x)[1 << L1], const u64x2* W, double q, double qinv) {
 #pragma clang fp contract(off)
 #pragma unroll
     for (int st = 0; st < L1; ++st) {
@@ -1308,10 +1327,10 @@ __device__ __forceinline__ void fwd_col_regs_d(double (&x)[1 << L1], const u64x2
         const int d = (1 << L1) >> (st + 1);
 #pragma unroll
         for (int i = 0; i < (1 << st); ++i) {
-            const f64x2 w = pair_d(W[(1 << st) + i]);
+            const double w = bits_d(W[(1 << st) + i].x);
 #pragma unroll
             for (int j = i * 2 * d; j < i * 2 * d + d; ++j) {
-                const double V = mulmod_d(x[j + d], w.x, w.y, q);
+                const double V = mulmod_d(x[j + d], w, q, qinv);
                 const double U = x[j];
                 x[j] = U + V;
                 x[j + d] = U - V;
@@ -1384,27 +1403,27 @@ __device__ __forceinline__ void inv_col_split_d(double (&x)[(1 << L1) / SP], con
             const double sgn = (v & d) ? -1.0 : 1.0;
 #pragma unroll
             for (int j = 0; j < M; ++j) {
-                const f64x2 w = pair_d(W[cross_twiddle<SP>(st, d, j, v)]);
+                const double w = bits_d(W[cross_twiddle<SP>(st, d, j, v)].x);
                 const double s = __fma_rn(x[j], sgn, lane_xor_d(x[j], 16 * d));
-                x[j] = mulmod_d(s, w.x, w.y, q);
+                x[j] = mulmod_d(s, w, q, qinv);
             }
         } else {
             const int dj = d / SP;
 #pragma unroll
             for (int i = 0; i < (1 << st); ++i) {
-                const f64x2 w = pair_d(W[(1 << st) + i]);
+                const double w = bits_d(W[(1 << st) + i].x);
 #pragma unroll
                 for (int j = i * 2 * dj; j < i * 2 * dj + dj; ++j) {
                     const double U = x[j], V = x[j + dj];
                     x[j] = U + V;
-                    x[j + dj] = mulmod_d(U - V, w.x, w.y, q);
+                    x[j + dj] = mulmod_d(U - V, w, q, qinv);
                 }
             }
         }
     }
 }
 template <int L1, int SP>
-__device__ __forceinline__ void fwd_col_split_d(double (&x)[(1 << L1) / SP], const u64x2* W, int v, double q) {
+__device__ __forceinline__ void fwd_col_split_d(double (&x)[(1 << L1) / SP], const u64x2* W, int v, double q, double qinv) {
 #pragma clang fp contract(off)
     constexpr int M = (1 << L1) / SP;
 #pragma unroll
@@ -1415,18 +1434,18 @@ __device__ __forceinline__ void fwd_col_split_d(double (&x)[(1 << L1) / SP], con
             const double sgn = (v & d) ? -1.0 : 1.0;
 #pragma unroll
             for (int j = 0; j < M; ++j) {
-                const f64x2 w = pair_d(W[cross_twiddle<SP>(st, d, j, v)]);
-                const double t = mulmod_d(x[j], w.x, w.y, q);
+                const double w = bits_d(W[cross_twiddle<SP>(st, d, j, v)].x);
+                const double t = mulmod_d(x[j], w, q, qinv);
                 x[j] = __fma_rn(t, sgn, lane_xor_d(t, 16 * d));
             }
         } else {
             const int dj = d / SP;
 #pragma unroll
             for (int i = 0; i < (1 << st); ++i) {
-                const f64x2 w = pair_d(W[(1 << st) + i]);
+                const double w = bits_d(W[(1 << st) + i].x);
 #pragma unroll
                 for (int j = i * 2 * dj; j < i * 2 * dj + dj; ++j) {
-                    const double V = mulmod_d(x[j + dj], w.x, w.y, q);
+                    const double V = mulmod_d(x[j + dj], w, q, qinv);
                     const double U = x[j];
                     x[j] = U + V;
                     x[j + dj] = U - V;
@@ -1553,7 +1572,7 @@ __device__ __forceinline__ void conv_source(u64 (&b)[(1 << L1) / SP], const ModP
     const u64 q = m.q;
     so += (uint32_t)v * (N2 * 8u);
     if (fp64_limb(q, L1, N2)) {
-        const double qd = (double)q, qinv = 1.0 / qd, fd = (double)f, fq = fd / qd;
+        const double qd = (double)q, qinv = 1.0 / qd, fd = (double)f;
         double x[M];
         unrolled<M>([&](auto j) { x[j] = *lane_at<double>(src + j * (SP * N2), so); });
         if constexpr (SP == 1) inv_col_regs_d<L1>(x, W, qd, qinv);
@@ -1562,7 +1581,7 @@ __device__ __forceinline__ void conv_source(u64 (&b)[(1 << L1) / SP], const ModP
             // centred exactly: |x f mod q| < q, so rint of the quotient is exact; as a word, the
             // bits of y + 1.5 2^52 less those of 1.5 2^52
             if (j % 4 == 0) stage_fence();
-            const double y = red_d(mulmod_d(x[j], fd, fq, qd), qd, qinv);
+            const double y = red_d(mulmod_d(x[j], fd, qd, qinv), qd, qinv);
             b[j] = signed_bytes(d_bits(y + 6755399441055744.0) - 0x4338000000000000ull);
             keep_here(b[j]);
         });
@@ -1601,8 +1620,8 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(conv_waves(
     const int col = x0 * 64 + (threadIdx.x >> 6) * 16 + (lane & 15);
     const ConvDig dg = D.dig[D.it_dig[item]];
 
-    // twiddles of the sources and of the item's targets into LDS, as (w, companion) pairs: one row of
-    // N1 (and a pad pair) per limb.  Read from global memory they cost the column stages 15 loads of
+    // twiddles of the sources and of the item's targets into LDS, as (w, w') pairs (w alone for FP64
+    // limbs): one row of N1 (and a pad pair) per limb.  Read from global memory they cost the column stages 15 loads of
     // 16 bytes per lane and target, which filled the CU's one address unit
     constexpr int LD = N1 + 1;
     extern __shared__ u64x2 tw[];
@@ -1611,9 +1630,9 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(conv_waves(
         const int r = e >> L1, i = e & (N1 - 1);
         const bool inv = r < dg.ns;
         const int k = r - dg.ns, mi = inv ? dg.smod + r : D.sets[s0 + (k >> 2)].dmod[k & 3];
-        u64x2 w;
+        u64x2 w = {0, 0};
         if (fp64_limb(T.mods[mi].q, L1, N2)) {
-            w = ld2(reinterpret_cast<const u64*>(inv ? T.icold : T.cold) + 2 * (mi * N1 + i));
+            w.x = d_bits((inv ? T.icold : T.cold)[mi * N1 + i]);
         } else {
             w.x = (inv ? T.ipsi : T.psi)[(int64_t)mi * N + i];
             w.y = (inv ? T.ipsi_sh : T.psi_sh)[(int64_t)mi * N + i];
@@ -1692,7 +1711,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(conv_waves(
                 if (S.fp) {
                     double x[M];
                     unrolled<M>([&](auto j) { x[j] = digits_mod_d(lo[j], hi[j], qd, qinv, small); });
-                    fwd_col_split_d<L1, 4>(x, W, grp, qd);
+                    fwd_col_split_d<L1, 4>(x, W, grp, qd, qinv);
                     unrolled<M>([&](auto j) { *lane_at<u64>(dst + j * (4 * N2), od) = d_bits(x[j]); });
                 } else {
                     u64 x[M];
@@ -1711,7 +1730,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(conv_waves(
                                     qinv, small);
                 keep_here(x[r]);
             });
-            fwd_col_regs_d<L1>(x, W, qd);
+            fwd_col_regs_d<L1>(x, W, qd, qinv);
             unrolled<N1>([&](auto r) { keep_here(x[r]); });
             if (grp < S.nt) unrolled<N1>([&](auto r) { *lane_at<u64>(dst + r * N2, od) = d_bits(x[r]); });
         } else {

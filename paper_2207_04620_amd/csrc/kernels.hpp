@@ -52,7 +52,8 @@ struct ModMap {
 };
 
 // Device-resident tables of one context.
-#define ROW_TW 2047  // twiddle pairs per row of the 2048-point row pass
+#define ROW_TW 2047   // twiddle pairs per row of the 2048-point row pass
+#define ROW_TWD 2632  // doubles per row of its FP64 tables
 
 struct DevTables {
     const ModP* mods;    // [M]
@@ -64,8 +65,8 @@ struct DevTables {
     // its rounds consume them (forward: rtw, inverse: irtw)
     const u64* rtw;
     const u64* irtw;
-    // the same twiddles as doubles (w, fl(w / q)) for the FP64 butterflies of primes below
-    // 2^46 (zero for the others): row tables as above, column tables [M][N1]
+    // the same twiddles as doubles for the FP64 butterflies of primes below 2^46 (zero for the
+    // others): row tables [M][N1][ROW_TWD], every group padded to 8 or 4 doubles, column tables [M][N1]
     const double* rtwd;
     const double* irtwd;
     const double* cold;
