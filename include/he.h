@@ -230,7 +230,8 @@ he_status he_transpose_batch(he_ctx *ctx, size_t n, const he_ct *const *a, uint3
 
 /* Scheduling knobs of the lockstep products; results never depend on them.  pair_batch:
  * rotation sets (Step-2 mask pairs, baby rotations) that share one key-switch inner-product
- * launch and one ModDown launch (1..16); max_group: members per lockstep group (1..256);
+ * launch and one ModDown launch (1..16; until it is set or tuned, and without a pool limit, direct
+ * calls with few members take more sets than the value read here); max_group: members per lockstep group (1..256);
  * overlap (0 or 1): the next Step-2 pair group's inner products run on the context's second
  * stream while the current group's ModDown runs on the context stream; concurrent_groups (0 or
  * 1): the (shape, level) groups of a batch with several of them are spread over the two

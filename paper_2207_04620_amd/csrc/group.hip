@@ -21,6 +21,31 @@ static void copy2d(Ctx* c, u64* dst, int64_t dpitch, const u64* src, int64_t spi
               "copy2d");
 }
 
+// Rotation sets per inner-product and ModDown launch.  A launch over 4 sets of one member has 104
+// limb transforms (N = 2^15, level 12) and leaves most of the device idle; 64 sets x members are
+// where a step of 16 members stops gaining (pair_batch 8: 371.0 against 370.7 products/s).  One
+// h = 64 product at N = 2^15: 5.5 ms with 4 sets per launch, 4.8 with 16.
+int Ctx::sets_per_launch(int B, bool direct) const {
+    if (!pair_auto || !direct || pool.limit || pool_side.limit) return std::max(1, pair_batch);
+    return std::max(4, std::min(IP_MAXSET, 64 / std::max(1, B)));
+}
+
+// f(direct): a direct call's work, again with the knob's sets per launch if the wider
+// launches' buffers do not fit the device (nothing of the first attempt is kept; a recording
+// capture has no second attempt)
+template <class F>
+void Ctx::direct_call(F&& f) {
+    int64_t before[6];
+    std::copy(cnt, cnt + 6, before);
+    try {
+        f(true);
+    } catch (const HeError& e) {
+        if (e.s != HE_ENOMEM || !pair_auto || pool.capture) throw;
+        std::copy(before, before + 6, cnt);
+        f(false);
+    }
+}
+
 Grp Ctx::g_new(int B, int level, int deg, const std::vector<double>& sc) {
     Grp g;
     g.B = B;
@@ -735,7 +760,7 @@ static int floordiv_g(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b
 //   sum_i Rot( sum_j R(mask_{b i + j}, -unit b i) . Rot(a, unit j), unit b i ),
 // under the packing iota_beta (amounts times beta); baby rotations share one lift, giant
 // steps share one ModDown under the hoisting flag.  No rescale.
-Grp Ctx::g_lintrans(const Grp& a, int kind, int h, int beta, int64_t unit, int dlo, int dhi) {
+Grp Ctx::g_lintrans(const Grp& a, int kind, int h, int beta, int64_t unit, int dlo, int dhi, bool direct) {
     const int b = bsgs(h);
     const double ms = scale;
     const bool hoist = (schedule & HE_SCHED_HOIST_MODDOWN) != 0;
@@ -744,14 +769,14 @@ Grp Ctx::g_lintrans(const Grp& a, int kind, int h, int beta, int64_t unit, int d
     if (b > 1) {
         auto lift = g_lift(a, 1);
         if (hoist) {
-            // up to pair_batch babies per launch, with one shared ModDown
+            // up to sets_per_launch babies per launch, with one shared ModDown
             // (a rotation that is the identity on the slots is the ciphertext itself)
             std::vector<int> js;
             for (int j = 1; j < b; ++j) {
                 if (galois((int64_t)beta * unit * j) == 1) baby[j] = g_drop(a, a.level);
                 else js.push_back(j);
             }
-            const size_t pb = (size_t)std::max(1, pair_batch);
+            const size_t pb = (size_t)sets_per_launch(a.B, direct);
             for (size_t j0 = 0; j0 < js.size(); j0 += pb) {
                 std::vector<int64_t> ks;
                 for (size_t j = j0; j < std::min(js.size(), j0 + pb); ++j) ks.push_back((int64_t)beta * unit * js[j]);
@@ -835,9 +860,9 @@ bool Ctx::matmul_step(MatmulJob& J, int k_chunk) {
     if (J.phase == 0) {
         Grp a = g_gather(J.A, J.lvl), bb = g_gather(J.B, J.lvl);
         // Step 1-1: A0 = U^mu A (diagonals k in (-h, h) at unit 1), then RS
-        J.A0 = g_rescale(g_lintrans(a, 0, h, beta, 1, 1 - h, h - 1));
+        J.A0 = g_rescale(g_lintrans(a, 0, h, beta, 1, 1 - h, h - 1, J.direct));
         // Step 1-2: B0 = U^zeta B (diagonals h k, k in [0, h)), then RS
-        J.B0 = g_rescale(g_lintrans(bb, 1, h, beta, h, 0, h - 1));
+        J.B0 = g_rescale(g_lintrans(bb, 1, h, beta, h, 0, h - 1, J.direct));
         // brought to the Step-3 level before its rotations (with late rescaling Step 3
         // multiplies at this level)
         if (!(schedule & HE_SCHED_RESCALE_LATE)) J.B0 = g_drop(J.B0, J.B0.level - 1);
@@ -856,14 +881,15 @@ bool Ctx::matmul_step(MatmulJob& J, int k_chunk) {
         const bool keep_baby = bg < t;
         if (keep_baby && J.babyB.empty()) J.babyB.resize(bg);
         const int kend = std::min(t, J.k + std::max(1, k_chunk));
-        // hoisted schedule: the mask pairs of up to pair_batch consecutive k share one ModDown;
+        const int nset = sets_per_launch(J.A0.B, J.direct);
+        // hoisted schedule: the mask pairs of up to nset consecutive k share one ModDown;
         // with overlap, the next group's inner products run on the side stream during this
         // group's ModDown (within this chunk of rounds only)
         std::vector<Grp> pairs, babies;
         int pairs_k0 = 0, babies_j0 = 0;
         auto pair_group = [&](int k0) {
             std::vector<MaskPair> pr;
-            for (int kk = k0; kk < std::min(kend, k0 + std::max(1, pair_batch)); ++kk) {
+            for (int kk = k0; kk < std::min(kend, k0 + nset); ++kk) {
                 const int64_t sh = (int64_t)h * bg * (kk / bg);
                 pr.push_back({beta * (kk - sh), mask(2, h, kk, -sh, beta), beta * (kk - h - sh),
                               mask(3, h, kk, -sh, beta)});
@@ -931,10 +957,10 @@ bool Ctx::matmul_step(MatmulJob& J, int k_chunk) {
             } else if (i > 0) {
                 Bj = J.babyB[j];
             } else if (hoist) {
-                // baby rotations of B0, up to pair_batch at a time with one shared ModDown
+                // baby rotations of B0, up to nset at a time with one shared ModDown
                 // (kept for the later blocks, or until used within this chunk)
                 if (keep_baby ? !J.babyB[j].p : (babies.empty() || j - babies_j0 >= (int)babies.size())) {
-                    const int jend = std::min(keep_baby ? bg : kend, j + std::max(1, pair_batch));
+                    const int jend = std::min(keep_baby ? bg : kend, j + nset);
                     std::vector<int64_t> ks;
                     for (int jj = j; jj < jend; ++jj) ks.push_back((int64_t)beta * h * jj);
                     babies = g_rotate_many_hoisted(J.B0, J.liftB->p, ks);
@@ -1009,16 +1035,21 @@ bool Ctx::matmul_step(MatmulJob& J, int k_chunk) {
 
 std::vector<CtPtr> Ctx::matmul_group(const std::vector<const CtData*>& A, const std::vector<const CtData*>& Bv,
                                      const MatShape& sh, int lvl) {
-    MatmulJob J;
-    J.A = A;
-    J.B = Bv;
-    J.h = sh.h;
-    J.t = sh.t;
-    J.beta = sh.beta;
-    J.lvl = lvl;
-    while (!matmul_step(J, sh.h)) {
-    }
-    return J.result;
+    std::vector<CtPtr> result;
+    direct_call([&](bool direct) {
+        MatmulJob J;
+        J.A = A;
+        J.B = Bv;
+        J.h = sh.h;
+        J.t = sh.t;
+        J.beta = sh.beta;
+        J.lvl = lvl;
+        J.direct = direct;
+        while (!matmul_step(J, sh.h)) {
+        }
+        result = J.result;
+    });
+    return result;
 }
 
 // ------------------------------------------------------------------ sign (Sec. 4.2), lockstep
@@ -1300,21 +1331,24 @@ std::vector<CtPtr> Ctx::matmul_batch(const std::vector<const CtData*>& A, const 
                               std::vector<size_t>(idx.begin() + s, idx.begin() + std::min(idx.size(), s + cap))});
     }
     auto run = [&](const Chunk& ch, bool keep_acc, Grp* acc) {
-        MatmulJob J;
-        for (size_t i : ch.idx) {
-            J.A.push_back(A[i]);
-            J.B.push_back(B[i]);
-        }
-        J.h = ch.sh.h;
-        J.t = ch.sh.t;
-        J.beta = ch.sh.beta;
-        J.lvl = ch.lvl;
-        J.keep_acc = keep_acc;
-        while (!matmul_step(J, ch.sh.h)) {
-        }
-        if (keep_acc) *acc = J.acc;
-        else
-            for (size_t t = 0; t < J.result.size(); ++t) out[ch.idx[t]] = J.result[t];
+        direct_call([&](bool direct) {
+            MatmulJob J;
+            for (size_t i : ch.idx) {
+                J.A.push_back(A[i]);
+                J.B.push_back(B[i]);
+            }
+            J.h = ch.sh.h;
+            J.t = ch.sh.t;
+            J.beta = ch.sh.beta;
+            J.lvl = ch.lvl;
+            J.keep_acc = keep_acc;
+            J.direct = direct;
+            while (!matmul_step(J, ch.sh.h)) {
+            }
+            if (keep_acc) *acc = J.acc;
+            else
+                for (size_t t = 0; t < J.result.size(); ++t) out[ch.idx[t]] = J.result[t];
+        });
     };
     if (groups.size() < 2 || !concurrent_groups || !ensure_side()) {
         for (auto& ch : chunks) run(ch, false, nullptr);
@@ -1324,11 +1358,17 @@ std::vector<CtPtr> Ctx::matmul_batch(const std::vector<const CtData*>& A, const 
     // launches of different groups fill the device together.  The side stream starts after the work issued
     // so far, takes its buffers from its own allocation cache, and leaves each group's result
     // in that group's accumulator; after the join the context stream copies the results out
-    // (into buffers of the main cache) and the side cache's free blocks return to the main one.
-    struct Absorb {
+    // (into buffers of the main cache).  The side cache keeps its blocks for the next mixed batch (moved to the
+    // main cache instead, every call took its side working set from the device again, until that
+    // was full); under a cap on the cache they go back to the device.
+    struct TrimSide {
         Ctx* c;
-        ~Absorb() { c->pool.absorb(c->pool_side); }
-    } absorb{this};
+        ~TrimSide() {
+            if (!c->pool.limit) return;
+            (void)hipStreamSynchronize(c->stream);
+            c->pool_side.trim();
+        }
+    } trim_side{this};
     std::vector<Grp> side_acc(chunks.size());
     struct SideGuard {  // error path: side work ends before its buffers go back
         Ctx* c;
@@ -1411,8 +1451,10 @@ std::vector<CtPtr> Ctx::transpose_batch(const std::vector<const CtData*>& X, int
         for (size_t s = 0; s < idx.size(); s += cap) {
             std::vector<const CtData*> v;
             for (size_t t = s; t < std::min(idx.size(), s + cap); ++t) v.push_back(X[idx[t]]);
-            auto r = g_scatter(g_rescale(g_lintrans(g_gather(v, kv.first), 4, h, beta, h - 1, 1 - h, h - 1)));
-            for (size_t t = 0; t < r.size(); ++t) out[idx[s + t]] = r[t];
+            direct_call([&](bool direct) {
+                auto r = g_scatter(g_rescale(g_lintrans(g_gather(v, kv.first), 4, h, beta, h - 1, 1 - h, h - 1, direct)));
+                for (size_t t = 0; t < r.size(); ++t) out[idx[s + t]] = r[t];
+            });
         }
     }
     return out;

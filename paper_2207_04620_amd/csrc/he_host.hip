@@ -124,22 +124,6 @@ DBuf::DBuf(Ctx* c, size_t n_u64) : ctx(c), pool(c->alloc_side ? &c->pool_side : 
 DBuf::~DBuf() {
     if (p) pool->release(p, n * 8);
 }
-void Pool::absorb(Pool& o) {
-    if (&o == this) return;
-    std::scoped_lock lk(m, o.m);
-    for (auto& kv : o.free_) {
-        auto& dst = free_[kv.first];
-        for (void* p : kv.second) {
-            dst.push_back(p);
-            o.held -= kv.first;
-            o.cached -= kv.first;
-            held += kv.first;
-            cached += kv.first;
-        }
-    }
-    o.free_.clear();
-}
-
 // ====================================================================== context setup
 static void gen_primes(int log_n, const std::vector<uint32_t>& bits, std::vector<uint64_t>& out) {
     const uint64_t m2n = 2ull << log_n;
@@ -225,7 +209,7 @@ void Ctx::build_tables() {
         e.ninv = invmod((u64)N % q, q);
         e.ninv_sh = shoup(e.ninv, q);
         e.half = (q - 1) / 2;
-        e.pad = 0;
+        e.qinv = 1.0 / (double)q;
         // psi^(bitrev k)
         std::vector<u64> pw(N), ipw(N);
         u64 a = 1, b = 1;
@@ -1366,7 +1350,7 @@ he_status he_counters(const he_ctx* ctx, int64_t out[6], int reset) {
 he_status he_memory(const he_ctx* ctx, uint64_t* keys_bytes, uint64_t* pool_bytes) {
     if (!ctx) return HE_EINVAL;
     if (keys_bytes) *keys_bytes = ctx->c->keys_bytes;
-    if (pool_bytes) *pool_bytes = ctx->c->pool.held;
+    if (pool_bytes) *pool_bytes = ctx->c->pool.held + ctx->c->pool_side.held;
     return HE_OK;
 }
 
@@ -1379,6 +1363,7 @@ he_status he_pool_limit(he_ctx* ctx, uint64_t bytes) {
         std::lock_guard<std::mutex> lk(P.m);
         P.limit = bytes;
         if (bytes && P.held > bytes) P.trim_locked();
+        if (bytes) ctx->c->pool_side.trim();
     });
 }
 he_status he_pool_stats(he_ctx* ctx, uint64_t* in_use, uint64_t* peak, int reset) {

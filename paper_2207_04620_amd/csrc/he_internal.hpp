@@ -53,8 +53,6 @@ struct Pool {
     void release(void* p, size_t bytes);
     void trim();
     void trim_locked();
-    // take over o's cached (free) blocks; only when none of o's work can still be pending
-    void absorb(Pool& o);
     // bytes in use now; restart the peak figure from it
     size_t restart_peak() {
         std::lock_guard<std::mutex> lk(m);
@@ -122,6 +120,7 @@ struct MatmulJob {
     std::shared_ptr<DBuf> liftA, liftB;
     std::vector<CtPtr> result;
     bool keep_acc = false;  // leave the result as the group acc (the caller scatters it)
+    bool direct = false;    // a direct call's job (sets_per_launch)
 };
 // resumable state of one lockstep sign/ReLU group
 // mode 0: g_d^(k)(x); mode 1: ReLU (x + x g) / 2; mode 2: AppMax(a, b) (Alg. 5) with
@@ -217,7 +216,7 @@ struct Ctx {
     Pool pool;
     // the side stream's own allocation cache: lockstep groups issued on the side stream take
     // their buffers from it (alloc_side set), so a block never passes between the streams while
-    // either may still use it; its free blocks return to the main cache after the streams join
+    // either may still use it
     Pool pool_side;
     bool alloc_side = false;
     hm::Encoder enc;
@@ -306,6 +305,14 @@ struct Ctx {
     std::vector<CtPtr> transpose_batch(const std::vector<const CtData*>& X, int h, int beta);
     int max_group = 32;
     int pair_batch = 4;  // Step-2 mask pairs per shared ModDown launch
+    // Until the caller sets the knobs, a direct call with fewer than 16 members takes more sets per
+    // launch, so that a launch still covers about 64 (sets x members): one h = 64 product at N = 2^15 takes
+    // 12 ModDowns of 16 sets instead of 31 of 4 (measured at sets_per_launch).  Serving
+    // keeps the knob (its admission counts bytes per member), and so does a capped allocation cache
+    bool pair_auto = true;
+    int sets_per_launch(int B, bool direct) const;
+    template <class F>
+    void direct_call(F&& f);
     int overlap = 0;     // Step-2 pair groups pipelined over the two streams (measured slower: off)
     int concurrent_groups = 1;  // lockstep groups of a mixed batch spread over the two streams
     // a group lift holds only the converted limbs of each digit; its own limbs are read from the
@@ -357,7 +364,7 @@ struct Ctx {
     void g_tensor_acc(Grp& acc, const Grp& a, const Grp& b);
     void g_tensor_sum(MatmulJob& J);
     Grp g_relin(const Grp& a);
-    Grp g_lintrans(const Grp& a, int kind, int h, int beta, int64_t unit, int dlo, int dhi);
+    Grp g_lintrans(const Grp& a, int kind, int h, int beta, int64_t unit, int dlo, int dhi, bool direct);
     std::vector<CtPtr> matmul_group(const std::vector<const CtData*>& A, const std::vector<const CtData*>& B,
                                     const MatShape& s, int lvl);
     bool matmul_step(MatmulJob& J, int k_chunk);

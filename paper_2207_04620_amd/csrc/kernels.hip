@@ -679,20 +679,20 @@ template <class F>
 __device__ __forceinline__ void fwd_rows_2048_d(double* s, const double* __restrict__ tw, double q, double qinv,
                                                 double (&x)[8], double (&y)[8], F&& after_first) {
     const int tid = threadIdx.x;
-    const TwD<3> t2 = ld_tw<3>(tw + 8 + 8 * (tid >> 5));
     fwd_group_d<3>(x, ld_tw<3>(tw), q, qinv);
     double* sb = s + row_at(tid);
 #pragma unroll
     for (int k = 0; k < 8; ++k) sb[row_at(256 * k)] = x[k];
+    const TwD<3> t2 = ld_tw<3>(tw + 8 + 8 * (tid >> 5));
     after_first();
     const TwD<3> t3 = ld_tw<3>(tw + 72 + 8 * (tid >> 2));
     __syncthreads();
     row_round_d<32>(s, ((tid >> 5) << 8) + (tid & 31), [&](double(&v)[8]) { fwd_group_d<3>(v, t2, q, qinv); });
+    __syncthreads();
+    row_round_d<4>(s, ((tid >> 2) << 5) + (tid & 3), [&](double(&v)[8]) { fwd_group_d<3>(v, t3, q, qinv); });
     TwD<2> t4[2];
 #pragma unroll
     for (int gg = 0; gg < 2; ++gg) t4[gg] = ld_tw<2>(tw + 584 + 4 * (gg * TPB + tid));
-    __syncthreads();
-    row_round_d<4>(s, ((tid >> 2) << 5) + (tid & 3), [&](double(&v)[8]) { fwd_group_d<3>(v, t3, q, qinv); });
     __syncthreads();
 #pragma unroll
     for (int gg = 0; gg < 2; ++gg) {
@@ -862,7 +862,7 @@ __global__ __launch_bounds__(TPB) void k_ntt_fwd_cols(DevTables T, Jobs J) {
             sd[e + 1] = u2d(v.y);
         }
         __syncthreads();
-        fwd_cols_any_d(sd, L1, T.cold + ((int64_t)mi << L1), (double)q, 1.0 / (double)q);
+        fwd_cols_any_d(sd, L1, T.cold + ((int64_t)mi << L1), (double)q, T.mods[mi].qinv);
         // raw double words for the FP64 row pass of this limb
         for (int e = 2 * threadIdx.x; e < NTT_E; e += 2 * TPB)
             st2(a + (int64_t)(e >> logC) * N2 + c0 + (e & (C - 1)), u64x2{d_bits(sd[e]), d_bits(sd[e + 1])});
@@ -899,7 +899,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(EPI ? 6 : 7
     // 2048-element rows: the last round's elements 4 g + k (g = tid, 256 + tid), as raw doubles (FP64
     // path) or words lazy in [0, 4q) (integer path)
     u64 y[8];
-    const double qd = (double)q, qinv = 1.0 / qd;
+    const double qd = (double)q, qinv = T.mods[mi].qinv;
     // the ModDown epilogue's u words of those elements, loaded while the middle rounds run
     u64x2 uu[4];
     const u64* u = nullptr;
@@ -1042,7 +1042,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(8))) void k
     // 2048-element rows: every lane loads its eight elements 8 tid + k before the first
     // barrier and stores g + 512 k (g = tid, 256 + tid) after the last, so in place is safe
     if (fp64_limb(q, L1, N2)) {
-        const double qd = (double)q, qinv = 1.0 / qd;
+        const double qd = (double)q, qinv = mp_.qinv;
         double x[8], y[8];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -1136,7 +1136,7 @@ __global__ __launch_bounds__(TPB) void k_ntt_inv_cols(DevTables T, Jobs J, const
     const u64* Ws = T.ipsi_sh + (int64_t)mi * N;
     const int c0 = blockIdx.x * C;
     if (fp64_limb(q, L1, N2)) {
-        const double qd = (double)q, qinv = 1.0 / qd;
+        const double qd = (double)q, qinv = mp_.qinv;
         double* sd = reinterpret_cast<double*>(s);
         for (int e = 2 * threadIdx.x; e < NTT_E; e += 2 * TPB) {  // raw doubles of the row pass
             const u64x2 v = ld2(a + (int64_t)(e >> logC) * N2 + c0 + (e & (C - 1)));
@@ -1243,7 +1243,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(8))) void k
     __syncthreads();
     u64* a = D.dst + c * D.dst_cstride + p * D.dst_pstride + (int64_t)D.doff[t] * N;
     if (fp) {  // raw double words for the FP64 row pass of this limb
-        fwd_cols_any_d(sd, L1, T.cold + ((int64_t)mi << L1), (double)m.q, 1.0 / (double)m.q);
+        fwd_cols_any_d(sd, L1, T.cold + ((int64_t)mi << L1), (double)m.q, m.qinv);
         for (int e = 2 * threadIdx.x; e < NTT_E; e += 2 * TPB)
             st2(a + (int64_t)(e >> logC) * N2 + col0 + (e & (C - 1)), u64x2{d_bits(sd[e]), d_bits(sd[e + 1])});
         return;
@@ -1381,8 +1381,14 @@ __device__ __forceinline__ void fwd_col_regs(u64 (&x)[1 << L1], const u64x2* W, 
 // The same columns spread over SP = 4 or 2 lane groups: lane group v = (lane >> 4) mod SP holds the rows SP j + v
 // of a column, j < N1 / SP.  The stages of distance 1 (and 2 for SP = 4) pair lanes 16 (and 32)
 // apart; both lanes of a pair run the product, the lower one by the unit twiddle of entry 0.
-__device__ __forceinline__ double lane_xor_d(double x, int mask) { return __shfl_xor(x, mask, 64); }
-__device__ __forceinline__ u64 lane_xor_u(u64 x, int mask) { return __shfl_xor((unsigned long long)x, mask, 64); }
+// (the partner's address comes from the group number, which callers in a loop keep opaque)
+__device__ __forceinline__ u64 lane_xor_u(u64 x, int grp, int d) {
+    const int at = (((grp ^ d) & 3) << 6) | ((threadIdx.x & 15) << 2);
+    const u32 lo = (u32)__builtin_amdgcn_ds_bpermute(at, (int)(u32)x);
+    const u32 hi = (u32)__builtin_amdgcn_ds_bpermute(at, (int)(u32)(x >> 32));
+    return ((u64)hi << 32) | lo;
+}
+__device__ __forceinline__ double lane_xor_d(double x, int grp, int d) { return bits_d(lane_xor_u(d_bits(x), grp, d)); }
 // twiddle entry of element j in a cross-lane stage (distance 1 or 2)
 template <int SP>
 __device__ __forceinline__ int cross_twiddle(int st, int d, int j, int v) {
@@ -1390,9 +1396,10 @@ __device__ __forceinline__ int cross_twiddle(int st, int d, int j, int v) {
     return up ? (1 << st) + ((SP * j + v) >> d) : 0;  // block (SP j + v) / (2 d), d = 1 or 2
 }
 template <int L1, int SP>
-__device__ __forceinline__ void inv_col_split_d(double (&x)[(1 << L1) / SP], const u64x2* W, int v, double q, double qinv) {
+__device__ __forceinline__ void inv_col_split_d(double (&x)[(1 << L1) / SP], const u64x2* W, int grp, double q, double qinv) {
 #pragma clang fp contract(off)
     constexpr int M = (1 << L1) / SP;
+    const int v = grp & (SP - 1);
 #pragma unroll
     for (int j = 0; j < M; ++j) x[j] = red_d(x[j], q, qinv);
 #pragma unroll
@@ -1404,7 +1411,7 @@ __device__ __forceinline__ void inv_col_split_d(double (&x)[(1 << L1) / SP], con
 #pragma unroll
             for (int j = 0; j < M; ++j) {
                 const double w = bits_d(W[cross_twiddle<SP>(st, d, j, v)].x);
-                const double s = __fma_rn(x[j], sgn, lane_xor_d(x[j], 16 * d));
+                const double s = __fma_rn(x[j], sgn, lane_xor_d(x[j], grp, d));
                 x[j] = mulmod_d(s, w, q, qinv);
             }
         } else {
@@ -1423,9 +1430,10 @@ __device__ __forceinline__ void inv_col_split_d(double (&x)[(1 << L1) / SP], con
     }
 }
 template <int L1, int SP>
-__device__ __forceinline__ void fwd_col_split_d(double (&x)[(1 << L1) / SP], const u64x2* W, int v, double q, double qinv) {
+__device__ __forceinline__ void fwd_col_split_d(double (&x)[(1 << L1) / SP], const u64x2* W, int grp, double q, double qinv) {
 #pragma clang fp contract(off)
     constexpr int M = (1 << L1) / SP;
+    const int v = grp & (SP - 1);
 #pragma unroll
     for (int st = 0; st < L1; ++st) {
         stage_fence();
@@ -1436,7 +1444,7 @@ __device__ __forceinline__ void fwd_col_split_d(double (&x)[(1 << L1) / SP], con
             for (int j = 0; j < M; ++j) {
                 const double w = bits_d(W[cross_twiddle<SP>(st, d, j, v)].x);
                 const double t = mulmod_d(x[j], w, q, qinv);
-                x[j] = __fma_rn(t, sgn, lane_xor_d(t, 16 * d));
+                x[j] = __fma_rn(t, sgn, lane_xor_d(t, grp, d));
             }
         } else {
             const int dj = d / SP;
@@ -1455,8 +1463,9 @@ __device__ __forceinline__ void fwd_col_split_d(double (&x)[(1 << L1) / SP], con
     }
 }
 template <int L1, int SP>
-__device__ __forceinline__ void inv_col_split(u64 (&x)[(1 << L1) / SP], const u64x2* W, int v, u64 q) {
+__device__ __forceinline__ void inv_col_split(u64 (&x)[(1 << L1) / SP], const u64x2* W, int grp, u64 q) {
     constexpr int M = (1 << L1) / SP;
+    const int v = grp & (SP - 1);
     const u64 q2 = 2 * q;
 #pragma unroll
     for (int st = L1 - 1; st >= 0; --st) {
@@ -1467,7 +1476,7 @@ __device__ __forceinline__ void inv_col_split(u64 (&x)[(1 << L1) / SP], const u6
 #pragma unroll
             for (int j = 0; j < M; ++j) {
                 const u64x2 w = W[cross_twiddle<SP>(st, d, j, v)];
-                const u64 o = lane_xor_u(x[j], 16 * d);
+                const u64 o = lane_xor_u(x[j], grp, d);
                 x[j] = mul_shoup_lazy(o + (up ? q2 - x[j] : x[j]), w.x, w.y, q);
             }
         } else {
@@ -1486,8 +1495,9 @@ __device__ __forceinline__ void inv_col_split(u64 (&x)[(1 << L1) / SP], const u6
     }
 }
 template <int L1, int SP>
-__device__ __forceinline__ void fwd_col_split(u64 (&x)[(1 << L1) / SP], const u64x2* W, int v, u64 q) {
+__device__ __forceinline__ void fwd_col_split(u64 (&x)[(1 << L1) / SP], const u64x2* W, int grp, u64 q) {
     constexpr int M = (1 << L1) / SP;
+    const int v = grp & (SP - 1);
     const u64 q2 = 2 * q;
 #pragma unroll
     for (int st = 0; st < L1; ++st) {
@@ -1499,7 +1509,7 @@ __device__ __forceinline__ void fwd_col_split(u64 (&x)[(1 << L1) / SP], const u6
             for (int j = 0; j < M; ++j) {
                 const u64x2 w = W[cross_twiddle<SP>(st, d, j, v)];
                 const u64 t = mul_shoup_lazy(x[j], w.x, w.y, q);
-                x[j] = lane_xor_u(t, 16 * d) + (up ? q2 - t : t);
+                x[j] = lane_xor_u(t, grp, d) + (up ? q2 - t : t);
             }
         } else {
             const int dj = d / SP;
@@ -1567,16 +1577,16 @@ __device__ __forceinline__ void unrolled(F&& f) {
 // centred, in signed bytes
 template <int L1, int SP>
 __device__ __forceinline__ void conv_source(u64 (&b)[(1 << L1) / SP], const ModP& m, const u64* src, uint32_t so,
-                                            const u64x2* W, int v, u64 f, u64 fs) {
+                                            const u64x2* W, int grp, u64 f, u64 fs) {
     constexpr int M = (1 << L1) / SP, N2 = NTT_E;
     const u64 q = m.q;
-    so += (uint32_t)v * (N2 * 8u);
+    so += (uint32_t)(grp & (SP - 1)) * (N2 * 8u);
     if (fp64_limb(q, L1, N2)) {
-        const double qd = (double)q, qinv = 1.0 / qd, fd = (double)f;
+        const double qd = (double)q, qinv = m.qinv, fd = (double)f;
         double x[M];
         unrolled<M>([&](auto j) { x[j] = *lane_at<double>(src + j * (SP * N2), so); });
         if constexpr (SP == 1) inv_col_regs_d<L1>(x, W, qd, qinv);
-        else inv_col_split_d<L1, SP>(x, W, v, qd, qinv);
+        else inv_col_split_d<L1, SP>(x, W, grp, qd, qinv);
         unrolled<M>([&](auto j) {
             // centred exactly: |x f mod q| < q, so rint of the quotient is exact; as a word, the
             // bits of y + 1.5 2^52 less those of 1.5 2^52
@@ -1589,7 +1599,7 @@ __device__ __forceinline__ void conv_source(u64 (&b)[(1 << L1) / SP], const ModP
         u64 x[M];
         unrolled<M>([&](auto j) { x[j] = *lane_at<u64>(src + j * (SP * N2), so); });
         if constexpr (SP == 1) inv_col_regs<L1>(x, W, q);
-        else inv_col_split<L1, SP>(x, W, v, q);
+        else inv_col_split<L1, SP>(x, W, grp, q);
         unrolled<M>([&](auto j) {
             if (j % 2 == 0) stage_fence();
             const u64 y = mul_shoup(x[j], f, fs, q);
@@ -1645,29 +1655,33 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(conv_waves(
     // fourth; lanes without a source repeat the first, times zero
     const u64* src = D.src + c * D.src_cs + p * D.src_ps;  // uniform
     u64 b0[N1], b1[M1];
+    // a shared source's words wait in LDS, each lane's own (with them in registers the sets spill)
+    u64* ext = reinterpret_cast<u64*>(tw + D.limbs * LD) + (threadIdx.x >> 6) * (M1 * 64) + lane;
     const auto source = [&](auto sp, auto& b, int s) {
         constexpr int SP = sp;
         const bool has = s < dg.ns;
         s = has ? s : 0;
         const u64 f = has ? D.scale[2 * (dg.slo + s)] : 0, fs = has ? D.scale[2 * (dg.slo + s) + 1] : 0;
         conv_source<L1, SP>(b, T.mods[dg.smod + s], src, ((uint32_t)(dg.slo + s) * N + col) * 8u, tw + s * LD,
-                            grp & (SP - 1), f, fs);
+                            grp, f, fs);
     };
     source(std::integral_constant<int, 1>{}, b0, grp);
     if constexpr (XS != 0) source(std::integral_constant<int, XS>{}, b1, 4 + grp / XS);
-    // the operand of row r (share is remade opaquely for every set: known to be the same, the selected
-    // words of all rows would be kept across the sets, in registers that are not there)
-    int share = grp & (XS ? XS - 1 : 0);
+    if constexpr (XS > 1) unrolled<M1>([&](auto j) { ext[j * 64] = b1[j]; });
+    // the operand of row r (gv, the lane group, is remade opaquely for every set: known to be the same, the
+    // selected words of all rows and the split transforms' twiddle addresses would be kept across
+    // the sets, in registers that are not there)
+    int gv = grp;
     const auto operand = [&](auto row, u64(&b)[KS]) {
         constexpr int r = row;
         b[0] = b0[r];
         if constexpr (XS == 1) b[1] = b1[r];
-        else if constexpr (XS > 1) b[1] = share == (r & (XS - 1)) ? b1[r / XS] : 0;
+        else if constexpr (XS > 1) b[1] = (gv & (XS - 1)) == (r & (XS - 1)) ? ext[(r / XS) * 64] : 0;
     };
 
     u64* dst = D.dst + c * D.dst_cs + p * D.dst_ps;  // uniform
     for (int si = s0; si < s1; ++si) {
-        if constexpr (XS > 1) keep_here(share);
+        keep_here(gv);
         const ConvSet& S = D.sets[si];
         const u64* ta = D.tab + S.tab + lane * KS;
         u64 a0[KS], a1[KS];
@@ -1676,20 +1690,14 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(conv_waves(
             a0[k] = ta[k];
             a1[k] = ta[64 * KS + k];
         }
-        const u64 q = T.mods[S.dmod[grp]].q;
-        const double qd = (double)q, qinv = 1.0 / qd;
-        const bool small = S.small;
-        const u64 w32 = S.w32[grp], w32s = S.w32_sh[grp], cc = S.off[grp];
-        const u64x2* W = tw + (dg.ns + 4 * (si - s0) + grp) * LD;
-        uint32_t od = ((uint32_t)S.doff[grp] * N + col) * 8u;
+        const u64x2* W = tw + (dg.ns + 4 * (si - s0) + gv) * LD;
         if (N1 >= 4 && S.nt == 1) {
             // one target: its rows are spread over the four lane groups (the set's operands and
             // descriptors repeat it): row group v of the product takes row 4 j + v, four products by
             // the operand masked to that row group
             constexpr int M = N1 >= 4 ? N1 / 4 : 1;
             i32x4 lo[M], hi[M];
-            const i32x4 zero = {0, 0, 0, 0};
-            unrolled<M>([&](auto j) { lo[j] = hi[j] = zero; });
+            unrolled<M>([&](auto j) { lo[j] = hi[j] = i32x4{0, 0, 0, 0}; });
             unrolled<4>([&](auto v) {
                 stage_fence();
                 u64 m0[KS], m1[KS];
@@ -1706,24 +1714,29 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(conv_waves(
                     hi[j] = mfma_bytes<KS>(m1, b, hi[j]);
                 });
             });
-            od += (uint32_t)grp * (N2 * 8u);
+            stage_fence();
+            const u64 q = T.mods[S.dmod[gv]].q;
+            const uint32_t od = ((uint32_t)S.doff[gv] * N + col) * 8u + (uint32_t)gv * (N2 * 8u);
             if constexpr (N1 >= 4) {
                 if (S.fp) {
+                    const double qd = (double)q, qinv = T.mods[S.dmod[gv]].qinv;
                     double x[M];
-                    unrolled<M>([&](auto j) { x[j] = digits_mod_d(lo[j], hi[j], qd, qinv, small); });
-                    fwd_col_split_d<L1, 4>(x, W, grp, qd, qinv);
+                    unrolled<M>([&](auto j) { x[j] = digits_mod_d(lo[j], hi[j], qd, qinv, S.small); });
+                    fwd_col_split_d<L1, 4>(x, W, gv, qd, qinv);
                     unrolled<M>([&](auto j) { *lane_at<u64>(dst + j * (4 * N2), od) = d_bits(x[j]); });
                 } else {
                     u64 x[M];
-                    unrolled<M>([&](auto j) { x[j] = digits_mod(lo[j], hi[j], q, w32, w32s, cc); });
-                    fwd_col_split<L1, 4>(x, W, grp, q);
+                    unrolled<M>([&](auto j) { x[j] = digits_mod(lo[j], hi[j], q, S.w32[gv], S.w32_sh[gv], S.off[gv]); });
+                    fwd_col_split<L1, 4>(x, W, gv, q);
                     unrolled<M>([&](auto j) { *lane_at<u64>(dst + j * (4 * N2), od) = x[j]; });
                 }
             }
         } else if (S.fp) {
+            const double qd = (double)T.mods[S.dmod[gv]].q, qinv = T.mods[S.dmod[gv]].qinv;
+            const bool small = S.small;
             double x[N1];
             unrolled<N1>([&](auto r) {
-                if (r % 2 == 0) stage_fence();
+                if (XS > 1 || r % 2 == 0) stage_fence();
                 u64 b[KS];
                 operand(r, b);
                 x[r] = digits_mod_d(mfma_bytes<KS>(a0, b, i32x4{0, 0, 0, 0}), mfma_bytes<KS>(a1, b, i32x4{0, 0, 0, 0}), qd,
@@ -1732,11 +1745,13 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(conv_waves(
             });
             fwd_col_regs_d<L1>(x, W, qd, qinv);
             unrolled<N1>([&](auto r) { keep_here(x[r]); });
-            if (grp < S.nt) unrolled<N1>([&](auto r) { *lane_at<u64>(dst + r * N2, od) = d_bits(x[r]); });
+            const uint32_t od = ((uint32_t)S.doff[gv] * N + col) * 8u;
+            if (gv < S.nt) unrolled<N1>([&](auto r) { *lane_at<u64>(dst + r * N2, od) = d_bits(x[r]); });
         } else {
+            const u64 q = T.mods[S.dmod[gv]].q, w32 = S.w32[gv], w32s = S.w32_sh[gv], cc = S.off[gv];
             u64 x[N1];
             unrolled<N1>([&](auto r) {
-                if (r % 2 == 0) stage_fence();
+                if (XS > 1 || r % 2 == 0) stage_fence();
                 u64 b[KS];
                 operand(r, b);
                 x[r] = digits_mod(mfma_bytes<KS>(a0, b, i32x4{0, 0, 0, 0}), mfma_bytes<KS>(a1, b, i32x4{0, 0, 0, 0}), q, w32,
@@ -1745,7 +1760,8 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(conv_waves(
             });
             fwd_col_regs<L1>(x, W, q);
             unrolled<N1>([&](auto r) { keep_here(x[r]); });
-            if (grp < S.nt) unrolled<N1>([&](auto r) { *lane_at<u64>(dst + r * N2, od) = x[r]; });
+            const uint32_t od = ((uint32_t)S.doff[gv] * N + col) * 8u;
+            if (gv < S.nt) unrolled<N1>([&](auto r) { *lane_at<u64>(dst + r * N2, od) = x[r]; });
         }
     }
 }
@@ -1762,8 +1778,9 @@ bool conv_mfma_fits(const DevTables& T) { return T.n2_log == 11 && T.n1_log >= 1
 bool rescale_mfma_fits(const DevTables& T) { return T.n2_log == 11 && T.n1_log >= 1 && T.n1_log <= 5; }
 
 template <int L1>
-static void launch_conv_mfma_l(int xs, dim3 grid, int limbs, hipStream_t st, const DevTables& T, const ConvPlanDesc& D) {
-    const size_t lds = (size_t)limbs * ((1 << L1) + 1) * sizeof(u64x2);
+static void launch_conv_mfma_l(int xs, dim3 grid, hipStream_t st, const DevTables& T, const ConvPlanDesc& D) {
+    const size_t tw = (size_t)D.limbs * ((1 << L1) + 1) * sizeof(u64x2);
+    const size_t lds = tw + (xs > 1 ? (size_t)TPB * ((1 << L1) / xs) * sizeof(u64) : 0);
     switch (xs) {
         case 0: HE_LAUNCH((k_conv_mfma<L1, 0>), grid, dim3(TPB), lds, st, T, D); return;
         case 1:
@@ -1820,9 +1837,9 @@ void launch_conv_mfma(const DevTables& T, const ConvPlan& P, const u64* src, int
         --per;
     }
     D.nitem = 0;
-    int limbs = 0;  // twiddle rows of the largest item
+    D.limbs = 0;
     for (int d = 0; d < P.ndig; ++d)
-        limbs = std::max(limbs, P.dig[d].ns + 4 * std::min(P.dig[d].nset, per));
+        D.limbs = std::max(D.limbs, P.dig[d].ns + 4 * std::min(P.dig[d].nset, per));
     for (int d = 0; d < P.ndig; ++d)
         for (int s = 0; s < P.dig[d].nset; s += per) {
             if (D.nitem == CONV_MAXITEM) throw std::runtime_error("conversion plan: too many items");
@@ -1836,11 +1853,11 @@ void launch_conv_mfma(const DevTables& T, const ConvPlan& P, const u64* src, int
                     (P.src_limbs + P.dst_limbs) * pc * (N / 2) * T.n1_log, P.fp_limbs * pc * (N / 2) * T.n1_log);
     dim3 grid((unsigned)((int64_t)(NTT_E / 64) * npoly * nct * D.nitem));
     switch (T.n1_log) {
-        case 1: launch_conv_mfma_l<1>(P.xs, grid, limbs, st, T, D); break;
-        case 2: launch_conv_mfma_l<2>(P.xs, grid, limbs, st, T, D); break;
-        case 3: launch_conv_mfma_l<3>(P.xs, grid, limbs, st, T, D); break;
-        case 4: launch_conv_mfma_l<4>(P.xs, grid, limbs, st, T, D); break;
-        default: launch_conv_mfma_l<5>(P.xs, grid, limbs, st, T, D); break;
+        case 1: launch_conv_mfma_l<1>(P.xs, grid, st, T, D); break;
+        case 2: launch_conv_mfma_l<2>(P.xs, grid, st, T, D); break;
+        case 3: launch_conv_mfma_l<3>(P.xs, grid, st, T, D); break;
+        case 4: launch_conv_mfma_l<4>(P.xs, grid, st, T, D); break;
+        default: launch_conv_mfma_l<5>(P.xs, grid, st, T, D); break;
     }
 }
 
@@ -2382,8 +2399,12 @@ __device__ __forceinline__ void ip_reduce(const u64 (&x)[NR][NB], const u64 (&z)
 // gather: the sets' blocks of one source block get consecutive numbers on one XCD
 // (workgroups are dealt to the 8 XCDs round-robin), run together there, and read the
 // lift and c0 words of each member through that XCD's L2 once for all sets.
-template <int NB, int NR>
-__global__ __launch_bounds__(TPB) void k_inner_product(DevTables T, IpDesc D) {
+// FOLD: the masks of a pair are multiplied into the key words once per thread (14 products for three digits, then
+// 185 instructions per member); without it each rotation's two sums are reduced and multiplied by its mask
+// (about 370 per member and no 500 up front), which is less for one and two members: there the fold is most of a
+// thread's work.  Sixteen pairs of one member at N = 2^15: 307 us folded, 251 not (1.1 GB, 4.4 TB/s).
+template <int NB, int NR, bool FOLD>
+__global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(!FOLD && NB <= 2 ? 5 : 1))) void k_inner_product(DevTables T, IpDesc D) {
     const int N = 1 << T.log_n, nb = N / TPB;
     int xb = blockIdx.x, sj = 0;
     if (D.nset > 1) {
@@ -2408,6 +2429,7 @@ __global__ __launch_bounds__(TPB) void k_inner_product(DevTables T, IpDesc D) {
     const bool with_c0 = D.c0 && t < D.nq;
     const u64 pmont = with_c0 ? D.pmont[t] : 0;
     IpKey<NB> kb[NR][NB], ka[NR][NB], pm[NR];
+    u64 mks[NR];  // the masks, where they are not folded
     int src[NR];
 #pragma unroll
     for (int r = 0; r < NR; r++) {
@@ -2416,18 +2438,19 @@ __global__ __launch_bounds__(TPB) void k_inner_product(DevTables T, IpDesc D) {
         const u64* mask = r ? S.mask2 : S.mask;
         src[r] = g == 1 ? i : perm_g(i, g, T.log_n);
         const u64 mk = mask ? mask[(int64_t)mi * N + i] : 0;
+        mks[r] = mk;
 #pragma unroll
         for (int j = 0; j < NB; j++) {
             u64 b = ldnt(key + (((int64_t)j * 2 + 0) * D.M + mi) * N + i);
             u64 a = ldnt(key + (((int64_t)j * 2 + 1) * D.M + mi) * N + i);
-            if (mask) {
+            if (FOLD && mask) {
                 b = mul_mont(b, mk, m.q, m.qninv);
                 a = mul_mont(a, mk, m.q, m.qninv);
             }
             kb[r][j] = ip_key<NB>(b);
             ka[r][j] = ip_key<NB>(a);
         }
-        pm[r] = ip_key<NB>(mask ? mul_mont(pmont, mk, m.q, m.qninv) : pmont);
+        pm[r] = ip_key<NB>(FOLD && mask ? mul_mont(pmont, mk, m.q, m.qninv) : pmont);
     }
     // the second rotation may read another ciphertext's lift and c0 (a rotation-sum term); the
     // digit whose own limbs include t (none for the special primes) is read from the lifted
@@ -2481,7 +2504,25 @@ __global__ __launch_bounds__(TPB) void k_inner_product(DevTables T, IpDesc D) {
     const uint32_t io = (uint32_t)i * 8u;
     auto finish = [&](const u64(&xv)[NR][NB], const u64(&zv)[NR]) {
         u64 v0, v1;
-        ip_reduce<NB, NR>(xv, zv, kb, ka, pm, with_c0, m, v0, v1);
+        if constexpr (FOLD) {
+            ip_reduce<NB, NR>(xv, zv, kb, ka, pm, with_c0, m, v0, v1);
+        } else {
+            v0 = v1 = 0;
+#pragma unroll
+            for (int r = 0; r < NR; r++) {
+                u64 x1[1][NB], z1[1] = {zv[r]}, w0, w1;
+                IpKey<NB> b1[1][NB], a1[1][NB], p1[1] = {pm[r]};
+#pragma unroll
+                for (int j = 0; j < NB; j++) {
+                    x1[0][j] = xv[r][j];
+                    b1[0][j] = kb[r][j];
+                    a1[0][j] = ka[r][j];
+                }
+                ip_reduce<NB, 1>(x1, z1, b1, a1, p1, with_c0, m, w0, w1);
+                v0 = add_mod(v0, mul_mont(w0, mks[r], m.q, m.qninv), m.q);
+                v1 = add_mod(v1, mul_mont(w1, mks[r], m.q, m.qninv), m.q);
+            }
+        }
         u64* p0 = reinterpret_cast<u64*>(reinterpret_cast<char*>(u0) + io);
         u64* p1 = reinterpret_cast<u64*>(reinterpret_cast<char*>(u1) + io);
         if (D.accumulate) {
@@ -2497,6 +2538,14 @@ __global__ __launch_bounds__(TPB) void k_inner_product(DevTables T, IpDesc D) {
     // of the next two members are in flight during the current member's arithmetic (one
     // member's arithmetic is shorter than a load's latency under full bandwidth)
     u64 x0[NR][NB], z0[NR], x1[NR][NB], z1[NR], x2[NR][NB], z2[NR];
+    if constexpr (!FOLD) {  // one or two members: the keys are the stream, more waves hide it
+        for (int c = 0; c < D.nct; ++c) {
+            load(x0, z0);
+            advance();
+            finish(x0, z0);
+        }
+        return;
+    }
     load(x0, z0);
     advance();
     if (D.nct > 1) {
@@ -2524,12 +2573,19 @@ __global__ __launch_bounds__(TPB) void k_inner_product(DevTables T, IpDesc D) {
     }
 }
 
+// members up to which a pair's masks are applied to the sums instead of to the key words
+#define IP_UNFOLDED 2
 template <int NB>
 static void launch_ip_nb(const DevTables& T, const IpDesc& D, dim3 grid, hipStream_t st) {
-    if (D.nrot == 2)
-        HE_LAUNCH((k_inner_product<NB, 2>), grid, dim3(TPB), 0, st, T, D);
+    // every set of a pair launch has both masks or none (two terms of a rotation sum have none)
+    bool masked = D.nrot == 2;
+    for (int j = 0; j < D.nset; ++j) masked = masked && D.s[j].mask && D.s[j].mask2;
+    if (masked && D.nct <= IP_UNFOLDED)
+        HE_LAUNCH((k_inner_product<NB, 2, false>), grid, dim3(TPB), 0, st, T, D);
+    else if (D.nrot == 2)
+        HE_LAUNCH((k_inner_product<NB, 2, true>), grid, dim3(TPB), 0, st, T, D);
     else
-        HE_LAUNCH((k_inner_product<NB, 1>), grid, dim3(TPB), 0, st, T, D);
+        HE_LAUNCH((k_inner_product<NB, 1, true>), grid, dim3(TPB), 0, st, T, D);
 }
 
 void launch_inner_product(const DevTables& T, const IpDesc& D, hipStream_t st) {
@@ -2725,11 +2781,11 @@ void launch_mask_mac(const DevTables& T, int nl, int npoly, const MacDesc& D, u6
 // of every output in registers and reads each input word once per member, so the baby-step
 // rotations cross HBM once per MM_OUT giant steps instead of once per giant step.
 template <int NI>
-__global__ __launch_bounds__(TPB) void k_mask_mac_multi(DevTables T, MultiMacDesc D) {
+__global__ __launch_bounds__(TPB) void k_mask_mac_multi(DevTables T, MultiMacDesc D, int npoly) {
     constexpr int G = NI > 8 ? 2 : MM_OUT;
     const int N = 1 << T.log_n;
     const int i = blockIdx.x * TPB + threadIdx.x;
-    const int l = blockIdx.y, p = blockIdx.z;
+    const int l = blockIdx.y;
     const ModP m = T.mods[l];
     const int64_t o = (int64_t)l * N + i;
     // up to eight terms: carry-free column sums (the inputs split once for all outputs);
@@ -2745,7 +2801,9 @@ __global__ __launch_bounds__(TPB) void k_mask_mac_multi(DevTables T, MultiMacDes
             if constexpr (COLS) mk[g][j] = split30(v);
             else mk[g][j] = v;
         }
-    for (int c = 0; c < D.nct; c++) {
+    // one polynomial per block row, or both in one block (the masks then cross HBM once)
+    for (int cp = blockIdx.z; cp < D.nct * npoly; cp += gridDim.z) {
+        const int c = cp / npoly, p = cp % npoly;
         u64 x[NI];
 #pragma unroll
         for (int j = 0; j < NI; j++) x[j] = ldnt(D.in[j] + (c * D.in_cs[j] + p * D.in_ps[j] + o));
@@ -2780,13 +2838,17 @@ void launch_mask_mac_multi(const DevTables& T, int nl, int npoly, const MultiMac
         for (int j = 0; j < D.nin; j++) terms += D.mask[g][j] != nullptr;
     ProfScope prof_(PK_MASKMAC, (terms + D.nct * npoly * ((double)D.nin + D.nout)) * nl * 8.0 * (1 << T.log_n), st);
     const int N = 1 << T.log_n;
-    dim3 grid(ceil_div(N, TPB), nl, npoly);
+    // a block takes both polynomials, so that the masks (up to 32 words per slot, against 8 inputs per member
+    // and polynomial) cross HBM once: N = 2^15, one member 65 -> 43 us, five 93 -> 76, sixteen 311 -> 290; a
+    // polynomial each where that leaves the device short of blocks (N = 2^12: 5.4 against 6.2 us)
+    const int64_t blocks = ceil_div(N, TPB) * nl;
+    dim3 grid(ceil_div(N, TPB), nl, blocks >= 512 ? 1 : npoly);
     switch (D.nin) {
-        case 1: HE_LAUNCH(k_mask_mac_multi<1>, grid, dim3(TPB), 0, st, T, D); break;
-        case 2: HE_LAUNCH(k_mask_mac_multi<2>, grid, dim3(TPB), 0, st, T, D); break;
-        case 4: HE_LAUNCH(k_mask_mac_multi<4>, grid, dim3(TPB), 0, st, T, D); break;
-        case 8: HE_LAUNCH(k_mask_mac_multi<8>, grid, dim3(TPB), 0, st, T, D); break;
-        default: HE_LAUNCH(k_mask_mac_multi<16>, grid, dim3(TPB), 0, st, T, D); break;
+        case 1: HE_LAUNCH(k_mask_mac_multi<1>, grid, dim3(TPB), 0, st, T, D, npoly); break;
+        case 2: HE_LAUNCH(k_mask_mac_multi<2>, grid, dim3(TPB), 0, st, T, D, npoly); break;
+        case 4: HE_LAUNCH(k_mask_mac_multi<4>, grid, dim3(TPB), 0, st, T, D, npoly); break;
+        case 8: HE_LAUNCH(k_mask_mac_multi<8>, grid, dim3(TPB), 0, st, T, D, npoly); break;
+        default: HE_LAUNCH(k_mask_mac_multi<16>, grid, dim3(TPB), 0, st, T, D, npoly); break;
     }
 }
 

@@ -142,9 +142,7 @@ struct ConvPlan {
 // A digit's sets are split over waves only while a launch has fewer waves than this (each wave
 // transforms its sources again): at N = 2^15, 16 members, a ModUp takes 98 us unsplit and 117 split to
 // 8192 waves; five members' ModDowns 35 us at this line, 42 at 8192; one member's ModUp 21 us, 28 at 512
-#ifndef CONV_WAVES
 #define CONV_WAVES 1024
-#endif
 struct ConvPlanDesc {
     const u64* src;
     u64* dst;
@@ -153,6 +151,7 @@ struct ConvPlanDesc {
     const u64* tab;
     const ConvSet* sets;
     int npoly, nitem;
+    int limbs;  // twiddle rows in LDS of the largest item
     ConvDig dig[HE_MAXDIG];
     uint8_t it_dig[CONV_MAXITEM], it_s0[CONV_MAXITEM], it_s1[CONV_MAXITEM];  // a wave's digit and sets
 };

@@ -22,7 +22,7 @@ struct ModP {
     u64 ninv;   // N^-1 mod q
     u64 ninv_sh;
     u64 half;   // (q - 1) / 2
-    u64 pad;
+    double qinv;  // fl(1 / q)
 };
 
 __device__ __forceinline__ u64 add_mod(u64 a, u64 b, u64 q) {
