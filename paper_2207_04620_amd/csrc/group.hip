@@ -30,6 +30,15 @@ int Ctx::sets_per_launch(int B, bool direct) const {
     return std::max(4, std::min(IP_MAXSET, 64 / std::max(1, B)));
 }
 
+// Giant steps lifted MM_OUT at a time, and the rounds of the schedules without ModDown hoisting or with a
+// relinearisation per product several at a time: a lift or a relinearisation is a handful of launches of 5
+// to 20 us for one member and takes nearly the same for four (h = 64 at N = 2^15: 4.56 ms with its 22
+// giant steps one at a time, 4.16 together; three h = 32 members at N = 2^14 as printed: 7.41 ms round
+// by round, 2.97 with 16 rounds together).  Nine members fill the launches by themselves.
+bool Ctx::wide_giants(int B, bool direct) const {
+    return direct && pair_auto && !pool.limit && !pool_side.limit && B <= 8;
+}
+
 // f(direct): a direct call's work, again with the knob's sets per launch if the wider
 // launches' buffers do not fit the device (nothing of the first attempt is kept; a recording
 // capture has no second attempt)
@@ -57,6 +66,18 @@ Grp Ctx::g_new(int B, int level, int deg, const std::vector<double>& sc) {
     g.buf = std::make_shared<DBuf>(this, (size_t)B * g.cs);
     g.p = g.buf->p;
     return g;
+}
+
+// the sets of a group of P x B members as views of B members each
+static std::vector<Grp> g_views(const Grp& g, int B) {
+    std::vector<Grp> res(g.B / B);
+    for (size_t j = 0; j < res.size(); ++j) {
+        res[j] = g;
+        res[j].B = B;
+        res[j].p = g.p + (int64_t)j * B * g.cs;
+        res[j].scale.assign(g.scale.begin() + j * B, g.scale.begin() + (j + 1) * B);
+    }
+    return res;
 }
 
 Grp Ctx::g_gather(const std::vector<const CtData*>& v, int level) {
@@ -224,27 +245,20 @@ static u64 galois_inverse(u64 g, int log_n) {
 // <lift o sigma_g, key> (+ P sigma_g(c0) on the Q limbs) of every member into
 // u + s B [2][ne][N] (added to what u holds with accumulate); with nrot = 2 a set is the
 // masked sum of two rotations (one ModDown then serves both)
-void Ctx::g_ks_inner_sets(u64* u, const u64* lift, int B, int level, std::vector<IpSet> sets, int nrot,
+void Ctx::g_ks_inner_sets(u64* u, const u64* lift, int B, int level, const std::vector<IpSet>& sets, int nrot,
                           const u64* c0, int64_t c0_cs, bool accumulate) {
     // every group lift leaves its digits' own limbs in the lifted polynomial
-    auto own_of = [&](const u64* l) {
-        auto it = lift_own.find(l);
-        if (it == lift_own.end()) throw HeError(HE_EUNSUPPORTED);
-        return it->second;
-    };
-    const auto own = own_of(lift);
-    for (auto& S : sets)
-        if (S.lift2) {
-            const auto o2 = own_of(S.lift2);
-            S.own2 = o2.first;
-            S.own2_cs = o2.second;
-        }
+    auto it = lift_own.find(lift);
+    if (it == lift_own.end()) throw HeError(HE_EUNSUPPORTED);
+    const auto own = it->second;
     ip_into(u, lift, own.first, own.second, B, level, sets, nrot, c0, c0_cs, accumulate);
 }
 
-// the same with the lifted polynomial (own, member stride own_cs) given
+// the same with the lifted polynomial (own, member stride own_cs) given; per_set: set s rotates
+// the members s B.. of the lift, own and c0
 void Ctx::ip_into(u64* u, const u64* lift, const u64* own, int64_t own_cs, int B, int level,
-                  const std::vector<IpSet>& sets, int nrot, const u64* c0, int64_t c0_cs, bool accumulate) {
+                  const std::vector<IpSet>& sets, int nrot, const u64* c0, int64_t c0_cs, bool accumulate,
+                  bool per_set) {
     const int nl = level + 1, ne = nl + n_p;
     const int beta = (int)mu[level].size();
     if (sets.empty() || sets.size() > IP_MAXSET) throw HeError(HE_EUNSUPPORTED);
@@ -276,51 +290,31 @@ void Ctx::ip_into(u64* u, const u64* lift, const u64* own, int64_t own_cs, int B
         D.s[j].ginv = galois_inverse(sets[j].g, log_n);
     }
     D.accumulate = accumulate ? 1 : 0;
+    if (per_set) {
+        D.lift_ss = B * D.lift_cs;
+        D.own_ss = B * own_cs;
+        D.c0_ss = B * c0_cs;
+    }
     launch_inner_product(T, D, stream);
     cnt[C_KS] += (int64_t)B * nrot * D.nset;
 }
 
-// Key-switch inner product <lift o sigma_g, key> (+ P sigma_g(c0) on the Q limbs) of every
-// member into u [B][2][ne][N] (added to what u holds with accumulate); with a second
-// (g2, key2) and masks, the masked sum of two rotations of the same lift (one ModDown then
-// serves both)
-void Ctx::g_ks_inner(u64* u, const u64* lift, int B, int level, const u64* key, u64 g, const u64* c0,
-                     int64_t c0_cs, const u64* mask, const u64* key2, u64 g2, const u64* mask2, bool accumulate) {
-    IpSet S;
-    memset(&S, 0, sizeof S);
-    S.key = key;
-    S.g = g;
-    S.mask = mask;
-    S.key2 = key2;
-    S.g2 = g2;
-    S.mask2 = mask2;
-    g_ks_inner_sets(u, lift, B, level, {S}, key2 ? 2 : 1, c0, c0_cs, accumulate);
-}
-
-// out = ModDown(u) (+ add gathered by add_g) (. mask) (+ acc), for every member; u as made
-// by g_ks_inner.  The combine runs in the epilogue of the forward NTT of the converted
-// special-prime part.
-void Ctx::g_moddown(u64* u, int B, int level, const u64* add0, const u64* add1, int64_t add_cs, u64* out0,
-                    u64* out1, int64_t out_cs, u64 add_g, const u64* mask, const u64* acc0, const u64* acc1,
-                    int64_t acc_cs) {
+// out = ModDown(u) (+ add) for every member; u as made by g_ks_inner_sets.  The combine runs in the
+// epilogue of the forward NTT of the converted special-prime part.
+void Ctx::g_moddown(u64* u, int B, int level, const u64* add0, const u64* add1, int64_t add_cs, const Grp& out) {
     DBuf conv(this, (size_t)B * 2 * (level + 1) * N);
     Epi E;
     memset(&E, 0, sizeof E);
     E.add[0] = add0;
     E.add[1] = add1;
     E.add_cs = add_cs;
-    E.out[0] = out0;
-    E.out[1] = out1;
-    E.out_cs = out_cs;
-    E.g = add_g;
-    E.mask = mask;
-    E.acc[0] = acc0;
-    E.acc[1] = acc1;
-    E.acc_cs = acc_cs;
+    E.out[0] = out.p;
+    E.out[1] = out.p + out.ps;
+    E.out_cs = out.cs;
     moddown_into(u, conv.p, B, level, E);
 }
 
-// the same with the epilogue's operands in E and the converted limbs in conv [B][2][level + 1][N]
+// ModDown(u) with the epilogue's operands in E and the converted limbs in conv [B][2][level + 1][N]
 void Ctx::moddown_into(u64* u, u64* conv, int B, int level, const Epi& part) {
     const int nl = level + 1, ne = nl + n_p;
     const int64_t ucs = 2 * (int64_t)ne * N, ccs = 2 * (int64_t)nl * N;
@@ -394,13 +388,16 @@ void Ctx::moddown_into(u64* u, u64* conv, int B, int level, const Epi& part) {
     launch_ntt_moddown(T, J, E, stream, !planned && !fused);
 }
 
-// ModDown(<lift o sigma_g, key>) (+ add) into out, for every member
+// ModDown(<lift o sigma_g, key> + P sigma_g(c0)) (+ add) into out, for every member
 void Ctx::g_ks_apply(const u64* lift, int B, int level, const u64* key, u64 g, const u64* add0, const u64* add1,
-                     int64_t add_cs, u64* out0, u64* out1, int64_t out_cs, u64 add_g, const u64* mask,
-                     const u64* acc0, const u64* acc1, int64_t acc_cs, const u64* c0, int64_t c0_cs) {
+                     int64_t add_cs, const Grp& out, const u64* c0, int64_t c0_cs) {
     DBuf u(this, (size_t)B * 2 * (level + 1 + n_p) * N);
-    g_ks_inner(u.p, lift, B, level, key, g, c0, c0_cs, nullptr, nullptr, 1, nullptr, false);
-    g_moddown(u.p, B, level, add0, add1, add_cs, out0, out1, out_cs, add_g, mask, acc0, acc1, acc_cs);
+    IpSet S;
+    memset(&S, 0, sizeof S);
+    S.key = key;
+    S.g = g;
+    g_ks_inner_sets(u.p, lift, B, level, {S}, 1, c0, c0_cs, false);
+    g_moddown(u.p, B, level, add0, add1, add_cs, out);
 }
 
 // Several rotation sets of one ciphertext at once: each set's inner product goes into its
@@ -423,20 +420,27 @@ Ctx::PendingSets Ctx::g_sets_ip(const Grp& a, const u64* lift, const std::vector
     return ps;
 }
 
-std::vector<Grp> Ctx::g_sets_finish(PendingSets& ps) {
-    const int P = ps.P, B = ps.B;
+// masks: one per set, applied to its members in the ModDown epilogue (then acc, the same members,
+// is added)
+std::vector<Grp> Ctx::g_sets_finish(PendingSets& ps, const std::vector<const u64*>* masks, const Grp* acc) {
+    const int n = ps.P * ps.B;
     Grp& out = ps.out;
-    g_moddown(ps.u->p, P * B, ps.level, nullptr, nullptr, 0, out.p, out.p + out.ps, out.cs, 1, nullptr, nullptr,
-              nullptr, 0);
-    ps.u.reset();
-    std::vector<Grp> res(P);
-    for (int j = 0; j < P; ++j) {
-        res[j] = out;
-        res[j].B = B;
-        res[j].p = out.p + (size_t)j * B * out.cs;
-        res[j].scale.assign(ps.sc.begin() + (size_t)j * B, ps.sc.begin() + (size_t)(j + 1) * B);
+    DBuf conv(this, (size_t)n * 2 * (ps.level + 1) * N);
+    Epi E;
+    memset(&E, 0, sizeof E);
+    for (int p = 0; p < 2; ++p) {
+        E.out[p] = out.p + p * out.ps;
+        if (acc) E.acc[p] = acc->p + p * acc->ps;
     }
-    return res;
+    E.out_cs = out.cs;
+    if (acc) E.acc_cs = acc->cs;
+    if (masks) {
+        E.set_b = ps.B;
+        std::copy(masks->begin(), masks->end(), E.set_mask);
+    }
+    moddown_into(ps.u->p, conv.p, n, ps.level, E);
+    ps.u.reset();
+    return g_views(out, ps.B);
 }
 
 std::vector<Grp> Ctx::g_rotate_sets_hoisted(const Grp& a, const u64* lift, const std::vector<IpSet>& sets,
@@ -469,12 +473,6 @@ Ctx::PendingSets Ctx::g_pairs_ip(const Grp& a, const u64* lift, const std::vecto
     return ps;
 }
 
-std::vector<Grp> Ctx::g_rotate_pairs_hoisted(const Grp& a, const u64* lift, const std::vector<MaskPair>& pr,
-                                             double mask_scale) {
-    PendingSets ps = g_pairs_ip(a, lift, pr, mask_scale);
-    return g_sets_finish(ps);
-}
-
 // Rot(a, k) for several k of one lift, with one shared ModDown (Step 3's baby rotations
 // under the hoisted-ModDown schedule); identical to rotating one at a time
 std::vector<Grp> Ctx::g_rotate_many_hoisted(const Grp& a, const u64* lift, const std::vector<int64_t>& ks) {
@@ -492,12 +490,90 @@ std::vector<Grp> Ctx::g_rotate_many_hoisted(const Grp& a, const u64* lift, const
     return res;
 }
 
+// The same sums with a ModDown per rotation (no ModDown hoisting), each mask and the Add in the
+// ModDown's epilogue: the first rotations of every pair in one pass, then the second ones.
+// Exact residues, so identical to rotating, masking and adding one at a time.  The results are one block
+std::vector<Grp> Ctx::g_pairs_printed(const Grp& a, const u64* lift, const std::vector<MaskPair>& pr,
+                                      double mask_scale) {
+    const int P = (int)pr.size(), B = a.B;
+    Grp first;
+    std::vector<Grp> res;
+    for (int r = 0; r < 2; ++r) {
+        std::vector<IpSet> sets(P);
+        std::vector<const u64*> masks(P);
+        for (int j = 0; j < P; ++j) {
+            const u64 g = galois(r ? pr[j].k2 : pr[j].k1);
+            if (g == 1) throw HeError(HE_EUNSUPPORTED);
+            memset(&sets[j], 0, sizeof(IpSet));
+            sets[j].key = rot_key(g, false);
+            sets[j].g = g;
+            masks[j] = r ? pr[j].m2 : pr[j].m1;
+        }
+        PendingSets ps = g_sets_ip(a, lift, sets, 1, mask_scale);
+        res = g_sets_finish(ps, &masks, r ? &first : nullptr);
+        if (!r) first = ps.out;
+    }
+    cnt[C_ROT] += 2 * P * B;
+    cnt[C_MULPT] += 2 * P * B;
+    cnt[C_ADD] += P * B;
+    return res;
+}
+
+// Rot(a_j, ks[j]) of the sets a_j of B members of one group, each set its own lift, in one pass
+std::vector<Grp> Ctx::g_rotate_each(const Grp& joint, const std::vector<int64_t>& ks, int B) {
+    const int P = (int)ks.size(), level = joint.level, nl = level + 1, ne = nl + n_p;
+    std::vector<IpSet> sets(P);
+    for (int j = 0; j < P; ++j) {
+        const u64 g = galois(ks[j]);
+        if (g == 1) throw HeError(HE_EUNSUPPORTED);
+        memset(&sets[j], 0, sizeof(IpSet));
+        sets[j].key = rot_key(g, false);
+        sets[j].g = g;
+    }
+    auto lift = g_lift(joint, 1);
+    PendingSets ps;
+    ps.out = g_new(P * B, level, 1, joint.scale);
+    ps.u = std::make_shared<DBuf>(this, (size_t)P * B * 2 * ne * N);
+    ps.P = P;
+    ps.B = B;
+    ps.level = level;
+    ip_into(ps.u->p, lift->p, joint.p + joint.ps, joint.cs, B, level, sets, 1, joint.p, joint.cs, false, true);
+    lift.reset();
+    cnt[C_ROT] += (int64_t)P * B;
+    return g_sets_finish(ps);
+}
+
+// acc (+)= the terms, one pass per 16 (acc = the first term while !have)
+void Ctx::g_sum_into(Grp& acc, bool& have, const std::vector<Grp>& terms) {
+    size_t t = 0;
+    if (!have) {
+        acc = terms[t++];
+        have = true;
+    }
+    while (t < terms.size()) {
+        SumDesc D;
+        memset(&D, 0, sizeof D);
+        for (; t < terms.size() && D.n < 16; ++t) {
+            const Grp& g = terms[t];
+            if (acc.B != g.B || acc.deg != g.deg || acc.level != g.level) throw HeError(HE_EMISMATCH);
+            if (acc.cs != (acc.deg + 1) * acc.ps || g.cs != (g.deg + 1) * g.ps) throw HeError(HE_EUNSUPPORTED);
+            D.in[D.n] = g.p;
+            D.in_ps[D.n] = g.ps;
+            ++D.n;
+            for (int i = 0; i < acc.B; ++i) acc.scale[i] = std::max(acc.scale[i], g.scale[i]);
+        }
+        launch_sum_many(T, acc.level + 1, acc.B * (acc.deg + 1), D, acc.p, acc.ps, 1, stream);
+        cnt[C_ADD] += (int64_t)D.n * acc.B;
+    }
+}
+
 // Hoisted rotation sums: base + sum_w Rot(a_w, r_w) with one ModDown.  The terms' key-switch
 // inner products (with P sigma_g(c0_w)) are accumulated in the extended basis two at a time
 // (a term waits for the next one, then both go in one launch and their lifts are freed);
 // finish adds a last unpaired term, brings the sum down once and adds the unrotated base in
 // the ModDown epilogue.  Exact apart from the one shared ModDown rounding.
-void Ctx::g_rotsum_add(RotSum& S, const Grp& a, int64_t r) {
+// A lift made for several terms at once comes with the term's digits in it
+void Ctx::g_rotsum_add(RotSum& S, const Grp& a, int64_t r, std::shared_ptr<DBuf> lift, const u64* digits) {
     if (a.deg != 1) throw HeError(HE_EMISMATCH);
     if (!S.u) {
         S.B = a.B;
@@ -511,9 +587,13 @@ void Ctx::g_rotsum_add(RotSum& S, const Grp& a, int64_t r) {
     const u64 g = galois(r);
     if (g == 1) throw HeError(HE_EUNSUPPORTED);
     rot_key(g, false);
-    auto lift = g_lift(a, 1);
+    if (!lift) {
+        lift = g_lift(a, 1);
+        digits = lift->p;
+    }
     if (!S.plift) {
         S.plift = lift;
+        S.pl = digits;
         S.pa = a;
         S.pg = g;
     } else {
@@ -524,10 +604,12 @@ void Ctx::g_rotsum_add(RotSum& S, const Grp& a, int64_t r) {
         st.g = S.pg;
         st.key2 = rot_key(g, false);
         st.g2 = g;
-        st.lift2 = lift->p;
+        st.lift2 = digits;
+        st.own2 = a.p + a.ps;
+        st.own2_cs = a.cs;
         st.c0_2 = a.p;
         st.c0_2_cs = a.cs;
-        g_ks_inner_sets(S.u->p, S.plift->p, a.B, a.level, {st}, 2, S.pa.p, S.pa.cs, S.filled);
+        ip_into(S.u->p, S.pl, S.pa.p + S.pa.ps, S.pa.cs, a.B, a.level, {st}, 2, S.pa.p, S.pa.cs, S.filled);
         S.filled = true;
         S.plift.reset();
         S.pa = Grp();
@@ -541,8 +623,11 @@ Grp Ctx::g_rotsum_finish(RotSum& S, const Grp* base) {
     if (!S.u) throw HeError(HE_EUNSUPPORTED);
     if (base && (base->B != S.B || base->level != S.level || base->deg != 1)) throw HeError(HE_EMISMATCH);
     if (S.plift) {  // a last term without a partner
-        g_ks_inner(S.u->p, S.plift->p, S.B, S.level, rot_key(S.pg, false), S.pg, S.pa.p, S.pa.cs, nullptr, nullptr,
-                   1, nullptr, S.filled);
+        IpSet st;
+        memset(&st, 0, sizeof st);
+        st.key = rot_key(S.pg, false);
+        st.g = S.pg;
+        ip_into(S.u->p, S.pl, S.pa.p + S.pa.ps, S.pa.cs, S.B, S.level, {st}, 1, S.pa.p, S.pa.cs, S.filled);
         S.filled = true;
         S.plift.reset();
         S.pa = Grp();
@@ -552,7 +637,7 @@ Grp Ctx::g_rotsum_finish(RotSum& S, const Grp* base) {
         for (int i = 0; i < S.B; ++i) sc[i] = std::max(sc[i], base->scale[i]);
     Grp out = g_new(S.B, S.level, 1, sc);
     g_moddown(S.u->p, S.B, S.level, base ? base->p : nullptr, base ? base->p + base->ps : nullptr, base ? base->cs : 0,
-              out.p, out.p + out.ps, out.cs, 1, nullptr, nullptr, nullptr, 0);
+              out);
     cnt[C_ADD] += (int64_t)S.B * (S.n - 1 + (base ? 1 : 0));
     S = RotSum();
     return out;
@@ -563,31 +648,9 @@ Grp Ctx::g_rotate_from_lift(const Grp& a, const u64* lift, int64_t k) {
     if (g == 1) return g_drop(a, a.level);
     const u64* key = rot_key(g, false);
     Grp out = g_new(a.B, a.level, 1, a.scale);
-    // out0 = ModDown(.) + sigma_g(c0): the automorphism of c0 is a gather in the epilogue
-    g_ks_apply(lift, a.B, a.level, key, g, nullptr, nullptr, 0, out.p, out.p + out.ps, out.cs, g, nullptr, nullptr,
-               nullptr, 0, a.p, a.cs);
+    // c0 rides through the ModDown (P sigma_g(c0) in the inner product): out0 = ModDown(.) + sigma_g(c0)
+    g_ks_apply(lift, a.B, a.level, key, g, nullptr, nullptr, 0, out, a.p, a.cs);
     cnt[C_ROT] += a.B;
-    return out;
-}
-
-// Rot(a, k) . mask (+ acc): the Mul_pt (and the Add of a diagonal sum) fused into the
-// rotation's ModDown epilogue; exact residues, so identical to rotating then masking
-Grp Ctx::g_rotate_mask_from_lift(const Grp& a, const u64* lift, int64_t k, const u64* mask, double mask_scale,
-                                 const Grp* acc) {
-    const u64 g = galois(k);
-    if (g == 1) throw HeError(HE_EUNSUPPORTED);
-    const u64* key = rot_key(g, false);
-    std::vector<double> sc(a.scale);
-    for (auto& v : sc) v *= mask_scale;
-    Grp out = g_new(a.B, a.level, 1, sc);
-    g_ks_apply(lift, a.B, a.level, key, g, nullptr, nullptr, 0, out.p, out.p + out.ps, out.cs, g, mask,
-               acc ? acc->p : nullptr, acc ? acc->p + acc->ps : nullptr, acc ? acc->cs : 0, a.p, a.cs);
-    cnt[C_ROT] += a.B;
-    cnt[C_MULPT] += a.B;
-    if (acc) {
-        cnt[C_ADD] += a.B;
-        for (int i = 0; i < a.B; ++i) out.scale[i] = std::max(out.scale[i], acc->scale[i]);
-    }
     return out;
 }
 
@@ -679,26 +742,39 @@ void Ctx::rescale_into(const u64* a, int64_t a_ps, int l, int np, int B, u64* ou
     E.out_cs = np * out_ps;
     E.pinv = qi;
     E.pinv_sh = qis;
-    E.g = 1;
     launch_ntt_moddown(T, J, E, stream, !planned);
 }
 
-Grp Ctx::g_tensor(const Grp& a, const Grp& b) {
-    if (a.deg != 1 || b.deg != 1 || a.B != b.B || a.level != b.level) throw HeError(HE_EMISMATCH);
-    std::vector<double> sc(a.B);
-    for (int i = 0; i < a.B; ++i) sc[i] = a.scale[i] * b.scale[i];
-    Grp out = g_new(a.B, a.level, 2, sc);
-    launch_tensor(T, a.level + 1, a.p, a.ps, b.p, b.ps, out.p, out.ps, 0, stream, a.B, a.cs, b.cs, out.cs);
-    cnt[C_MULCT] += a.B;
+// a_j (x) b_j of every pair (of B members each) at the level of the lowest operand, as one group
+Grp Ctx::g_tensor_each(const std::vector<Grp>& a, const std::vector<Grp>& b) {
+    const int P = (int)a.size(), B = a[0].B;
+    if (b.size() != a.size() || P < 1 || P > 16) throw HeError(HE_EUNSUPPORTED);
+    int level = a[0].level;
+    std::vector<double> sc;
+    for (int j = 0; j < P; ++j) {
+        if (a[j].deg != 1 || b[j].deg != 1 || a[j].B != B || b[j].B != B) throw HeError(HE_EMISMATCH);
+        level = std::min(level, std::min(a[j].level, b[j].level));
+        for (int i = 0; i < B; ++i) sc.push_back(a[j].scale[i] * b[j].scale[i]);
+    }
+    Grp out = g_new(P * B, level, 2, sc);
+    TensorSumDesc D;
+    memset(&D, 0, sizeof D);
+    D.n = P;
+    D.nct = B;
+    D.d = out.p;
+    D.d_ps = out.ps;
+    D.d_cs = out.cs;
+    for (int j = 0; j < P; ++j) {
+        D.a[j] = a[j].p;
+        D.a_ps[j] = a[j].ps;
+        D.a_cs[j] = a[j].cs;
+        D.b[j] = b[j].p;
+        D.b_ps[j] = b[j].ps;
+        D.b_cs[j] = b[j].cs;
+    }
+    launch_tensor_each(T, level + 1, D, stream);
+    cnt[C_MULCT] += (int64_t)P * B;
     return out;
-}
-
-void Ctx::g_tensor_acc(Grp& acc, const Grp& a, const Grp& b) {
-    if (a.deg != 1 || b.deg != 1 || acc.deg != 2 || a.level != acc.level || b.level != acc.level)
-        throw HeError(HE_EMISMATCH);
-    launch_tensor(T, a.level + 1, a.p, a.ps, b.p, b.ps, acc.p, acc.ps, 1, stream, a.B, a.cs, b.cs, acc.cs);
-    cnt[C_MULCT] += a.B;
-    cnt[C_ADD] += a.B;
 }
 
 // J.S (+)= sum over the pending pairs of A (x) B in one pass (relin-once schedules)
@@ -739,36 +815,43 @@ void Ctx::g_tensor_sum(MatmulJob& J) {
     J.pendB.clear();
 }
 
+// J.S (+)= the relinearised products of the pending pairs
+void Ctx::g_relin_sum(MatmulJob& J) {
+    if (J.pendA.empty()) return;
+    for (size_t j = 0; j < J.pendA.size(); ++j)
+        if (J.pendA[j].level != J.pendB[j].level) throw HeError(HE_EMISMATCH);
+    g_sum_into(J.S, J.haveS, g_views(g_relin(g_tensor_each(J.pendA, J.pendB)), J.pendA[0].B));
+    J.pendA.clear();
+    J.pendB.clear();
+}
+
 Grp Ctx::g_relin(const Grp& a) {
     if (a.deg != 2) throw HeError(HE_EMISMATCH);
     const u64* key = relin_key();
     auto lift = g_lift(a, 2);
     Grp out = g_new(a.B, a.level, 1, a.scale);
-    g_ks_apply(lift->p, a.B, a.level, key, 1, a.p, a.p + a.ps, a.cs, out.p, out.p + out.ps, out.cs, 1, nullptr,
-               nullptr, nullptr, 0, nullptr, 0);
+    g_ks_apply(lift->p, a.B, a.level, key, 1, a.p, a.p + a.ps, a.cs, out, nullptr, 0);
     return out;
 }
 
 // ------------------------------------------------------------------ the product
 static int floordiv_g(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
 
-// Phase 0: Step 1-1 and Step 1-2 and the lifts of A0, B0.  Phases 1..: k_chunk rounds
-// of Steps 2-3 each.  Last phase: relinearisation (relin-once schedule) and the final
-// RS.  The phases follow the order of the unphased evaluation exactly.
 // HE-LinTrans (Alg. 2) with the baby-step/giant-step split (App. B) for every member: the sum
 // over diagonals d in [dlo, dhi] of mask_d . R(a, unit d), as
 //   sum_i Rot( sum_j R(mask_{b i + j}, -unit b i) . Rot(a, unit j), unit b i ),
 // under the packing iota_beta (amounts times beta); baby rotations share one lift, giant
 // steps share one ModDown under the hoisting flag.  No rescale.
+// For few members the giant steps of a chunk are lifted (and without the flag rotated) together.
 Grp Ctx::g_lintrans(const Grp& a, int kind, int h, int beta, int64_t unit, int dlo, int dhi, bool direct) {
     const int b = bsgs(h);
     const double ms = scale;
-    const bool hoist = (schedule & HE_SCHED_HOIST_MODDOWN) != 0;
+    const bool hoist = (schedule & HE_SCHED_HOIST_MODDOWN) != 0, wide = wide_giants(a.B, direct);
     std::vector<Grp> baby(b);
     baby[0] = a;
     if (b > 1) {
         auto lift = g_lift(a, 1);
-        if (hoist) {
+        if (hoist || wide) {
             // up to sets_per_launch babies per launch, with one shared ModDown
             // (a rotation that is the identity on the slots is the ciphertext itself)
             std::vector<int> js;
@@ -806,6 +889,11 @@ Grp Ctx::g_lintrans(const Grp& a, int kind, int h, int beta, int64_t unit, int d
             D.in_cs[j] = baby[j].cs;
         }
         std::vector<std::pair<int, Grp>> inners;
+        // the chunk's sums that are rotated lie in one block where they are lifted together
+        Grp joint;
+        const int last = std::min(ghi, i0 + per - 1);
+        const int nrot = last - i0 + 1 - (i0 <= 0 && last >= 0 ? 1 : 0);
+        std::vector<int64_t> rots;
         for (int i = i0; i <= std::min(ghi, i0 + per - 1); ++i) {
             int nterm = 0;
             const u64* mk[16] = {nullptr};
@@ -818,7 +906,24 @@ Grp Ctx::g_lintrans(const Grp& a, int kind, int h, int beta, int64_t unit, int d
             if (!nterm) continue;
             std::vector<double> sc(a.scale);
             for (auto& v : sc) v *= ms;
-            Grp g = g_new(a.B, a.level, 1, sc);
+            const int64_t r = (int64_t)beta * unit * b * i;
+            Grp g;
+            if (wide && i && galois(r) != 1) {
+                if (!joint.p) {
+                    joint = g_new(nrot * a.B, a.level, 1, sc);
+                    joint.B = 0;
+                    joint.scale.clear();
+                }
+                g = joint;
+                g.B = a.B;
+                g.p = joint.p + joint.B * joint.cs;
+                g.scale = sc;
+                joint.B += a.B;
+                joint.scale.insert(joint.scale.end(), sc.begin(), sc.end());
+                rots.push_back(r);
+            } else {
+                g = g_new(a.B, a.level, 1, sc);
+            }
             D.out_ps = g.ps;
             D.out_cs = g.cs;
             for (int j = 0; j < b; ++j) D.mask[D.nout][j] = mk[j];
@@ -828,7 +933,18 @@ Grp Ctx::g_lintrans(const Grp& a, int kind, int h, int beta, int64_t unit, int d
             cnt[C_ADD] += (int64_t)(nterm - 1) * a.B;
         }
         if (D.nout) launch_mask_mac_multi(T, a.level + 1, 2, D, stream);
+        if (joint.B) {
+            if (hoist) {
+                auto lift = g_lift(joint, 1);
+                const int64_t set = (int64_t)a.B * mu[a.level].size() * (a.level + 1 + n_p) * N;
+                const auto sums = g_views(joint, a.B);
+                for (size_t w = 0; w < rots.size(); ++w) g_rotsum_add(gsum, sums[w], rots[w], lift, lift->p + w * set);
+            } else {
+                g_sum_into(acc, have, g_rotate_each(joint, rots, a.B));
+            }
+        }
         for (auto& ig : inners) {
+            if (joint.p && ig.second.buf == joint.buf) continue;
             const int i = ig.first;
             Grp inner = ig.second;
             const int64_t r = (int64_t)beta * unit * b * i;
@@ -881,7 +997,10 @@ bool Ctx::matmul_step(MatmulJob& J, int k_chunk) {
         const bool keep_baby = bg < t;
         if (keep_baby && J.babyB.empty()) J.babyB.resize(bg);
         const int kend = std::min(t, J.k + std::max(1, k_chunk));
-        const int nset = sets_per_launch(J.A0.B, J.direct);
+        // without ModDown hoisting (the algorithm as printed): several rounds at a time in direct calls
+        // whose launches are small, otherwise one
+        const bool wide = wide_giants(J.A0.B, J.direct);
+        const int nset = hoist || wide ? sets_per_launch(J.A0.B, J.direct) : 1;
         // hoisted schedule: the mask pairs of up to nset consecutive k share one ModDown;
         // with overlap, the next group's inner products run on the side stream during this
         // group's ModDown (within this chunk of rounds only)
@@ -895,6 +1014,19 @@ bool Ctx::matmul_step(MatmulJob& J, int k_chunk) {
                               mask(3, h, kk, -sh, beta)});
             }
             return pr;
+        };
+        // the group's rescales (rescale early) in one
+        auto rescale_pairs = [&]() {
+            if ((schedule & HE_SCHED_RESCALE_LATE) || !wide) return;
+            Grp all = pairs[0];
+            all.B = 0;
+            all.scale.clear();
+            for (auto& g : pairs) {
+                all.B += g.B;
+                all.scale.insert(all.scale.end(), g.scale.begin(), g.scale.end());
+            }
+            pairs.clear();
+            pairs = g_views(g_rescale(all), J.A0.B);
         };
         PendingSets next;
         int next_k0 = -1;
@@ -911,7 +1043,15 @@ bool Ctx::matmul_step(MatmulJob& J, int k_chunk) {
             Grp Ak;
             if (k == 0) {
                 Ak = g_mask_sum({{&J.A0, mask(2, h, 0, 0, beta)}}, ms);
-            } else if (hoist) {
+            } else if (!hoist) {
+                // masks applied in the ModDown epilogues
+                if (pairs.empty() || k - pairs_k0 >= (int)pairs.size()) {
+                    pairs = g_pairs_printed(J.A0, J.liftA->p, pair_group(k), ms);
+                    pairs_k0 = k;
+                    rescale_pairs();
+                }
+                Ak = pairs[k - pairs_k0];
+            } else {
                 if (pairs.empty() || k - pairs_k0 >= (int)pairs.size()) {
                     PendingSets cur;
                     if (next_k0 == k) {  // issued on the side stream: join it
@@ -941,22 +1081,17 @@ bool Ctx::matmul_step(MatmulJob& J, int k_chunk) {
                     }
                     pairs = g_sets_finish(cur);
                     pairs_k0 = k;
+                    rescale_pairs();
                 }
                 Ak = pairs[k - pairs_k0];
-            } else {
-                // masks applied in the ModDown epilogues
-                Grp t1 = g_rotate_mask_from_lift(J.A0, J.liftA->p, beta * (k - shift), mask(2, h, k, -shift, beta), ms,
-                                                 nullptr);
-                Ak = g_rotate_mask_from_lift(J.A0, J.liftA->p, beta * (k - h - shift), mask(3, h, k, -shift, beta), ms,
-                                             &t1);
             }
-            if (!(schedule & HE_SCHED_RESCALE_LATE)) Ak = g_rescale(Ak);
+            if ((k == 0 || !wide) && !(schedule & HE_SCHED_RESCALE_LATE)) Ak = g_rescale(Ak);
             Grp Bj;
             if (j == 0) {
                 Bj = J.B0;
             } else if (i > 0) {
                 Bj = J.babyB[j];
-            } else if (hoist) {
+            } else {
                 // baby rotations of B0, up to nset at a time with one shared ModDown
                 // (kept for the later blocks, or until used within this chunk)
                 if (keep_baby ? !J.babyB[j].p : (babies.empty() || j - babies_j0 >= (int)babies.size())) {
@@ -969,26 +1104,19 @@ bool Ctx::matmul_step(MatmulJob& J, int k_chunk) {
                         for (int jj = j; jj < jend; ++jj) J.babyB[jj] = babies[jj - j];
                 }
                 Bj = keep_baby ? J.babyB[j] : babies[j - babies_j0];
-            } else {
-                Bj = g_rotate_from_lift(J.B0, J.liftB->p, (int64_t)beta * h * j);
-                if (keep_baby) J.babyB[j] = Bj;
             }
+            J.pendA.push_back(Ak);
+            J.pendB.push_back(Bj);
             if (!(schedule & HE_SCHED_RELIN_ONCE)) {
-                Grp prod = g_relin(g_tensor(Ak, Bj));
-                if (!J.haveS) {
-                    J.S = prod;
-                    J.haveS = true;
-                } else {
-                    g_add_into(J.S, prod);
-                }
+                // each product relinearised, up to nset in one pass
+                if ((int)J.pendA.size() >= (wide ? nset : 1)) g_relin_sum(J);
             } else {
                 // products of a block are summed in one pass (at most 16 pairs per pass)
-                J.pendA.push_back(Ak);
-                J.pendB.push_back(Bj);
                 if (J.pendA.size() == 16) g_tensor_sum(J);
             }
             if (j == bg - 1 || k == t - 1) {
-                g_tensor_sum(J);
+                if (schedule & HE_SCHED_RELIN_ONCE) g_tensor_sum(J);
+                else g_relin_sum(J);
                 Grp blk = J.S;
                 J.S = Grp();
                 J.haveS = false;

@@ -885,8 +885,16 @@ CtPtr Ctx::tensor(const CtData& a, const CtData& b) {
     if (a.deg != 1 || b.deg != 1) throw HeError(HE_EMISMATCH);
     const int level = std::min(a.level, b.level), nl = level + 1;
     CtPtr r = new_ct(level, 2, a.scale * b.scale);
-    launch_tensor(T, nl, a.buf->p, (int64_t)(a.level + 1) * N, b.buf->p, (int64_t)(b.level + 1) * N, r->buf->p,
-                  (int64_t)nl * N, 0, stream);
+    TensorSumDesc D;
+    memset(&D, 0, sizeof D);
+    D.a[0] = a.buf->p;
+    D.a_ps[0] = (int64_t)(a.level + 1) * N;
+    D.b[0] = b.buf->p;
+    D.b_ps[0] = (int64_t)(b.level + 1) * N;
+    D.d = r->buf->p;
+    D.d_ps = (int64_t)nl * N;
+    D.n = D.nct = 1;
+    launch_tensor_each(T, nl, D, stream);
     cnt[C_MULCT]++;
     return r;
 }
@@ -911,7 +919,6 @@ void Ctx::ks_single_into(const u64* d, int level, const u64* key, u64 g, const u
     }
     E.out[0] = out;
     E.out[1] = out + ps;
-    E.g = 1;
     moddown_into(u, tmp, 1, level, E);
 }
 

@@ -104,6 +104,7 @@ struct RotSum {
     // a term waiting for a partner: two terms share one inner-product launch, so u is read
     // and rewritten once per pair (its lift, its ciphertext for c0, its Galois element)
     std::shared_ptr<DBuf> plift;
+    const u64* pl = nullptr;  // the term's digits in plift
     Grp pa;
     u64 pg = 0;
 };
@@ -274,7 +275,8 @@ struct Ctx {
     // allocation-free rotation alike)
     void lift_into(const u64* d, int64_t d_cs, int B, int level, u64* lift, u64* coef);
     void ip_into(u64* u, const u64* lift, const u64* own, int64_t own_cs, int B, int level,
-                 const std::vector<IpSet>& sets, int nrot, const u64* c0, int64_t c0_cs, bool accumulate);
+                 const std::vector<IpSet>& sets, int nrot, const u64* c0, int64_t c0_cs, bool accumulate,
+                 bool per_set = false);
     void moddown_into(u64* u, u64* conv, int B, int level, const Epi& part);
     void rescale_into(const u64* a, int64_t a_ps, int l, int np, int B, u64* out, int64_t out_ps);
     void ks_single(const u64* d, int level, const u64* key, u64 g, const u64* c0, const u64* add, u64* out);
@@ -326,15 +328,15 @@ struct Ctx {
     Grp g_drop(const Grp& a, int level);
     void g_add_into(Grp& acc, const Grp& t);
     std::shared_ptr<DBuf> g_lift(const Grp& a, int poly);
-    void g_ks_inner(u64* u, const u64* lift, int B, int level, const u64* key, u64 g, const u64* c0, int64_t c0_cs,
-                    const u64* mask, const u64* key2, u64 g2, const u64* mask2, bool accumulate);
-    void g_ks_inner_sets(u64* u, const u64* lift, int B, int level, std::vector<IpSet> sets, int nrot,
+    void g_ks_inner_sets(u64* u, const u64* lift, int B, int level, const std::vector<IpSet>& sets, int nrot,
                          const u64* c0, int64_t c0_cs, bool accumulate);
-    void g_rotsum_add(RotSum& S, const Grp& a, int64_t r);
+    bool wide_giants(int B, bool direct) const;
+    void g_rotsum_add(RotSum& S, const Grp& a, int64_t r, std::shared_ptr<DBuf> lift = nullptr,
+                      const u64* digits = nullptr);
+    void g_sum_into(Grp& acc, bool& have, const std::vector<Grp>& terms);
+    std::vector<Grp> g_rotate_each(const Grp& joint, const std::vector<int64_t>& ks, int B);
     Grp g_rotsum_finish(RotSum& S, const Grp* base);
-    void g_moddown(u64* u, int B, int level, const u64* add0, const u64* add1, int64_t add_cs, u64* out0,
-                   u64* out1, int64_t out_cs, u64 add_g, const u64* mask, const u64* acc0, const u64* acc1,
-                   int64_t acc_cs);
+    void g_moddown(u64* u, int B, int level, const u64* add0, const u64* add1, int64_t add_cs, const Grp& out);
     std::vector<Grp> g_rotate_sets_hoisted(const Grp& a, const u64* lift, const std::vector<IpSet>& sets, int nrot,
                                            double mask_scale);
     // the two halves of g_rotate_sets_hoisted: the inner products of every set (on the stream
@@ -346,23 +348,21 @@ struct Ctx {
         int P = 0, B = 0, level = 0;
     };
     PendingSets g_sets_ip(const Grp& a, const u64* lift, const std::vector<IpSet>& sets, int nrot, double mask_scale);
-    std::vector<Grp> g_sets_finish(PendingSets& ps);
+    std::vector<Grp> g_sets_finish(PendingSets& ps, const std::vector<const u64*>* masks = nullptr,
+                                   const Grp* acc = nullptr);
     PendingSets g_pairs_ip(const Grp& a, const u64* lift, const std::vector<MaskPair>& pr, double mask_scale);
     std::vector<Grp> g_rotate_many_hoisted(const Grp& a, const u64* lift, const std::vector<int64_t>& ks);
-    std::vector<Grp> g_rotate_pairs_hoisted(const Grp& a, const u64* lift, const std::vector<MaskPair>& pr,
-                                            double mask_scale);
     void g_ks_apply(const u64* lift, int B, int level, const u64* key, u64 g, const u64* add0, const u64* add1,
-                    int64_t add_cs, u64* out0, u64* out1, int64_t out_cs, u64 add_g, const u64* mask,
-                    const u64* acc0, const u64* acc1, int64_t acc_cs, const u64* c0, int64_t c0_cs);
-    Grp g_rotate_mask_from_lift(const Grp& a, const u64* lift, int64_t k, const u64* mask, double mask_scale,
-                                const Grp* acc);
+                    int64_t add_cs, const Grp& out, const u64* c0, int64_t c0_cs);
+    std::vector<Grp> g_pairs_printed(const Grp& a, const u64* lift, const std::vector<MaskPair>& pr, double mask_scale);
     Grp g_rotate_from_lift(const Grp& a, const u64* lift, int64_t k);
     Grp g_rotate(const Grp& a, int64_t k);
     Grp g_mask_sum(const std::vector<std::pair<const Grp*, const u64*>>& terms, double mask_scale);
     Grp g_rescale(const Grp& a);
-    Grp g_tensor(const Grp& a, const Grp& b);
-    void g_tensor_acc(Grp& acc, const Grp& a, const Grp& b);
+    Grp g_tensor_each(const std::vector<Grp>& a, const std::vector<Grp>& b);
+    Grp g_tensor(const Grp& a, const Grp& b) { return g_tensor_each({a}, {b}); }
     void g_tensor_sum(MatmulJob& J);
+    void g_relin_sum(MatmulJob& J);
     Grp g_relin(const Grp& a);
     Grp g_lintrans(const Grp& a, int kind, int h, int beta, int64_t unit, int dlo, int dhi, bool direct);
     std::vector<CtPtr> matmul_group(const std::vector<const CtData*>& A, const std::vector<const CtData*>& B,

@@ -981,7 +981,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(EPI ? 6 : 7
     u64* out = E.out[p] + c * E.out_cs + (int64_t)t * N;
     const u64 pi = E.pinv[t], pis = E.pinv_sh[t];
     const double pd = (double)pi;
-    const u64* mask = E.mask ? E.mask + (int64_t)t * N : nullptr;
+    const u64* mask = E.set_b ? E.set_mask[c / E.set_b] + (int64_t)t * N : nullptr;
     const u64* acc = E.acc[p] ? E.acc[p] + c * E.acc_cs + (int64_t)t * N : nullptr;
     const u64 qninv = T.mods[mi].qninv;
     for_pairs([&](int slot, int e, u64 v0, u64 v1) {
@@ -1000,14 +1000,9 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(EPI ? 6 : 7
             w[1] = mul_shoup(uw.y + 2 * q2 - v1, pi, pis, q);
         }
         if (add) {
-            if (E.g == 1) {
-                const u64x2 ad = ld2(add + i);
-                w[0] = add_mod(w[0], ad.x, q);
-                w[1] = add_mod(w[1], ad.y, q);
-            } else {
-                w[0] = add_mod(w[0], add[perm_g(i, E.g, T.log_n)], q);
-                w[1] = add_mod(w[1], add[perm_g(i + 1, E.g, T.log_n)], q);
-            }
+            const u64x2 ad = ld2(add + i);
+            w[0] = add_mod(w[0], ad.x, q);
+            w[1] = add_mod(w[1], ad.y, q);
         }
         if (mask) {
             const u64x2 m = ld2(mask + i);
@@ -1861,13 +1856,13 @@ void launch_conv_mfma(const DevTables& T, const ConvPlan& P, const u64* src, int
     }
 }
 
-
 // the NTT kernels move two residues per lane with 16-byte accesses
 static void check_ntt_alignment(const Jobs& J, const Epi* E) {
     bool bad = misaligned16(J.base) || (J.cstride & 1);
     if (E && E->on) {
-        bad = bad || misaligned16(E->u) || ((E->u_cs | E->u_ps | E->add_cs | E->out_cs | E->acc_cs) & 1) ||
-              misaligned16(E->mask);
+        bad = bad || misaligned16(E->u) || ((E->u_cs | E->u_ps | E->add_cs | E->out_cs | E->acc_cs) & 1);
+        if (E->set_b)
+            for (int s = 0; s < J.nct / E->set_b; ++s) bad = bad || misaligned16(E->set_mask[s]);
         for (int p = 0; p < 3; ++p) bad = bad || misaligned16(E->add[p]) || misaligned16(E->out[p]) ||
                                           misaligned16(E->acc[p]);
     }
@@ -1895,7 +1890,7 @@ void launch_ntt_moddown(const DevTables& T, const Jobs& J, const Epi& E, hipStre
     // accumulator operands (per ciphertext) and the mask (shared by the group)
     double per_ct = 0;
     for (int p = 0; p < 3; ++p) per_ct += (E.add[p] ? 1 : 0) + (E.acc[p] ? 1 : 0);
-    const double rows_bytes = 8.0 * N * (3 * limbs + per_ct * E.nl * J.nct + (E.mask ? E.nl : 0));
+    const double rows_bytes = 8.0 * N * (3 * limbs + per_ct * E.nl * J.nct + (E.set_b ? E.nl * (J.nct / E.set_b) : 0));
     ProfScope p(PK_NTT_FWD_ROWS, rows_bytes, st, limbs * (N / 2) * T.n2_log, fl * (N / 2) * T.n2_log);
     if (!E.on) throw std::runtime_error("ModDown row pass without its epilogue");
     HE_LAUNCH(k_ntt_fwd_rows<true>, grid_rows, dim3(TPB), 0, st, T, J, E);
@@ -2469,8 +2464,8 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(!FOLD && NB
 #pragma unroll
     for (int r = 0; r < NR; r++) {
         const bool other = r && S.lift2;
-        const u64* lift = (other ? S.lift2 : D.lift) + (int64_t)t * N;
-        const u64* own = other ? S.own2 : D.own;
+        const u64* lift = (other ? S.lift2 : D.lift + sj * D.lift_ss) + (int64_t)t * N;
+        const u64* own = other ? S.own2 : D.own + sj * D.own_ss;
         const int64_t owncs = other ? S.own2_cs : D.own_cs;
 #pragma unroll
         for (int j = 0; j < NB; j++) {
@@ -2478,7 +2473,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(!FOLD && NB
             xp[r][j] = from_own ? own + (int64_t)t * N : lift + (int64_t)j * D.ne * N;
             xcs[r][j] = from_own ? owncs : D.lift_cs;
         }
-        zb[r] = with_c0 ? (other ? S.c0_2 : D.c0) + (int64_t)t * N : nullptr;
+        zb[r] = with_c0 ? (other ? S.c0_2 : D.c0 + sj * D.c0_ss) + (int64_t)t * N : nullptr;
         zcs[r] = other ? S.c0_2_cs : D.c0_cs;
         so[r] = (uint32_t)src[r] * 8u;
     }
@@ -2598,7 +2593,7 @@ void launch_inner_product(const DevTables& T, const IpDesc& D, hipStream_t st) {
     double masks = 0, lifts = 1;
     for (int j = 0; j < ns; ++j) {
         masks += (D.s[j].mask ? 1.0 : 0.0) + (nr == 2 && D.s[j].mask2 ? 1.0 : 0.0);
-        if (nr == 2 && D.s[j].lift2) lifts += 1;  // another ciphertext's lift and c0
+        if ((nr == 2 && D.s[j].lift2) || (j && D.lift_ss)) lifts += 1;  // another ciphertext's lift and c0
     }
     const double words = (double)D.ne * (ns * nr * 2.0 * D.beta + masks +
                                          D.nct * (lifts * D.beta + ns * (D.accumulate ? 4.0 : 2.0))) +
@@ -2666,42 +2661,31 @@ void launch_rescale_spread(const DevTables& T, int nl_out, int npoly, const u64*
 }
 
 // ------------------------------------------------------------------ products
-__global__ __launch_bounds__(TPB) void k_tensor(DevTables T, const u64* a, int64_t a_ps, const u64* b,
-                                                int64_t b_ps, u64* d, int64_t d_ps, int acc, int64_t a_cs,
-                                                int64_t b_cs, int64_t d_cs) {
+// D.n products a_j (x) b_j of D.nct members each, product j of member c into member j nct + c of d; the
+// operands' polynomial strides may be larger than the output's (a limb prefix)
+__global__ __launch_bounds__(TPB) void k_tensor_each(DevTables T, TensorSumDesc D) {
     const int N = 1 << T.log_n;
     const int i = blockIdx.x * TPB + threadIdx.x;
-    const int l = blockIdx.y, c = blockIdx.z;
-    a += c * a_cs;
-    b += c * b_cs;
-    d += c * d_cs;
+    const int l = blockIdx.y, j = blockIdx.z / D.nct, c = blockIdx.z % D.nct;
     const ModP m = T.mods[l];
     const int64_t o = (int64_t)l * N + i;
-    const u64 a0 = a[o], a1 = a[a_ps + o];
-    const u64 b0 = to_mont(b[o], m), b1 = to_mont(b[b_ps + o], m);
-    const u64 d0 = mul_mont(a0, b0, m.q, m.qninv);
+    const u64 *a = D.a[j] + c * D.a_cs[j] + o, *b = D.b[j] + c * D.b_cs[j] + o;
+    u64* d = D.d + blockIdx.z * D.d_cs + o;
+    const u64 a0 = a[0], a1 = a[D.a_ps[j]];
+    const u64 b0 = to_mont(b[0], m), b1 = to_mont(b[D.b_ps[j]], m);
     Acc128 t = {0, 0};
     mac128(t, a0, b1);
     mac128(t, a1, b0);
-    const u64 d1 = redc(t.lo, t.hi, m.q, m.qninv);
-    const u64 d2 = mul_mont(a1, b1, m.q, m.qninv);
-    if (acc) {
-        d[o] = add_mod(d[o], d0, m.q);
-        d[d_ps + o] = add_mod(d[d_ps + o], d1, m.q);
-        d[2 * d_ps + o] = add_mod(d[2 * d_ps + o], d2, m.q);
-    } else {
-        d[o] = d0;
-        d[d_ps + o] = d1;
-        d[2 * d_ps + o] = d2;
-    }
+    d[0] = mul_mont(a0, b0, m.q, m.qninv);
+    d[D.d_ps] = redc(t.lo, t.hi, m.q, m.qninv);
+    d[2 * D.d_ps] = mul_mont(a1, b1, m.q, m.qninv);
 }
 
-void launch_tensor(const DevTables& T, int nl, const u64* a, int64_t a_ps, const u64* b, int64_t b_ps, u64* d,
-                   int64_t d_ps, int acc, hipStream_t st, int nct, int64_t a_cs, int64_t b_cs, int64_t d_cs) {
-    ProfScope prof_(PK_TENSOR, (acc ? 10.0 : 7.0) * nl * nct * 8.0 * (1 << T.log_n), st);
+void launch_tensor_each(const DevTables& T, int nl, const TensorSumDesc& D, hipStream_t st) {
+    ProfScope prof_(PK_TENSOR, 7.0 * nl * D.n * D.nct * 8.0 * (1 << T.log_n), st);
     const int N = 1 << T.log_n;
-    dim3 grid(ceil_div(N, TPB), nl, nct);
-    HE_LAUNCH(k_tensor, grid, dim3(TPB), 0, st, T, a, a_ps, b, b_ps, d, d_ps, acc, a_cs, b_cs, d_cs);
+    dim3 grid(ceil_div(N, TPB), nl, D.n * D.nct);
+    HE_LAUNCH(k_tensor_each, grid, dim3(TPB), 0, st, T, D);
 }
 
 // Step-3 block: d = sum_j a_j (x) b_j (d0 = sum a0 b0, d1 = sum a0 b1 + a1 b0, d2 = sum a1 b1),

@@ -208,7 +208,9 @@ struct IpDesc {
     int64_t own_cs;
     uint8_t dlo[HE_MAXSRC], dhi[HE_MAXSRC];
     int nrot;            // rotations per set (1 or 2)
-    int nset;            // sets of the same lift in this launch (at most IP_MAXSET)
+    int nset;            // sets in this launch (at most IP_MAXSET): of the same lift, or with
+    // set strides each of its own lift, own limbs and c0 (0: shared)
+    int64_t lift_ss, own_ss, c0_ss;
     IpSet s[IP_MAXSET];
     int accumulate;    // u += the result (a sum of rotations of different ciphertexts)
 };
@@ -245,6 +247,7 @@ struct TensorSumDesc {
     int64_t d_ps, d_cs;
     int n, nct, acc;
 };
+void launch_tensor_each(const DevTables& T, int nl, const TensorSumDesc& D, hipStream_t st);  // acc unused
 void launch_tensor_sum(const DevTables& T, int nl, const TensorSumDesc& D, hipStream_t st);
 
 struct MacDesc {
@@ -260,8 +263,7 @@ enum EwOp { EW_ADD = 0, EW_SUB = 1, EW_MUL_MONT = 2, EW_MUL_PLAIN = 3 };
 
 // ModDown epilogue fused into a forward NTT over the converted P-part: for job k of
 // ciphertext c (limb t = k % nl of poly p = k / nl) the transformed value v is not
-// stored; instead out_p[c][t][i] = (u[c][p][t][i] - v) * P^-1 + add_p[c][t][perm_g(i)]
-// (add_p may be null; g = 1 is the identity gather).
+// stored; instead out_p[c][t][i] = (u[c][p][t][i] - v) * P^-1 + add_p[c][t][i] (add_p may be null).
 struct Epi {
     int on;
     int nl;
@@ -272,12 +274,13 @@ struct Epi {
     int64_t add_cs, out_cs;
     const u64* pinv;
     const u64* pinv_sh;
-    u64 g;
-    // optional Mul_pt fused into the epilogue: out = w * mask (Montgomery form, rows = limbs)
-    // (+ acc_p[c][t][i] when acc_p is set): one term of a diagonal sum (Eq. 1)
-    const u64* mask;
+    // optional Mul_pt fused into the epilogue, out = w * mask (Montgomery form, rows = limbs)
+    // (+ acc_p[c][t][i] when acc_p is set): one term of a diagonal sum (Eq. 1).  With set_b, member c
+    // belongs to rotation set c / set_b and has that set's mask
     const u64* acc[3];
     int64_t acc_cs;
+    int set_b;
+    const u64* set_mask[IP_MAXSET];
 };
 
 // ------------------------------------------------------------------ launch timing
@@ -368,9 +371,6 @@ void launch_inner_product(const DevTables& T, const IpDesc& D, hipStream_t st);
 void launch_rescale_spread(const DevTables& T, int nl_out, int npoly, const u64* last, int64_t last_ps,
                            int last_mod, u64* tmp, int64_t tmp_ps, hipStream_t st);
 // d0 (+)= a0 b0, d1 (+)= a0 b1 + a1 b0, d2 (+)= a1 b1
-void launch_tensor(const DevTables& T, int nl, const u64* a, int64_t a_ps, const u64* b, int64_t b_ps, u64* d,
-                   int64_t d_ps, int acc, hipStream_t st, int nct = 1, int64_t a_cs = 0, int64_t b_cs = 0,
-                   int64_t d_cs = 0);
 // out[p][i] (+)= sum_r in_r[p][i] mask_r[i]  (masks in Montgomery form, compact [nl_top][N])
 void launch_mask_mac(const DevTables& T, int nl, int npoly, const MacDesc& D, u64* out, int64_t out_ps, int acc,
                      hipStream_t st, int64_t out_cs = 0);

@@ -8,8 +8,8 @@ from paper_2207_04620_amd import inputs as I
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("schedule", [15, 2, 0])
-@pytest.mark.parametrize("members", [1, 2, 3, 5, 16])
+@pytest.mark.parametrize("schedule", [15, 2, 0, 3, 4, 5, 8, 10])
+@pytest.mark.parametrize("members", [1, 2, 3, 5, 8, 16])
 def test_default_equals_every_setting(schedule, members):
     import torch
     assert torch.cuda.is_available()
