@@ -49,7 +49,7 @@ void Ctx::direct_call(F&& f) {
     try {
         f(true);
     } catch (const HeError& e) {
-        if (e.s != HE_ENOMEM || !pair_auto || pool.capture) throw;
+        if (e.s != HE_ENOMEM || pool.capture) throw;
         std::copy(before, before + 6, cnt);
         f(false);
     }
@@ -130,8 +130,9 @@ Grp Ctx::g_drop(const Grp& a, int level) {
     return g;
 }
 
+// acc += t (its limbs up to acc's level)
 void Ctx::g_add_into(Grp& acc, const Grp& t) {
-    if (acc.B != t.B || acc.deg != t.deg || acc.level != t.level) throw HeError(HE_EMISMATCH);
+    if (acc.B != t.B || acc.deg != t.deg || acc.level > t.level) throw HeError(HE_EMISMATCH);
     launch_ew(T, ModMap{1 << 20, n_q}, acc.level + 1, acc.deg + 1, acc.p, acc.ps, acc.p, acc.ps, t.p, t.ps, EW_ADD,
               stream, acc.B, acc.cs, acc.cs, t.cs);
     for (int i = 0; i < acc.B; ++i) acc.scale[i] = std::max(acc.scale[i], t.scale[i]);
@@ -826,12 +827,16 @@ void Ctx::g_relin_sum(MatmulJob& J) {
 }
 
 Grp Ctx::g_relin(const Grp& a) {
+    Grp out = g_new(a.B, a.level, 1, a.scale);
+    g_relin_into(a, out);
+    return out;
+}
+
+void Ctx::g_relin_into(const Grp& a, const Grp& out) {
     if (a.deg != 2) throw HeError(HE_EMISMATCH);
     const u64* key = relin_key();
     auto lift = g_lift(a, 2);
-    Grp out = g_new(a.B, a.level, 1, a.scale);
     g_ks_apply(lift->p, a.B, a.level, key, 1, a.p, a.p + a.ps, a.cs, out, nullptr, 0);
-    return out;
 }
 
 // ------------------------------------------------------------------ the product
@@ -1205,83 +1210,130 @@ static int64_t scaled_const(int64_t num, int e, u64 ql, double ratio) {
     return std::llround((double)num / (double)((int64_t)1 << e) * (double)ql * ratio);
 }
 
-// every member times its own integer constant k[m] (members with equal constants share a
-// launch)
-Grp Ctx::g_mul_int(const Grp& a, const std::vector<int64_t>& k) {
-    const int nl = a.level + 1;
-    Grp r = g_new(a.B, a.level, a.deg, a.scale);
-    std::vector<u64> c(2 * nl);
-    for (int m0 = 0; m0 < a.B;) {
-        int m1 = m0 + 1;
-        while (m1 < a.B && k[m1] == k[m0]) ++m1;
-        for (int i = 0; i < nl; ++i) {
-            const u64 q = mods[i];
-            const u64 v = k[m0] >= 0 ? (u64)k[m0] % q : (q - (u64)(-(k[m0] + 1)) % q - 1) % q;
-            c[i] = v;
-            c[nl + i] = hm::shoup(v, q);
-        }
-        DBuf dc(this, 2 * (size_t)nl);
-        hip_check(hipMemcpyAsync(dc.p, c.data(), c.size() * 8, hipMemcpyHostToDevice, stream), "mul_int consts");
-        hip_check(hipStreamSynchronize(stream), "mul_int consts");
-        // members m0..m1-1 are (m1 - m0) * (deg+1) polynomials with a uniform poly stride
-        launch_mul_const(T, ModMap{1 << 20, n_q}, nl, (m1 - m0) * (a.deg + 1), r.p + (size_t)m0 * r.cs, r.ps,
-                         a.p + (size_t)m0 * a.cs, a.ps, dc.p, dc.p + nl, stream);
-        m0 = m1;
+// out's k-th set of a.B members = a, every member times its own integer K[k a.B + member]
+void Ctx::g_mul_ints(const Grp& a, const std::vector<int64_t>& K, const Grp& out) {
+    const int n = (int)K.size() / a.B, per = std::min(a.B, MI_MAX / n);
+    if (a.cs != out.cs || a.ps != out.ps) throw HeError(HE_EUNSUPPORTED);
+    for (int m0 = 0; m0 < a.B; m0 += per) {
+        MulIntDesc D;
+        D.nct = std::min(per, a.B - m0);
+        D.n = n;
+        D.npoly = a.deg + 1;
+        D.a = a.p + m0 * a.cs;
+        D.out = out.p + m0 * a.cs;
+        D.ps = a.ps;
+        D.a_cs = a.cs;
+        D.out_ks = a.B * a.cs;
+        for (int k = 0; k < n; ++k)
+            for (int c = 0; c < D.nct; ++c) D.k[k * D.nct + c] = K[k * a.B + m0 + c];
+        launch_mul_ints(T, a.level + 1, D, stream);
     }
-    return r;
 }
 
-Grp Ctx::g_mul_rs(const Grp& x, const Grp& y) {
-    const int l = std::min(x.level, y.level);
-    Grp a = x.level == l ? x : g_drop(x, l);
-    Grp b = y.level == l ? y : g_drop(y, l);
-    return g_rescale(g_relin(g_tensor(a, b)));
-}
+Grp Ctx::g_mul_rs(const Grp& x, const Grp& y) { return g_rescale(g_relin(g_tensor(x, y))); }
 
 // g_d(x) = sum_i c_{2i+1} x^(2i+1): x_c = RS(x * round(c q_l)) lands at the scale of x;
 // x^(2i) comes from the powers x^2, x^4, ... multiplied in along the set bits of i.
-Grp Ctx::g_eval_gd(const Grp& x, int d, const std::vector<double>& target) {
+// A direct call takes everything of one level in one pass: the multiples x_c with x^2, then per power its
+// square with the products of the terms that it enters, and one sum: 35 launches instead of 90 per
+// composition of d = 3 (N = 2^15, one member, k = 2: 1.83 ms term by term, 1.08 so; N = 2^16, 16 members,
+// k = 3: 36.1 and 31.4 ms).  A call that does not fit the device, a capped cache and serving go term by term.
+Grp Ctx::g_eval_gd(const Grp& x, int d, const std::vector<double>& target, bool direct) {
     const auto num = gd_numerators(d);
-    const int e = 2 * d - 1;
+    const int e = 2 * d - 1, B = x.B;
     int nb = 0;
     while ((1 << nb) <= d) ++nb;
-    std::vector<Grp> pw(nb);
-    for (int b = 0; b < nb; ++b) pw[b] = b ? g_mul_rs(pw[b - 1], pw[b - 1]) : g_mul_rs(x, x);
+    // the powers' scales, as their products and rescales make them
+    std::vector<std::vector<double>> pws(nb, std::vector<double>(B));
+    for (int b = 0; b < nb; ++b)
+        for (int m = 0; m < B; ++m) {
+            const double s = b ? pws[b - 1][m] : x.scale[m];
+            pws[b][m] = s * s / (double)mods[x.level - b];
+        }
     const u64 ql = mods[x.level];
-    Grp y;
-    bool have = false;
-    for (int i = 0; i <= d; ++i) {
-        // scale matching: x_c carries the scale 'need' that the products with the powers
-        // and their rescales bring back exactly to the scale of x, so every term of the sum
-        // lands on one scale; need / scale(x) is folded into the integer constant
-        std::vector<double> need(x.B);
-        std::vector<int64_t> K(x.B);
-        for (int m = 0; m < x.B; ++m) {
+    // scale matching: x_c carries the scale 'need' that the products with the powers
+    // and their rescales bring back exactly to the scale of x, so every term of the sum
+    // lands on one scale; need / scale(x) is folded into the integer constant
+    std::vector<double> need((d + 1) * B);
+    std::vector<int64_t> K((d + 1) * B);
+    for (int i = 0; i <= d; ++i)
+        for (int m = 0; m < B; ++m) {
             double nd = target[m];
             int lv = x.level - 1;
             for (int b = 0; b < nb; ++b)
                 if ((i >> b) & 1) {
-                    const int l = std::min(lv, pw[b].level);
-                    nd = nd * (double)mods[l] / pw[b].scale[m];
+                    const int l = std::min(lv, x.level - 1 - b);
+                    nd = nd * (double)mods[l] / pws[b][m];
                     lv = l - 1;
                 }
-            need[m] = nd;
-            K[m] = scaled_const(num[i], e, ql, nd / x.scale[m]);
+            need[i * B + m] = nd;
+            K[i * B + m] = scaled_const(num[i], e, ql, nd / x.scale[m]);
         }
-        Grp term = g_rescale(g_mul_int(x, K));
-        term.scale = need;  // value c_i x carried at scale need
+    std::vector<Grp> pw(nb), term(d + 1);
+    auto set_need = [&](int i) { term[i].scale.assign(need.begin() + i * B, need.begin() + (i + 1) * B); };
+    const int low = x.level - 1 - nb;  // the deepest term's level
+    std::vector<double> sc(B, 0.0);
+    Grp y = g_new(B, low, 1, sc);
+    // y (+)= terms (their limbs up to y's level; Add: level min, scale max)
+    auto add = [&](const std::vector<Grp>& v, bool first) {
+        SumDesc D;
+        memset(&D, 0, sizeof D);
+        for (const Grp& t : v) {
+            D.in[D.n] = t.p;
+            D.in_ps[D.n] = t.ps;
+            ++D.n;
+            for (int m = 0; m < B; ++m) y.scale[m] = std::max(y.scale[m], t.scale[m]);
+        }
+        launch_sum_many(T, low + 1, 2 * B, D, y.p, y.ps, !first, stream);
+        cnt[C_ADD] += (int64_t)B * (D.n - (first ? 1 : 0));
+    };
+    if (direct && !pool.limit) {
+        std::vector<double> s0(x.scale);
+        for (auto& s : s0) s *= s;
+        for (int i = 0; i <= d; ++i) s0.insert(s0.end(), x.scale.begin(), x.scale.end());
+        Grp top = g_new((d + 2) * B, x.level, 1, s0);
+        Grp sq = top, mult = top;
+        sq.B = B;
+        mult.p = top.p + B * top.cs;
+        g_relin_into(g_tensor(x, x), sq);
+        g_mul_ints(x, K, mult);
+        auto v = g_views(g_rescale(top), B);
+        pw[0] = v[0];
+        for (int i = 0; i <= d; ++i) {
+            term[i] = v[1 + i];
+            set_need(i);
+        }
+        top = sq = mult = Grp();
+        for (int b = 0; b < nb; ++b) {
+            std::vector<Grp> l, r;
+            if (b + 1 < nb) {
+                l.push_back(pw[b]);
+                r.push_back(pw[b]);
+            }
+            for (int i = 0; i <= d; ++i)
+                if ((i >> b) & 1) {
+                    l.push_back(term[i]);
+                    r.push_back(pw[b]);
+                }
+            v = g_views(g_rescale(g_relin(g_tensor_each(l, r))), B);
+            size_t at = 0;
+            if (b + 1 < nb) pw[b + 1] = v[at++];
+            for (int i = 0; i <= d; ++i)
+                if ((i >> b) & 1) term[i] = v[at++];
+        }
+        add(term, true);
+        return y;
+    }
+    for (int b = 0; b < nb; ++b) pw[b] = b ? g_mul_rs(pw[b - 1], pw[b - 1]) : g_mul_rs(x, x);
+    for (int i = 0; i <= d; ++i) {
+        Grp xc = g_new(B, x.level, 1, x.scale);
+        g_mul_ints(x, std::vector<int64_t>(K.begin() + i * B, K.begin() + (i + 1) * B), xc);
+        term[i] = g_rescale(xc);
+        set_need(i);
         for (int b = 0; b < nb; ++b)
-            if ((i >> b) & 1) term = g_mul_rs(term, pw[b]);
-        if (!have) {
-            y = term;
-            have = true;
-        } else {
-            // Add: level min, scale max (Fig. 1)
-            const int l = std::min(y.level, term.level);
-            if (y.level != l) y = g_drop(y, l);
-            if (term.level != l) term = g_drop(term, l);
-            g_add_into(y, term);
-        }
+            if ((i >> b) & 1) term[i] = g_mul_rs(term[i], pw[b]);
+        add({term[i]}, i == 0);
+        term[i] = Grp();
     }
     return y;
 }
@@ -1329,14 +1381,13 @@ bool Ctx::sign_step(SignJob& J) {
             while ((1 << nb) <= J.d) ++nb;
             for (auto& t : target) t = (double)mods[J.cur.level - (nb + 1)];
         }
-        J.cur = g_eval_gd(J.cur, J.d, target);
+        J.cur = g_eval_gd(J.cur, J.d, target, J.direct);
         ++J.it;
         if (J.it < J.k || J.mode) return false;
     }
     if (J.mode) {  // ReLU: (x + x g) / 2; AppMax: ((a + b) + m g) / 2; the halving kept in the scale
         Grp r = g_mul_rs(J.x, J.cur);
-        Grp xd = g_drop(J.mode == 2 ? J.s : J.x, r.level);
-        g_add_into(r, xd);
+        g_add_into(r, J.mode == 2 ? J.s : J.x);
         for (auto& sc : r.scale) sc *= 2.0;
         J.cur = r;
     }
@@ -1352,17 +1403,22 @@ bool Ctx::sign_step(SignJob& J) {
 
 // Alg. 5 on groups (used by max pooling)
 Grp Ctx::g_appmax(const Grp& a, const Grp& b, int d, int k) {
-    SignJob J;
-    J.pre = J.keep = true;
-    J.ga = a;
-    J.gb = b;
-    J.d = d;
-    J.k = k;
-    J.mode = 2;
-    J.lvl = a.level;
-    while (!sign_step(J)) {
-    }
-    return J.out;
+    Grp out;
+    direct_call([&](bool direct) {
+        SignJob J;
+        J.pre = J.keep = true;
+        J.ga = a;
+        J.gb = b;
+        J.d = d;
+        J.k = k;
+        J.mode = 2;
+        J.lvl = a.level;
+        J.direct = direct;
+        while (!sign_step(J)) {
+        }
+        out = J.out;
+    });
+    return out;
 }
 
 // 2 x 2 max pooling of packed h x h matrices: AppMax over horizontal neighbours (rotation by
@@ -1413,16 +1469,21 @@ std::vector<CtPtr> Ctx::sign_group(const std::vector<const CtData*>& X, int d, i
         lvl = std::min(lvl, y->level);
     }
     if (lvl < k * (nb + 1) + (mode ? 1 : 0)) throw HeError(HE_ELEVEL);
-    SignJob J;
-    J.X = X;
-    J.Y = Y;
-    J.lvl = lvl;
-    J.d = d;
-    J.k = k;
-    J.mode = mode;
-    while (!sign_step(J)) {
-    }
-    return J.result;
+    std::vector<CtPtr> result;
+    direct_call([&](bool direct) {
+        SignJob J;
+        J.X = X;
+        J.Y = Y;
+        J.lvl = lvl;
+        J.d = d;
+        J.k = k;
+        J.mode = mode;
+        J.direct = direct;
+        while (!sign_step(J)) {
+        }
+        result = J.result;
+    });
+    return result;
 }
 
 CtPtr Ctx::matmul(const CtData& A, const CtData& B, int h) {

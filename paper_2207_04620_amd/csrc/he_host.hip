@@ -959,20 +959,16 @@ CtPtr Ctx::rotate(const CtData& a, int64_t k) {
 
 CtPtr Ctx::mul_int(const CtData& a, int64_t k) {
     const int nl = a.level + 1;
-    std::vector<u64> c(nl), cs(nl);
-    for (int i = 0; i < nl; ++i) {
-        const u64 q = mods[i];
-        const u64 r = k >= 0 ? (u64)k % q : (q - (u64)(-(k + 1)) % q - 1) % q;
-        c[i] = r;
-        cs[i] = shoup(r, q);
-    }
-    DBuf dc(this, 2 * (size_t)nl);
-    upload(this, dc.p, c.data(), nl * 8);
-    upload(this, dc.p + nl, cs.data(), nl * 8);
     CtPtr r = new_ct(a.level, a.deg, a.scale);
-    const int64_t ps = (int64_t)nl * N;
-    launch_mul_const(T, qmap(this), nl, a.deg + 1, r->buf->p, ps, a.buf->p, ps, dc.p, dc.p + nl, stream);
-    hip_check(hipStreamSynchronize(stream), "mul_int");
+    MulIntDesc D;
+    D.a = a.buf->p;
+    D.out = r->buf->p;
+    D.ps = (int64_t)nl * N;
+    D.a_cs = D.out_ks = 0;
+    D.n = D.nct = 1;
+    D.npoly = a.deg + 1;
+    D.k[0] = k;
+    launch_mul_ints(T, nl, D, stream);
     return r;
 }
 

@@ -132,6 +132,7 @@ struct SignJob {
     int lvl = 0, d = 3, k = 1, mode = 0, it = 0;
     bool started = false;
     bool pre = false, keep = false;  // inputs given as groups (ga, gb); result kept as a group
+    bool direct = false;             // a direct call's job (one pass per level of the polynomial)
     Grp ga, gb, out;
     Grp x, s, cur;
     std::vector<CtPtr> result;
@@ -364,13 +365,14 @@ struct Ctx {
     void g_tensor_sum(MatmulJob& J);
     void g_relin_sum(MatmulJob& J);
     Grp g_relin(const Grp& a);
+    void g_relin_into(const Grp& a, const Grp& out);
     Grp g_lintrans(const Grp& a, int kind, int h, int beta, int64_t unit, int dlo, int dhi, bool direct);
     std::vector<CtPtr> matmul_group(const std::vector<const CtData*>& A, const std::vector<const CtData*>& B,
                                     const MatShape& s, int lvl);
     bool matmul_step(MatmulJob& J, int k_chunk);
-    Grp g_mul_int(const Grp& a, const std::vector<int64_t>& k);
+    void g_mul_ints(const Grp& a, const std::vector<int64_t>& k, const Grp& out);
     Grp g_mul_rs(const Grp& x, const Grp& y);
-    Grp g_eval_gd(const Grp& x, int d, const std::vector<double>& target);
+    Grp g_eval_gd(const Grp& x, int d, const std::vector<double>& target, bool direct);
     bool sign_step(SignJob& J);
     std::vector<CtPtr> sign_group(const std::vector<const CtData*>& X, int d, int k, int mode,
                                   const std::vector<const CtData*>& Y = {});

@@ -2231,22 +2231,27 @@ void launch_ew(const DevTables& T, ModMap mm, int nl, int npoly, u64* out, int64
                        b_cs);
 }
 
-__global__ __launch_bounds__(TPB) void k_mul_const(DevTables T, ModMap mm, u64* out, int64_t out_ps,
-                                                   const u64* a, int64_t a_ps, const u64* c, const u64* c_sh) {
+// D.n integer multiples of one group in one read: out_k = a . K[k][member], the constants reduced here
+// (tables of residues cost a copy to the device and a wait for it per multiple)
+__global__ __launch_bounds__(TPB) void k_mul_ints(DevTables T, MulIntDesc D) {
     const int N = 1 << T.log_n;
     const int i = blockIdx.x * TPB + threadIdx.x;
-    const int l = blockIdx.y, p = blockIdx.z;
-    const u64 q = T.mods[mm(l)].q;
-    const int64_t o = (int64_t)l * N + i;
-    out[p * out_ps + o] = mul_shoup(a[p * a_ps + o], c[l], c_sh[l], q);
+    const int l = blockIdx.y, p = blockIdx.z % D.npoly, c = blockIdx.z / D.npoly;
+    const ModP m = T.mods[l];
+    const int64_t o = p * D.ps + (int64_t)l * N + i;
+    const u64 x = D.a[c * D.a_cs + o];
+    for (int k = 0; k < D.n; ++k) {
+        const int64_t v = D.k[k * D.nct + c];
+        const u64 r = v >= 0 ? reduce64((u64)v, m) : m.q - 1 - reduce64(~(u64)v, m);
+        D.out[k * D.out_ks + c * D.a_cs + o] = mul_mont(x, to_mont(r, m), m.q, m.qninv);
+    }
 }
 
-void launch_mul_const(const DevTables& T, ModMap mm, int nl, int npoly, u64* out, int64_t out_ps, const u64* a,
-                      int64_t a_ps, const u64* c, const u64* c_sh, hipStream_t st) {
-    ProfScope prof_(PK_EW, 2.0 * nl * npoly * 8.0 * (1 << T.log_n), st);
-    const int N = 1 << T.log_n;
-    dim3 grid(ceil_div(N, TPB), nl, npoly);
-    HE_LAUNCH(k_mul_const, grid, dim3(TPB), 0, st, T, mm, out, out_ps, a, a_ps, c, c_sh);
+void launch_mul_ints(const DevTables& T, int nl, const MulIntDesc& D, hipStream_t st) {
+    if (D.n < 1 || D.nct < 1 || D.n * D.nct > MI_MAX) throw std::runtime_error("integer multiples: out of range");
+    ProfScope prof_(PK_EW, (1.0 + D.n) * nl * D.npoly * D.nct * 8.0 * (1 << T.log_n), st);
+    dim3 grid(ceil_div(1 << T.log_n, TPB), nl, D.npoly * D.nct);
+    HE_LAUNCH(k_mul_ints, grid, dim3(TPB), 0, st, T, D);
 }
 
 // position j of the bit-reversed evaluation layout holds a(psi^(2 brev(j) + 1)); sigma_g

@@ -357,8 +357,16 @@ void launch_ew(const DevTables& T, ModMap mm, int nl, int npoly, u64* out, int64
                int64_t a_ps, const u64* b, int64_t b_ps, int op, hipStream_t st, int nct = 1, int64_t out_cs = 0,
                int64_t a_cs = 0, int64_t b_cs = 0);
 // out[p][i] = a[p][i] * c_i (Shoup constants in device arrays c, c_sh indexed by limb)
-void launch_mul_const(const DevTables& T, ModMap mm, int nl, int npoly, u64* out, int64_t out_ps, const u64* a,
-                      int64_t a_ps, const u64* c, const u64* c_sh, hipStream_t st);
+// out_k[c] = K[k nct + c] a[c] for npoly polynomials of nct members (member stride a_cs in both)
+#define MI_MAX 256
+struct MulIntDesc {
+    const u64* a;
+    u64* out;
+    int64_t ps, a_cs, out_ks;
+    int n, nct, npoly;
+    int64_t k[MI_MAX];
+};
+void launch_mul_ints(const DevTables& T, int nl, const MulIntDesc& D, hipStream_t st);
 // evaluation-domain automorphism: out[p][i][j] = in[p][i][perm_g(j)]
 void launch_automorph(const DevTables& T, int nl, int npoly, u64* out, int64_t out_ps, const u64* in,
                       int64_t in_ps, u64 g, hipStream_t st, int nct = 1, int64_t out_cs = 0, int64_t in_cs = 0);

@@ -38,3 +38,30 @@ def test_default_equals_every_setting(schedule, members):
         got, again = product()
         assert again == counts and all(np.array_equal(x, y) for x, y in zip(got, ref)), sets
     ctx.close()
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("d", [1, 2, 3, 4, 6, 7])
+@pytest.mark.parametrize("members", [1, 3, 33])
+def test_polynomial_levels_equal_terms(d, mode, members):
+    """a level of g_d in one pass against term by term (under a cap): limbs, scales and counts"""
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2207_04620_amd import he
+    ctx = he.Context(I.small(log_n=12, n_q=10, alpha=2, q_bits=40, p_bits=50))
+    xs = [ctx.encrypt(I.sign_inputs(7 + i, 1, 16)[0].ravel(), nonce=i) for i in range(members)]
+
+    def evaluate():
+        ctx.counters(reset=True)
+        ys = ctx.sign_approx_batch(xs, d, 2, mode)
+        return [(ctx.export(y), y.scale, y.level) for y in ys], ctx.counters()
+
+    ref, counts = evaluate()
+    in_use, _ = ctx.pool_stats()
+    ctx.pool_limit(in_use + (1 << 31))
+    got, again = evaluate()
+    ctx.pool_limit(0)
+    assert again == counts
+    for (x, s, l), (y, t, m) in zip(got, ref):
+        assert np.array_equal(x, y) and s == t and l == m
+    ctx.close()
