@@ -209,7 +209,15 @@ struct Ctx {
         ev_join = e2;
         return true;
     }
+    // pinned slots of read_back (made by the first large one; the call holds api_mu)
+    static constexpr size_t STAGE_SLOT = 512 << 10;
+    static constexpr int STAGE_SLOTS = 8;
+    char* stage = nullptr;
+    hipEvent_t stage_ev[STAGE_SLOTS] = {};
+    void read_back(void* dst, const void* src, size_t bytes);
+    void free_stage();
     ~Ctx() {
+        free_stage();
         if (side) (void)hipStreamSynchronize(side);
         if (side) (void)hipStreamDestroy(side);
         if (ev_fork) (void)hipEventDestroy(ev_fork);

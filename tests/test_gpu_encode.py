@@ -75,3 +75,28 @@ def test_decrypt_matches_oracle(log_n, level):
                 f(g.import_(bad, level, 1.0))
             assert e.value.name == "HE_ESCALE"
     g.close()
+
+
+@pytest.mark.parametrize("log_n", [12, 15])
+def test_export_of_every_size_and_alignment(log_n):
+    """64 KiB to 6.5 MB through the pinned slots: every level is the prefix of the whole, into buffers at
+    any 8-byte offset, and nothing beside the buffer is written"""
+    import ctypes
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2207_04620_amd import he
+    ctx = he.Context(I.small(log_n=log_n, n_q=13, alpha=4, q_bits=45, p_bits=60))
+    ct = ctx.encrypt(np.linspace(-1, 1, 64), nonce=5)
+    whole = ctx.export(ct)
+    back = ctx.import_(whole, ct.level, ct.scale)
+    assert np.array_equal(ctx.decrypt(back, 64), ctx.decrypt(ct, 64))
+    for level in range(13):
+        low = ctx.drop(ct, level)
+        size = 2 * (level + 1) << log_n
+        for offset in (1, 255, 512):
+            buf = np.full(offset + size + 3, 7, np.uint64)
+            out = buf[offset:offset + size]
+            assert he.lib().he_ct_export(ctx.ptr, low.ptr, out.ctypes.data_as(ctypes.POINTER(ctypes.c_uint64)), size) == 0
+            assert np.array_equal(out.reshape(2, level + 1, -1), whole[:, :level + 1])
+            assert (buf[:offset] == 7).all() and (buf[offset + size:] == 7).all()
+    ctx.close()
