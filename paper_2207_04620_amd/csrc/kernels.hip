@@ -215,7 +215,7 @@ __device__ __forceinline__ void inv_round(u64* s, int L, int s0, int logT, u64 X
     constexpr int G = 1 << R, NG = 8 / G;
     // the round covers stages s0-R+1 .. s0; its smallest distance belongs to stage s0
     const int ld = L - s0 - 1, d = 1 << ld, T = 1 << logT;
-    const u64 q2 = 2 * q;
+    const u64 q4 = 4 * q;
 #pragma unroll
     for (int gg = 0; gg < NG; ++gg) {
         const int g = gg * TPB + threadIdx.x;
@@ -234,8 +234,8 @@ __device__ __forceinline__ void inv_round(u64* s, int L, int s0, int logT, u64 X
 #pragma unroll
                 for (int k = b * 2 * half; k < b * 2 * half + half; ++k) {
                     const u64 U = x[k], V = x[k + half];
-                    x[k] = red4(U + V, q2);
-                    x[k + half] = mul_shoup_lazy(U - V + q2, w, ws, q);
+                    x[k] = red4(U + V, q4);
+                    x[k + half] = mul_shoup_lazy(U - V + q4, w, ws, q);
                 }
             }
         }
@@ -291,11 +291,12 @@ __device__ __forceinline__ void inv_all(u64* s, int L, int logT, u64 X, const u6
 // measured 0.54 conflict cycles per LDS cycle in the forward pass and 0.35 in the inverse).
 __host__ __device__ constexpr int row_at(int a) { return a + ((a >> 5) << 2); }
 #define ROW_LDS (NTT_E + NTT_E / 8)
-// butterflies of one forward group of 2^R elements in registers, twiddle pairs at t
+// butterflies of one forward group of 2^R <= 8 elements in registers, twiddle pairs at t: below 16q in,
+// below (4R + 3) q out
 template <int R>
-__device__ __forceinline__ void fwd_group(u64 (&x)[1 << R], const u64* __restrict__ t, u64 q) {
+__device__ __forceinline__ void fwd_group(u64 (&x)[1 << R], const u64* __restrict__ t, const Lean& m) {
     constexpr int G = 1 << R;
-    const u64 q2 = 2 * q;
+    const u64 q4 = 4 * m.q;
     u64x2 w[G - 1];
 #pragma unroll
     for (int i = 0; i < G - 1; ++i) w[i] = ld2(t + 2 * i);
@@ -307,22 +308,26 @@ __device__ __forceinline__ void fwd_group(u64 (&x)[1 << R], const u64* __restric
             const u64x2 wb = w[(1 << r) - 1 + b];
 #pragma unroll
             for (int k = b * 2 * half; k < b * 2 * half + half; ++k) {
-                const u64 U = red4(x[k], q2);
-                const u64 V = mul_shoup_lazy(x[k + half], wb.x, wb.y, q);
-                x[k] = U + V;
-                x[k + half] = U - V + q2;
+                const u64 U = r ? x[k] : red16(x[k], m);
+                x[k] = mul_lean(U, x[k + half], wb.x, wb.y, m.nq);
+                x[k + half] = 2 * U + q4 - x[k];
             }
         }
     }
 }
 
+// below 4q in and out.  An element's bound before stage r is 4q, doubled for each earlier stage in
+// which it was the sum: 16q for the last pair of sums, which are reduced first
 template <int R>
-__device__ __forceinline__ void inv_group(u64 (&x)[1 << R], const u64* __restrict__ t, u64 q) {
+__device__ __forceinline__ void inv_group(u64 (&x)[1 << R], const u64* __restrict__ t, const Lean& m) {
     constexpr int G = 1 << R;
-    const u64 q2 = 2 * q;
+    static_assert(R <= 3, "bounds");
     u64x2 w[G - 1];
 #pragma unroll
     for (int i = 0; i < G - 1; ++i) w[i] = ld2(t + 2 * i);
+    int b4[G];  // bounds in units of 4q
+#pragma unroll
+    for (int i = 0; i < G; ++i) b4[i] = 1;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int half = 1 << r;
@@ -331,16 +336,26 @@ __device__ __forceinline__ void inv_group(u64 (&x)[1 << R], const u64* __restric
             const u64x2 wb = w[G - (G >> r) + b];
 #pragma unroll
             for (int k = b * 2 * half; k < b * 2 * half + half; ++k) {
+                if (b4[k] == 4) {
+                    x[k] = red16(x[k], m);
+                    x[k + half] = red16(x[k + half], m);
+                    b4[k] = 1;
+                }
                 const u64 U = x[k], V = x[k + half];
-                x[k] = red4(U + V, q2);
-                x[k + half] = mul_shoup_lazy(U - V + q2, wb.x, wb.y, q);
+                x[k] = U + V;
+                x[k + half] = mul_lean(0, U + 4 * b4[k] * m.q - V, wb.x, wb.y, m.nq);
+                b4[k] *= 2;
+                b4[k + half] = 1;
             }
         }
     }
+#pragma unroll
+    for (int k = 0; k < G; ++k)
+        if (b4[k] > 1) x[k] = red16(x[k], m);
 }
 
 template <int R, int S0>
-__device__ __forceinline__ void fwd_row_round(u64* s, const u64* __restrict__ tw, int off, u64 q) {
+__device__ __forceinline__ void fwd_row_round(u64* s, const u64* __restrict__ tw, int off, const Lean& q) {
     constexpr int G = 1 << R, NG = 8 / G, LD = 11 - S0 - R, D = 1 << LD;
 #pragma unroll
     for (int gg = 0; gg < NG; ++gg) {
@@ -358,7 +373,7 @@ __device__ __forceinline__ void fwd_row_round(u64* s, const u64* __restrict__ tw
 }
 
 template <int R, int S0>
-__device__ __forceinline__ void inv_row_round(u64* s, const u64* __restrict__ tw, int off, u64 q) {
+__device__ __forceinline__ void inv_row_round(u64* s, const u64* __restrict__ tw, int off, const Lean& q) {
     constexpr int G = 1 << R, NG = 8 / G, LD = 11 - S0 - 1, D = 1 << LD;
 #pragma unroll
     for (int gg = 0; gg < NG; ++gg) {
@@ -384,7 +399,7 @@ __device__ __forceinline__ void inv_row_round(u64* s, const u64* __restrict__ tw
 // after_first() runs once the first round's results are in LDS: the lane's registers of the
 // first round are free there, so the caller can start its epilogue loads early
 template <class F>
-__device__ __forceinline__ void fwd_rows_2048(u64* s, const u64* tw, u64 q, u64 (&x)[8], u64 (&y)[8],
+__device__ __forceinline__ void fwd_rows_2048(u64* s, const u64* tw, const Lean& q, u64 (&x)[8], u64 (&y)[8],
                                               F&& after_first) {
     const int tid = threadIdx.x;
     fwd_group<3>(x, tw, q);
@@ -409,7 +424,7 @@ __device__ __forceinline__ void fwd_rows_2048(u64* s, const u64* tw, u64 q, u64 
     }
 }
 
-__device__ __forceinline__ void inv_rows_2048(u64* s, const u64* tw, u64 q, u64 (&x)[8], u64 (&y)[8]) {
+__device__ __forceinline__ void inv_rows_2048(u64* s, const u64* tw, const Lean& q, u64 (&x)[8], u64 (&y)[8]) {
     const int tid = threadIdx.x;
     inv_group<3>(x, tw + 2 * 7 * tid, q);
     u64* sb = s + row_at(8 * tid);
@@ -476,7 +491,7 @@ template <int R, int S0, int L1>
 __device__ __forceinline__ void inv_col_round(u64* s, const u64* __restrict__ W, const u64* __restrict__ Ws,
                                               u64 q) {
     constexpr int G = 1 << R, NG = 8 / G, LD = L1 - S0 - 1, D = 1 << LD, LOGT = 11 - L1, TC = 1 << LOGT;
-    const u64 q2 = 2 * q;
+    const u64 q4 = 4 * q;
 #pragma unroll
     for (int gg = 0; gg < NG; ++gg) {
         const int g = gg * TPB + threadIdx.x;
@@ -497,8 +512,8 @@ __device__ __forceinline__ void inv_col_round(u64* s, const u64* __restrict__ W,
 #pragma unroll
                 for (int k = b * 2 * half; k < b * 2 * half + half; ++k) {
                     const u64 U = x[k], V = x[k + half];
-                    x[k] = red4(U + V, q2);
-                    x[k + half] = mul_shoup_lazy(U - V + q2, w, ws, q);
+                    x[k] = red4(U + V, q4);
+                    x[k + half] = mul_shoup_lazy(U - V + q4, w, ws, q);
                 }
             }
         }
@@ -897,9 +912,10 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(EPI ? 6 : 7
     const u64 q = T.mods[mi].q, q2 = 2 * q;
     const bool fp = fp64_limb(q, L1, N2), full = N2 == NTT_E;
     // 2048-element rows: the last round's elements 4 g + k (g = tid, 256 + tid), as raw doubles (FP64
-    // path) or words lazy in [0, 4q) (integer path)
+    // path) or words lazy in [0, 11q) (integer path)
     u64 y[8];
     const double qd = (double)q, qinv = T.mods[mi].qinv;
+    const Lean ln = lean_of(q, T.mods[mi].bar);
     // the ModDown epilogue's u words of those elements, loaded while the middle rounds run
     u64x2 uu[4];
     const u64* u = nullptr;
@@ -927,7 +943,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(EPI ? 6 : 7
         u64 x[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) x[i] = a[tid + TPB * i];
-        fwd_rows_2048(s, T.rtw + ((int64_t)mi * N1 + r) * (2 * ROW_TW), q, x, y, prefetch_u);
+        fwd_rows_2048(s, T.rtw + ((int64_t)mi * N1 + r) * (2 * ROW_TW), ln, x, y, prefetch_u);
     } else {  // small rings (N < 2048): the row through LDS, plain radix-2 stages
         const u64* W = T.psi + (int64_t)mi * N;
         const u64* Ws = T.psi_sh + (int64_t)mi * N;
@@ -951,7 +967,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(EPI ? 6 : 7
             __syncthreads();
         }
     }
-    // emit(i, e, v0, v1): elements e, e + 1 of the row (words below 4q, or the bits of raw doubles on
+    // emit(i, e, v0, v1): elements e, e + 1 of the row (words below 11q, or the bits of raw doubles on
     // the FP64 path) to their destination; i is the pair's slot in uu (2048-element rows), or -1
     auto for_pairs = [&](auto&& emit) {
         if (fp || full) {
@@ -967,8 +983,8 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(EPI ? 6 : 7
                 v0 = canon_d(bits_d(v0), qd, qinv);
                 v1 = canon_d(bits_d(v1), qd, qinv);
             } else {
-                v0 = red4(v0, q2);
-                v1 = red4(v1, q2);
+                v0 = red4(red16(v0, ln), q2);
+                v1 = red4(red16(v1, ln), q2);
                 v0 = v0 >= q ? v0 - q : v0;
                 v1 = v1 >= q ? v1 - q : v1;
             }
@@ -994,10 +1010,10 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(EPI ? 6 : 7
             w[0] = signed_word_d(mulmod_d(u2d(uw.x) - bits_d(v0), pd, qd, qinv), qd);
             w[1] = signed_word_d(mulmod_d(u2d(uw.y) - bits_d(v1), pd, qd, qinv), qd);
         } else {
-            // v is below 4q and u < q, so u + 4q - v lies in (0, 5q); the Shoup product
+            // v is below 11q and u < q, so u + 12q - v lies in (0, 13q); the Shoup product
             // reduces any 64-bit operand to [0, q)
-            w[0] = mul_shoup(uw.x + 2 * q2 - v0, pi, pis, q);
-            w[1] = mul_shoup(uw.y + 2 * q2 - v1, pi, pis, q);
+            w[0] = mul_shoup(uw.x + 6 * q2 - v0, pi, pis, q);
+            w[1] = mul_shoup(uw.y + 6 * q2 - v1, pi, pis, q);
         }
         if (add) {
             const u64x2 ad = ld2(add + i);
@@ -1069,7 +1085,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(8))) void k
             x[2 * i] = v.x;
             x[2 * i + 1] = v.y;
         }
-        inv_rows_2048(s, T.irtw + ((int64_t)mi * N1 + r) * (2 * ROW_TW), q, x, y);
+        inv_rows_2048(s, T.irtw + ((int64_t)mi * N1 + r) * (2 * ROW_TW), lean_of(q, mp_.bar), x, y);
         if (L1 == 0) {
             const u64 f = scale ? scale[2 * (k % scale_n)] : mp_.ninv;
             const u64 fs = scale ? scale[2 * (k % scale_n) + 1] : mp_.ninv_sh;
@@ -1079,7 +1095,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(8))) void k
                 if (scale) w = w > mp_.half ? w - q : w;
                 a[(i >> 2) * TPB + tid + 512 * (i & 3)] = w;
             }
-        } else {  // lazy in [0, 2q)
+        } else {  // lazy in [0, 4q)
 #pragma unroll
             for (int i = 0; i < 8; ++i) a[(i >> 2) * TPB + tid + 512 * (i & 3)] = y[i];
         }
@@ -1333,9 +1349,13 @@ __device__ __forceinline__ void fwd_col_regs_d(double (&x)[1 << L1], const u64x2
         }
     }
 }
+// integer columns: below 4q in, below 16q out; the bound of the elements that were sums in every
+// stage so far doubles from stage to stage, and they are reduced where it would pass 16q
 template <int L1>
-__device__ __forceinline__ void inv_col_regs(u64 (&x)[1 << L1], const u64x2* W, u64 q) {
-    const u64 q2 = 2 * q;
+__device__ __forceinline__ void inv_col_regs(u64 (&x)[1 << L1], const u64x2* W, const Lean& m) {
+    int b4[1 << L1];
+#pragma unroll
+    for (int j = 0; j < (1 << L1); ++j) b4[j] = 1;
 #pragma unroll
     for (int st = L1 - 1; st >= 0; --st) {
         stage_fence();
@@ -1345,29 +1365,38 @@ __device__ __forceinline__ void inv_col_regs(u64 (&x)[1 << L1], const u64x2* W, 
             const u64x2 w = W[(1 << st) + i];
 #pragma unroll
             for (int j = i * 2 * d; j < i * 2 * d + d; ++j) {
+                if (b4[j] == 4) {
+                    x[j] = red16(x[j], m);
+                    x[j + d] = red16(x[j + d], m);
+                    b4[j] = 1;
+                }
                 const u64 U = x[j], V = x[j + d];
-                x[j] = red4(U + V, q2);
-                x[j + d] = mul_shoup_lazy(U - V + q2, w.x, w.y, q);
+                x[j] = U + V;
+                x[j + d] = mul_lean(0, U + 4 * b4[j] * m.q - V, w.x, w.y, m.nq);
+                b4[j] *= 2;
+                b4[j + d] = 1;
             }
         }
     }
 }
+// below 6q in, below 16q out: 4q more per stage
 template <int L1>
-__device__ __forceinline__ void fwd_col_regs(u64 (&x)[1 << L1], const u64x2* W, u64 q) {
-    const u64 q2 = 2 * q;
+__device__ __forceinline__ void fwd_col_regs(u64 (&x)[1 << L1], const u64x2* W, const Lean& m) {
+    int bound = 6;
 #pragma unroll
     for (int st = 0; st < L1; ++st) {
         stage_fence();
         const int d = (1 << L1) >> (st + 1);
+        const bool red = bound + 4 > 16;
+        bound = (red ? 3 : bound) + 4;
 #pragma unroll
         for (int i = 0; i < (1 << st); ++i) {
             const u64x2 w = W[(1 << st) + i];
 #pragma unroll
             for (int j = i * 2 * d; j < i * 2 * d + d; ++j) {
-                const u64 U = red4(x[j], q2);
-                const u64 V = mul_shoup_lazy(x[j + d], w.x, w.y, q);
-                x[j] = U + V;
-                x[j + d] = U - V + q2;
+                const u64 U = red ? red16(x[j], m) : x[j];
+                x[j] = mul_lean(U, x[j + d], w.x, w.y, m.nq);
+                x[j + d] = 2 * U + 4 * m.q - x[j];
             }
         }
     }
@@ -1458,10 +1487,10 @@ __device__ __forceinline__ void fwd_col_split_d(double (&x)[(1 << L1) / SP], con
     }
 }
 template <int L1, int SP>
-__device__ __forceinline__ void inv_col_split(u64 (&x)[(1 << L1) / SP], const u64x2* W, int grp, u64 q) {
+__device__ __forceinline__ void inv_col_split(u64 (&x)[(1 << L1) / SP], const u64x2* W, int grp, const Lean& m) {
     constexpr int M = (1 << L1) / SP;
     const int v = grp & (SP - 1);
-    const u64 q2 = 2 * q;
+    const u64 q4 = 4 * m.q;
 #pragma unroll
     for (int st = L1 - 1; st >= 0; --st) {
         stage_fence();
@@ -1472,7 +1501,7 @@ __device__ __forceinline__ void inv_col_split(u64 (&x)[(1 << L1) / SP], const u6
             for (int j = 0; j < M; ++j) {
                 const u64x2 w = W[cross_twiddle<SP>(st, d, j, v)];
                 const u64 o = lane_xor_u(x[j], grp, d);
-                x[j] = mul_shoup_lazy(o + (up ? q2 - x[j] : x[j]), w.x, w.y, q);
+                x[j] = mul_lean(0, o + (up ? q4 - x[j] : x[j]), w.x, w.y, m.nq);
             }
         } else {
             const int dj = d / SP;
@@ -1482,18 +1511,19 @@ __device__ __forceinline__ void inv_col_split(u64 (&x)[(1 << L1) / SP], const u6
 #pragma unroll
                 for (int j = i * 2 * dj; j < i * 2 * dj + dj; ++j) {
                     const u64 U = x[j], V = x[j + dj];
-                    x[j] = red4(U + V, q2);
-                    x[j + dj] = mul_shoup_lazy(U - V + q2, w.x, w.y, q);
+                    x[j] = red4(U + V, q4);
+                    x[j + dj] = mul_lean(0, U - V + q4, w.x, w.y, m.nq);
                 }
             }
         }
     }
 }
 template <int L1, int SP>
-__device__ __forceinline__ void fwd_col_split(u64 (&x)[(1 << L1) / SP], const u64x2* W, int grp, u64 q) {
+__device__ __forceinline__ void fwd_col_split(u64 (&x)[(1 << L1) / SP], const u64x2* W, int grp, const Lean& m) {
     constexpr int M = (1 << L1) / SP;
     const int v = grp & (SP - 1);
-    const u64 q2 = 2 * q;
+    const u64 q4 = 4 * m.q;
+    int bound = 6;
 #pragma unroll
     for (int st = 0; st < L1; ++st) {
         stage_fence();
@@ -1503,20 +1533,21 @@ __device__ __forceinline__ void fwd_col_split(u64 (&x)[(1 << L1) / SP], const u6
 #pragma unroll
             for (int j = 0; j < M; ++j) {
                 const u64x2 w = W[cross_twiddle<SP>(st, d, j, v)];
-                const u64 t = mul_shoup_lazy(x[j], w.x, w.y, q);
-                x[j] = lane_xor_u(t, grp, d) + (up ? q2 - t : t);
+                const u64 t = mul_lean(0, x[j], w.x, w.y, m.nq);
+                x[j] = lane_xor_u(t, grp, d) + (up ? q4 - t : t);
             }
         } else {
             const int dj = d / SP;
+            const bool red = bound + 4 > 16;
+            bound = (red ? 3 : bound) + 4;
 #pragma unroll
             for (int i = 0; i < (1 << st); ++i) {
                 const u64x2 w = W[(1 << st) + i];
 #pragma unroll
                 for (int j = i * 2 * dj; j < i * 2 * dj + dj; ++j) {
-                    const u64 U = red4(x[j], q2);
-                    const u64 V = mul_shoup_lazy(x[j + dj], w.x, w.y, q);
-                    x[j] = U + V;
-                    x[j + dj] = U - V + q2;
+                    const u64 U = red ? red16(x[j], m) : x[j];
+                    x[j] = mul_lean(U, x[j + dj], w.x, w.y, m.nq);
+                    x[j + dj] = 2 * U + q4 - x[j];
                 }
             }
         }
@@ -1548,13 +1579,13 @@ __device__ __forceinline__ double digits_mod_d(i32x4 lo, i32x4 hi, double q, dou
     if (small) x = red_d(x, q, qinv);
     return x;
 }
-// sum_{e<8} a_e 2^(8e) mod q in [0, 4q) for an integer target (q > 2^46): V = H 2^32 + L with
-// |H|, |L| < 2^45; (H + 2^45) 2^32 by one lazy Shoup product (< 2q), L and the constant c = -2^77 mod
+// sum_{e<8} a_e 2^(8e) mod q in [0, 6q) for an integer target (q > 2^46): V = H 2^32 + L with
+// |H|, |L| < 2^45; (H + 2^45) 2^32 by one lazy product (< 4q), L and the constant c = -2^77 mod
 // q (taken in [2^45, q + 2^45)) added
-__device__ __forceinline__ u64 digits_mod(i32x4 lo, i32x4 hi, u64 q, u64 w, u64 w_sh, u64 c) {
+__device__ __forceinline__ u64 digits_mod(i32x4 lo, i32x4 hi, u64 nq, u64 w, u64 w_sh, u64 c) {
     const int64_t L = (int64_t)(lo.x + (lo.y << 8)) + ((int64_t)(lo.z + (lo.w << 8)) << 16);
     const int64_t H = (int64_t)(hi.x + (hi.y << 8)) + ((int64_t)(hi.z + (hi.w << 8)) << 16);
-    return mul_shoup_lazy((u64)(H + (1ll << 45)), w, w_sh, q) + (u64)L + c;
+    return mul_lean((u64)L + c, (u64)(H + (1ll << 45)), w, w_sh, nq);
 }
 
 // f(0), ..., f(N - 1) with compile-time arguments (the unroller gives up on 32 rows)
@@ -1593,8 +1624,9 @@ __device__ __forceinline__ void conv_source(u64 (&b)[(1 << L1) / SP], const ModP
     } else {
         u64 x[M];
         unrolled<M>([&](auto j) { x[j] = *lane_at<u64>(src + j * (SP * N2), so); });
-        if constexpr (SP == 1) inv_col_regs<L1>(x, W, q);
-        else inv_col_split<L1, SP>(x, W, grp, q);
+        const Lean ln = lean_of(q, m.bar);
+        if constexpr (SP == 1) inv_col_regs<L1>(x, W, ln);
+        else inv_col_split<L1, SP>(x, W, grp, ln);
         unrolled<M>([&](auto j) {
             if (j % 2 == 0) stage_fence();
             const u64 y = mul_shoup(x[j], f, fs, q);
@@ -1721,8 +1753,9 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(conv_waves(
                     unrolled<M>([&](auto j) { *lane_at<u64>(dst + j * (4 * N2), od) = d_bits(x[j]); });
                 } else {
                     u64 x[M];
-                    unrolled<M>([&](auto j) { x[j] = digits_mod(lo[j], hi[j], q, S.w32[gv], S.w32_sh[gv], S.off[gv]); });
-                    fwd_col_split<L1, 4>(x, W, gv, q);
+                    const Lean ln = lean_of(q, T.mods[S.dmod[gv]].bar);
+                    unrolled<M>([&](auto j) { x[j] = digits_mod(lo[j], hi[j], ln.nq, S.w32[gv], S.w32_sh[gv], S.off[gv]); });
+                    fwd_col_split<L1, 4>(x, W, gv, ln);
                     unrolled<M>([&](auto j) { *lane_at<u64>(dst + j * (4 * N2), od) = x[j]; });
                 }
             }
@@ -1743,17 +1776,18 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(conv_waves(
             const uint32_t od = ((uint32_t)S.doff[gv] * N + col) * 8u;
             if (gv < S.nt) unrolled<N1>([&](auto r) { *lane_at<u64>(dst + r * N2, od) = d_bits(x[r]); });
         } else {
-            const u64 q = T.mods[S.dmod[gv]].q, w32 = S.w32[gv], w32s = S.w32_sh[gv], cc = S.off[gv];
+            const Lean ln = lean_of(T.mods[S.dmod[gv]].q, T.mods[S.dmod[gv]].bar);
+            const u64 w32 = S.w32[gv], w32s = S.w32_sh[gv], cc = S.off[gv];
             u64 x[N1];
             unrolled<N1>([&](auto r) {
                 if (XS > 1 || r % 2 == 0) stage_fence();
                 u64 b[KS];
                 operand(r, b);
-                x[r] = digits_mod(mfma_bytes<KS>(a0, b, i32x4{0, 0, 0, 0}), mfma_bytes<KS>(a1, b, i32x4{0, 0, 0, 0}), q, w32,
-                                  w32s, cc);
+                x[r] = digits_mod(mfma_bytes<KS>(a0, b, i32x4{0, 0, 0, 0}), mfma_bytes<KS>(a1, b, i32x4{0, 0, 0, 0}), ln.nq,
+                                  w32, w32s, cc);
                 keep_here(x[r]);
             });
-            fwd_col_regs<L1>(x, W, q);
+            fwd_col_regs<L1>(x, W, ln);
             unrolled<N1>([&](auto r) { keep_here(x[r]); });
             const uint32_t od = ((uint32_t)S.doff[gv] * N + col) * 8u;
             if (gv < S.nt) unrolled<N1>([&](auto r) { *lane_at<u64>(dst + r * N2, od) = x[r]; });

@@ -44,6 +44,29 @@ __device__ __forceinline__ u64 mul_shoup_lazy(u64 a, u64 w, u64 w_sh, u64 q) {
     return a * w - qh * q;
 }
 
+// Butterflies of primes too wide for FP64 (q < 2^60), lazy below 16 q.  Every instruction of a product
+// costs the same here (v_mul_hi_u32, v_mad_u64_u32 and v_mul_lo_u32 issue at the full rate, 4.3 cycles a
+// wave), a 64-bit compare and select as much as four of them (18).  So the quotient drops its low
+// partial product (50 cycles a product, 58 with it), and values are reduced only where 16 q is near.
+struct Lean {
+    u64 q, nq;   // the prime, -q mod 2^64
+    u32 c, sh;   // red16's quotient: floor(2^(32 + sh) / q) and sh = max(bits(q) - 28, 0)
+};
+__device__ __forceinline__ Lean lean_of(u64 q, u64 bar) {
+    const int sh = 36 - __builtin_clzll(q) > 0 ? 36 - __builtin_clzll(q) : 0;
+    return {q, 0 - q, (u32)(bar >> (32 - sh)), (u32)sh};
+}
+// u + a w mod q in [u, u + 4q), any a < 2^64: the three partial products above 2^32 give the Shoup quotient or
+// up to two less
+__device__ __forceinline__ u64 mul_lean(u64 u, u64 a, u64 w, u64 w_sh, u64 nq) {
+    const u32 a0 = (u32)a, a1 = (u32)(a >> 32), s0 = (u32)w_sh, s1 = (u32)(w_sh >> 32);
+    const u64 h = (u64)a1 * s1 + __umulhi(a1, s0) + __umulhi(a0, s1);
+    return u + a * w + h * nq;
+}
+// x mod q in [0, 3q) for x < 16 q: x >> sh is below 2^32, so the quotient is short by less than 1 for
+// the truncated constant, less than 1 for its own truncation and 2^-27 for x's
+__device__ __forceinline__ u64 red16(u64 x, const Lean& m) { return x + (u64)__umulhi((u32)(x >> m.sh), m.c) * m.nq; }
+
 // (hi 2^64 + lo) R^-1 mod q for hi 2^64 + lo < q 2^64
 __device__ __forceinline__ u64 redc(u64 lo, u64 hi, u64 q, u64 qninv) {
     u64 m = lo * qninv;
