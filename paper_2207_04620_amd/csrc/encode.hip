@@ -185,7 +185,7 @@ __global__ __launch_bounds__(TPB) void k_lift_centred(DevTables T, int nl, const
     const ModP m0 = T.mods[0];
     const u64 x0 = m[i];
     if (nl == 1) {
-        out[i] = to_double(x0 > m0.half ? (i128)x0 - (i128)m0.q : (i128)x0);
+        out[i] = to_double(x0 > (m0.q >> 1) ? (i128)x0 - (i128)m0.q : (i128)x0);
         return;
     }
     // x0 + q0 ((x1 - x0) q0^-1 mod q1), centred modulo q0 q1

@@ -277,7 +277,7 @@ void Ctx::ip_into(u64* u, const u64* lift, const u64* own, int64_t own_cs, int B
     D.c0 = c0;
     D.c0_cs = c0_cs;
     D.nq = nl;
-    for (int t = 0; t < nl; ++t) D.pmont[t] = pmod_mont[t];
+    for (int t = 0; t < nl; ++t) D.pkey[t] = pmod_key[t];
     D.own = own;
     D.own_cs = own_cs;
     for (int j = 0; j < beta; ++j) {

@@ -209,7 +209,9 @@ void Ctx::build_tables() {
         e.bar = ~0ull / q;
         e.ninv = invmod((u64)N % q, q);
         e.ninv_sh = shoup(e.ninv, q);
-        e.half = (q - 1) / 2;
+        const int bits = 64 - __builtin_clzll(q);
+        e.sh = (u32)(bits - 16);
+        e.c = (u32)(((unsigned __int128)1 << (bits + 16)) / q);
         e.qinv = 1.0 / (double)q;
         // psi^(bitrev k)
         std::vector<u64> pw(N), ipw(N);
@@ -444,7 +446,7 @@ void Ctx::build_tables() {
         upload(this, d_md_scale->p, mds.data(), mds.size() * 8);
     }
     gauss_cdt(cdt);
-    for (int t = 0; t < n_q; ++t) pmod_mont.push_back(to_mont(pmod[t], mods[t]));
+    for (int t = 0; t < n_q; ++t) pmod_key.push_back((u64)((unsigned __int128)pmod[t] * (1ull << 60) % mods[t]));
     if (rescale_mfma_fits(T)) build_plans();
 }
 
@@ -625,7 +627,7 @@ void Ctx::keygen_base() {
     keys_bytes += (size_t)(2 * M + 2 * n_q) * N * 8;
 }
 
-// switching key from s' (evaluation form over all M primes) to s; layout [beta][2][M][N]
+// switching key from s' (evaluation form over all M primes) to s, words times 2^60; layout [beta][2][M][N]
 std::unique_ptr<DBuf> Ctx::make_swk(u64 key_id, const u64* sp) {
     const int M = n_q + n_p, beta = (n_q + alpha - 1) / alpha;
     auto key = std::make_unique<DBuf>(this, (size_t)beta * 2 * M * N);
@@ -650,7 +652,7 @@ std::unique_ptr<DBuf> Ctx::make_swk(u64 key_id, const u64* sp) {
         for (int m = 0; m < M; ++m) flag[m] = (m < n_q && m / alpha == j) ? 1 : 0;
         upload(this, d_flag.p, flag.data(), M);
         launch_swk_finish(T, M, b, a, e.p, s_eval->p, sp, d_pm.p, (const uint8_t*)d_flag.p, stream);
-        launch_to_mont(T, ModMap{1 << 20, n_q}, M, 2, b, (int64_t)M * N, stream);
+        launch_to_key(T, ModMap{1 << 20, n_q}, M, 2, b, (int64_t)M * N, stream);
         hip_check(hipStreamSynchronize(stream), "swk");  // flag buffer reused
     }
     keys_bytes += (size_t)beta * 2 * M * N * 8;

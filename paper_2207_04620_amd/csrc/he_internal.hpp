@@ -230,7 +230,7 @@ struct Ctx {
     Pool pool_side;
     bool alloc_side = false;
     hm::Encoder enc;
-    std::vector<u64> mods, roots, pmod, pmod_mont;  // pmod: P mod q_t, plain and in Montgomery form
+    std::vector<u64> mods, roots, pmod, pmod_key;  // P mod q_t, plain and times 2^60
     std::vector<ModP> host_mods;
     DevTables T{};
     u64 cdt[19];

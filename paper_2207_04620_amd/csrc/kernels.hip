@@ -292,7 +292,7 @@ __device__ __forceinline__ void inv_all(u64* s, int L, int logT, u64 X, const u6
 __host__ __device__ constexpr int row_at(int a) { return a + ((a >> 5) << 2); }
 #define ROW_LDS (NTT_E + NTT_E / 8)
 // butterflies of one forward group of 2^R <= 8 elements in registers, twiddle pairs at t: below 16q in,
-// below (4R + 3) q out
+// below (4R + 2) q out
 template <int R>
 __device__ __forceinline__ void fwd_group(u64 (&x)[1 << R], const u64* __restrict__ t, const Lean& m) {
     constexpr int G = 1 << R;
@@ -912,10 +912,10 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(EPI ? 6 : 7
     const u64 q = T.mods[mi].q, q2 = 2 * q;
     const bool fp = fp64_limb(q, L1, N2), full = N2 == NTT_E;
     // 2048-element rows: the last round's elements 4 g + k (g = tid, 256 + tid), as raw doubles (FP64
-    // path) or words lazy in [0, 11q) (integer path)
+    // path) or words lazy in [0, 10q) (integer path)
     u64 y[8];
     const double qd = (double)q, qinv = T.mods[mi].qinv;
-    const Lean ln = lean_of(q, T.mods[mi].bar);
+    const Lean ln = lean_of(T.mods[mi]);
     // the ModDown epilogue's u words of those elements, loaded while the middle rounds run
     u64x2 uu[4];
     const u64* u = nullptr;
@@ -967,7 +967,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(EPI ? 6 : 7
             __syncthreads();
         }
     }
-    // emit(i, e, v0, v1): elements e, e + 1 of the row (words below 11q, or the bits of raw doubles on
+    // emit(i, e, v0, v1): elements e, e + 1 of the row (words below 10q, or the bits of raw doubles on
     // the FP64 path) to their destination; i is the pair's slot in uu (2048-element rows), or -1
     auto for_pairs = [&](auto&& emit) {
         if (fp || full) {
@@ -983,10 +983,8 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(EPI ? 6 : 7
                 v0 = canon_d(bits_d(v0), qd, qinv);
                 v1 = canon_d(bits_d(v1), qd, qinv);
             } else {
-                v0 = red4(red16(v0, ln), q2);
-                v1 = red4(red16(v1, ln), q2);
-                v0 = v0 >= q ? v0 - q : v0;
-                v1 = v1 >= q ? v1 - q : v1;
+                v0 = canon16(v0, ln);
+                v1 = canon16(v1, ln);
             }
             st2(a + e, u64x2{v0, v1});
         });
@@ -1010,7 +1008,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(EPI ? 6 : 7
             w[0] = signed_word_d(mulmod_d(u2d(uw.x) - bits_d(v0), pd, qd, qinv), qd);
             w[1] = signed_word_d(mulmod_d(u2d(uw.y) - bits_d(v1), pd, qd, qinv), qd);
         } else {
-            // v is below 11q and u < q, so u + 12q - v lies in (0, 13q); the Shoup product
+            // v is below 10q and u < q, so u + 12q - v lies in (0, 13q); the Shoup product
             // reduces any 64-bit operand to [0, q)
             w[0] = mul_shoup(uw.x + 6 * q2 - v0, pi, pis, q);
             w[1] = mul_shoup(uw.y + 6 * q2 - v1, pi, pis, q);
@@ -1068,7 +1066,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(8))) void k
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 u64 w = canon_d(mulmod_d(y[i], fd, qd, qinv), qd, qinv);
-                if (scale) w = w > mp_.half ? w - q : w;
+                if (scale) w = w > (q >> 1) ? w - q : w;
                 a[(i >> 2) * TPB + tid + 512 * (i & 3)] = w;
             }
         } else {  // raw double words for the FP64 column pass of this limb
@@ -1085,14 +1083,14 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(8))) void k
             x[2 * i] = v.x;
             x[2 * i + 1] = v.y;
         }
-        inv_rows_2048(s, T.irtw + ((int64_t)mi * N1 + r) * (2 * ROW_TW), lean_of(q, mp_.bar), x, y);
+        inv_rows_2048(s, T.irtw + ((int64_t)mi * N1 + r) * (2 * ROW_TW), lean_of(mp_), x, y);
         if (L1 == 0) {
             const u64 f = scale ? scale[2 * (k % scale_n)] : mp_.ninv;
             const u64 fs = scale ? scale[2 * (k % scale_n) + 1] : mp_.ninv_sh;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 u64 w = mul_shoup(y[i], f, fs, q);
-                if (scale) w = w > mp_.half ? w - q : w;
+                if (scale) w = w > (q >> 1) ? w - q : w;
                 a[(i >> 2) * TPB + tid + 512 * (i & 3)] = w;
             }
         } else {  // lazy in [0, 4q)
@@ -1127,8 +1125,8 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(8))) void k
     for (int e = 2 * tid; e < N2; e += 2 * TPB) {
         u64 y0 = mul_shoup(s[lds_at<true>(e)], f, fs, q), y1 = mul_shoup(s[lds_at<true>(e + 1)], f, fs, q);
         if (scale) {
-            y0 = y0 > mp_.half ? y0 - q : y0;
-            y1 = y1 > mp_.half ? y1 - q : y1;
+            y0 = y0 > (q >> 1) ? y0 - q : y0;
+            y1 = y1 > (q >> 1) ? y1 - q : y1;
         }
         st2(a + e, u64x2{y0, y1});
     }
@@ -1163,7 +1161,7 @@ __global__ __launch_bounds__(TPB) void k_ntt_inv_cols(DevTables T, Jobs J, const
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 y[h] = canon_d(mulmod_d(sd[e + h], fd, qd, qinv), qd, qinv);
-                if (scale) y[h] = y[h] > mp_.half ? y[h] - q : y[h];
+                if (scale) y[h] = y[h] > (q >> 1) ? y[h] - q : y[h];
             }
             st2(a + (int64_t)(e >> logC) * N2 + c0 + (e & (C - 1)), u64x2{y[0], y[1]});
         }
@@ -1180,8 +1178,8 @@ __global__ __launch_bounds__(TPB) void k_ntt_inv_cols(DevTables T, Jobs J, const
     for (int e = 2 * threadIdx.x; e < NTT_E; e += 2 * TPB) {
         u64 y0 = mul_shoup(s[e], f, fs, q), y1 = mul_shoup(s[e + 1], f, fs, q);
         if (scale) {
-            y0 = y0 > mp_.half ? y0 - q : y0;
-            y1 = y1 > mp_.half ? y1 - q : y1;
+            y0 = y0 > (q >> 1) ? y0 - q : y0;
+            y1 = y1 > (q >> 1) ? y1 - q : y1;
         }
         st2(a + (int64_t)(e >> logC) * N2 + c0 + (e & (C - 1)), u64x2{y0, y1});
     }
@@ -1388,7 +1386,7 @@ __device__ __forceinline__ void fwd_col_regs(u64 (&x)[1 << L1], const u64x2* W, 
         stage_fence();
         const int d = (1 << L1) >> (st + 1);
         const bool red = bound + 4 > 16;
-        bound = (red ? 3 : bound) + 4;
+        bound = (red ? 2 : bound) + 4;
 #pragma unroll
         for (int i = 0; i < (1 << st); ++i) {
             const u64x2 w = W[(1 << st) + i];
@@ -1539,7 +1537,7 @@ __device__ __forceinline__ void fwd_col_split(u64 (&x)[(1 << L1) / SP], const u6
         } else {
             const int dj = d / SP;
             const bool red = bound + 4 > 16;
-            bound = (red ? 3 : bound) + 4;
+            bound = (red ? 2 : bound) + 4;
 #pragma unroll
             for (int i = 0; i < (1 << st); ++i) {
                 const u64x2 w = W[(1 << st) + i];
@@ -1624,13 +1622,13 @@ __device__ __forceinline__ void conv_source(u64 (&b)[(1 << L1) / SP], const ModP
     } else {
         u64 x[M];
         unrolled<M>([&](auto j) { x[j] = *lane_at<u64>(src + j * (SP * N2), so); });
-        const Lean ln = lean_of(q, m.bar);
+        const Lean ln = lean_of(m);
         if constexpr (SP == 1) inv_col_regs<L1>(x, W, ln);
         else inv_col_split<L1, SP>(x, W, grp, ln);
         unrolled<M>([&](auto j) {
             if (j % 2 == 0) stage_fence();
             const u64 y = mul_shoup(x[j], f, fs, q);
-            b[j] = signed_bytes(y > m.half ? y - q : y);
+            b[j] = signed_bytes(y > (m.q >> 1) ? y - q : y);
             keep_here(b[j]);
         });
     }
@@ -1753,7 +1751,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(conv_waves(
                     unrolled<M>([&](auto j) { *lane_at<u64>(dst + j * (4 * N2), od) = d_bits(x[j]); });
                 } else {
                     u64 x[M];
-                    const Lean ln = lean_of(q, T.mods[S.dmod[gv]].bar);
+                    const Lean ln = lean_of(T.mods[S.dmod[gv]]);
                     unrolled<M>([&](auto j) { x[j] = digits_mod(lo[j], hi[j], ln.nq, S.w32[gv], S.w32_sh[gv], S.off[gv]); });
                     fwd_col_split<L1, 4>(x, W, gv, ln);
                     unrolled<M>([&](auto j) { *lane_at<u64>(dst + j * (4 * N2), od) = x[j]; });
@@ -1776,7 +1774,7 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(conv_waves(
             const uint32_t od = ((uint32_t)S.doff[gv] * N + col) * 8u;
             if (gv < S.nt) unrolled<N1>([&](auto r) { *lane_at<u64>(dst + r * N2, od) = d_bits(x[r]); });
         } else {
-            const Lean ln = lean_of(T.mods[S.dmod[gv]].q, T.mods[S.dmod[gv]].bar);
+            const Lean ln = lean_of(T.mods[S.dmod[gv]]);
             const u64 w32 = S.w32[gv], w32s = S.w32_sh[gv], cc = S.off[gv];
             u64 x[N1];
             unrolled<N1>([&](auto r) {
@@ -2048,7 +2046,7 @@ __global__ __launch_bounds__(TPB) void k_baseconv(DevTables T, ConvDesc D) {
         for (int h = 0; h < 2; ++h) {
             const u64 v = mul_shoup(x[h], D.hinv[s], D.hinv_sh[s], m.q);
             y[s][h] = split30(v);
-            negm[s][h] = v > m.half ? ~0ull : 0ull;
+            negm[s][h] = v > (m.q >> 1) ? ~0ull : 0ull;
         }
     }
     u64* dst = D.dst + c * D.dst_cstride + p * D.dst_pstride;
@@ -2329,6 +2327,24 @@ void launch_to_mont(const DevTables& T, ModMap mm, int nl, int npoly, u64* x, in
     HE_LAUNCH(k_to_mont, grid, dim3(TPB), 0, st, T, mm, x, ps);
 }
 
+// to the form of the switching keys, words times 2^60 mod q: 2^64 x, halved four times
+__global__ __launch_bounds__(TPB) void k_to_key(DevTables T, ModMap mm, u64* x, int64_t ps) {
+    const int N = 1 << T.log_n;
+    const int i = blockIdx.x * TPB + threadIdx.x;
+    const int l = blockIdx.y, p = blockIdx.z;
+    const ModP m = T.mods[mm(l)];
+    u64* v = x + p * ps + (int64_t)l * N + i;
+    u64 w = to_mont(*v, m);
+    for (int k = 0; k < 4; ++k) w = (w >> 1) + ((w & 1) ? (m.q >> 1) + 1 : 0);
+    *v = w;
+}
+
+void launch_to_key(const DevTables& T, ModMap mm, int nl, int npoly, u64* x, int64_t ps, hipStream_t st) {
+    ProfScope prof_(PK_EW, 2.0 * nl * npoly * 8.0 * (1 << T.log_n), st);
+    dim3 grid(ceil_div(1 << T.log_n, TPB), nl, npoly);
+    HE_LAUNCH(k_to_key, grid, dim3(TPB), 0, st, T, mm, x, ps);
+}
+
 __global__ __launch_bounds__(TPB) void k_swk_finish(DevTables T, u64* b, const u64* a, const u64* e,
                                                     const u64* s, const u64* sp, const u64* pmod,
                                                     const uint8_t* in_digit) {
@@ -2361,64 +2377,37 @@ void launch_swk_finish(const DevTables& T, int M, u64* b, const u64* a, const u6
 // lift words at the automorphism source position
 // up to seven digits (plus the c0 term) use the carry-free column sums with the key words
 // split at bit 30; eight digits use 128-bit accumulation
-template <int NB>
-using IpKey = typename std::conditional<(NB <= 7), Split30, u64>::type;
-template <int NB>
-__device__ __forceinline__ IpKey<NB> ip_key(u64 v) {
-    if constexpr (NB <= 7) return split30(v);
-    else return v;
-}
-
-// The inner products of all NR rotations of one member for one slot: sum_r sum_j x_rj k_rj
-// (+ z_r pm_r on the Q limbs), the masks already folded into the key words and the c0
-// constant (mask . sum_j x_j k_j = sum_j x_j (k_j . mask) mod q).  Up to eight products share
-// one set of column sums and one REDC; otherwise each rotation is reduced on its own.
+// The inner products of all NR rotations of one member for one slot, below 16 q: sum_r sum_j x_rj k_rj (+ z_r pm_r
+// on the Q limbs), k and pm times 2^60, a rotation's mask folded into them (mask . sum_j x_j k_j = sum_j x_j (k_j
+// . mask) mod q).  Up to eight products share one set of column sums and one reduction.
 template <int NB, int NR>
-__device__ __forceinline__ void ip_reduce(const u64 (&x)[NR][NB], const u64 (&z)[NR], const IpKey<NB> (&kb)[NR][NB],
-                                          const IpKey<NB> (&ka)[NR][NB], const IpKey<NB> (&pm)[NR], bool with_c0,
+__device__ __forceinline__ void ip_reduce(const u64 (&x)[NR][NB], const u64 (&z)[NR], const Split30 (&kb)[NR][NB],
+                                          const Split30 (&ka)[NR][NB], const Split30 (&pm)[NR], bool with_c0,
                                           const ModP& m, u64& v0, u64& v1) {
-    if constexpr (NB <= 7 && NR * (NB + 1) <= 8) {
-        Acc3 a0 = {0, 0, 0}, a1 = {0, 0, 0};
+    constexpr bool ONE = NR * (NB + 1) <= 8;  // all rotations in one sum
+    constexpr int H = ONE ? NB : NB <= 7 ? NB : 4;  // digits per sum
+    Acc3 a0 = {0, 0, 0}, a1 = {0, 0, 0};
+    v0 = v1 = 0;
 #pragma unroll
-        for (int r = 0; r < NR; r++) {
+    for (int r = 0; r < NR; r++) {
 #pragma unroll
-            for (int j = 0; j < NB; j++) {
+        for (int j0 = 0; j0 < NB; j0 += H) {
+#pragma unroll
+            for (int j = j0; j < j0 + H; j++) {
                 const Split30 xs = split30(x[r][j]);
                 mac3(a0, xs, kb[r][j]);
                 mac3(a1, xs, ka[r][j]);
             }
-            if (with_c0) mac3(a0, split30(z[r]), pm[r]);
-        }
-        v0 = redc3(a0, m.q, m.qninv);
-        v1 = redc3(a1, m.q, m.qninv);
-    } else if constexpr (NB <= 7) {
-        v0 = v1 = 0;
-#pragma unroll
-        for (int r = 0; r < NR; r++) {
-            Acc3 a0 = {0, 0, 0}, a1 = {0, 0, 0};
-#pragma unroll
-            for (int j = 0; j < NB; j++) {
-                const Split30 xs = split30(x[r][j]);
-                mac3(a0, xs, kb[r][j]);
-                mac3(a1, xs, ka[r][j]);
+            if (j0 == 0 && with_c0) mac3(a0, split30(z[r]), pm[r]);
+            if (ONE && r < NR - 1) continue;
+            constexpr int P0 = ONE ? NR * (NB + 1) : H + 1, P1 = ONE ? NR * NB : H;
+            v0 += redc60<P0>(a0, m.q, m.qninv);
+            v1 += redc60<P1>(a1, m.q, m.qninv);
+            if (r < NR - 1 || j0 + H < NB) {
+                v0 = red16(v0, lean_of(m));
+                v1 = red16(v1, lean_of(m));
+                a0 = a1 = Acc3{0, 0, 0};
             }
-            if (with_c0) mac3(a0, split30(z[r]), pm[r]);
-            v0 = add_mod(v0, redc3(a0, m.q, m.qninv), m.q);
-            v1 = add_mod(v1, redc3(a1, m.q, m.qninv), m.q);
-        }
-    } else {
-        v0 = v1 = 0;
-#pragma unroll
-        for (int r = 0; r < NR; r++) {
-            Acc128 a0 = {0, 0}, a1 = {0, 0};
-#pragma unroll
-            for (int j = 0; j < NB; j++) {
-                mac128(a0, x[r][j], kb[r][j]);
-                mac128(a1, x[r][j], ka[r][j]);
-            }
-            if (with_c0) mac128(a0, z[r], pm[r]);
-            v0 = add_mod(v0, redc(a0.lo, a0.hi, m.q, m.qninv), m.q);
-            v1 = add_mod(v1, redc(a1.lo, a1.hi, m.q, m.qninv), m.q);
         }
     }
 }
@@ -2459,10 +2448,10 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(!FOLD && NB
     const int t = blockIdx.y;
     const int mi = D.mod[t];
     const ModP m = T.mods[mi];
-    // key words (and P . c0's constant) with the rotation's mask folded in, Montgomery form
+    // key words (and P . c0's constant), times 2^60, with the rotation's mask folded in
     const bool with_c0 = D.c0 && t < D.nq;
-    const u64 pmont = with_c0 ? D.pmont[t] : 0;
-    IpKey<NB> kb[NR][NB], ka[NR][NB], pm[NR];
+    const u64 pkey = with_c0 ? D.pkey[t] : 0;
+    Split30 kb[NR][NB], ka[NR][NB], pm[NR];
     u64 mks[NR];  // the masks, where they are not folded
     int src[NR];
 #pragma unroll
@@ -2481,10 +2470,10 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(!FOLD && NB
                 b = mul_mont(b, mk, m.q, m.qninv);
                 a = mul_mont(a, mk, m.q, m.qninv);
             }
-            kb[r][j] = ip_key<NB>(b);
-            ka[r][j] = ip_key<NB>(a);
+            kb[r][j] = split30(b);
+            ka[r][j] = split30(a);
         }
-        pm[r] = ip_key<NB>(FOLD && mask ? mul_mont(pmont, mk, m.q, m.qninv) : pmont);
+        pm[r] = split30(FOLD && mask ? mul_mont(pkey, mk, m.q, m.qninv) : pkey);
     }
     // the second rotation may read another ciphertext's lift and c0 (a rotation-sum term); the
     // digit whose own limbs include t (none for the special primes) is read from the lifted
@@ -2541,11 +2530,12 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(!FOLD && NB
         if constexpr (FOLD) {
             ip_reduce<NB, NR>(xv, zv, kb, ka, pm, with_c0, m, v0, v1);
         } else {
-            v0 = v1 = 0;
+            // a sum is below (NB + 2) q: up to 8 q twice by a mask stays below q 2^64
+            Acc128 s0 = {0, 0}, s1 = {0, 0};
 #pragma unroll
             for (int r = 0; r < NR; r++) {
                 u64 x1[1][NB], z1[1] = {zv[r]}, w0, w1;
-                IpKey<NB> b1[1][NB], a1[1][NB], p1[1] = {pm[r]};
+                Split30 b1[1][NB], a1[1][NB], p1[1] = {pm[r]};
 #pragma unroll
                 for (int j = 0; j < NB; j++) {
                     x1[0][j] = xv[r][j];
@@ -2553,18 +2543,24 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(!FOLD && NB
                     a1[0][j] = ka[r][j];
                 }
                 ip_reduce<NB, 1>(x1, z1, b1, a1, p1, with_c0, m, w0, w1);
-                v0 = add_mod(v0, mul_mont(w0, mks[r], m.q, m.qninv), m.q);
-                v1 = add_mod(v1, mul_mont(w1, mks[r], m.q, m.qninv), m.q);
+                if constexpr (NB > 6) {
+                    w0 = red16(w0, lean_of(m));
+                    w1 = red16(w1, lean_of(m));
+                }
+                mac128(s0, w0, mks[r]);
+                mac128(s1, w1, mks[r]);
             }
+            v0 = redc(s0.lo, s0.hi, m.q, m.qninv);
+            v1 = redc(s1.lo, s1.hi, m.q, m.qninv);
         }
         u64* p0 = reinterpret_cast<u64*>(reinterpret_cast<char*>(u0) + io);
         u64* p1 = reinterpret_cast<u64*>(reinterpret_cast<char*>(u1) + io);
-        if (D.accumulate) {
-            v0 = add_mod(v0, *p0, m.q);
-            v1 = add_mod(v1, *p1, m.q);
+        if (D.accumulate) {  // below 12 q
+            v0 += *p0;
+            v1 += *p1;
         }
-        *p0 = v0;
-        *p1 = v1;
+        *p0 = FOLD || D.accumulate ? canon16(v0, lean_of(m)) : v0;
+        *p1 = FOLD || D.accumulate ? canon16(v1, lean_of(m)) : v1;
         u0 += D.u_cs;
         u1 += D.u_cs;
     };
@@ -2687,7 +2683,7 @@ __global__ __launch_bounds__(TPB) void k_rescale_spread(DevTables T, const u64* 
     const ModP ml = T.mods[last_mod], m = T.mods[l];
     const u64 r = last[p * last_ps + i];
     u64 v = reduce64(r, m);
-    if (r > ml.half) v = sub_mod(v, reduce64(ml.q, m), m.q);
+    if (r > (ml.q >> 1)) v = sub_mod(v, reduce64(ml.q, m), m.q);
     tmp[p * tmp_ps + (int64_t)l * N + i] = v;
 }
 

@@ -174,7 +174,7 @@ struct SampleArgs {
 // masked sum mask . IP(g, key) + mask2 . IP(g2, key2) of two rotations of the same lift (one
 // ModDown then serves both).  ginv = g^-1 mod 2N numbers the set's blocks by lift region.
 struct IpSet {
-    const u64* key;    // [beta_top][2][M][N] Montgomery form
+    const u64* key;    // [beta_top][2][M][N], words times 2^60
     const u64* key2;
     const u64* mask;   // [M][N] Montgomery form, row = modulus index; null = no mask
     const u64* mask2;
@@ -201,7 +201,7 @@ struct IpDesc {
     const u64* c0;
     int64_t c0_cs;
     int nq;
-    u64 pmont[HE_MAXT];  // (P mod q_t) R mod q_t
+    u64 pkey[HE_MAXT];  // P 2^60 mod q_t
     // optional: each digit's own limbs [dlo[j], dhi[j]) are not in the lift but read from the
     // lifted polynomial itself (evaluation form): limb t of member c at own + c * own_cs + t N
     const u64* own;
@@ -371,6 +371,7 @@ void launch_mul_ints(const DevTables& T, int nl, const MulIntDesc& D, hipStream_
 void launch_automorph(const DevTables& T, int nl, int npoly, u64* out, int64_t out_ps, const u64* in,
                       int64_t in_ps, u64 g, hipStream_t st, int nct = 1, int64_t out_cs = 0, int64_t in_cs = 0);
 void launch_to_mont(const DevTables& T, ModMap mm, int nl, int npoly, u64* x, int64_t ps, hipStream_t st);
+void launch_to_key(const DevTables& T, ModMap mm, int nl, int npoly, u64* x, int64_t ps, hipStream_t st);
 // b = e - a s (+ pmod_i s' on flagged limbs), all limbs of the full chain [M][N]
 void launch_swk_finish(const DevTables& T, int M, u64* b, const u64* a, const u64* e, const u64* s,
                        const u64* sp, const u64* pmod, const uint8_t* in_digit, hipStream_t st);

@@ -21,7 +21,7 @@ struct ModP {
     u64 bar;    // floor((2^64 - 1) / q)
     u64 ninv;   // N^-1 mod q
     u64 ninv_sh;
-    u64 half;   // (q - 1) / 2
+    u32 c, sh;  // red16's quotient: floor(2^(bits + 16) / q) and bits - 16, bits the width of q (20 to 60)
     double qinv;  // fl(1 / q)
 };
 
@@ -50,12 +50,9 @@ __device__ __forceinline__ u64 mul_shoup_lazy(u64 a, u64 w, u64 w_sh, u64 q) {
 // partial product (50 cycles a product, 58 with it), and values are reduced only where 16 q is near.
 struct Lean {
     u64 q, nq;   // the prime, -q mod 2^64
-    u32 c, sh;   // red16's quotient: floor(2^(32 + sh) / q) and sh = max(bits(q) - 28, 0)
+    u32 c, sh;   // ModP's
 };
-__device__ __forceinline__ Lean lean_of(u64 q, u64 bar) {
-    const int sh = 36 - __builtin_clzll(q) > 0 ? 36 - __builtin_clzll(q) : 0;
-    return {q, 0 - q, (u32)(bar >> (32 - sh)), (u32)sh};
-}
+__device__ __forceinline__ Lean lean_of(const ModP& m) { return {m.q, 0 - m.q, m.c, m.sh}; }
 // u + a w mod q in [u, u + 4q), any a < 2^64: the three partial products above 2^32 give the Shoup quotient or
 // up to two less
 __device__ __forceinline__ u64 mul_lean(u64 u, u64 a, u64 w, u64 w_sh, u64 nq) {
@@ -63,9 +60,14 @@ __device__ __forceinline__ u64 mul_lean(u64 u, u64 a, u64 w, u64 w_sh, u64 nq) {
     const u64 h = (u64)a1 * s1 + __umulhi(a1, s0) + __umulhi(a0, s1);
     return u + a * w + h * nq;
 }
-// x mod q in [0, 3q) for x < 16 q: x >> sh is below 2^32, so the quotient is short by less than 1 for
-// the truncated constant, less than 1 for its own truncation and 2^-27 for x's
+// x mod q in [0, (1 + 2^-10) q) for x < 16 q: x >> sh is below 2^20, so the quotient loses less than 2^-11 to the
+// shift, less than 2^-12 to the constant's truncation and less than 1 to its own
 __device__ __forceinline__ u64 red16(u64 x, const Lean& m) { return x + (u64)__umulhi((u32)(x >> m.sh), m.c) * m.nq; }
+// x mod q for x < 16 q
+__device__ __forceinline__ u64 canon16(u64 x, const Lean& m) {
+    const u64 r = red16(x, m);
+    return r >= m.q ? r - m.q : r;
+}
 
 // (hi 2^64 + lo) R^-1 mod q for hi 2^64 + lo < q 2^64
 __device__ __forceinline__ u64 redc(u64 lo, u64 hi, u64 q, u64 qninv) {
@@ -143,6 +145,28 @@ __device__ __forceinline__ u64 redc3(const Acc3& a, u64 q, u64 qninv) {
     u64 lo, hi;
     acc3_wide(a, lo, hi);
     return redc(lo, hi, q, qninv);
+}
+
+// V 2^-60 mod q of the column sums of NP products of words below q (NP <= 8), below (NP + 1) q: two
+// Montgomery digits of 30 bits, the sums staying in their columns (12 instructions; bringing
+// the columns into two words for a 64-bit digit takes 36 with its carries and register pairs).  A column of
+// eight products has no room for the digits' terms: its part above 2^30 moves up first.
+template <int NP>
+__device__ __forceinline__ u64 redc60(Acc3 a, u64 q, u64 qninv) {
+    constexpr u32 LOW = 0x3fffffffu;
+    const u32 q0 = (u32)q & LOW, q1 = (u32)(q >> 30), n = (u32)qninv & LOW;
+    if constexpr (NP > 7) {
+        a.c2 += a.c1 >> 30;
+        a.c1 &= LOW;
+    }
+    const u32 m0 = ((u32)a.c0 * n) & LOW;
+    a.c0 += (u64)m0 * q0;
+    a.c1 += (u64)m0 * q1;
+    a.c1 += a.c0 >> 30;
+    const u32 m1 = ((u32)a.c1 * n) & LOW;
+    a.c1 += (u64)m1 * q0;
+    a.c2 += (u64)m1 * q1;
+    return a.c2 + (a.c1 >> 30);
 }
 
 // Signed form for centred inputs |y| < 2^59 (y = y_c, the centred representative of a residue
