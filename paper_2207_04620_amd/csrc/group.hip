@@ -30,11 +30,12 @@ int Ctx::sets_per_launch(int B, bool direct) const {
     return std::max(4, std::min(IP_MAXSET, 64 / std::max(1, B)));
 }
 
-// Giant steps lifted MM_OUT at a time, and the rounds of the schedules without ModDown hoisting or with a
-// relinearisation per product several at a time: a lift or a relinearisation is a handful of launches of 5
-// to 20 us for one member and takes nearly the same for four (h = 64 at N = 2^15: 4.56 ms with its 22
-// giant steps one at a time, 4.16 together; three h = 32 members at N = 2^14 as printed: 7.41 ms round
-// by round, 2.97 with 16 rounds together).  Nine members fill the launches by themselves.
+// Up to 16 giant steps lifted and added together, and the rounds of the schedules without ModDown hoisting or
+// with a relinearisation per product several at a time: a lift or a relinearisation is a handful of launches
+// of 5 to 20 us for one member and takes little more for four (h = 64 at N = 2^15: 4.56 ms with its 22
+// giant steps one at a time, 4.16 four at a time, 3.73 together after other gains of 0.2; three h = 32 members at
+// N = 2^14 as printed: 7.41 ms round by round, 2.81 with 16 rounds together).  Nine members fill the
+// launches by themselves.
 bool Ctx::wide_giants(int B, bool direct) const {
     return direct && pair_auto && !pool.limit && !pool_side.limit && B <= 8;
 }
@@ -256,10 +257,10 @@ void Ctx::g_ks_inner_sets(u64* u, const u64* lift, int B, int level, const std::
 }
 
 // the same with the lifted polynomial (own, member stride own_cs) given; per_set: set s rotates
-// the members s B.. of the lift, own and c0
+// the members s B.. of the lift, own and c0; sum: u [B] takes the sum over the sets
 void Ctx::ip_into(u64* u, const u64* lift, const u64* own, int64_t own_cs, int B, int level,
                   const std::vector<IpSet>& sets, int nrot, const u64* c0, int64_t c0_cs, bool accumulate,
-                  bool per_set) {
+                  bool per_set, bool sum) {
     const int nl = level + 1, ne = nl + n_p;
     const int beta = (int)mu[level].size();
     if (sets.empty() || sets.size() > IP_MAXSET) throw HeError(HE_EUNSUPPORTED);
@@ -291,6 +292,7 @@ void Ctx::ip_into(u64* u, const u64* lift, const u64* own, int64_t own_cs, int B
         D.s[j].ginv = galois_inverse(sets[j].g, log_n);
     }
     D.accumulate = accumulate ? 1 : 0;
+    D.sum = sum ? 1 : 0;
     if (per_set) {
         D.lift_ss = B * D.lift_cs;
         D.own_ss = B * own_cs;
@@ -573,28 +575,47 @@ void Ctx::g_sum_into(Grp& acc, bool& have, const std::vector<Grp>& terms) {
 // (a term waits for the next one, then both go in one launch and their lifts are freed);
 // finish adds a last unpaired term, brings the sum down once and adds the unrotated base in
 // the ModDown epilogue.  Exact apart from the one shared ModDown rounding.
-// A lift made for several terms at once comes with the term's digits in it
-void Ctx::g_rotsum_add(RotSum& S, const Grp& a, int64_t r, std::shared_ptr<DBuf> lift, const u64* digits) {
-    if (a.deg != 1) throw HeError(HE_EMISMATCH);
+void Ctx::g_rotsum_start(RotSum& S, int B, int level, const std::vector<double>& scale) {
     if (!S.u) {
-        S.B = a.B;
-        S.level = a.level;
+        S.B = B;
+        S.level = level;
         S.n = 0;
         S.filled = false;
-        S.scale = a.scale;
-        S.u = std::make_shared<DBuf>(this, (size_t)a.B * 2 * (a.level + 1 + n_p) * N);
+        S.scale = scale;
+        S.u = std::make_shared<DBuf>(this, (size_t)B * 2 * (level + 1 + n_p) * N);
     }
-    if (a.B != S.B || a.level != S.level) throw HeError(HE_EMISMATCH);
+    if (B != S.B || level != S.level) throw HeError(HE_EMISMATCH);
+}
+
+// the terms joint_j (B members each) rotated by rs[j], lifted together and added in one launch
+void Ctx::g_rotsum_add_each(RotSum& S, const Grp& joint, const std::vector<int64_t>& rs, int B) {
+    const int P = (int)rs.size();
+    g_rotsum_start(S, B, joint.level, std::vector<double>(joint.scale.begin(), joint.scale.begin() + B));
+    std::vector<IpSet> sets(P);
+    for (int j = 0; j < P; ++j) {
+        const u64 g = galois(rs[j]);
+        if (g == 1) throw HeError(HE_EUNSUPPORTED);
+        memset(&sets[j], 0, sizeof(IpSet));
+        sets[j].key = rot_key(g, false);
+        sets[j].g = g;
+        for (int i = 0; i < B; ++i) S.scale[i] = std::max(S.scale[i], joint.scale[j * B + i]);
+    }
+    auto lift = g_lift(joint, 1);
+    ip_into(S.u->p, lift->p, joint.p + joint.ps, joint.cs, B, joint.level, sets, 1, joint.p, joint.cs, S.filled, true, true);
+    S.filled = true;
+    S.n += P;
+    cnt[C_ROT] += (int64_t)P * B;
+}
+
+void Ctx::g_rotsum_add(RotSum& S, const Grp& a, int64_t r) {
+    if (a.deg != 1) throw HeError(HE_EMISMATCH);
+    g_rotsum_start(S, a.B, a.level, a.scale);
     const u64 g = galois(r);
     if (g == 1) throw HeError(HE_EUNSUPPORTED);
     rot_key(g, false);
-    if (!lift) {
-        lift = g_lift(a, 1);
-        digits = lift->p;
-    }
+    auto lift = g_lift(a, 1);
     if (!S.plift) {
         S.plift = lift;
-        S.pl = digits;
         S.pa = a;
         S.pg = g;
     } else {
@@ -605,12 +626,12 @@ void Ctx::g_rotsum_add(RotSum& S, const Grp& a, int64_t r, std::shared_ptr<DBuf>
         st.g = S.pg;
         st.key2 = rot_key(g, false);
         st.g2 = g;
-        st.lift2 = digits;
+        st.lift2 = lift->p;
         st.own2 = a.p + a.ps;
         st.own2_cs = a.cs;
         st.c0_2 = a.p;
         st.c0_2_cs = a.cs;
-        ip_into(S.u->p, S.pl, S.pa.p + S.pa.ps, S.pa.cs, a.B, a.level, {st}, 2, S.pa.p, S.pa.cs, S.filled);
+        ip_into(S.u->p, S.plift->p, S.pa.p + S.pa.ps, S.pa.cs, a.B, a.level, {st}, 2, S.pa.p, S.pa.cs, S.filled);
         S.filled = true;
         S.plift.reset();
         S.pa = Grp();
@@ -628,7 +649,7 @@ Grp Ctx::g_rotsum_finish(RotSum& S, const Grp* base) {
         memset(&st, 0, sizeof st);
         st.key = rot_key(S.pg, false);
         st.g = S.pg;
-        ip_into(S.u->p, S.pl, S.pa.p + S.pa.ps, S.pa.cs, S.B, S.level, {st}, 1, S.pa.p, S.pa.cs, S.filled);
+        ip_into(S.u->p, S.plift->p, S.pa.p + S.pa.ps, S.pa.cs, S.B, S.level, {st}, 1, S.pa.p, S.pa.cs, S.filled);
         S.filled = true;
         S.plift.reset();
         S.pa = Grp();
@@ -883,6 +904,16 @@ Grp Ctx::g_lintrans(const Grp& a, int kind, int h, int beta, int64_t unit, int d
     // before the next is made
     const int glo = floordiv_g(dlo, b), ghi = floordiv_g(dhi, b);
     const int per = b > 8 ? 2 : MM_OUT;
+    // the sums that are rotated lie in one block where several are lifted together: up to 'most'
+    const int most = wide ? std::max(per, sets_per_launch(a.B, direct) / per * per) : 0;
+    Grp joint;
+    std::vector<int64_t> rots;
+    auto flush = [&]() {
+        if (hoist) g_rotsum_add_each(gsum, joint, rots, a.B);
+        else g_sum_into(acc, have, g_rotate_each(joint, rots, a.B));
+        joint = Grp();
+        rots.clear();
+    };
     for (int i0 = glo; i0 <= ghi; i0 += per) {
         MultiMacDesc D;
         memset(&D, 0, sizeof D);
@@ -894,11 +925,6 @@ Grp Ctx::g_lintrans(const Grp& a, int kind, int h, int beta, int64_t unit, int d
             D.in_cs[j] = baby[j].cs;
         }
         std::vector<std::pair<int, Grp>> inners;
-        // the chunk's sums that are rotated lie in one block where they are lifted together
-        Grp joint;
-        const int last = std::min(ghi, i0 + per - 1);
-        const int nrot = last - i0 + 1 - (i0 <= 0 && last >= 0 ? 1 : 0);
-        std::vector<int64_t> rots;
         for (int i = i0; i <= std::min(ghi, i0 + per - 1); ++i) {
             int nterm = 0;
             const u64* mk[16] = {nullptr};
@@ -915,7 +941,7 @@ Grp Ctx::g_lintrans(const Grp& a, int kind, int h, int beta, int64_t unit, int d
             Grp g;
             if (wide && i && galois(r) != 1) {
                 if (!joint.p) {
-                    joint = g_new(nrot * a.B, a.level, 1, sc);
+                    joint = g_new(std::min(most, ghi - i + 1) * a.B, a.level, 1, sc);
                     joint.B = 0;
                     joint.scale.clear();
                 }
@@ -938,18 +964,10 @@ Grp Ctx::g_lintrans(const Grp& a, int kind, int h, int beta, int64_t unit, int d
             cnt[C_ADD] += (int64_t)(nterm - 1) * a.B;
         }
         if (D.nout) launch_mask_mac_multi(T, a.level + 1, 2, D, stream);
-        if (joint.B) {
-            if (hoist) {
-                auto lift = g_lift(joint, 1);
-                const int64_t set = (int64_t)a.B * mu[a.level].size() * (a.level + 1 + n_p) * N;
-                const auto sums = g_views(joint, a.B);
-                for (size_t w = 0; w < rots.size(); ++w) g_rotsum_add(gsum, sums[w], rots[w], lift, lift->p + w * set);
-            } else {
-                g_sum_into(acc, have, g_rotate_each(joint, rots, a.B));
-            }
-        }
+        const auto block = joint.buf;  // the chunk's rotated sums are in it
+        if (joint.B && ((int)rots.size() + per > most || i0 + per > ghi)) flush();
         for (auto& ig : inners) {
-            if (joint.p && ig.second.buf == joint.buf) continue;
+            if (block && ig.second.buf == block) continue;
             const int i = ig.first;
             Grp inner = ig.second;
             const int64_t r = (int64_t)beta * unit * b * i;

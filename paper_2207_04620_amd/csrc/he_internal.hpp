@@ -104,7 +104,6 @@ struct RotSum {
     // a term waiting for a partner: two terms share one inner-product launch, so u is read
     // and rewritten once per pair (its lift, its ciphertext for c0, its Galois element)
     std::shared_ptr<DBuf> plift;
-    const u64* pl = nullptr;  // the term's digits in plift
     Grp pa;
     u64 pg = 0;
 };
@@ -285,7 +284,7 @@ struct Ctx {
     void lift_into(const u64* d, int64_t d_cs, int B, int level, u64* lift, u64* coef);
     void ip_into(u64* u, const u64* lift, const u64* own, int64_t own_cs, int B, int level,
                  const std::vector<IpSet>& sets, int nrot, const u64* c0, int64_t c0_cs, bool accumulate,
-                 bool per_set = false);
+                 bool per_set = false, bool sum = false);
     void moddown_into(u64* u, u64* conv, int B, int level, const Epi& part);
     void rescale_into(const u64* a, int64_t a_ps, int l, int np, int B, u64* out, int64_t out_ps);
     void ks_single(const u64* d, int level, const u64* key, u64 g, const u64* c0, const u64* add, u64* out);
@@ -340,8 +339,9 @@ struct Ctx {
     void g_ks_inner_sets(u64* u, const u64* lift, int B, int level, const std::vector<IpSet>& sets, int nrot,
                          const u64* c0, int64_t c0_cs, bool accumulate);
     bool wide_giants(int B, bool direct) const;
-    void g_rotsum_add(RotSum& S, const Grp& a, int64_t r, std::shared_ptr<DBuf> lift = nullptr,
-                      const u64* digits = nullptr);
+    void g_rotsum_start(RotSum& S, int B, int level, const std::vector<double>& scale);
+    void g_rotsum_add(RotSum& S, const Grp& a, int64_t r);
+    void g_rotsum_add_each(RotSum& S, const Grp& joint, const std::vector<int64_t>& rs, int B);
     void g_sum_into(Grp& acc, bool& have, const std::vector<Grp>& terms);
     std::vector<Grp> g_rotate_each(const Grp& joint, const std::vector<int64_t>& ks, int B);
     Grp g_rotsum_finish(RotSum& S, const Grp* base);

@@ -2603,10 +2603,92 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(!FOLD && NB
     }
 }
 
+// The sum over up to 16 rotations, each of its own lift, in one launch: a thread goes through the sets, so u is
+// written once instead of read and written per pair of them (N = 2^15, fifteen and seven terms of one member: 2 x 90
+// us against ten launches of pairs of 21 and two of single terms).  The keys are most of the bytes, so
+// a thread has up to MB members, which share them (the grid has the members in equal parts).
+template <int NB, int MB>
+__global__ __launch_bounds__(TPB) void k_ip_terms(DevTables T, IpDesc D, int per) {
+    const int N = 1 << T.log_n;
+    const int i = blockIdx.x * TPB + threadIdx.x, t = blockIdx.y, cb = blockIdx.z * per;
+    const int nc = min(per, D.nct - cb);
+    const int mi = D.mod[t];
+    const ModP m = T.mods[mi];
+    const bool with_c0 = D.c0 && t < D.nq;
+    const Split30 pm[1] = {split30(with_c0 ? D.pkey[t] : 0)};
+    int jo = -1;
+#pragma unroll
+    for (int j = 0; j < NB; j++)
+        if (t >= D.dlo[j] && t < D.dhi[j]) jo = j;
+    const u64* lift = D.lift + cb * D.lift_cs + (int64_t)t * N;
+    const u64* own = D.own + cb * D.own_cs + (int64_t)t * N;
+    const u64* c0 = D.c0 + cb * D.c0_cs + (int64_t)t * N;
+    u64 v0[MB] = {}, v1[MB] = {};
+#pragma unroll 2
+    for (int s = 0; s < D.nset; s++) {
+        const u64* key = D.s[s].key + (int64_t)mi * N + i;
+        const int src = perm_g(i, D.s[s].g, T.log_n);
+        u64 x[MB][NB], z[MB], b[NB], a[NB];
+#pragma unroll
+        for (int j = 0; j < NB; j++) {
+            b[j] = ldnt(key + (int64_t)j * 2 * D.M * N);
+            a[j] = ldnt(key + ((int64_t)j * 2 + 1) * D.M * N);
+        }
+#pragma unroll
+        for (int c = 0; c < MB; c++) {
+            if (c >= nc) break;
+#pragma unroll
+            for (int j = 0; j < NB; j++)
+                x[c][j] = j == jo ? own[s * D.own_ss + c * D.own_cs + src]
+                                  : lift[s * D.lift_ss + c * D.lift_cs + (int64_t)j * D.ne * N + src];
+            z[c] = with_c0 ? c0[s * D.c0_ss + c * D.c0_cs + src] : 0;
+        }
+        Split30 kb[1][NB], ka[1][NB];
+#pragma unroll
+        for (int j = 0; j < NB; j++) {
+            kb[0][j] = split30(b[j]);
+            ka[0][j] = split30(a[j]);
+        }
+#pragma unroll
+        for (int c = 0; c < MB; c++) {
+            if (c >= nc) break;
+            u64 xc[1][NB], zc[1] = {z[c]}, w0, w1;
+#pragma unroll
+            for (int j = 0; j < NB; j++) xc[0][j] = x[c][j];
+            ip_reduce<NB, 1>(xc, zc, kb, ka, pm, with_c0, m, w0, w1);
+            v0[c] = red16(v0[c] + w0, lean_of(m));  // a term is below 9 q
+            v1[c] = red16(v1[c] + w1, lean_of(m));
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < MB; c++) {
+        if (c >= nc) break;
+        u64* p0 = D.u + (cb + c) * D.u_cs + (int64_t)t * N + i;
+        u64* p1 = p0 + (int64_t)D.ne * N;
+        if (D.accumulate) {
+            v0[c] += *p0;
+            v1[c] += *p1;
+        }
+        *p0 = canon16(v0[c], lean_of(m));
+        *p1 = canon16(v1[c], lean_of(m));
+    }
+}
+
 // members up to which a pair's masks are applied to the sums instead of to the key words
 #define IP_UNFOLDED 2
 template <int NB>
 static void launch_ip_nb(const DevTables& T, const IpDesc& D, dim3 grid, hipStream_t st) {
+    if (D.sum) {
+        const int parts = (int)ceil_div(D.nct, 4), per = (int)ceil_div(D.nct, parts);
+        grid = dim3((1 << T.log_n) / TPB, D.ne, parts);
+        if (per == 1)
+            HE_LAUNCH((k_ip_terms<NB, 1>), grid, dim3(TPB), 0, st, T, D, per);
+        else if (per == 2)
+            HE_LAUNCH((k_ip_terms<NB, 2>), grid, dim3(TPB), 0, st, T, D, per);
+        else
+            HE_LAUNCH((k_ip_terms<NB, 4>), grid, dim3(TPB), 0, st, T, D, per);
+        return;
+    }
     // every set of a pair launch has both masks or none (two terms of a rotation sum have none)
     bool masked = D.nrot == 2;
     for (int j = 0; j < D.nset; ++j) masked = masked && D.s[j].mask && D.s[j].mask2;
@@ -2631,9 +2713,11 @@ void launch_inner_product(const DevTables& T, const IpDesc& D, hipStream_t st) {
         if ((nr == 2 && D.s[j].lift2) || (j && D.lift_ss)) lifts += 1;  // another ciphertext's lift and c0
     }
     const double words = (double)D.ne * (ns * nr * 2.0 * D.beta + masks +
-                                         D.nct * (lifts * D.beta + ns * (D.accumulate ? 4.0 : 2.0))) +
+                                         D.nct * (lifts * D.beta + (D.sum ? 1 : ns) * (D.accumulate ? 4.0 : 2.0))) +
                          (D.c0 ? lifts * D.nq * D.nct : 0.0);
     for (int j = 0; j < ns; ++j) {
+        if (D.sum && (nr != 1 || D.s[j].mask || !D.own))
+            throw std::runtime_error("inner product: a sum over sets has one unmasked rotation each");
         if (D.s[j].lift2 && (nr != 2 || (D.c0 != nullptr) != (D.s[j].c0_2 != nullptr)))
             throw std::runtime_error("inner product: second lift without a second rotation or c0");
         if (D.s[j].lift2 && (D.own != nullptr) != (D.s[j].own2 != nullptr))

@@ -213,6 +213,7 @@ struct IpDesc {
     int64_t lift_ss, own_ss, c0_ss;
     IpSet s[IP_MAXSET];
     int accumulate;    // u += the result (a sum of rotations of different ciphertexts)
+    int sum;           // u [nct][2][ne][N] is the sum over the sets (no masks, nrot = 1)
 };
 
 // n-ary sum of ciphertext polynomials (up to 16 inputs per launch), each input with its own
