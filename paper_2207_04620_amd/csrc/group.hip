@@ -806,7 +806,18 @@ void Ctx::g_tensor_sum(MatmulJob& J) {
     if (!J.haveS) {
         std::vector<double> sc(a0.B);
         for (int i = 0; i < a0.B; ++i) sc[i] = a0.scale[i] * J.pendB[0].scale[i];
-        J.S = g_new(a0.B, a0.level, 2, sc);
+        if (J.nblk > 1) {
+            if (!J.blks.p) {
+                J.blks = g_new(J.nblk * a0.B, a0.level, 2, sc);
+                J.blks.scale.clear();
+            }
+            J.S = J.blks;
+            J.S.B = a0.B;
+            J.S.p = J.blks.p + (int64_t)J.blk_rot.size() * a0.B * J.blks.cs;
+            J.S.scale = sc;
+        } else {
+            J.S = g_new(a0.B, a0.level, 2, sc);
+        }
     }
     TensorSumDesc D;
     memset(&D, 0, sizeof D);
@@ -835,6 +846,22 @@ void Ctx::g_tensor_sum(MatmulJob& J) {
     J.haveS = true;
     J.pendA.clear();
     J.pendB.clear();
+}
+
+// J.acc = the relinearised block sums, every one but the first rotated by its amount, summed
+void Ctx::g_blocks_finish(MatmulJob& J) {
+    const int B = J.blks.B / J.nblk;
+    Grp all = g_relin(J.blks);
+    J.blks = Grp();
+    J.acc = g_views(all, B)[0];
+    J.have = true;
+    Grp rest = all;
+    rest.B -= B;
+    rest.p += B * all.cs;
+    rest.scale.erase(rest.scale.begin(), rest.scale.begin() + B);
+    const std::vector<int64_t> rs(J.blk_rot.begin() + 1, J.blk_rot.end());
+    if (schedule & HE_SCHED_HOIST_MODDOWN) g_rotsum_add_each(J.giant, rest, rs, B);
+    else g_sum_into(J.acc, J.have, g_rotate_each(rest, rs, B));
 }
 
 // J.S (+)= the relinearised products of the pending pairs
@@ -1024,6 +1051,9 @@ bool Ctx::matmul_step(MatmulJob& J, int k_chunk) {
         // whose launches are small, otherwise one
         const bool wide = wide_giants(J.A0.B, J.direct);
         const int nset = hoist || wide ? sets_per_launch(J.A0.B, J.direct) : 1;
+        // the blocks' sums relinearised and rotated together (h = 64 at N = 2^15, one member: 3.73 ms block by
+        // block, 3.50 together)
+        if (J.k == 0 && wide && (schedule & HE_SCHED_RELIN_ONCE) && (t - 1) / bg <= IP_MAXSET) J.nblk = (t - 1) / bg + 1;
         // hoisted schedule: the mask pairs of up to nset consecutive k share one ModDown;
         // with overlap, the next group's inner products run on the side stream during this
         // group's ModDown (within this chunk of rounds only)
@@ -1143,6 +1173,12 @@ bool Ctx::matmul_step(MatmulJob& J, int k_chunk) {
                 Grp blk = J.S;
                 J.S = Grp();
                 J.haveS = false;
+                if (J.nblk > 1) {
+                    J.blk_rot.push_back(beta * shift);
+                    J.blks.scale.insert(J.blks.scale.end(), blk.scale.begin(), blk.scale.end());
+                    if (k == t - 1) g_blocks_finish(J);
+                    continue;
+                }
                 if (schedule & HE_SCHED_RELIN_ONCE) blk = g_relin(blk);
                 if (i > 0 && hoist) {
                     g_rotsum_add(J.giant, blk, beta * shift);

@@ -117,6 +117,11 @@ struct MatmulJob {
     std::vector<Grp> babyB;  // Rot(B0, h j), j < bg, kept across blocks (Step-3 split)
     RotSum giant;            // Step-3 giant-step rotations sharing one ModDown (ModDown hoisting)
     std::vector<Grp> pendA, pendB;  // Step-3 pairs awaiting one block tensor-sum (relin-once)
+    // few members: the blocks' sums side by side, relinearised and rotated together (nblk of them, with
+    // their rotation amounts so far)
+    int nblk = 0;
+    Grp blks;
+    std::vector<int64_t> blk_rot;
     std::shared_ptr<DBuf> liftA, liftB;
     std::vector<CtPtr> result;
     bool keep_acc = false;  // leave the result as the group acc (the caller scatters it)
@@ -372,6 +377,7 @@ struct Ctx {
     Grp g_tensor(const Grp& a, const Grp& b) { return g_tensor_each({a}, {b}); }
     void g_tensor_sum(MatmulJob& J);
     void g_relin_sum(MatmulJob& J);
+    void g_blocks_finish(MatmulJob& J);
     Grp g_relin(const Grp& a);
     void g_relin_into(const Grp& a, const Grp& out);
     Grp g_lintrans(const Grp& a, int kind, int h, int beta, int64_t unit, int dlo, int dhi, bool direct);
