@@ -160,7 +160,7 @@ void Ctx::lift_into(const u64* d, int64_t d_cs, int B, int level, u64* lift, u64
     const auto& infos = mu[level];
     const int beta = (int)infos.size();
     const int64_t lcs = (int64_t)beta * ne * N;
-    const bool planned = conv_mfma_fits(T);
+    const bool planned = conv_mfma_fits(T, std::max(alpha, n_p), B);
     // otherwise with the fused conversion the inverse transform applies each digit's (D/q_s)^-1
     bool fused = !planned;
     for (const auto& inf : infos) fused = fused && conv_cols_fits(T, inf.hi - inf.lo);
@@ -321,7 +321,7 @@ void Ctx::g_moddown(u64* u, int B, int level, const u64* add0, const u64* add1, 
 void Ctx::moddown_into(u64* u, u64* conv, int B, int level, const Epi& part) {
     const int nl = level + 1, ne = nl + n_p;
     const int64_t ucs = 2 * (int64_t)ne * N, ccs = 2 * (int64_t)nl * N;
-    const bool planned = conv_mfma_fits(T);
+    const bool planned = conv_mfma_fits(T, std::max(alpha, n_p), B);
     // otherwise with the fused conversion the inverse transform applies (P/p_k)^-1
     const bool fused = !planned && conv_cols_fits(T, n_p);
     {

@@ -519,7 +519,7 @@ void Ctx::build_plans() {
         first.push_back(sets.size());
         ConvPlan& U = plan_mu[l];
         U.xs = conv_mfma_share(T, std::min(alpha, nl));
-        for (size_t j = 0; j < mu[l].size() && conv_mfma_fits(T); ++j) {
+        for (size_t j = 0; j < mu[l].size() && conv_mfma_fits(T, std::max(alpha, n_p), 1 << 16); ++j) {
             std::vector<std::pair<int, int>> t;
             for (int i = 0; i < ne; ++i)
                 if (i < mu[l][j].lo || i >= mu[l][j].hi) t.push_back({(int)j * ne + i, ext_mod(l, i)});
@@ -530,7 +530,7 @@ void Ctx::build_plans() {
         D.xs = conv_mfma_share(T, n_p);
         std::vector<std::pair<int, int>> t;
         for (int i = 0; i < nl; ++i) t.push_back({i, i});
-        if (conv_mfma_fits(T)) add_digit(D, 0, n_p, n_q, t);
+        if (conv_mfma_fits(T, std::max(alpha, n_p), 1 << 16)) add_digit(D, 0, n_p, n_q, t);
         first.push_back(sets.size());
         ConvPlan& R = plan_rs[l];
         t.pop_back();

@@ -1797,11 +1797,14 @@ int conv_mfma_share(const DevTables& T, int ns) {
     if (ns <= 4) return 0;
     return T.n1_log < 3 || ns > 6 ? 1 : ns == 5 ? 4 : 2;
 }
-// With five column stages (N = 2^16) a lane's 32 rows of up to eight sources leave two waves per
-// SIMD, and the conversions of five and six sources took 190 and 262 us where k_conv_cols and the
-// inverse column pass took 130 and 198 (16 members, 17 + 5 limbs); a rescale's single source is 120
-// us against 250 for the separate passes.
-bool conv_mfma_fits(const DevTables& T) { return T.n2_log == 11 && T.n1_log >= 1 && T.n1_log <= 4; }
+// With five column stages (N = 2^16) a lane holds 32 rows of a source, at two waves per SIMD.  Conversions of
+// five and six sources still beat k_conv_cols and the inverse column pass (48 ReLU members of 17 + 5
+// limbs: 228 and 320 us against 259 and 386), but a few members' do not (a rotation 150 us against 140, a sign
+// evaluation 1.84 ms against 1.78: too few waves to hide each other's latency); a second source a lane, for seven and eight, has no registers.
+bool conv_mfma_fits(const DevTables& T, int sources, int members) {
+    if (T.n2_log != 11 || T.n1_log < 1) return false;
+    return T.n1_log <= 4 || (T.n1_log == 5 && sources <= 6 && members >= 8);
+}
 bool rescale_mfma_fits(const DevTables& T) { return T.n2_log == 11 && T.n1_log >= 1 && T.n1_log <= 5; }
 
 template <int L1>
@@ -1817,13 +1820,13 @@ static void launch_conv_mfma_l(int xs, dim3 grid, hipStream_t st, const DevTable
             }
             break;
         case 2:
-            if constexpr (L1 == 3 || L1 == 4) {
+            if constexpr (L1 >= 3) {
                 HE_LAUNCH((k_conv_mfma<L1, 2>), grid, dim3(TPB), lds, st, T, D);
                 return;
             }
             break;
         case 4:
-            if constexpr (L1 == 3 || L1 == 4) {
+            if constexpr (L1 >= 3) {
                 HE_LAUNCH((k_conv_mfma<L1, 4>), grid, dim3(TPB), lds, st, T, D);
                 return;
             }

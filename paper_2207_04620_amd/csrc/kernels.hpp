@@ -340,7 +340,7 @@ bool conv_cols_fits(const DevTables& T, int ns);
 // inverse column pass, conversion and forward column pass of a plan in one launch, for rings with
 // 2048-element rows and one to five column stages; sources as the inverse row pass leaves them
 // (launch_ntt(..., inverse, ..., cols = false)), targets as the forward row pass takes them
-bool conv_mfma_fits(const DevTables& T);     // for ModUp and ModDown
+bool conv_mfma_fits(const DevTables& T, int sources, int members);  // ModUp and ModDown of at most so many sources
 bool rescale_mfma_fits(const DevTables& T);  // for rescales
 // k blocks that repeat one source beyond the fourth in the operands, for digits of up to ns sources (0: none)
 int conv_mfma_share(const DevTables& T, int ns);

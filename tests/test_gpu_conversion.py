@@ -24,7 +24,8 @@ CASES = [
     (15, [60] + [45] * 9, [60, 60, 60, 56, 45], 5, (9, 6, 5)),
     (15, [46] * 8, [47] * 6, 6, (7, 6)),
     (15, [60] * 2 + [45] * 7, [60] * 8, 8, (8, 7)),
-    (16, [60] + [45] * 6, [60] * 5, 6, (6, 2)),           # five stages: the rescale alone
+    (16, [60] + [45] * 6, [60] * 5, 6, (6, 2)),           # five stages, one member: the rescale alone
+    (16, [60] + [45] * 7, [60] * 7, 7, (7,)),             # five stages, seven sources
     (17, [60, 45, 45], [60, 60], 2, (2, 1)),              # six stages: separate passes
 ]
 
@@ -52,4 +53,20 @@ def test_conversion_edges(log_n, q_bits, p_bits, alpha, levels):
         same(g.rescale(gm), o.rescale(om))
         same(g.rescale(gt), o.rescale(ot))  # three polynomials
         same(g.rotate(ga, 3), o.rotate(oa, 3))
+    g.close()
+
+
+@pytest.mark.parametrize("p_count,alpha", [(4, 4), (5, 6), (6, 5)])
+def test_five_stages_of_several_members(p_count, alpha):
+    """N = 2^16, eight members a launch: ModUp and ModDown as one column pass"""
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2207_04620_amd import he
+    prm = I.Params("conv16", 16, [60] + [45] * 6, [60] * p_count, alpha, 40.0, 5, [])
+    g, o = he.Context(prm, h_list=[]), O.Ctx.from_params(prm)
+    xs = [I.sign_inputs(3 + i, 1, 16)[0].ravel() for i in range(8)]
+    ys = g.sign_approx_batch([g.encrypt(x, nonce=1 + i) for i, x in enumerate(xs)], 1, 1, 0)
+    for i in (0, 7):
+        oy = o.sign(o.encrypt(xs[i], nonce=1 + i), 1, 1, relu=False)
+        assert np.array_equal(g.export(ys[i]), oy.export()) and ys[i].scale == oy.scale
     g.close()
