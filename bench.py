@@ -25,17 +25,18 @@ import numpy as np  # noqa: E402
 METRIC = "ct×ct h=64 HE-matmuls/s at N=2^15 vs plain path; p50/p99 serve latency"
 HBM_PEAK_GBS = 8000.0
 # ALU peak of the NTT butterfly on gfx950, from unit counts and clock: 256 CUs x 4 SIMD
-# x 16 lanes x 2.4 GHz = 39.32 T VALU lane-instructions/s.  One lazy Shoup butterfly
-# (x' = x - 2q if x >= 2q; t = x1 w - floor(x1 w' / 2^64) q; (x' + t, x' - t + 2q)) is 28 VALU
-# instructions on gfx950: 10 integer multiplies (v_mad_u64_u32, v_mul_lo_u32, v_mul_hi_u32)
-# and 18 adds/subtracts/compares/selects/moves, all issued at the full rate.
+# x 16 lanes x 2.4 GHz = 39.32 T VALU lane-instructions/s.  One lazy integer
+# butterfly (t = x1 w - h q with h the three upper partial products of x1 w' / 2^64; x + t,
+# 2x + 4q - (x + t); a five-instruction reduction of x every third stage) is 17 VALU instructions
+# on gfx950: 9 integer multiplies (v_mad_u64_u32, v_mul_lo_u32, v_mul_hi_u32) and 8 adds,
+# subtracts and shifts, all issued at the full rate.
 # The limbs of primes below 2^46 run FP64 butterflies instead: hi = x w, lo = fma(x, w, -hi),
 # c = rint(x fl(w/q)), t = fma(-c, q, hi) + lo, then x + t and x - t: 8 VALU instructions
 # (v_mul/v_fma/v_rndne/v_add_f64, full rate on gfx950).  A transform launch is bound by
 # whichever floor is larger: its algorithmic bytes at 8 TB/s, or its butterflies' VALU
 # instructions at the VALU rate.
 VALU_LANE_OPS = 256 * 4 * 16 * 2.4e9
-BFLY_INSTR = 28
+BFLY_INSTR = 17
 FP64_BFLY_INSTR = 8
 NTT_KERNELS = ("ntt_fwd_cols", "ntt_fwd_rows", "ntt_inv_rows", "ntt_inv_cols")
 
@@ -689,7 +690,7 @@ def main():
                            "fp64_share": round(ntt_fp / max(1.0, ntt_ops), 3),
                            "butterfly_valu_frac": round(ntt_instr / (ntt_ms * 1e-3) / VALU_LANE_OPS, 4),
                            "algorithmic_GB/s": round(ntt_bytes / (ntt_ms * 1e-3) / 1e9, 1),
-                           "note": "butterfly_valu_frac: the butterflies' VALU instructions (28 per 64-bit integer "
+                           "note": "butterfly_valu_frac: the butterflies' VALU instructions (17 per 64-bit integer "
                                    "butterfly of a 60-bit prime, 8 per FP64 butterfly of a prime below 2^46) over "
                                    "the VALU rate of 39.32 T lane-instructions/s"},
         "hbm_probe": probe,

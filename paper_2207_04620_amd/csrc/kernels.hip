@@ -137,8 +137,8 @@ std::string prof_report() {
 // a multiple of N2 apart (column pass), the last log N2 stages stay inside contiguous
 // rows of N2 elements (row pass).  A block holds NTT_E = 2048 elements: one row, or
 // NTT_E/N1 columns.  Each thread keeps 8 elements in registers and runs up to three
-// stages on them (a radix-8 round) between LDS exchanges; butterflies use Harvey's
-// lazy reduction (values in [0, 4q) forward, [0, 2q) inverse; q < 2^61).
+// stages on them (a radix-8 round) between LDS exchanges; integer butterflies are lazy
+// (below 16q in the 2048-point rows and the register columns, below 4q elsewhere; q < 2^60).
 //
 // Element (transform u, position j) of a block lives at LDS address j * T + u where
 // T is the number of transforms in the block (1 for rows, NTT_E / N1 for columns);
@@ -573,7 +573,7 @@ __device__ __forceinline__ void inv_cols_any(u64* s, int L1, const u64* W, const
 // stage: |x| < 19.3 q after 15 stages, where |x w mod q| < 0.95 q for q < 2^46.  Inverse
 // (Gentleman-Sande) rounds reduce their inputs to |x| <= q/2 + 1 first (x - rint(x / q) q) and stay
 // below 16 q.  One FP64 butterfly is 8 instructions (v_mul_f64, v_fma_f64, v_rndne_f64,
-// v_add_f64), against 27 for the 64-bit integer Shoup butterfly.  The quotient comes from the
+// v_add_f64), against 17 for the lazy integer butterfly.  The quotient comes from the
 // product instead of from a second table word w / q: one more step in the chain, but half the
 // twiddle bytes, loads and registers (the row passes spent more address-unit cycles on twiddles
 // than on the limbs).  Per batched step of 16 h = 64 products at N = 2^15, with the bank padding and the

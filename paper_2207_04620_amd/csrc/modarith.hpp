@@ -1,10 +1,11 @@
-// Device modular arithmetic over word-size primes q < 2^61 (gfx950, 64-wide waves).
+// Device modular arithmetic over word-size primes q < 2^60 (gfx950, 64-wide waves).
 //
 // Two reductions are used, both exact:
 //  - Shoup/Harvey products a*w mod q with a precomputed companion
 //    w' = floor(w 2^64 / q) for fixed operands (twiddles, per-limb constants);
-//  - Montgomery REDC with R = 2^64 for products with keys and masks stored as
-//    x R mod q, and for 128-bit multiply-accumulate chains (sum < q 2^64).
+//  - Montgomery reduction: R = 2^64 for products with masks stored as x R mod q and for
+//    128-bit multiply-accumulate chains (sum < q 2^64), R = 2^60 for column sums with
+//    switching keys (stored as x 2^60 mod q).
 // gfx950 has no 64-bit multiplier: the compiler lowers the 64x64 products to
 // v_mad_u64_u32 / v_mul_hi_u32 chains.
 #pragma once
