@@ -1341,7 +1341,8 @@ Grp Ctx::g_eval_gd(const Grp& x, int d, const std::vector<double>& target, bool 
         launch_sum_many(T, low + 1, 2 * B, D, y.p, y.ps, !first, stream);
         cnt[C_ADD] += (int64_t)B * (D.n - (first ? 1 : 0));
     };
-    if (direct && !pool.limit) {
+    // (from a few hundred members one term fills any launch, and a launch's jobs stay below the grid's limit)
+    if (direct && !pool.limit && (d + 2) * B <= 256) {
         std::vector<double> s0(x.scale);
         for (auto& s : s0) s *= s;
         for (int i = 0; i <= d; ++i) s0.insert(s0.end(), x.scale.begin(), x.scale.end());
