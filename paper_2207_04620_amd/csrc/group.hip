@@ -1341,8 +1341,9 @@ Grp Ctx::g_eval_gd(const Grp& x, int d, const std::vector<double>& target, bool 
         launch_sum_many(T, low + 1, 2 * B, D, y.p, y.ps, !first, stream);
         cnt[C_ADD] += (int64_t)B * (D.n - (first ? 1 : 0));
     };
-    // (from a few hundred members one term fills any launch, and a launch's jobs stay below the grid's limit)
-    if (direct && !pool.limit && (d + 2) * B <= 256) {
+    // up to about a hundred members a launch: sixteen ReLU at N = 2^16 25.2 ms so and 26.6 term by term, 32
+    // 50.0 and 52.4 but on 78 GB of buffers against 31
+    if (direct && !pool.limit && (d + 2) * B <= 96) {
         std::vector<double> s0(x.scale);
         for (auto& s : s0) s *= s;
         for (int i = 0; i <= d; ++i) s0.insert(s0.end(), x.scale.begin(), x.scale.end());
