@@ -968,10 +968,11 @@ CtPtr Ctx::tensor(const CtData& a, const CtData& b) {
 }
 
 // ---------------------------------------------------------------- key switching
-// out [2][nl][N] = ModDown(<digits of d permuted by g, key>) (+ sigma_g(c0) in out_0 for a rotation,
-// + add [2][nl][N] for a relinearisation), on the caller's lift [beta][ne][N], u [2][ne][N] and tmp [2][nl][N]
+// out (two polynomials of nl limbs, out_ps apart) = ModDown(<digits of d permuted by g, key>) (+ sigma_g(c0) in
+// out_0 for a rotation, + add [2][nl][N] for a relinearisation), on the caller's lift [beta][ne][N], u
+// [2][ne][N] and tmp [2][nl][N]
 void Ctx::ks_single_into(const u64* d, int level, const u64* key, u64 g, const u64* c0, const u64* add, u64* out,
-                         u64* lift, u64* u, u64* tmp) {
+                         int64_t out_ps, u64* lift, u64* u, u64* tmp) {
     const int64_t ps = (int64_t)(level + 1) * N;
     lift_into(d, 0, 1, level, lift, tmp);
     IpSet S;
@@ -986,7 +987,7 @@ void Ctx::ks_single_into(const u64* d, int level, const u64* key, u64 g, const u
         E.add[1] = add + ps;
     }
     E.out[0] = out;
-    E.out[1] = out + ps;
+    E.out[1] = out + out_ps;
     moddown_into(u, tmp, 1, level, E);
 }
 
@@ -994,7 +995,7 @@ void Ctx::ks_single_into(const u64* d, int level, const u64* key, u64 g, const u
 void Ctx::ks_single(const u64* d, int level, const u64* key, u64 g, const u64* c0, const u64* add, u64* out) {
     const int nl = level + 1, ne = nl + n_p;
     DBuf lift(this, mu[level].size() * (size_t)ne * N), u(this, 2 * (size_t)ne * N), tmp(this, 2 * (size_t)nl * N);
-    ks_single_into(d, level, key, g, c0, add, out, lift.p, u.p, tmp.p);
+    ks_single_into(d, level, key, g, c0, add, out, (int64_t)nl * N, lift.p, u.p, tmp.p);
 }
 
 CtPtr Ctx::relin(const CtData& a) {
@@ -1628,7 +1629,12 @@ he_status he_rotate_noalloc(he_ctx* ctx, const uint64_t* in, uint32_t level, int
         }
         const u64* key = c->rot_key(g, false);
         u64 *lift = c->scratch, *u = lift + lift_w, *tmp = u + u_w;
-        c->ks_single_into(in + (size_t)nl * N, (int)level, key, g, in, nullptr, out, lift, u, tmp);
+        // the row pass stores 16 bytes a lane: a result at an odd multiple of 8 bytes is made in place of
+        // the Q limbs of u (every lane reads its words of u before it writes them) and copied word by word
+        const bool odd = ((uintptr_t)out & 15) != 0;
+        c->ks_single_into(in + (size_t)nl * N, (int)level, key, g, in, nullptr, odd ? u : out,
+                          odd ? (int64_t)ne * N : (int64_t)nl * N, lift, u, tmp);
+        if (odd) launch_automorph(c->T, nl, 2, out, (int64_t)nl * N, u, (int64_t)ne * N, 1, c->stream);
         c->cnt[C_ROT]++;
     });
 }

@@ -294,7 +294,7 @@ struct Ctx {
     void rescale_into(const u64* a, int64_t a_ps, int l, int np, int B, u64* out, int64_t out_ps);
     void ks_single(const u64* d, int level, const u64* key, u64 g, const u64* c0, const u64* add, u64* out);
     void ks_single_into(const u64* d, int level, const u64* key, u64 g, const u64* c0, const u64* add, u64* out,
-                        u64* lift, u64* u, u64* tmp);
+                        int64_t out_ps, u64* lift, u64* u, u64* tmp);
     CtPtr relin(const CtData& a);
     CtPtr rescale(const CtData& a);
     CtPtr rotate(const CtData& a, int64_t k);
