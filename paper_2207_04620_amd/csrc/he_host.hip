@@ -68,24 +68,27 @@ void* Pool::alloc_locked(size_t bytes) {
         peak = std::max(peak, held - cached);
         return p;
     }
-    void* p = nullptr;
+    // the stream of a recording capture cannot be waited for (and nothing runs on it)
+    const bool wait = !capture && !(sibling && sibling->capture);
     if (limit && held + bytes > limit) {
-        trim_locked();  // cached blocks of other sizes go back to the device first
+        trim_locked(wait);  // cached blocks of other sizes go back to the device first
         if (held + bytes > limit) throw HeError(HE_ENOMEM);
     }
-    if (dev_alloc) {
-        p = dev_alloc(bytes, user);
-    } else if (hipMalloc(&p, bytes) != hipSuccess) {
+    const auto take = [&]() -> void* {
+        if (dev_alloc) return dev_alloc(bytes, user);
+        void* p = nullptr;
+        if (hipMalloc(&p, bytes) == hipSuccess) return p;
         (void)hipGetLastError();
-        trim_locked();
-        if (sibling) {  // the other cache's free blocks too (hipFree waits for the device)
+        return nullptr;
+    };
+    void* p = take();
+    if (!p) {  // the cached blocks of other sizes go back, the other cache's too
+        trim_locked(wait);
+        if (sibling) {
             std::lock_guard<std::mutex> lk2(sibling->m);
-            sibling->trim_locked();
+            sibling->trim_locked(wait);
         }
-        if (hipMalloc(&p, bytes) != hipSuccess) {
-            (void)hipGetLastError();
-            p = nullptr;
-        }
+        p = take();
     }
     if (!p) throw HeError(HE_ENOMEM);
     held += bytes;
@@ -108,7 +111,9 @@ void Pool::trim() {
     std::lock_guard<std::mutex> lk(m);
     trim_locked();
 }
-void Pool::trim_locked() {
+void Pool::trim_locked(bool wait) {
+    // hipFree waits for the device; a caller's free need not
+    if (dev_free && wait && owner && !free_.empty()) owner->drain();
     for (auto& kv : free_)
         for (void* p : kv.second) {
             if (dev_free) dev_free(p, user);
@@ -117,6 +122,11 @@ void Pool::trim_locked() {
             cached -= kv.first;
         }
     free_.clear();
+}
+
+void Ctx::drain() {
+    (void)hipStreamSynchronize(home);
+    if (side) (void)hipStreamSynchronize(side);
 }
 
 DBuf::DBuf(Ctx* c, size_t n_u64) : ctx(c), pool(c->alloc_side ? &c->pool_side : &c->pool), n(n_u64) {
@@ -1368,8 +1378,10 @@ he_status he_ctx_create(const he_params* prm, const he_device* dev, he_ctx** out
             hip_check(hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking), "stream");
             c->own_stream = true;
         }
+        c->home = c->stream;
         c->pool.sibling = &c->pool_side;
         c->pool_side.sibling = &c->pool;
+        c->pool.owner = c->pool_side.owner = c.get();
 
         std::vector<uint32_t> qb(prm->q_bits, prm->q_bits + prm->n_q), pb(prm->p_bits, prm->p_bits + prm->n_p);
         gen_primes(c->log_n, qb, c->mods);

@@ -37,6 +37,7 @@ struct GraphBlocks {
     std::unordered_map<size_t, std::vector<void*>> free_;
 };
 
+struct Ctx;
 struct Pool {
     std::mutex m;
     std::unordered_map<size_t, std::vector<void*>> free_;
@@ -45,6 +46,7 @@ struct Pool {
     size_t limit = 0;             // cap on held bytes (0: none); beyond it alloc is HE_ENOMEM
     size_t peak = 0;              // largest in-use byte count (held - cached) since the last reset
     Pool* sibling = nullptr;  // the context's other cache: its free blocks go back too when memory runs out
+    Ctx* owner = nullptr;     // drained before blocks go back to a caller's allocator
     void* (*dev_alloc)(size_t, void*) = nullptr;
     void (*dev_free)(void*, void*) = nullptr;
     void* user = nullptr;
@@ -52,7 +54,7 @@ struct Pool {
     void* alloc_locked(size_t bytes);
     void release(void* p, size_t bytes);
     void trim();
-    void trim_locked();
+    void trim_locked(bool wait = true);
     // bytes in use now; restart the peak figure from it
     size_t restart_peak() {
         std::lock_guard<std::mutex> lk(m);
@@ -66,7 +68,6 @@ struct Pool {
     }
 };
 
-struct Ctx;
 struct DBuf {
     Ctx* ctx;
     Pool* pool;  // the allocation cache it came from and goes back to
@@ -186,7 +187,9 @@ struct Ctx {
     int device = 0;            // the HIP device current at creation
     u64* scratch = nullptr;    // that device's copy of the allocation-free entry point's scratch
     hipStream_t stream = nullptr;
+    hipStream_t home = nullptr;  // the context stream, also while 'stream' stands for the side stream
     bool own_stream = false;
+    void drain();  // waits for both streams
     // second stream of the context: the next Step-2 pair group's key-switch inner products
     // run there while the current group's ModDown runs on the context stream (fork and join by
     // the two events; every buffer it touches is allocated after the fork and released only
