@@ -230,12 +230,13 @@ he_status he_transpose_batch(he_ctx *ctx, size_t n, const he_ct *const *a, uint3
 
 /* Scheduling knobs of the lockstep products; results never depend on them.  pair_batch:
  * rotation sets (Step-2 mask pairs, baby rotations) that share one key-switch inner-product
- * launch and one ModDown launch (1..16; until it is set or tuned, and without a pool limit, direct
- * calls with few members take more sets than the value read here); max_group: members per lockstep group (1..256);
- * overlap (0 or 1): the next Step-2 pair group's inner products run on the context's second
- * stream while the current group's ModDown runs on the context stream; concurrent_groups (0 or
- * 1): the (shape, level) groups of a batch with several of them are spread over the two
- * streams (the autotuner leaves it as set). */
+ * launch and one ModDown launch (1..16; default 4.  From 4 up, and without a pool limit, direct
+ * calls with fewer than 16 members share wider launches: more sets, and with up to 8 members the
+ * giant steps and block sums together; 1 to 3 keep every launch at that width, and the buffers
+ * with it); max_group: members per lockstep group (1..256); overlap (0 or 1): the next Step-2 pair
+ * group's inner products run on the context's second stream while the current group's ModDown runs
+ * on the context stream; concurrent_groups (0 or 1): the (shape, level) groups of a batch with
+ * several of them are spread over the two streams (the autotuner leaves it as set). */
 typedef struct {
     uint32_t pair_batch;
     uint32_t max_group;

@@ -26,8 +26,8 @@ static void copy2d(Ctx* c, u64* dst, int64_t dpitch, const u64* src, int64_t spi
 // where a step of 16 members stops gaining (pair_batch 8: 371.0 against 370.7 products/s).  One
 // h = 64 product at N = 2^15: 5.5 ms with 4 sets per launch, 4.8 with 16.
 int Ctx::sets_per_launch(int B, bool direct) const {
-    if (!pair_auto || !direct || pool.limit || pool_side.limit) return std::max(1, pair_batch);
-    return std::max(4, std::min(IP_MAXSET, 64 / std::max(1, B)));
+    if (!few_wide(direct)) return std::max(1, pair_batch);
+    return std::max(pair_batch, std::min(IP_MAXSET, 64 / std::max(1, B)));
 }
 
 // Up to 16 giant steps lifted and added together, and the rounds of the schedules without ModDown hoisting or
@@ -37,7 +37,7 @@ int Ctx::sets_per_launch(int B, bool direct) const {
 // N = 2^14 as printed: 7.41 ms round by round, 2.81 with 16 rounds together).  Nine members fill the
 // launches by themselves.
 bool Ctx::wide_giants(int B, bool direct) const {
-    return direct && pair_auto && !pool.limit && !pool_side.limit && B <= 8;
+    return few_wide(direct) && B <= 8;
 }
 
 // f(direct): a direct call's work, again with the knob's sets per launch if the wider

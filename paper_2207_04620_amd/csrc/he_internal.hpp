@@ -322,12 +322,14 @@ struct Ctx {
                                     const std::vector<MatShape>& shapes);
     std::vector<CtPtr> transpose_batch(const std::vector<const CtData*>& X, int h, int beta);
     int max_group = 32;
-    int pair_batch = 4;  // Step-2 mask pairs per shared ModDown launch
-    // Until the caller sets the knobs, a direct call with fewer than 16 members takes more sets per
+    int pair_batch = PAIR_DEFAULT;  // Step-2 mask pairs per shared ModDown launch
+    // From the default up, a direct call with fewer than 16 members takes more sets per
     // launch, so that a launch still covers about 64 (sets x members): one h = 64 product at N = 2^15 takes
-    // 12 ModDowns of 16 sets instead of 31 of 4 (measured at sets_per_launch).  Serving
-    // keeps the knob (its admission counts bytes per member), and so does a capped allocation cache
-    bool pair_auto = true;
+    // 12 ModDowns of 16 sets instead of 31 of 4 (measured at sets_per_launch).  A smaller knob is taken as it
+    // is.  Serving keeps the knob (its admission counts bytes per member), and so does a capped
+    // allocation cache
+    static constexpr int PAIR_DEFAULT = 4;
+    bool few_wide(bool direct) const { return direct && pair_batch >= PAIR_DEFAULT && !pool.limit; }
     int sets_per_launch(int B, bool direct) const;
     template <class F>
     void direct_call(F&& f);

@@ -82,7 +82,6 @@ he_status he_tuning_set(he_ctx* ctx, const he_tuning* t) {
         return HE_EINVAL;
     std::lock_guard<std::recursive_mutex> lk(ctx->c->api_mu);
     ctx->c->pair_batch = (int)t->pair_batch;
-    ctx->c->pair_auto = false;
     ctx->c->max_group = (int)t->max_group;
     ctx->c->overlap = (int)t->overlap;
     ctx->c->concurrent_groups = (int)t->concurrent_groups;
@@ -129,14 +128,12 @@ he_status he_autotune(he_ctx* ctx, uint32_t h, uint32_t level, uint32_t batch, c
             struct Restore {
                 Ctx* c;
                 int pb, mg, ov;
-                bool pa;
                 ~Restore() {
-                    c->pair_auto = pa;
                     c->pair_batch = pb;
                     c->max_group = mg;
                     c->overlap = ov;
                 }
-            } restore{c, c->pair_batch, c->max_group, c->overlap, c->pair_auto};
+            } restore{c, c->pair_batch, c->max_group, c->overlap};
             hipEvent_t e0, e1;
             hip_check(hipEventCreate(&e0), "tune event");
             hip_check(hipEventCreate(&e1), "tune event");
@@ -158,7 +155,6 @@ he_status he_autotune(he_ctx* ctx, uint32_t h, uint32_t level, uint32_t batch, c
                 return ms;
             };
             auto candidate = [&](int pb, int mg, int ov) {
-                c->pair_auto = false;
                 c->pair_batch = pb;
                 c->max_group = mg;
                 c->overlap = ov;
@@ -177,7 +173,7 @@ he_status he_autotune(he_ctx* ctx, uint32_t h, uint32_t level, uint32_t batch, c
                 }
             };
             // the context's own setting first: another candidate must beat it by 1 % to replace it
-            const int mg0 = std::min(restore.mg, (int)batch), pb0 = c->sets_per_launch(mg0, true);
+            const int pb0 = restore.pb, mg0 = std::min(restore.mg, (int)batch);
             candidate(pb0, mg0, 0);
             const int groups[2] = {(int)batch, (int)batch / 2};
             for (int gi = 0; gi < (batch >= 16 ? 2 : 1); ++gi)
@@ -199,7 +195,6 @@ he_status he_autotune(he_ctx* ctx, uint32_t h, uint32_t level, uint32_t batch, c
     }
     {
         std::lock_guard<std::recursive_mutex> lk(c->api_mu);
-        c->pair_auto = false;
         c->pair_batch = (int)best.pair_batch;
         c->max_group = (int)best.max_group;
         c->overlap = (int)best.overlap;
