@@ -115,8 +115,9 @@ he_status he_pool_stats(he_ctx *ctx, uint64_t *in_use, uint64_t *peak, int reset
 
 /* Ecd + Enc (Fig. 1 items 3 and 5): n_vals values (n_vals divides N/2) replicated to
  * N/2 slots, encoded at Delta (exact rounding, computed in 128-bit fixed point on the device, or in
- * 113-bit floating point on the host for values that are not finite or reach 2^62 when scaled),
- * encrypted with the public key at 'level' (<= L) using stream index 'nonce'. */
+ * 113-bit floating point on the host for values that are not finite or reach 2^62 when scaled, and
+ * where the device transform's buffers do not fit), encrypted with the public key at 'level' (<= L)
+ * using stream index 'nonce'. */
 he_status he_encrypt(he_ctx *ctx, const double *vals, size_t n_vals, uint32_t level, uint64_t nonce,
                      he_ct **out);
 /* Enc of an already-encoded plaintext: N signed integer coefficients at 'scale' */

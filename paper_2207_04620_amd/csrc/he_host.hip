@@ -742,7 +742,8 @@ CtPtr Ctx::encrypt_dev(const int64_t* dev_coeffs, int level, double scale, u64 n
 }
 
 // Ecd of host values into N device coefficients, on the device where its fixed point holds them: finite
-// values, a positive scale, results below 2^62; the 113-bit host encoder takes the rest
+// values, a positive scale, results below 2^62, and memory for the transform; the 113-bit host encoder takes
+// the rest
 void Ctx::encode_into(const double* vals, int64_t n_vals, double sc, int64_t* dev_out) {
     double mx = 0;
     bool finite = true;
@@ -754,23 +755,31 @@ void Ctx::encode_into(const double* vals, int64_t n_vals, double sc, int64_t* de
     int e = 0, es = 0;
     const double f = std::frexp(sc, &es);
     (void)std::frexp(mx, &e);
-    if (!finite || !(sc >= 2.2250738585072014e-308 && sc <= 1.7976931348623157e308) || (mx > 0 && e + es > 62) ||
-        !E.w) {
+    std::unique_ptr<DBuf> z, x;
+    const bool fixed = finite && sc >= 2.2250738585072014e-308 && sc <= 1.7976931348623157e308 && !(mx > 0 && e + es > 62);
+    try {
+        if (fixed) {
+            z = std::make_unique<DBuf>(this, (size_t)n_vals);
+            x = std::make_unique<DBuf>(this, (size_t)N * (sizeof(FixC) / 8));
+        }
+    } catch (const HeError& err) {
+        if (err.s != HE_ENOMEM) throw;
+    }
+    if (!x) {
         std::vector<int64_t> m(N);
         enc.encode(vals, n_vals, sc, m.data());
         upload(this, dev_out, m.data(), N * 8);
         return;
     }
     if (mx == 0) e = 62 - es;  // any range will do
-    DBuf z(this, (size_t)n_vals), x(this, (size_t)N * (sizeof(FixC) / 8));
-    upload(this, z.p, vals, n_vals * 8);
+    upload(this, z->p, vals, n_vals * 8);
     EncArgs A;
-    A.z = (const double*)z.p;
+    A.z = (const double*)z->p;
     A.vmask = (uint32_t)(n_vals - 1);
     A.shift = 125 - log_n - e;  // |values| 2^shift < 2^(125 - log N): sums of N stay below 2^125
     A.mant = (u64)std::ldexp(f, 53);
     A.sh = std::min(191, A.shift + log_n + 53 - es);  // 116 and up; at 191 every result rounds to 0
-    launch_encode(E, A, (FixC*)x.p, dev_out, stream);
+    launch_encode(E, A, (FixC*)x->p, dev_out, stream);
 }
 
 // device tables of the encoder and decoder, from the host encoder's
@@ -829,8 +838,38 @@ std::unique_ptr<DBuf> Ctx::decrypt_lifted(const CtData& c) {
     return out;
 }
 
+// The same on the host, with no more device memory than the residues take
+void Ctx::decrypt_lifted_host(const CtData& c, double* out) {
+    const int nl = c.level + 1;
+    DBuf m(this, (size_t)nl * N);
+    launch_dec_dot(T, nl, c.deg, c.buf->p, (int64_t)nl * N, s_eval->p, s2_eval->p, m.p, stream);
+    ntt(m.p, 1, 0, nl, true, -1);
+    std::vector<u64> h((size_t)nl * N);
+    hip_check(hipMemcpyAsync(h.data(), m.p, h.size() * 8, hipMemcpyDeviceToHost, stream), "dec copy");
+    hip_check(hipStreamSynchronize(stream), "dec sync");
+    const u64 q0 = mods[0], q1 = nl > 1 ? mods[1] : 1, q0inv = nl > 1 ? invmod(q0 % q1, q1) : 0;
+    const u128h Q = (u128h)q0 * q1;
+    for (int64_t t = 0; t < N; ++t) {
+        u128h w = h[t];
+        if (nl > 1) w += (u128h)q0 * mulmod((h[N + t] + q1 - h[t] % q1) % q1, q0inv, q1);
+        const __int128 v = w > Q / 2 ? (__int128)w - (__int128)Q : (__int128)w;
+        for (int i = 2; i < nl; ++i) {
+            const __int128 r = v % (__int128)mods[i];
+            if ((u64)(r < 0 ? r + (__int128)mods[i] : r) != h[(size_t)i * N + t]) throw HeError(HE_ESCALE);
+        }
+        out[t] = (double)v;
+    }
+}
+
 void Ctx::decrypt_coeffs(const CtData& c, double* out) {
-    auto v = decrypt_lifted(c);
+    std::unique_ptr<DBuf> v;
+    try {
+        v = decrypt_lifted(c);
+    } catch (const HeError& e) {
+        if (e.s != HE_ENOMEM) throw;
+        decrypt_lifted_host(c, out);
+        return;
+    }
     std::vector<double> h((size_t)N + 1);
     hip_check(hipMemcpyAsync(h.data(), v->p, h.size() * 8, hipMemcpyDeviceToHost, stream), "dec copy");
     hip_check(hipStreamSynchronize(stream), "dec sync");
@@ -843,13 +882,25 @@ void Ctx::decrypt_coeffs(const CtData& c, double* out) {
 // Dec + Dcd: the first n_out slot values (at most N / 2)
 void Ctx::decrypt_values(const CtData& c, double* out, size_t n_out) {
     const size_t n = std::min(n_out, (size_t)N / 2);
-    auto v = decrypt_lifted(c);
-    // the transform's buffer takes the values after use: x [N] complex, then values [n] and the flag
-    DBuf x(this, 2 * (size_t)N), vals(this, n + 1);
-    launch_decode(D, (const double*)v->p, c.scale, (DblC*)x.p, (int)n, (double*)vals.p, stream);
-    hip_check(hipMemcpyAsync(vals.p + n, v->p + N, 8, hipMemcpyDeviceToDevice, stream), "dec flag");
+    // the transform's buffer x [N] complex, then values [n] and the flag
+    std::unique_ptr<DBuf> v, x, vals;
+    try {
+        v = decrypt_lifted(c);
+        x = std::make_unique<DBuf>(this, 2 * (size_t)N);
+        vals = std::make_unique<DBuf>(this, n + 1);
+    } catch (const HeError& e) {  // does not fit: the residues alone may
+        if (e.s != HE_ENOMEM) throw;
+        v.reset();
+        x.reset();
+        std::vector<double> m((size_t)N);
+        decrypt_lifted_host(c, m.data());
+        enc.decode(m.data(), c.scale, out, (int64_t)n);
+        return;
+    }
+    launch_decode(D, (const double*)v->p, c.scale, (DblC*)x->p, (int)n, (double*)vals->p, stream);
+    hip_check(hipMemcpyAsync(vals->p + n, v->p + N, 8, hipMemcpyDeviceToDevice, stream), "dec flag");
     std::vector<double> h(n + 1);
-    hip_check(hipMemcpyAsync(h.data(), vals.p, h.size() * 8, hipMemcpyDeviceToHost, stream), "dec copy");
+    hip_check(hipMemcpyAsync(h.data(), vals->p, h.size() * 8, hipMemcpyDeviceToHost, stream), "dec copy");
     hip_check(hipStreamSynchronize(stream), "dec sync");
     uint32_t bad;
     memcpy(&bad, &h[n], 4);
@@ -1100,9 +1151,10 @@ CtPtr Ctx::fl_update(const CtData& w, const std::vector<const CtData*>& grads, d
     }
     cnt[C_ADD] += (int64_t)grads.size() - 1;
     const double ql = (double)mods[lvl];
-    DBuf m(this, N);
-    encode_into(&coeff, 1, ql, (int64_t*)m.p);
-    auto pt = plaintext_mont_dev((const int64_t*)m.p);
+    auto m = std::make_unique<DBuf>(this, N);
+    encode_into(&coeff, 1, ql, (int64_t*)m->p);
+    auto pt = plaintext_mont_dev((const int64_t*)m->p);
+    m.reset();
     CtPtr t = mask_sum({{sum.get(), pt->p}}, ql);
     CtPtr u = rescale(*t);
     CtPtr wd = drop(w, std::min(u->level, w.level));
@@ -1464,9 +1516,16 @@ he_status he_encode(he_ctx* ctx, const double* vals, size_t n_vals, double scale
     if (!ctx || !vals || !out || n_vals == 0 || (size_t)(ctx->c->N / 2) % n_vals) return HE_EINVAL;
     return guardc(ctx, [&]() {
         Ctx* c = ctx->c.get();
-        DBuf m(c, c->N);
-        c->encode_into(vals, (int64_t)n_vals, scale, (int64_t*)m.p);
-        hip_check(hipMemcpyAsync(out, m.p, c->N * 8, hipMemcpyDeviceToHost, c->stream), "encode d2h");
+        std::unique_ptr<DBuf> m;
+        try {
+            m = std::make_unique<DBuf>(c, c->N);
+        } catch (const HeError& e) {  // no device memory at all: on the host
+            if (e.s != HE_ENOMEM) throw;
+            c->enc.encode(vals, (int64_t)n_vals, scale, out);
+            return;
+        }
+        c->encode_into(vals, (int64_t)n_vals, scale, (int64_t*)m->p);
+        hip_check(hipMemcpyAsync(out, m->p, c->N * 8, hipMemcpyDeviceToHost, c->stream), "encode d2h");
         hip_check(hipStreamSynchronize(c->stream), "encode sync");
     });
 }

@@ -259,6 +259,7 @@ struct Ctx {
     CtPtr encrypt_dev(const int64_t* dev_coeffs, int level, double scale, u64 nonce);
     std::unique_ptr<DBuf> plaintext_mont_dev(const int64_t* dev_coeffs);
     std::unique_ptr<DBuf> decrypt_lifted(const CtData& c);
+    void decrypt_lifted_host(const CtData& c, double* out);
     void decrypt_values(const CtData& c, double* out, size_t n_out);
     // keys
     std::unique_ptr<DBuf> s_eval, s2_eval, pk, rlk;
