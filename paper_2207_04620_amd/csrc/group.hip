@@ -1382,9 +1382,11 @@ Grp Ctx::g_eval_gd(const Grp& x, int d, const std::vector<double>& target, bool 
     }
     for (int b = 0; b < nb; ++b) pw[b] = b ? g_mul_rs(pw[b - 1], pw[b - 1]) : g_mul_rs(x, x);
     for (int i = 0; i <= d; ++i) {
-        Grp xc = g_new(B, x.level, 1, x.scale);
-        g_mul_ints(x, std::vector<int64_t>(K.begin() + i * B, K.begin() + (i + 1) * B), xc);
-        term[i] = g_rescale(xc);
+        {
+            Grp xc = g_new(B, x.level, 1, x.scale);
+            g_mul_ints(x, std::vector<int64_t>(K.begin() + i * B, K.begin() + (i + 1) * B), xc);
+            term[i] = g_rescale(xc);
+        }
         set_need(i);
         for (int b = 0; b < nb; ++b)
             if ((i >> b) & 1) term[i] = g_mul_rs(term[i], pw[b]);
