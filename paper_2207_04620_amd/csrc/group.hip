@@ -1286,6 +1286,21 @@ void Ctx::g_mul_ints(const Grp& a, const std::vector<int64_t>& K, const Grp& out
 
 Grp Ctx::g_mul_rs(const Grp& x, const Grp& y) { return g_rescale(g_relin(g_tensor(x, y))); }
 
+// Whether g_d of B members may go by level.  Its largest steps, a launch over x^2 and the d + 1 multiples of x
+// at the top and the first power's products below it, stay within the launch grid (65535 limbs in y) and
+// within GD_BYTES.  By level is faster at every size tried, by less as the launches fill the device: N = 2^12, d = 1,
+// 20 members 0.20 ms and 0.23 term by term, 200 members 1.01 and 1.07; N = 2^14, d = 3, 32 members 3.36 and 3.82;
+// N = 2^16, d = 3, 16 members 24.1 and 25.6.  But the cache then holds three times the bytes (blocks of
+// every level's sizes: 37.9 GB against 15.2 in the last case, five to six times the largest step), so the line is
+// the memory: 20 members at N = 2^16, 32 at N = 2^15.
+bool Ctx::gd_by_level(int level, int B, int d) const {
+    const int64_t nl = level, ne = nl + n_p, beta = (int64_t)mu[level - 1].size();  // of the products
+    const int64_t all = (int64_t)(d + 2) * B, prod = (int64_t)((d + 1) / 2 + 1) * B;
+    // top, its rescale's converted limbs and result; then that result, the tensor, lift, u, conv and result
+    const int64_t top = all * (2 * (nl + 1) + 1 + 4 * nl), mul = all * 2 * nl + prod * (3 * nl + beta * ne + 2 * ne + 4 * nl);
+    return std::max(all * 2 * nl, prod * (beta * ne - nl)) <= 65535 && std::max(top, mul) * 8 * N <= GD_BYTES;
+}
+
 // g_d(x) = sum_i c_{2i+1} x^(2i+1): x_c = RS(x * round(c q_l)) lands at the scale of x;
 // x^(2i) comes from the powers x^2, x^4, ... multiplied in along the set bits of i.
 // A direct call takes everything of one level in one pass: the multiples x_c with x^2, then per power its
@@ -1341,9 +1356,7 @@ Grp Ctx::g_eval_gd(const Grp& x, int d, const std::vector<double>& target, bool 
         launch_sum_many(T, low + 1, 2 * B, D, y.p, y.ps, !first, stream);
         cnt[C_ADD] += (int64_t)B * (D.n - (first ? 1 : 0));
     };
-    // up to about a hundred members a launch: sixteen ReLU at N = 2^16 25.2 ms so and 26.6 term by term, 32
-    // 50.0 and 52.4 but on 78 GB of buffers against 31
-    if (direct && !pool.limit && (d + 2) * B <= 96) {
+    if (few_wide(direct) && gd_by_level(x.level, B, d)) {
         std::vector<double> s0(x.scale);
         for (auto& s : s0) s *= s;
         for (int i = 0; i <= d; ++i) s0.insert(s0.end(), x.scale.begin(), x.scale.end());

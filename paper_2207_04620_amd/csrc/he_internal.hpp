@@ -392,6 +392,8 @@ struct Ctx {
     bool matmul_step(MatmulJob& J, int k_chunk);
     void g_mul_ints(const Grp& a, const std::vector<int64_t>& k, const Grp& out);
     Grp g_mul_rs(const Grp& x, const Grp& y);
+    static constexpr int64_t GD_BYTES = 8ll << 30;
+    bool gd_by_level(int level, int B, int d) const;
     Grp g_eval_gd(const Grp& x, int d, const std::vector<double>& target, bool direct);
     bool sign_step(SignJob& J);
     std::vector<CtPtr> sign_group(const std::vector<const CtData*>& X, int d, int k, int mode,
