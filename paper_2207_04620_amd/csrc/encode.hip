@@ -1,12 +1,11 @@
 // Encoding and decoding on the device.
 //
 // Ecd (Fig. 1 item 3) is m_i = round(scale / N Re(zeta^-i sum_u W_u omega^(-u i))) with the slot
-// values at the odd exponents 2u + 1 = +-5^j.  The transform runs in 128-bit fixed point: values
-// scaled by the power of two that leaves log2 N bits of growth below 2^125, twiddles by 2^126
-// (converted from the host's 113-bit tables), every product exact to 2^-126 of its operand, and
-// the last product with the scale exact before the one rounding (half away from zero).  A slot value keeps
-// 2^-110 of the largest one at N = 2^15; the 113-bit floating-point form on the host keeps 2^-113 of
-// a sum that grows by up to N.  Both round to the same integers.
+// values at the odd exponents 2u + 1 = +-5^j.  The transform runs in 128-bit fixed point (fix128.hpp):
+// values scaled by the power of two that brings the largest below 2^125, halved in every stage, twiddles by
+// 2^126, every product rounded once, and the last product with the scale exact before the one rounding (half
+// away from zero).  Its error is below that of the 113-bit floating-point form on the host, and both
+// round to the same integers.
 //
 // The work is N / 2 log2 N butterflies of four 128-bit products (about 270 instructions each): nothing for the device, so
 // the time is launches and their latency, and a pass takes two stages per thread (three would halve
@@ -16,29 +15,13 @@
 // limbs check that), rounded to doubles and transformed in double precision in the host
 // decoder's order of operations.
 #include "kernels.hpp"
+#include "fix128.hpp"
 
 #include <stdexcept>
 
 #define TPB 256
-typedef __int128 i128;
-typedef unsigned __int128 u128;
 
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
-
-// a b 2^-126 (floor), for |b| <= 2^126
-__device__ __forceinline__ i128 mul_fix(i128 a, i128 b) {
-    const u64 al = (u64)a, ah = (u64)((u128)a >> 64), bl = (u64)b, bh = (u64)((u128)b >> 64);
-    u64 l0, h0, l1, h1, l2, h2, l3, h3;
-    mul_wide(al, bl, l0, h0);
-    mul_wide(al, bh, l1, h1);
-    mul_wide(ah, bl, l2, h2);
-    mul_wide(ah, bh, l3, h3);
-    const u128 mid = (u128)h0 + l1 + l2;
-    u128 top = (((u128)h3 << 64) | l3) + h1 + h2 + (u64)(mid >> 64);
-    if (a < 0) top -= (u128)b;  // the two's-complement words as signed numbers
-    if (b < 0) top -= (u128)a;
-    return (i128)((top << 2) | ((u64)mid >> 62));
-}
 
 struct FixOps {
     typedef FixC C;
@@ -48,10 +31,10 @@ struct FixOps {
         return C{(u64)re, (u64)((u128)re >> 64), (u64)im, (u64)((u128)im >> 64)};
     }
     static __device__ __forceinline__ void bfly(C& p, C& q, const C& w) {
-        const i128 pr = val(p.rl, p.rh), pi = val(p.il, p.ih), qr = val(q.rl, q.rh), qi = val(q.il, q.ih);
-        const i128 c = val(w.rl, w.rh), s = val(w.il, w.ih), ur = pr - qr, ui = pi - qi;
-        p = pack(pr + qr, pi + qi);
-        q = pack(mul_fix(ur, c) - mul_fix(ui, s), mul_fix(ur, s) + mul_fix(ui, c));
+        i128 pr = val(p.rl, p.rh), pi = val(p.il, p.ih), qr = val(q.rl, q.rh), qi = val(q.il, q.ih);
+        bfly_fix(pr, pi, qr, qi, val(w.rl, w.rh), val(w.il, w.ih));
+        p = pack(pr, pi);
+        q = pack(qr, qi);
     }
 };
 // the host decoder's arithmetic: no contraction into fused multiply-adds
@@ -98,16 +81,6 @@ __device__ __forceinline__ void fft_pass(int log_n, int log_half, const typename
     }
 }
 
-// z 2^shift as an integer, truncated
-__device__ __forceinline__ i128 to_fix(double z, int shift) {
-    const u64 b = (u64)__double_as_longlong(z);
-    const int eb = (int)(b >> 52) & 2047;
-    const u64 m = (b & 0xfffffffffffffull) | (eb ? 1ull << 52 : 0);
-    const int s = (eb ? eb : 1) - 1075 + shift;
-    const i128 v = s >= 0 ? (i128)((u128)m << s) : s > -64 ? (i128)(m >> -s) : 0;
-    return (int64_t)b < 0 ? -v : v;
-}
-
 template <int R, bool FIRST, bool LAST>
 __global__ __launch_bounds__(TPB) void k_encode_pass(EncTables E, EncArgs A, int log_half, FixC* x, int64_t* out) {
     const auto load = [&](int p) {
@@ -120,8 +93,8 @@ __global__ __launch_bounds__(TPB) void k_encode_pass(EncTables E, EncArgs A, int
         } else {
             const int i = (int)brev_bits((u32)p, E.log_n);
             const FixC z = E.twist[i];
-            const i128 y = mul_fix(FixOps::val(v.rl, v.rh), FixOps::val(z.rl, z.rh)) -
-                           mul_fix(FixOps::val(v.il, v.ih), FixOps::val(z.il, z.ih));
+            const i128 y = mul_fix<126>(FixOps::val(v.rl, v.rh), FixOps::val(z.rl, z.rh)) -
+                           mul_fix<126>(FixOps::val(v.il, v.ih), FixOps::val(z.il, z.ih));
             // |y| mant 2^-sh, rounded half up
             const u128 a = (u128)(y < 0 ? -y : y);
             u64 p0, p1, c, t;

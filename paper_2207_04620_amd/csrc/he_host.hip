@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "../../include/he.h"
+#include "fix128.hpp"
 #include "he_internal.hpp"
 
 using namespace hm;
@@ -776,28 +777,22 @@ void Ctx::encode_into(const double* vals, int64_t n_vals, double sc, int64_t* de
     EncArgs A;
     A.z = (const double*)z->p;
     A.vmask = (uint32_t)(n_vals - 1);
-    A.shift = 125 - log_n - e;  // |values| 2^shift < 2^(125 - log N): sums of N stay below 2^125
+    A.shift = 125 - e;  // |values| 2^shift < 2^125, and every stage halves
     A.mant = (u64)std::ldexp(f, 53);
-    A.sh = std::min(191, A.shift + log_n + 53 - es);  // 116 and up; at 191 every result rounds to 0
+    A.sh = std::min(191, A.shift + 53 - es);  // 116 and up; at 191 every result rounds to 0
     launch_encode(E, A, (FixC*)x->p, dev_out, stream);
 }
 
-// device tables of the encoder and decoder, from the host encoder's
+// device tables of the encoder and decoder
 void Ctx::build_encoder() {
-    const auto fix = [](f128 v, u64& lo, u64& hi) {
-        const __int128 r = (__int128)(v * (f128)((__int128)1 << 126));  // exact: 113 bits
-        lo = (u64)r;
-        hi = (u64)((unsigned __int128)r >> 64);
-    };
     const size_t n = (size_t)N;
-    std::vector<FixC> f(n + n / 2);
-    for (size_t k = 0; k < n / 2; ++k) {
-        fix(enc.wr[k], f[k].rl, f[k].rh);
-        fix(enc.wi[k], f[k].il, f[k].ih);
-    }
+    std::vector<i128> zr(n), zi(n);
+    twist_fix(log_n, zr.data(), zi.data());
+    std::vector<FixC> f(n + n / 2);  // w, then twist
     for (size_t i = 0; i < n; ++i) {
-        fix(enc.zr[i], f[n / 2 + i].rl, f[n / 2 + i].rh);
-        fix(enc.zi[i], f[n / 2 + i].il, f[n / 2 + i].ih);
+        const FixC z = {(u64)zr[i], (u64)((u128)zr[i] >> 64), (u64)zi[i], (u64)((u128)zi[i] >> 64)};
+        f[n / 2 + i] = z;
+        if (i % 2 == 0) f[i / 2] = z;
     }
     std::vector<uint32_t> slot(n), pos(n / 2);
     for (size_t j = 0; j < n / 2; ++j) {
