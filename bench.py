@@ -59,6 +59,21 @@ def log(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
+def settle(nbytes):
+    """wait until the driver has cleared memory just returned to the device.  It does so at about 45
+    GB/s, and hipMalloc waits for it once the rest is taken: 170 GB taken again at once need 3.9 s, single
+    calls up to 2.5 s; four seconds later 0.08 s.  The legs return up to 108 GB each, and one in four
+    bursts on the servers made right after them stood still for 0.3 to 1 s."""
+    time.sleep(nbytes / 40e9)
+
+
+def close(*contexts):
+    held = sum(c.memory()[1] for c in contexts)
+    for c in contexts:
+        c.close()
+    settle(held)
+
+
 SCHEDULES = {"each": 0, "once": 1, "once+hoist": 3, "once+hoist+late": 7, "fast": 15}
 SCHEDULE_TEXT = {0: "relinearise every Step-3 product (Alg. 3 as printed)",
                  1: "relinearise once per product",
@@ -201,7 +216,7 @@ def mixed_leg(he, I, prm, sched, stream, count):
     ctx.matmul_batch(As, Bs, hs)
     ctx.sync()
     dt = time.perf_counter() - t0
-    ctx.close()
+    close(ctx)
     counts = {h: hs.count(h) for h in (16, 32, 64)}
     return {"products": count, "h_counts": counts, "levels": "uniform over [3, 13]",
             "matmuls_per_s": round(count / dt, 3), "ms": round(dt * 1e3, 1)}
@@ -233,7 +248,7 @@ def c4_leg(he, I, sched, stream, count):
     g3 = lambda v: (35 * v - 35 * v ** 3 + 21 * v ** 5 - 5 * v ** 7) / 16  # noqa: E731
     relu = (X[0] + X[0] * g3(g3(g3(X[0])))) / 2
     err = float(np.abs(ctx.decrypt(ms[0], 1024).reshape(32, 32) - relu @ W).max())
-    ctx.close()
+    close(ctx)
     return {"ciphertexts": count, "relu_per_s": round(count / (t1 - t0), 2),
             "h32_matmuls_per_s": round(count / (t2 - t1), 2),
             "end_to_end_per_s": round(count / (t2 - t0), 2), "max_abs_error": err}
@@ -354,8 +369,7 @@ def serve_rings_leg(he, I, sched, nreq, load):
         runs.append({"load": ld, **run_at(ld * pcap)})
     for srv in servers.values():
         srv.stop()
-    for c in rings:
-        c.close()
+    close(*rings)
     return {"requests": nreq, "rings": "N=2^14 (C2), 2^15 (C3), 2^16 (C4)", "types": len(set(kinds)),
             "batching_window": {"min_batch": 8, "max_wait_ms": 40, "per_type": True},
             "burst_capacity_per_s": round(capacity, 1), "poisson_capacity_per_s": round(pcap, 1),
@@ -390,7 +404,7 @@ def shapes_leg(he, I, prm, sched, stream, batch):
     ctx.sync()
     dt = time.perf_counter() - t0
     out["transpose_h64"] = {"transposes_per_s": round(batch / dt, 2), "ms_per_batch": round(dt * 1e3, 1)}
-    ctx.close()
+    close(ctx)
     out["batch"] = batch
     return out
 
@@ -616,7 +630,7 @@ def main():
             others[name] = round(args.batch / (time.perf_counter() - t0), 4)
             log(f"schedule '{name}': {others[name]:.3f} products/s")
             del As2, Bs2
-            ctx2.close()
+            close(ctx2)
 
     # the dominant kernel, timed over the timed region, against the roof that binds it: HBM
     # for every kernel whose algorithmic bytes at 8 TB/s take longer than its arithmetic (a
@@ -705,8 +719,10 @@ def main():
     }
     # the other legs make contexts of their own: the headline context gives its cached device
     # blocks back first (it keeps its keys and inputs)
+    held = ctx.memory()[1]
     ctx.pool_limit(1)
     ctx.pool_limit(0)
+    settle(held - ctx.memory()[1])
     if not args.no_shapes:
         log("packed (iota_4), rectangular (16 x 64) and transposition legs")
         result["shapes"] = shapes_leg(he, I, prm, sched, stream, args.batch)
