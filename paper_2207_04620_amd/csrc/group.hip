@@ -1220,25 +1220,6 @@ bool Ctx::matmul_step(MatmulJob& J, int k_chunk) {
     return true;
 }
 
-std::vector<CtPtr> Ctx::matmul_group(const std::vector<const CtData*>& A, const std::vector<const CtData*>& Bv,
-                                     const MatShape& sh, int lvl) {
-    std::vector<CtPtr> result;
-    direct_call([&](bool direct) {
-        MatmulJob J;
-        J.A = A;
-        J.B = Bv;
-        J.h = sh.h;
-        J.t = sh.t;
-        J.beta = sh.beta;
-        J.lvl = lvl;
-        J.direct = direct;
-        while (!matmul_step(J, sh.h)) {
-        }
-        result = J.result;
-    });
-    return result;
-}
-
 // ------------------------------------------------------------------ sign (Sec. 4.2), lockstep
 // numerators of the m^(2i+1) coefficients of g_d over 2^(2d-1)
 static std::vector<int64_t> gd_numerators(int d) {

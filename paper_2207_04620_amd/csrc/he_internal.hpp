@@ -387,8 +387,6 @@ struct Ctx {
     Grp g_relin(const Grp& a);
     void g_relin_into(const Grp& a, const Grp& out);
     Grp g_lintrans(const Grp& a, int kind, int h, int beta, int64_t unit, int dlo, int dhi, bool direct);
-    std::vector<CtPtr> matmul_group(const std::vector<const CtData*>& A, const std::vector<const CtData*>& B,
-                                    const MatShape& s, int lvl);
     bool matmul_step(MatmulJob& J, int k_chunk);
     void g_mul_ints(const Grp& a, const std::vector<int64_t>& k, const Grp& out);
     Grp g_mul_rs(const Grp& x, const Grp& y);

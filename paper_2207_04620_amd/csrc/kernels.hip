@@ -28,7 +28,7 @@ static bool misaligned16(const void* p) { return ((uintptr_t)p & 15) != 0; }
 // and each result written once (tables of constants excluded).
 static const char* const kProfNames[PK_COUNT] = {
     "ntt_fwd_cols", "ntt_fwd_rows", "ntt_inv_rows", "ntt_inv_cols", "baseconv", "inner_product",
-    "moddown_combine", "rescale_spread", "rescale_combine", "tensor", "mask_mac", "automorph", "elementwise",
+    "rescale_spread", "tensor", "mask_mac", "automorph", "elementwise",
     "conv_ntt_cols", "copy"};
 struct ProfRec {
     int kind;
@@ -1976,10 +1976,9 @@ __global__ __launch_bounds__(TPB) void k_copy(CopyDesc D) {
         st2(dst + c, ld2(src + c));
 }
 
-void launch_copy(CopyDesc& D, hipStream_t st) {
+void launch_copy(const CopyDesc& D, hipStream_t st) {
     if (D.n <= 0) return;
     if (D.n > CP_MAX) throw std::runtime_error("copy: too many regions");
-    D.start[0] = 0;
     double bytes = 0;
     int64_t wmax = 0;
     int rmax = 0;
@@ -1987,12 +1986,11 @@ void launch_copy(CopyDesc& D, hipStream_t st) {
         if ((D.width[r] & 1) || (D.spitch[r] & 1) || (D.dpitch[r] & 1) || misaligned16(D.src[r]) ||
             misaligned16(D.dst[r]) || D.rows[r] < 0 || D.width[r] < 0 || D.rows[r] > 65535)
             throw std::runtime_error("copy: region not 16-byte aligned");
-        D.start[r + 1] = D.start[r] + (D.width[r] >> 1) * D.rows[r];
         bytes += 16.0 * D.width[r] * D.rows[r];
         wmax = std::max(wmax, D.width[r]);
         rmax = std::max(rmax, D.rows[r]);
     }
-    if (D.start[D.n] == 0) return;
+    if (bytes == 0) return;
     // about 4 word pairs per thread along a row
     const int64_t bx = std::max<int64_t>(1, std::min<int64_t>(ceil_div(wmax / 2, 4 * TPB), 1024));
     ProfScope p(PK_COPY, bytes, st);
@@ -2250,7 +2248,6 @@ __global__ __launch_bounds__(TPB) void k_ew(DevTables T, ModMap mm, int npoly, u
     switch (op) {
         case EW_ADD: r = add_mod(x, y, m.q); break;
         case EW_SUB: r = sub_mod(x, y, m.q); break;
-        case EW_MUL_MONT: r = mul_mont(x, y, m.q, m.qninv); break;
         default: r = mul_plain(x, y, m); break;
     }
     out[p * out_ps + o] = r;
@@ -2375,14 +2372,11 @@ void launch_swk_finish(const DevTables& T, int M, u64* b, const u64* a, const u6
 // gather: the digits of sigma_g(c1) are the permuted digits of c1 (hoisting).
 // The key values of one (limb, coefficient) are loaded once and reused for every
 // ciphertext of the group: a switching key crosses HBM once per launch.
-// one rotation's key-switch inner product of one member, reduced: sum_j x_j key_j (+ P
-// sigma_g(c0) on the Q limbs), optionally times a Montgomery-form mask; x are the member's
-// lift words at the automorphism source position
-// up to seven digits (plus the c0 term) use the carry-free column sums with the key words
-// split at bit 30; eight digits use 128-bit accumulation
 // The inner products of all NR rotations of one member for one slot, below 16 q: sum_r sum_j x_rj k_rj (+ z_r pm_r
-// on the Q limbs), k and pm times 2^60, a rotation's mask folded into them (mask . sum_j x_j k_j = sum_j x_j (k_j
-// . mask) mod q).  Up to eight products share one set of column sums and one reduction.
+// on the Q limbs), x_r the member's lift words at the automorphism source position, k and pm times 2^60 and split at
+// bit 30, a rotation's mask folded into them (mask . sum_j x_j k_j = sum_j x_j (k_j . mask) mod q).  Up to eight
+// products share one set of carry-free column sums and one reduction; eight digits take two sets, of four and the
+// c0 term and of four.
 template <int NB, int NR>
 __device__ __forceinline__ void ip_reduce(const u64 (&x)[NR][NB], const u64 (&z)[NR], const Split30 (&kb)[NR][NB],
                                           const Split30 (&ka)[NR][NB], const Split30 (&pm)[NR], bool with_c0,

@@ -41,7 +41,6 @@ struct CopyDesc {
     u64* dst[CP_MAX];
     int64_t width[CP_MAX], spitch[CP_MAX], dpitch[CP_MAX];
     int rows[CP_MAX];
-    int64_t start[CP_MAX + 1];  // word pairs before region r
 };
 
 // limb i of an (extended) polynomial -> prime index
@@ -260,7 +259,7 @@ struct MacDesc {
     int nct;
 };
 
-enum EwOp { EW_ADD = 0, EW_SUB = 1, EW_MUL_MONT = 2, EW_MUL_PLAIN = 3 };
+enum EwOp { EW_ADD, EW_SUB, EW_MUL_PLAIN };
 
 // ModDown epilogue fused into a forward NTT over the converted P-part: for job k of
 // ciphertext c (limb t = k % nl of poly p = k / nl) the transformed value v is not
@@ -286,8 +285,8 @@ struct Epi {
 
 // ------------------------------------------------------------------ launch timing
 enum ProfKind {
-    PK_NTT_FWD_COLS = 0, PK_NTT_FWD_ROWS, PK_NTT_INV_ROWS, PK_NTT_INV_COLS, PK_BASECONV, PK_INNER, PK_MODDOWN,
-    PK_RS_SPREAD, PK_RS_COMBINE, PK_TENSOR, PK_MASKMAC, PK_AUTOMORPH, PK_EW, PK_CONV_COLS, PK_COPY, PK_COUNT
+    PK_NTT_FWD_COLS = 0, PK_NTT_FWD_ROWS, PK_NTT_INV_ROWS, PK_NTT_INV_COLS, PK_BASECONV, PK_INNER,
+    PK_RS_SPREAD, PK_TENSOR, PK_MASKMAC, PK_AUTOMORPH, PK_EW, PK_CONV_COLS, PK_COPY, PK_COUNT
 };
 #include <string>
 // times the launches in its scope while launch timing is on; ops: butterflies of the launch, fp_ops of
@@ -350,14 +349,13 @@ void launch_conv_cols(const DevTables& T, const ConvDesc& D, hipStream_t st);
 void launch_sample(const DevTables& T, const Jobs& J, const SampleArgs& A, hipStream_t st);
 // n words to zero
 void launch_zero(u64* p, int64_t n, hipStream_t st);
-// the regions of D (start[] is filled here)
-void launch_copy(CopyDesc& D, hipStream_t st);
+// the regions of D
+void launch_copy(const CopyDesc& D, hipStream_t st);
 // out[p][i] = a[p][i] (op) b[p][i] over nl limbs (prime map mm) and npoly polys;
 // b_ps = 0 broadcasts one b polynomial to every poly
 void launch_ew(const DevTables& T, ModMap mm, int nl, int npoly, u64* out, int64_t out_ps, const u64* a,
                int64_t a_ps, const u64* b, int64_t b_ps, int op, hipStream_t st, int nct = 1, int64_t out_cs = 0,
                int64_t a_cs = 0, int64_t b_cs = 0);
-// out[p][i] = a[p][i] * c_i (Shoup constants in device arrays c, c_sh indexed by limb)
 // out_k[c] = K[k nct + c] a[c] for npoly polynomials of nct members (member stride a_cs in both)
 #define MI_MAX 256
 struct MulIntDesc {
@@ -380,7 +378,6 @@ void launch_inner_product(const DevTables& T, const IpDesc& D, hipStream_t st);
 // tmp[p][i] = centered(last[p]) mod q_i (coefficient form)
 void launch_rescale_spread(const DevTables& T, int nl_out, int npoly, const u64* last, int64_t last_ps,
                            int last_mod, u64* tmp, int64_t tmp_ps, hipStream_t st);
-// d0 (+)= a0 b0, d1 (+)= a0 b1 + a1 b0, d2 (+)= a1 b1
 // out[p][i] (+)= sum_r in_r[p][i] mask_r[i]  (masks in Montgomery form, compact [nl_top][N])
 void launch_mask_mac(const DevTables& T, int nl, int npoly, const MacDesc& D, u64* out, int64_t out_ps, int acc,
                      hipStream_t st, int64_t out_cs = 0);

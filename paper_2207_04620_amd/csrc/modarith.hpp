@@ -108,10 +108,6 @@ __device__ __forceinline__ void mac128(Acc128& acc, u64 a, u64 b) {
     acc.lo += lo;
     acc.hi += hi + (acc.lo < lo ? 1 : 0);
 }
-__device__ __forceinline__ void add128(Acc128& acc, u64 a) {
-    acc.lo += a;
-    acc.hi += (acc.lo < a ? 1 : 0);
-}
 
 // Sums of up to eight products of residues below 2^60 with no carry handling: each operand
 // is split at bit 30 (x = x.hi 2^30 + x.lo), and the four 30 x 30-bit partial products go
