@@ -1283,11 +1283,12 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(8))) void k
 // forward column stages of target l >> 4 in registers too: only the twiddles are in LDS, and neither
 // the prepared sources nor an unconverted word cross memory.  It replaces the inverse column pass
 // (a read and a write of every source limb) and a conversion of 4 v_mad_i64_i32 per source and
-// output on the vector unit.  Bound: the vector unit, about 85 % busy in the butterflies and
-// reductions (3890 instructions per wave of a ModDown from 4 primes to 13); the matrix unit is
-// busy a sixth of the time.  Measured at N = 2^15 (14 + 4 limbs), per batched step of 16 h = 64
-// products: 7.7 ms for every ModUp, ModDown and rescale against 10.4 ms of inverse column passes
-// and conversions (and 0.5 ms of separate rescale kernels) before; one rotation 137 -> 84 us.
+// output on the vector unit.  Bound: the vector unit (a wave issues
+// its instructions in 20 % of its cycles, at four waves per SIMD; 3375 a wave of a ModDown from 4 primes to 13
+// in the batched step, 4070 of a ModUp); the matrix unit is busy a tenth of the time.  Measured at N = 2^15 (14 +
+// 4 limbs), per batched step of 16 h = 64 products: 6.5 ms for every ModUp, ModDown and rescale (150 us a ModDown
+// of four pairs, 574 MB) against 10.4 ms of inverse column passes and conversions (and 0.5 ms of
+// separate rescale kernels) before; one rotation 137 -> 75 us with the launches that went.
 // keeps the scheduler from moving work across: without it every stage's twiddles and every row's
 // products are hoisted to the front and the registers spill
 __device__ __forceinline__ void stage_fence() { __builtin_amdgcn_sched_barrier(0); }
@@ -2419,10 +2420,11 @@ __device__ __forceinline__ void ip_reduce(const u64 (&x)[NR][NB], const u64 (&z)
 // gather: the sets' blocks of one source block get consecutive numbers on one XCD
 // (workgroups are dealt to the 8 XCDs round-robin), run together there, and read the
 // lift and c0 words of each member through that XCD's L2 once for all sets.
-// FOLD: the masks of a pair are multiplied into the key words once per thread (14 products for three digits, then
-// 185 instructions per member); without it each rotation's two sums are reduced and multiplied by its mask
-// (about 370 per member and no 500 up front), which is less for one and two members: there the fold is most of a
-// thread's work.  Sixteen pairs of one member at N = 2^15: 307 us folded, 251 not (1.1 GB, 4.4 TB/s).
+// FOLD: the masks of a pair are multiplied into the key words once per thread (2825 instructions for three
+// digits and sixteen members); without it each rotation's two sums are reduced and multiplied by its mask (325
+// for one member and nothing up front), which is less for one and two members: there the fold is most of a
+// thread's work.  Sixteen pairs of one member at N = 2^15: 257 us folded, 239 not (1.16 GB, 4.8 TB/s); four pairs
+// of sixteen members 309 us (1.09 GB, 3.5 TB/s, half of it written, the address unit 90 % busy).
 template <int NB, int NR, bool FOLD>
 __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(!FOLD && NB <= 2 ? 5 : 1))) void k_inner_product(DevTables T, IpDesc D) {
     const int N = 1 << T.log_n, nb = N / TPB;
