@@ -31,7 +31,7 @@ HBM_PEAK_GBS = 8000.0
 # on gfx950: 9 integer multiplies (v_mad_u64_u32, v_mul_lo_u32, v_mul_hi_u32) and 8 adds,
 # subtracts and shifts, all issued at the full rate.
 # The limbs of primes below 2^46 run FP64 butterflies instead: hi = x w, lo = fma(x, w, -hi),
-# c = rint(x fl(w/q)), t = fma(-c, q, hi) + lo, then x + t and x - t: 8 VALU instructions
+# c = rint(hi fl(1/q)), t = fma(-c, q, hi) + lo, then x + t and x - t: 8 VALU instructions
 # (v_mul/v_fma/v_rndne/v_add_f64, full rate on gfx950).  A transform launch is bound by
 # whichever floor is larger: its algorithmic bytes at 8 TB/s, or its butterflies' VALU
 # instructions at the VALU rate.
