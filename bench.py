@@ -60,7 +60,7 @@ def log(msg):
 
 
 def settle(nbytes):
-    """wait until the driver has cleared memory just returned to the device.  It does so at about 45
+    """wait until amdgpu has cleared memory just returned to the device.  It does so at about 45
     GB/s, and hipMalloc waits for it once the rest is taken: 170 GB taken again at once need 3.9 s, single
     calls up to 2.5 s; four seconds later 0.08 s.  The legs return up to 108 GB each, and one in four
     bursts on the servers made right after them stood still for 0.3 to 1 s."""
